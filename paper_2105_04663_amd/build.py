@@ -4,20 +4,24 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
+OBJ = os.path.join(HERE, "build")
 LIB = os.path.join(HERE, "libgspmd.so")
-SOURCES = ["gspmd.hip", "plan.cpp"]
+# (source, object, extra flags); dot_mfma.hip is compiled once per operand layout
+UNITS = [(os.path.join(CSRC, "dot_mfma.hip"), f"dot_mfma_l{n}.o", [f"-DGSPMD_TU_LAYOUT={n}"]) for n in range(4)] + [
+    (os.path.join(CSRC, "gspmd.hip"), "gspmd.o", []),
+    (os.path.join(CSRC, "plan.cpp"), "plan.o", []),
+]
 # packed-fp32 code generation is switched off: some of its forms have given wrong results on this hardware
-HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option", "-Wno-inline-asm"]
 
 
-def build(verbose: bool = False) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIP_FLAGS + ["-x", "hip"] + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB + ".tmp"]
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -26,9 +30,21 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed building libgspmd.so")
     if verbose and res.stderr:
         sys.stderr.write(res.stderr)
+
+
+def build(verbose: bool = False, only=None) -> str:
+    """Compile every unit (`only`: those whose object name starts so, the other objects being there) and link."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    os.makedirs(OBJ, exist_ok=True)
+    objects = [os.path.join(OBJ, obj) for _, obj, _ in UNITS]
+    cmds = [[hipcc] + HIP_FLAGS + flags + ["-x", "hip", "-c", src, "-o", os.path.join(OBJ, obj)] for src, obj, flags in UNITS
+            if only is None or obj.startswith(tuple(only))]
+    with ThreadPoolExecutor(max_workers=min(8, int(os.environ.get("MAX_JOBS", "8")))) as pool:
+        list(pool.map(lambda c: _run(c, verbose), cmds))
+    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", LIB + ".tmp"], verbose)
     os.replace(LIB + ".tmp", LIB)
     return LIB
 
 
 if __name__ == "__main__":
-    print(build(verbose=True))
+    print(build(verbose=True, only=sys.argv[1:] or None))

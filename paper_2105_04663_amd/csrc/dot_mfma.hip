@@ -1,0 +1,8 @@
+// dot_mfma_kernel for one operand layout (GSPMD_TU_LAYOUT, GSPMD_LAYOUT_* bits): compiled once per layout.
+#include "kernels_mfma.h"
+
+namespace gspmd {
+
+template bool launch_dot_mfma_layout<GSPMD_TU_LAYOUT>(const MfmaLaunch& l, int32_t out_dtype, bool staged, hipStream_t stream);
+
+}  // namespace gspmd

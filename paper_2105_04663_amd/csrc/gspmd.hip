@@ -2,15 +2,18 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <vector>
 
 #include "../../include/gspmd.h"
 #include "kernels_basic.h"
-#include "kernels_mfma.h"
+#include "launch.h"
 #include "plan.h"
+#include "tile_index.h"
 
 using namespace gspmd;
 
@@ -175,9 +178,9 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
         hipLaunchKernelGGL(zero_words_kernel, dim3(blocks), dim3(256), 0, stream, join->counters, join->tiles);
         if (hipGetLastError() != hipSuccess) return GSPMD_ERR_DEVICE;
       }
-      if (!launch_dot_mfma(inl, tab, n, static_cast<int>(tiles), layout, out_dtype, path == kPathMfmaStaged, epilogue, join ? join->partials : nullptr,
-                           join ? join->counters : nullptr, g_timeline.load(std::memory_order_acquire),
-                           g_timeline_records.load(std::memory_order_acquire), stream)) return GSPMD_ERR_DEVICE;
+      const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, join ? join->partials : nullptr, join ? join->counters : nullptr,
+                         g_timeline.load(std::memory_order_acquire), g_timeline_records.load(std::memory_order_acquire)};
+      if (!launch_dot_mfma(l, layout, out_dtype, path == kPathMfmaStaged, stream)) return GSPMD_ERR_DEVICE;
     } else {
       const dim3 grid(static_cast<unsigned>(tiles)), block(256);
       if (in_dtype == GSPMD_F32)

@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "kernels_basic.h"
+#include "launch.h"
 #include "mainloop_asm.h"
 #include "plan.h"
 #include "tile_index.h"
@@ -363,10 +364,17 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
             default: GSPMD_RUN_WAVES(GSPMD_MAINLOOP_L##L##_G1R4) break; \
           } \
         }
-        if constexpr (LAYOUT == 0) { GSPMD_RUN_MAINLOOP(0) }
-        else if constexpr (LAYOUT == 1) { GSPMD_RUN_MAINLOOP(1) }
-        else if constexpr (LAYOUT == 2) { GSPMD_RUN_MAINLOOP(2) }
-        else { GSPMD_RUN_MAINLOOP(3) }
+        // a source that includes this header compiles one layout (the four loops' assembly together takes minutes)
+        static_assert(LAYOUT == GSPMD_TU_LAYOUT, "one operand layout per compiled source");
+#if GSPMD_TU_LAYOUT == 0
+        GSPMD_RUN_MAINLOOP(0)
+#elif GSPMD_TU_LAYOUT == 1
+        GSPMD_RUN_MAINLOOP(1)
+#elif GSPMD_TU_LAYOUT == 2
+        GSPMD_RUN_MAINLOOP(2)
+#else
+        GSPMD_RUN_MAINLOOP(3)
+#endif
       }
     }
     // ---- what is left of K (< 64): up to two tiles, the last one possibly partial.  Group 0 fetches the first and
@@ -687,13 +695,10 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
   }
 }
 
-constexpr int kMaxDevices = 64;
-
 // The kernel needs all 160 KiB of LDS as dynamic shared memory: raised once per instantiation and device.  Callable
 // from several host threads.
 template <typename TOut, int LAYOUT, bool STAGED>
-inline bool launch_dot_mfma_as(const InlineProblems& inl, const Problem* tab, int n_prob, int tiles, int epilogue, float* join_partials,
-                               uint32_t* join_counters, unsigned long long* timeline, int timeline_records, hipStream_t stream) {
+inline bool launch_dot_mfma_as(const MfmaLaunch& l, hipStream_t stream) {
   static std::once_flag once[kMaxDevices];
   static bool ok[kMaxDevices];
   int dev = 0;
@@ -703,34 +708,16 @@ inline bool launch_dot_mfma_as(const InlineProblems& inl, const Problem* tab, in
                                   hipFuncAttributeMaxDynamicSharedMemorySize, kMfmaLds) == hipSuccess;
   });
   if (!ok[dev]) return false;
-  const dim3 grid(static_cast<unsigned>(tiles)), block(kMfmaThreads);
-  hipLaunchKernelGGL((dot_mfma_kernel<TOut, LAYOUT, STAGED>), grid, block, kMfmaLds, stream, inl, tab, n_prob, epilogue, join_partials, join_counters,
-                     timeline, timeline_records);
+  const dim3 grid(static_cast<unsigned>(l.tiles)), block(kMfmaThreads);
+  hipLaunchKernelGGL((dot_mfma_kernel<TOut, LAYOUT, STAGED>), grid, block, kMfmaLds, stream, *l.inl, l.tab, l.n_prob, l.epilogue, l.join_partials,
+                     l.join_counters, l.timeline, l.timeline_records);
   return hipGetLastError() == hipSuccess;
 }
 
-template <typename TOut, bool STAGED>
-inline bool launch_dot_mfma_layout(const InlineProblems& inl, const Problem* tab, int n_prob, int tiles, int32_t layout, int epilogue,
-                                   float* join_partials, uint32_t* join_counters, unsigned long long* timeline, int timeline_records,
-                                   hipStream_t stream) {
-  switch (layout & 3) {
-    case 0: return launch_dot_mfma_as<TOut, 0, STAGED>(inl, tab, n_prob, tiles, epilogue, join_partials, join_counters, timeline, timeline_records, stream);
-    case 1: return launch_dot_mfma_as<TOut, 1, STAGED>(inl, tab, n_prob, tiles, epilogue, join_partials, join_counters, timeline, timeline_records, stream);
-    case 2: return launch_dot_mfma_as<TOut, 2, STAGED>(inl, tab, n_prob, tiles, epilogue, join_partials, join_counters, timeline, timeline_records, stream);
-    default: return launch_dot_mfma_as<TOut, 3, STAGED>(inl, tab, n_prob, tiles, epilogue, join_partials, join_counters, timeline, timeline_records, stream);
-  }
-}
-
-// `staged`: the operands allow 4-byte but not 16-byte aligned chunk loads
-inline bool launch_dot_mfma(const InlineProblems& inl, const Problem* tab, int n_prob, int tiles, int32_t layout, int32_t out_dtype,
-                            bool staged, int epilogue, float* join_partials, uint32_t* join_counters, unsigned long long* timeline,
-                            int timeline_records, hipStream_t stream) {
-  const bool f32 = out_dtype == GSPMD_F32;
-  if (staged)
-    return f32 ? launch_dot_mfma_layout<float, true>(inl, tab, n_prob, tiles, layout, epilogue, join_partials, join_counters, timeline, timeline_records, stream)
-               : launch_dot_mfma_layout<bf16_bits, true>(inl, tab, n_prob, tiles, layout, epilogue, join_partials, join_counters, timeline, timeline_records, stream);
-  return f32 ? launch_dot_mfma_layout<float, false>(inl, tab, n_prob, tiles, layout, epilogue, join_partials, join_counters, timeline, timeline_records, stream)
-             : launch_dot_mfma_layout<bf16_bits, false>(inl, tab, n_prob, tiles, layout, epilogue, join_partials, join_counters, timeline, timeline_records, stream);
+template <int LAYOUT>
+bool launch_dot_mfma_layout(const MfmaLaunch& l, int32_t out_dtype, bool staged, hipStream_t stream) {
+  if (out_dtype == GSPMD_F32) return staged ? launch_dot_mfma_as<float, LAYOUT, true>(l, stream) : launch_dot_mfma_as<float, LAYOUT, false>(l, stream);
+  return staged ? launch_dot_mfma_as<bf16_bits, LAYOUT, true>(l, stream) : launch_dot_mfma_as<bf16_bits, LAYOUT, false>(l, stream);
 }
 
 }  // namespace gspmd

@@ -1,0 +1,40 @@
+// Host-side launchers of the contraction kernels.  The kernels are compiled in sources of their own (one per operand
+// layout), so that a build compiles them side by side.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernels_basic.h"
+#include "plan.h"
+
+namespace gspmd {
+
+constexpr int kMaxDevices = 64;
+
+// One launch of dot_mfma_kernel over `tiles` workgroups.
+struct MfmaLaunch {
+  const InlineProblems* inl;             // table that travels in the kernel arguments (tab null), or
+  const Problem* tab;                    // table in device memory
+  int n_prob, tiles, epilogue;
+  float* join_partials;                  // joined problems: slots and arrival counters
+  uint32_t* join_counters;
+  unsigned long long* timeline;
+  int timeline_records;
+};
+
+// `staged`: the operands allow 4-byte but not 16-byte aligned chunk loads
+template <int LAYOUT>
+bool launch_dot_mfma_layout(const MfmaLaunch& l, int32_t out_dtype, bool staged, hipStream_t stream);
+
+#ifndef GSPMD_TU_LAYOUT     // not where one layout is compiled
+inline bool launch_dot_mfma(const MfmaLaunch& l, int32_t layout, int32_t out_dtype, bool staged, hipStream_t stream) {
+  switch (layout & 3) {
+    case 0: return launch_dot_mfma_layout<0>(l, out_dtype, staged, stream);
+    case 1: return launch_dot_mfma_layout<1>(l, out_dtype, staged, stream);
+    case 2: return launch_dot_mfma_layout<2>(l, out_dtype, staged, stream);
+    default: return launch_dot_mfma_layout<3>(l, out_dtype, staged, stream);
+  }
+}
+#endif
+
+}  // namespace gspmd
