@@ -22,7 +22,7 @@
  *   - HIP graphs: a kernel-launching call whose launch tables fit its kernels' arguments enqueues kernels only and
  *     may be recorded into a graph: a Dot lowered to at most 32 GEMM problems (every benchmark configuration; the
  *     count is what gspmd_plan_dot reports, summed over the partitions of a grouped call), a resharding on a mesh of
- *     at most 64 partitions with at most 8 distinct destination buffers.  Beyond that the tables are uploaded into
+ *     at most 64 partitions with at most 32 distinct destination buffers.  Beyond that the tables are uploaded into
  *     the workspace with a stream-ordered copy from a temporary host buffer, and such a call must not be recorded.
  *   - Tensors are row-major.  A shard buffer has the STATIC shard shape (ceil(D/n) per split dimension,
  *     Section 4.1), whatever the partition's valid length.  Padding may hold anything, including NaN: no value at

@@ -241,6 +241,36 @@ int32_t launch_reduce(const float* const* partials, int n_partials, int64_t rows
   return hipGetLastError() == hipSuccess ? GSPMD_OK : GSPMD_ERR_DEVICE;
 }
 
+// Largest extent whose index arithmetic (a padded dimension: partitions x shard size) stays within 31 bits.
+constexpr int64_t kMoveMaxExtent = INT32_MAX >> 1;
+
+// Launch shape of a move of `boxes` boxes (`dst_bits`: their addresses or-ed together) in 16-byte chunks of `vec` elements; fills in the shape's divisors, lanes per
+// row and column block.  A row of fewer chunks than a wave has lanes shares the wave with other rows.  A workgroup takes
+// at most kMoveUnroll chunks per lane of a row (columns beyond that go to another one), and loops over rows once there
+// are more than 8192 workgroups (enough to fill the chip several times; more pay the set-up once more: a reshard of 537
+// MB ran at 4.2 TB/s with 65536 and at 5.4 with 8192).
+dim3 move_grid(MoveShape* s, uintptr_t dst_bits, int64_t boxes, int vec) {
+  const int last = s->rank - 1;
+  bool aligned = !(dst_bits & 15);
+  for (int i = 0; i < last; ++i) aligned = aligned && s->dst_stride[i] % vec == 0;
+  for (int i = 0; i < s->rank; ++i) {
+    s->div_shard[i] = fast_div(static_cast<uint32_t>(s->shard[i]));
+    s->div_per[i] = fast_div(static_cast<uint32_t>(s->src_per[i]));
+  }
+  // a row that does not start on 16 bytes in dst has a chunk more
+  const int64_t chunks = (static_cast<int64_t>(s->shard[last]) + vec - 1) / vec + (aligned ? 0 : 1);
+  int log_lanes = 0;
+  while (log_lanes < 6 && (int64_t(1) << log_lanes) < chunks) ++log_lanes;
+  const int64_t lanes = int64_t(1) << log_lanes, per_block = kMoveUnroll * lanes;
+  const int64_t gx = (chunks + per_block - 1) / per_block;
+  const int64_t each = ((chunks + gx - 1) / gx + lanes - 1) / lanes * lanes;        // even split in whole waves
+  s->log_lanes = log_lanes;
+  s->block_chunks = static_cast<int32_t>(each);
+  const int64_t rows_per = 256 >> log_lanes, groups = (s->rows + rows_per - 1) / rows_per;
+  const int64_t gy = std::min<int64_t>(std::min<int64_t>(groups, 65535), std::max<int64_t>(1, 8192 / (gx * boxes)));
+  return dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(boxes));
+}
+
 bool is_contracting(int32_t c) { return c == GSPMD_AXIS_CONTRACTING || c == GSPMD_AXIS_CONTRACTING_SCATTER; }
 
 bool has_contracting(const gspmd_mesh* mesh, const int32_t* cls) {
@@ -813,6 +843,41 @@ static int32_t shard_copy(const gspmd_mesh* mesh, const gspmd_sharding* sh, int6
   for (int i = 0; i < b.rank; ++i) any_valid = any_valid && b.valid[i] > 0;
   if (!any_valid) goff = 0;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  // 32-bit index arithmetic in shard_move_kernel: extents and rows must fit
+  int64_t rows = 1;
+  bool fits = true;
+  for (int i = 0; i < b.rank; ++i) {
+    fits = fits && sh->global_shape[i] <= kMoveMaxExtent;
+    if (i < b.rank - 1) rows = std::min<int64_t>(rows * (extract ? b.shard[i] : b.valid[i]), int64_t(INT32_MAX) + 1);
+  }
+  if (fits && rows <= INT32_MAX) {
+    if (!extract && !any_valid) return GSPMD_OK;
+    ShardCopy sc;
+    std::memset(&sc, 0, sizeof(sc));
+    sc.shape.rank = b.rank;
+    sc.shape.rows = static_cast<int32_t>(rows);
+    sc.shape.pad = pad_bits;
+    // the tensor's side starts where the shard begins in it; either side is one src "shard" that holds everything
+    const int64_t esz = shard->dtype == GSPMD_BF16 ? 2 : 4;
+    if (extract) {
+      sc.src = static_cast<const char*>(src_global) + goff * esz;
+      sc.box.dst = shard->data;
+    } else {
+      sc.src = shard->data;
+      sc.box.dst = static_cast<char*>(dst_global) + goff * esz;
+    }
+    for (int i = 0; i < b.rank; ++i) {
+      sc.shape.shard[i] = static_cast<int32_t>(extract ? b.shard[i] : b.valid[i]);
+      sc.box.valid[i] = static_cast<int32_t>(b.valid[i]);
+      sc.shape.src_per[i] = INT32_MAX;
+      sc.shape.dst_stride[i] = extract ? d.sstride[i] : d.gstride[i];
+      sc.shape.src_stride[i] = extract ? d.gstride[i] : d.sstride[i];
+    }
+    const dim3 grid = move_grid(&sc.shape, reinterpret_cast<uintptr_t>(sc.box.dst), 1, static_cast<int>(16 / esz));
+    if (shard->dtype == GSPMD_BF16) hipLaunchKernelGGL((shard_move_kernel<bf16_bits>), grid, dim3(256), 0, stream, sc);
+    else hipLaunchKernelGGL((shard_move_kernel<uint32_t>), grid, dim3(256), 0, stream, sc);
+    return hipGetLastError() == hipSuccess ? GSPMD_OK : GSPMD_ERR_DEVICE;
+  }
   const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((total + 255) / 256, 256 * 32));
   const dim3 grid(blocks), block(256);
   if (shard->dtype == GSPMD_BF16) {
@@ -837,12 +902,16 @@ int32_t gspmd_shard_assemble(const gspmd_mesh* mesh, const gspmd_sharding* sh, i
   return shard_copy(mesh, sh, pid, nullptr, global_data, shard, 0, false, hip_stream);
 } catch (...) { return GSPMD_ERR_HOST_MEMORY; }
 
+// bytes of workspace per partition that the query asks for beside the src pointers (a MoveBox needs 80)
+constexpr int64_t kReshardTableBytes = 312;
+static_assert(sizeof(MoveBox) <= kReshardTableBytes, "the tables fit the workspace");
+
 int32_t gspmd_reshard_workspace_bytes(const gspmd_mesh* mesh, int64_t* bytes) try {
   if (!bytes) return GSPMD_ERR_NULL;
   int64_t P = 0;
   const int32_t st = validate_mesh(mesh, &P);
   if (st != GSPMD_OK) return st;
-  *bytes = round_up(P * 8, kWsAlign) + round_up(P * static_cast<int64_t>(sizeof(ReshardDesc)), kWsAlign);
+  *bytes = round_up(P * 8, kWsAlign) + round_up(P * kReshardTableBytes, kWsAlign);
   return GSPMD_OK;
 } catch (...) { return GSPMD_ERR_HOST_MEMORY; }
 
@@ -892,16 +961,11 @@ int32_t gspmd_reshard(const gspmd_mesh* mesh, const gspmd_sharding* src_sh, cons
     for (int i = rank - 3; i >= 0; --i) src_stride[i] = src_stride[i + 1] * sb0.shard[i + 1];
   }
 
-  const size_t esize = dtype == GSPMD_BF16 ? 2 : 4;
-  const int vec_elems = static_cast<int>(16 / esize);
-  uintptr_t bits = 0;
-  for (int64_t p = 0; p < P; ++p) bits |= reinterpret_cast<uintptr_t>(src_shards[p].data) | reinterpret_cast<uintptr_t>(dst_shards[p].data);
-  bool vec = !(bits & 15) && sb0.shard[last] % vec_elems == 0;
-  for (int i = 0; i < last; ++i) vec = vec && src_stride[i] % vec_elems == 0;
-
-  std::vector<ReshardDesc> descs;
+  InlineReshard inl;
+  std::memset(&inl, 0, sizeof(inl));
+  MoveShape& shape = inl.shape;
+  std::vector<MoveBox> boxes;
   std::vector<void*> seen;
-  int64_t max_rows = 0, max_cols = 0;
   for (int64_t p = 0; p < P; ++p) {
     void* dst = dst_shards[p].data;
     if (std::find(seen.begin(), seen.end(), dst) != seen.end()) continue;   // replicas sharing a buffer: fill it once
@@ -910,75 +974,64 @@ int32_t gspmd_reshard(const gspmd_mesh* mesh, const gspmd_sharding* src_sh, cons
     if ((st = shard_bounds(mesh, dst_sh, p, &db)) != GSPMD_OK) return st;
     int64_t coords[kMaxRank];
     if ((st = mesh_coords(mesh, p, coords)) != GSPMD_OK) return st;
-    ReshardDesc d;
+    MoveBox d;
     std::memset(&d, 0, sizeof(d));
     d.dst = dst;
-    d.rank = rank;
-    int64_t rows = 1, total = 1;
     for (int i = 0; i < rank; ++i) {
       if (db.shard[i] > INT32_MAX) return GSPMD_ERR_UNSUPPORTED;
-      d.shard[i] = static_cast<int32_t>(db.shard[i]);
       d.valid[i] = static_cast<int32_t>(db.valid[i]);
       d.dst_off[i] = static_cast<int32_t>(db.offset[i]);
-      d.src_per[i] = static_cast<int32_t>(std::max<int64_t>(sb0.shard[i], 1));
-      d.src_stride[i] = src_stride[i];
-      const int a = src_sh->dims_mapping[i];
-      d.pos_stride[i] = a >= 0 ? static_cast<int32_t>(mesh_stride[a]) : 0;
-      if (i < last) rows *= db.shard[i];
-      total *= db.shard[i];
     }
     for (int a = 0; a < mesh->rank; ++a) if (!src_uses[a]) d.base_pos += static_cast<int32_t>(coords[a] * mesh_stride[a]);
-    d.dst_stride[last] = 1;
-    if (rank >= 2) {
-      const int64_t rs = dst_shards[p].row_stride > 0 ? dst_shards[p].row_stride : db.shard[last];
-      if (rs < db.shard[last]) return GSPMD_ERR_BAD_BUFFER;
-      d.dst_stride[rank - 2] = rs;
-      for (int i = rank - 3; i >= 0; --i) d.dst_stride[i] = d.dst_stride[i + 1] * db.shard[i + 1];
+    if (boxes.empty()) {                     // static shapes and strides are the same for every partition
+      int64_t rows = 1, total = 1;
+      shape.rank = rank;
+      for (int i = 0; i < rank; ++i) {
+        shape.shard[i] = static_cast<int32_t>(db.shard[i]);
+        shape.src_per[i] = static_cast<int32_t>(std::max<int64_t>(sb0.shard[i], 1));
+        shape.src_stride[i] = src_stride[i];
+        const int a = src_sh->dims_mapping[i];
+        shape.pos_stride[i] = a >= 0 ? static_cast<int32_t>(mesh_stride[a]) : 0;
+        if (i < last) rows *= db.shard[i];
+        total *= db.shard[i];
+      }
+      shape.dst_stride[last] = 1;
+      if (rank >= 2) {
+        const int64_t rs = dst_shards[0].row_stride > 0 ? dst_shards[0].row_stride : db.shard[last];
+        if (rs < db.shard[last]) return GSPMD_ERR_BAD_BUFFER;
+        shape.dst_stride[rank - 2] = rs;
+        for (int i = rank - 3; i >= 0; --i) shape.dst_stride[i] = shape.dst_stride[i + 1] * db.shard[i + 1];
+      }
+      if (total == 0) return GSPMD_OK;
+      if (rows > INT32_MAX) return GSPMD_ERR_UNSUPPORTED;
+      shape.rows = static_cast<int32_t>(rows);
     }
-    if (total == 0) continue;
-    if (rows > INT32_MAX) return GSPMD_ERR_UNSUPPORTED;
-    d.rows = static_cast<int32_t>(rows);
-    vec = vec && db.shard[last] % vec_elems == 0;
-    for (int i = 0; i < last; ++i) vec = vec && d.dst_stride[i] % vec_elems == 0;
-    max_rows = std::max(max_rows, rows);
-    max_cols = std::max<int64_t>(max_cols, db.shard[last]);
-    descs.push_back(d);
+    boxes.push_back(d);
   }
-  if (descs.empty()) return GSPMD_OK;
 
-  // tables: [src shard of the partition at each mesh position][descriptors]; as kernel arguments when they fit,
-  // else uploaded into the workspace (stream-ordered copy from a temporary host buffer)
+  // tables: [src shard of the partition at each mesh position][dst boxes]; as kernel arguments when they fit, else
+  // uploaded into the workspace (stream-ordered copy from a temporary host buffer)
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  InlineReshard inl;
-  std::memset(&inl, 0, sizeof(inl));
   const void* const* d_ptrs = nullptr;
-  const ReshardDesc* d_descs = nullptr;
-  if (P <= kInlineReshardSrc && descs.size() <= static_cast<size_t>(kInlineReshardDescs)) {
+  const MoveBox* d_boxes = nullptr;
+  if (P <= kInlineReshardSrc && boxes.size() <= static_cast<size_t>(kInlineReshardDescs)) {
     for (int64_t pos = 0; pos < P; ++pos) inl.src[pos] = src_shards[mesh->device_ids[pos]].data;
-    std::memcpy(inl.d, descs.data(), descs.size() * sizeof(ReshardDesc));
+    std::memcpy(inl.d, boxes.data(), boxes.size() * sizeof(MoveBox));
   } else {
     const int64_t ids_bytes = round_up(P * 8, kWsAlign);
-    std::vector<char> host(static_cast<size_t>(ids_bytes + descs.size() * sizeof(ReshardDesc)), 0);
+    std::vector<char> host(static_cast<size_t>(ids_bytes + boxes.size() * sizeof(MoveBox)), 0);
     for (int64_t pos = 0; pos < P; ++pos) std::memcpy(host.data() + pos * 8, &src_shards[mesh->device_ids[pos]].data, 8);
-    std::memcpy(host.data() + ids_bytes, descs.data(), descs.size() * sizeof(ReshardDesc));
+    std::memcpy(host.data() + ids_bytes, boxes.data(), boxes.size() * sizeof(MoveBox));
     if (hipMemcpyAsync(workspace, host.data(), host.size(), hipMemcpyHostToDevice, stream) != hipSuccess) return GSPMD_ERR_DEVICE;
     const char* ws = static_cast<const char*>(workspace);
     d_ptrs = reinterpret_cast<const void* const*>(ws);
-    d_descs = reinterpret_cast<const ReshardDesc*>(ws + ids_bytes);
+    d_boxes = reinterpret_cast<const MoveBox*>(ws + ids_bytes);
   }
-
-  const int v = vec ? vec_elems : 1;
-  const int64_t gx = ((max_cols + v - 1) / v + 255) / 256;
-  // about 8192 workgroups in all; each thread walks down its column of rows (more, smaller workgroups are slower: 65536 gave 4.2 instead of 5.4 TB/s)
-  const int64_t gy = std::min<int64_t>(std::min<int64_t>(max_rows, 65535), std::max<int64_t>(1, 8192 / (gx * static_cast<int64_t>(descs.size()))));
-  const dim3 block(256), grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy), static_cast<unsigned>(descs.size()));
-  if (dtype == GSPMD_BF16) {
-    if (vec) hipLaunchKernelGGL((reshard_kernel<bf16_bits, 8>), grid, block, 0, stream, inl, d_descs, d_ptrs);
-    else hipLaunchKernelGGL((reshard_kernel<bf16_bits, 1>), grid, block, 0, stream, inl, d_descs, d_ptrs);
-  } else {
-    if (vec) hipLaunchKernelGGL((reshard_kernel<uint32_t, 4>), grid, block, 0, stream, inl, d_descs, d_ptrs);
-    else hipLaunchKernelGGL((reshard_kernel<uint32_t, 1>), grid, block, 0, stream, inl, d_descs, d_ptrs);
-  }
+  uintptr_t dst_bits = 0;
+  for (const MoveBox& d : boxes) dst_bits |= reinterpret_cast<uintptr_t>(d.dst);
+  const dim3 grid = move_grid(&shape, dst_bits, static_cast<int64_t>(boxes.size()), dtype == GSPMD_BF16 ? 8 : 4);
+  if (dtype == GSPMD_BF16) hipLaunchKernelGGL((reshard_kernel<bf16_bits>), grid, dim3(256), 0, stream, inl, d_boxes, d_ptrs);
+  else hipLaunchKernelGGL((reshard_kernel<uint32_t>), grid, dim3(256), 0, stream, inl, d_boxes, d_ptrs);
   return hipGetLastError() == hipSuccess ? GSPMD_OK : GSPMD_ERR_DEVICE;
 } catch (...) { return GSPMD_ERR_HOST_MEMORY; }
 
