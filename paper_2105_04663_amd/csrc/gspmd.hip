@@ -117,8 +117,42 @@ int64_t tiles_of(const Problem& p, int bm, int bn) {
   return ((static_cast<int64_t>(p.Mv) + bm - 1) / bm) * ((static_cast<int64_t>(p.Nv) + bn - 1) / bn);
 }
 
+// Row blocks (of 16) per tile if the launch goes to dot_split_kernel, 0 if not.  That kernel splits K over a workgroup's
+// waves, so it suits launches whose time is one workgroup's chain of K steps on a chip that 256 x 256 tiles leave mostly
+// idle: products of at most kSplitMaxRows rows.  The estimates are straight lines through measured times (one problem,
+// bf16, rows x K x N, us; dot_mfma_kernel / dot_split_kernel with 1, 2, 4 row blocks):
+//   32 x 8192 x 8192: 101 / 43, 51, 54     64 x 8192 x 8192: 105 / 62, 47, 65     256 x 8192 x 8192: 135 / 222, 140, 97
+//   32 x 2048 x 16384: 31 / 26, 19, 20     256 x 2048 x 2048: 39 / 22, 13, 17     64 x 1024 x 1024: 14 / 6, 7, 10
+// a workgroup of dot_mfma_kernel takes about 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step, one of dot_split_kernel 4 us
+// and 1.0, 1.3, 1.7 us per round of eight 32-wide steps; rounds of 256 workgroups follow each other.
+// Partial sums along a contracting mesh dimension keep dot_mfma_kernel's order of summation (`ordered`): the joined sum,
+// the two-launch sum and partials that a caller sums agree bit for bit.
+constexpr int kSplitMaxRows = 256;
+int split_row_blocks(const std::vector<Problem>& ps, KernelPath path, int32_t in_dtype, bool ordered) {
+  if (in_dtype != GSPMD_BF16 || ordered || path != kPathMfmaDirect) return 0;
+  int64_t rows = 0, k = 0, big = 0;
+  for (const auto& p : ps) {
+    if (p.lda > (1 << 24) || p.ldb > (1 << 24)) return 0;        // 32-bit offsets of 64 rows
+    rows = std::max<int64_t>(rows, p.Mv);
+    k = std::max<int64_t>(k, p.Kv);
+    big += tiles_of(p, kMfmaBM, kMfmaBN);
+  }
+  if (rows == 0 || rows > kSplitMaxRows) return 0;
+  const double steps64 = static_cast<double>((k + 63) / 64), rounds8 = static_cast<double>((k + 255) / 256);
+  double best = static_cast<double>((big + 255) / 256) * (9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95));
+  int blocks = 0;
+  const struct { int blocks; double per_round; } kinds[] = {{1, 1.0}, {2, 1.3}, {4, 1.7}};
+  for (const auto& kind : kinds) {
+    int64_t tiles = 0;
+    for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
+    const double us = static_cast<double>((tiles + 255) / 256) * (4.0 + rounds8 * kind.per_round);
+    if (us < best) { best = us; blocks = kind.blocks; }
+  }
+  return blocks;
+}
+
 int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dtype, int32_t out_dtype, int32_t epilogue,
-                        void* workspace, int64_t workspace_bytes, hipStream_t stream, const JoinSpace* join = nullptr) {
+                        bool ordered, void* workspace, int64_t workspace_bytes, hipStream_t stream, const JoinSpace* join = nullptr) {
   // problems with an empty static output block write nothing
   all.erase(std::remove_if(all.begin(), all.end(), [](const Problem& p) { return p.Ms == 0 || p.Ns == 0; }), all.end());
   if (all.empty()) return GSPMD_OK;
@@ -128,7 +162,8 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   const KernelPath path = kernel_path(ps, in_dtype, layout);
   const bool mfma = path != kPathFallback;
   if (join && !mfma) return GSPMD_ERR_UNSUPPORTED;              // the caller checks before it joins problems
-  const int bm = mfma ? kMfmaBM : kGenTile, bn = mfma ? kMfmaBN : kGenTile;
+  const int split = join ? 0 : split_row_blocks(ps, path, in_dtype, ordered);
+  const int bm = split ? 16 * split : mfma ? kMfmaBM : kGenTile, bn = split ? kSplitBN : mfma ? kMfmaBN : kGenTile;
   // Workgroups start in tile order and the launch ends when the last one does: problems whose tiles take longest
   // (the most K steps) go first, so that the compute units that are still busy at the end are busy with short tiles.
   if (!join)
@@ -140,7 +175,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
     if (p.join_slot > 0) continue;                              // one of the joined problems speaks for their common output
     // rows that the contraction kernel's tiles write or clear; the MFMA kernel's last tile row also clears up to
     // kRowsBelow rows below its footprint
-    const int32_t rows_done = mfma ? rows_cleared(p.Mv, p.Ms)
+    const int32_t rows_done = mfma || split ? rows_cleared(p.Mv, p.Ms)
                                    : static_cast<int32_t>(std::min<int64_t>(p.Ms, (static_cast<int64_t>(p.Mv) + bm - 1) / bm * bm));
     const int32_t cols_done = static_cast<int32_t>(std::min<int64_t>(p.Ns, (static_cast<int64_t>(p.Nv) + bn - 1) / bn * bn));
     if (rows_done < p.Ms) rects.push_back(ZeroRect{p.C, p.ldc, rows_done, p.Ms, 0, p.Ns, 0});
@@ -172,7 +207,11 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   }
   const int n = static_cast<int>(ps.size());
   if (tiles > 0) {
-    if (mfma) {
+    if (split) {
+      const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, g_timeline.load(std::memory_order_acquire),
+                         g_timeline_records.load(std::memory_order_acquire)};
+      if (!launch_dot_split(l, layout, out_dtype, split, stream)) return GSPMD_ERR_DEVICE;
+    } else if (mfma) {
       if (join && join->tiles > 0) {
         const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((join->tiles + 255) / 256, 1024));
         hipLaunchKernelGGL(zero_words_kernel, dim3(blocks), dim3(256), 0, stream, join->counters, join->tiles);
@@ -562,7 +601,8 @@ int32_t gspmd_local_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     return st;
   for (const auto& p : ps)
     if ((p.Kv && (!p.A || !p.B)) || !p.C) return GSPMD_ERR_NULL;
-  return launch_problems(ps, layout, lhs->dtype, out->dtype, epilogue, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
+  return launch_problems(ps, layout, lhs->dtype, out->dtype, epilogue, has_contracting(mesh, cls), workspace, workspace_bytes,
+                         static_cast<hipStream_t>(hip_stream));
 } catch (...) { return GSPMD_ERR_HOST_MEMORY; }
 
 int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
@@ -736,7 +776,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
       js.counters = reinterpret_cast<uint32_t*>(partial_base);
       js.partials = reinterpret_cast<float*>(partial_base + round_up(jtiles * 4, kWsAlign));
       js.tiles = jtiles;
-      return launch_problems(joined, jlayout, in_dtype, out_dtype, epilogue, workspace, workspace_bytes, stream, &js);
+      return launch_problems(joined, jlayout, in_dtype, out_dtype, epilogue, true, workspace, workspace_bytes, stream, &js);
     }
   }
 
@@ -760,7 +800,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
       if ((ps[i].Kv && (!ps[i].A || !ps[i].B)) || !ps[i].C) return GSPMD_ERR_NULL;
   }
   st = launch_problems(ps, layout, in_dtype, contracting ? GSPMD_F32 : out_dtype, contracting ? GSPMD_EPILOGUE_NONE : epilogue,
-                       workspace, workspace_bytes, stream);
+                       contracting, workspace, workspace_bytes, stream);
   if (st != GSPMD_OK || !contracting) return st;
 
   // Sum the partials of each reduce group, ascending in mesh position, into every distinct out buffer of the group.

@@ -102,6 +102,26 @@ __device__ __forceinline__ Problem lookup_problem(const Problem* __restrict__ ta
   return copy_from_kernarg(inl + lo);
 }
 
+// Profiling aid (gspmd_set_tile_timeline): one record of eight 64-bit words per workgroup, written by its thread 0.
+// Words 0-7 hold the 100 MHz constant-rate counter at: kernel entry (bits 52-63: XCD id << 8 | compute-unit bits
+// 8-15 of the hardware id register), tile decoded, first tile loads issued, first tiles landed (K loop starts), K
+// loop left, epilogue starts (leftover K and joined sums done), stores issued, stores complete.  `rec` is null
+// when the timeline is off; the branch is uniform and costs two scalar instructions per stamp.
+constexpr int kTimelineWords = 8;
+__device__ __forceinline__ unsigned long long* timeline_record(unsigned long long* timeline, int records) {
+  return (timeline != nullptr && static_cast<int>(blockIdx.x) < records) ? timeline + static_cast<size_t>(blockIdx.x) * kTimelineWords : nullptr;
+}
+// what word 0 holds beside the time: where the workgroup runs
+__device__ __forceinline__ unsigned timeline_where() {
+  return ((__builtin_amdgcn_s_getreg((31 << 11) | 20) & 15u) << 8) | ((__builtin_amdgcn_s_getreg((31 << 11) | 4) >> 8) & 255u);
+}
+__device__ __forceinline__ void timeline_stamp(unsigned long long* rec, int word, int t, unsigned long long tag = 0) {
+  if (rec == nullptr) return;
+  unsigned long long now;
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_memrealtime %0\n\ts_waitcnt lgkmcnt(0)" : "=s"(now) :: "memory");
+  if (t == 0) rec[word] = now | (tag << 52);
+}
+
 constexpr int kGenTile = 64;   // output tile edge of the fallback kernel
 constexpr int kGenBK = 16;
 

@@ -71,19 +71,6 @@ __device__ __forceinline__ u32x4_t mask_tail8(u32x4_t v, int keep) {   // keep f
 typedef uint32_t u32x4_align4_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef __attribute__((address_space(1))) u32x4_t global_u32x4_t;
 
-// Profiling aid (gspmd_set_tile_timeline): one record of eight 64-bit words per workgroup, written by its thread 0.
-// Words 0-7 hold the 100 MHz constant-rate counter at: kernel entry (bits 52-63: XCD id << 8 | compute-unit bits
-// 8-15 of the hardware id register), tile decoded, first tile loads issued, first tiles landed (K loop starts), K
-// loop left, epilogue starts (leftover K and joined sums done), stores issued, stores complete.  `rec` is null
-// when the timeline is off; the branch is uniform and costs two scalar instructions per stamp.
-constexpr int kTimelineWords = 8;
-__device__ __forceinline__ void timeline_stamp(unsigned long long* rec, int word, int t, unsigned long long tag = 0) {
-  if (rec == nullptr) return;
-  unsigned long long now;
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_memrealtime %0\n\ts_waitcnt lgkmcnt(0)" : "=s"(now) :: "memory");
-  if (t == 0) rec[word] = now | (tag << 52);
-}
-
 // Zeros over rows [row_begin, row_end) x columns [col_begin, col_end) of an output block, by all kMfmaThreads threads of
 // the workgroup: the rows of the static block below the last tile row's footprint.  `vec`: 16-byte stores are
 // aligned (checked by the caller for the block's pointer, row stride and col_begin) and the width is a multiple of them.
@@ -125,12 +112,8 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave >> 2, wn = wave & 3;     // wm is also the ping-pong group
 
-  unsigned long long* const rec = (timeline != nullptr && static_cast<int>(blockIdx.x) < timeline_records)
-                                      ? timeline + static_cast<size_t>(blockIdx.x) * kTimelineWords : nullptr;
-  if (rec != nullptr) {
-    const unsigned where = ((__builtin_amdgcn_s_getreg((31 << 11) | 20) & 15u) << 8) | ((__builtin_amdgcn_s_getreg((31 << 11) | 4) >> 8) & 255u);
-    timeline_stamp(rec, 0, t, where);
-  }
+  unsigned long long* const rec = timeline_record(timeline, timeline_records);
+  if (rec != nullptr) timeline_stamp(rec, 0, t, timeline_where());
   const int tile = logical_tile(blockIdx.x, gridDim.x);
   const Problem P = lookup_problem(tab, n_prob, tile);
   const int local = tile - P.tile_begin;            // which of its problem's output tiles this workgroup computes
