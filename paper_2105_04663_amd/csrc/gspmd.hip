@@ -67,8 +67,8 @@ int64_t assign_tiles(std::vector<Problem>& ps, int bm, int bn) {
 }
 
 // Which contraction kernel a launch can take: the MFMA kernel with direct global->LDS loads needs 16-byte aligned
-// operand pointers and leading dimensions that are multiples of 8 elements; its register-staged variant 4-byte aligned
-// pointers and even leading dimensions; anything else (and fp32 operands) goes to the scalar-FMA kernel.
+// operand pointers and leading dimensions that are multiples of 8 elements; its register-staged variant takes elements
+// at any (even) address; longer rows (and fp32 operands) go to the scalar-FMA kernel.
 enum KernelPath { kPathFallback = 0, kPathMfmaStaged = 1, kPathMfmaDirect = 2 };
 
 KernelPath kernel_path(const std::vector<Problem>& ps, int32_t in_dtype, int32_t layout, bool check_pointers = true) {
@@ -79,8 +79,7 @@ KernelPath kernel_path(const std::vector<Problem>& ps, int32_t in_dtype, int32_t
   KernelPath path = kPathMfmaDirect;
   for (const auto& p : ps) {
     const uintptr_t ptrs = check_pointers ? reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B) : 0;
-    if (p.lda > max_lda || p.ldb > max_ldb) return kPathFallback;
-    if ((ptrs & 3) || ((p.lda | p.ldb) & 1)) return kPathFallback;
+    if (p.lda > max_lda || p.ldb > max_ldb || (ptrs & 1)) return kPathFallback;
     if ((ptrs & 15) || ((p.lda | p.ldb) & 7)) path = kPathMfmaStaged;
   }
   return path;
@@ -527,7 +526,9 @@ int32_t gspmd_plan_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
   std::vector<Problem> live;
   for (const auto& p : ps) if (p.Mv > 0) live.push_back(p);
   const KernelPath kp = kernel_path(live, GSPMD_BF16, layout, false);
-  const int32_t path = kp == kPathMfmaDirect ? GSPMD_KERNEL_MFMA : kp == kPathMfmaStaged ? GSPMD_KERNEL_MFMA_STAGED : GSPMD_KERNEL_SCALAR;
+  bool odd = false;             // rows that are not 4-byte aligned are reported as what they were before the staged kernel took them
+  for (const auto& p : live) odd = odd || ((p.lda | p.ldb) & 1);
+  const int32_t path = kp == kPathMfmaDirect ? GSPMD_KERNEL_MFMA : kp == kPathMfmaStaged && !odd ? GSPMD_KERNEL_MFMA_STAGED : GSPMD_KERNEL_SCALAR;
   for (int64_t i = 0; i < std::min<int64_t>(capacity, *count); ++i) {
     const Problem& p = ps[static_cast<size_t>(i)];
     gspmd_gemm_desc& d = descs[i];

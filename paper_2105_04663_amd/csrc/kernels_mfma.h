@@ -97,11 +97,10 @@ __device__ __forceinline__ void zero_rows_below(TOut* __restrict__ C, int ldc, i
   }
 }
 
-// STAGED: the variant for operands whose rows are only 4-byte aligned (an even row stride that is not a multiple of
-// 8 elements, e.g. dense shards of 1250 columns): direct global->LDS loads need 16-byte aligned chunks, so every K
-// tile goes through registers instead -- the path the other variant uses for what is left of K after its assembly
-// loop -- with the next K step's chunks in flight while the current one is multiplied.  Chunks that are only partly
-// valid are loaded 4 bytes at a time, so that no read leaves the rows' valid part by more than one element.
+// STAGED: the variant for operands that are not 16-byte aligned (a row stride that is not a multiple of 8 elements, e.g.
+// dense shards of 1250 or 697 columns): direct global->LDS loads need 16-byte aligned chunks, so every K tile goes
+// through registers instead, in 16-byte loads at element alignment.  No read leaves the rows' valid part: a chunk that
+// would reach past the last valid column is fetched from 8 columns before it and moved down in registers.
 template <typename TOut, int LAYOUT, bool STAGED>
 __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue,
                                                                 float* __restrict__ join_partials, uint32_t* __restrict__ join_counters,
@@ -168,9 +167,8 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
       for (int j = 0; j < 4; ++j) global_to_lds16(bb, b_off[j], sa + kStageA + j * 1024);
     };
     // one 16-byte chunk of a K tile that may be partial: into a register, zero where it lies beyond the valid K (in
-    // BOTH operands: the padding may hold anything).  `cols_valid`: valid columns of a K-major operand, counted like
-    // `c0`, the tile's first column.
-    auto tail_chunk = [&](bool kmajor, const bf16_bits* base, int off, int q, int k0, int c0, int cols_valid) -> u32x4_t {
+    // BOTH operands: the padding may hold anything)
+    auto tail_chunk = [&](bool kmajor, const bf16_bits* base, int off, int q, int k0) -> u32x4_t {
       u32x4_t v = {0u, 0u, 0u, 0u};
       // operands live in global memory: loads through a global (not generic) pointer count in vmcnt only, so waiting for
       // LDS reads does not wait for them
@@ -178,34 +176,12 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
       gptr_t at = (gptr_t)(reinterpret_cast<const unsigned char*>(base) + off);
       if (kmajor) {         // a whole k row per 32 lanes
         const int kr = k0 + q * 2 + (lane >> 5);
-        if (kr < P.Kv) {
-          if constexpr (!STAGED) {
-            v = *(__attribute__((address_space(1))) const u32x4_t*)at;
-          } else {
-            int n = c0 + (((lane & 31) ^ swz_b(q * 2 + (lane >> 5))) << 3);    // the chunk km_load_offset addresses
-            if (n >= cols_valid) n = ((cols_valid - 1) >> 3) << 3;
-            if (n + 8 <= cols_valid) {
-              v = *(__attribute__((address_space(1))) const u32x4_align4_t*)at;
-            } else {
-#pragma unroll
-              for (int d = 0; d < 4; ++d)
-                if (n + 2 * d < cols_valid) v[d] = *(__attribute__((address_space(1))) const uint32_t*)(at + 4 * d);
-            }
-          }
-        }
+        if (kr < P.Kv) v = *(__attribute__((address_space(1))) const u32x4_t*)at;
       } else {              // 8 consecutive k per lane
         const int r = q * 16 + (lane >> 2);
         const int k = k0 + ((lane & 3) ^ swz_a(r)) * 8;
         if (k < P.Kv) {
-          if constexpr (!STAGED) {
-            v = *(__attribute__((address_space(1))) const u32x4_t*)at;
-          } else if (k + 8 <= P.Kv) {
-            v = *(__attribute__((address_space(1))) const u32x4_align4_t*)at;
-          } else {
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-              if (k + 2 * d < P.Kv) v[d] = *(__attribute__((address_space(1))) const uint32_t*)(at + 4 * d);
-          }
+          v = *(__attribute__((address_space(1))) const u32x4_t*)at;
           if (k + 8 > P.Kv) v = mask_tail8(v, P.Kv - k);
         }
       }
@@ -222,8 +198,8 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
         const int q = wn * 4 + j;
         const int ao = AKM ? km_load_offset(q, lane, m0, m_end, P.lda) : kc_load_offset(q, lane, m0, m_end, P.lda);
         const int bo = BKC ? kc_load_offset(q, lane, n0, P.Nv, P.ldb) : km_load_offset(q, lane, n0, P.Nv, P.ldb);
-        ta[j] = tail_chunk(AKM, ab, ao, q, k0, m0, m_end);
-        tb[j] = tail_chunk(!BKC, bb, bo, q, k0, n0, P.Nv);
+        ta[j] = tail_chunk(AKM, ab, ao, q, k0);
+        tb[j] = tail_chunk(!BKC, bb, bo, q, k0);
       }
     };
     auto store_tail = [&](int stage, const u32x4_t (&ta)[4], const u32x4_t (&tb)[4]) {
@@ -268,24 +244,116 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
     };
 
     if constexpr (STAGED) {
-      // ---- every K tile through registers, two tiles (one per wave group) per step; the next step's chunks are in
-      // flight while this step is multiplied
+      // ---- every K tile through registers, two tiles (one per wave group) per step, two pairs of LDS stages: while a step
+      // is multiplied from one pair, the next step's chunks (loaded a step ago) go to the other and the one after is
+      // fetched, so a step has one barrier and the waves' LDS writes, loads and MFMAs overlap
+      // per lane: byte offset of its four chunks of each operand, and by how many elements to move a chunk down that
+      // was fetched early because it would have reached past the last valid column
+      uint32_t ao[4], bo[4], a_shift = 0, b_shift = 0;
+      auto place = [&](bool kmajor, int j, int c0, int valid, int ld, uint32_t& off, uint32_t& shift) {
+        const int q = wn * 4 + j;
+        if (!kmajor) {
+          off = static_cast<uint32_t>(kc_load_offset(q, lane, c0, valid, ld));
+          return;
+        }
+        const int kr = q * 2 + (lane >> 5), c = c0 + (((lane & 31) ^ swz_b(kr)) << 3);
+        const int at = max(0, min(c, valid - 8));
+        off = static_cast<uint32_t>((kr * ld + (at - c0)) * 2);
+        if (c < valid) shift |= static_cast<uint32_t>(c - at) << (j * 4);
+      };
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        place(AKM, j, m0, m_end, P.lda, ao[j], a_shift);
+        place(!BKC, j, n0, P.Nv, P.ldb, bo[j], b_shift);
+      }
+      const bool a_moves = AKM && (m_end & 7) && m0 + kMfmaBM > m_end, b_moves = !BKC && (P.Nv & 7) && n0 + kMfmaBN > P.Nv;
+      const bool tiny = (AKM && m_end < 8) || (!BKC && P.Nv < 8);            // no whole chunk anywhere
+      auto move_down = [](u32x4_t v, uint32_t s) -> u32x4_t {                // by s of 8 elements
+        if (s & 4) v = u32x4_t{v[2], v[3], 0u, 0u};
+        if (s & 2) v = u32x4_t{v[1], v[2], v[3], 0u};
+        if (s & 1) v = u32x4_t{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+        return v;
+      };
+      typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+      typedef __attribute__((address_space(1))) const unsigned char* gbytes_t;
+      auto fetch = [&](int kt, u32x4_t (&ta)[4], u32x4_t (&tb)[4]) {
+        const gbytes_t ab = (gbytes_t)(Abase + kt * a_tile), bb = (gbytes_t)(Bbase + kt * b_tile);
+        const int k0 = kt * kMfmaBK;
+        if (k0 + kMfmaBK <= P.Kv && !tiny) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            ta[j] = *(__attribute__((address_space(1))) const u32x4_any_t*)(ab + static_cast<int64_t>(static_cast<int32_t>(ao[j])));
+            tb[j] = *(__attribute__((address_space(1))) const u32x4_any_t*)(bb + static_cast<int64_t>(static_cast<int32_t>(bo[j])));
+          }
+          return;
+        }
+        // the last, partial tile (or an extent below 8): element by element, zero beyond the valid K in BOTH operands
+        auto chunk = [&](bool kmajor, gbytes_t base, int j, int c0, int valid, int ld) -> u32x4_t {
+          const int q = wn * 4 + j;
+          int c, k;                                                          // first element: along m or n, along K from k0
+          if (kmajor) {
+            k = q * 2 + (lane >> 5);
+            c = c0 + (((lane & 31) ^ swz_b(k)) << 3);
+          } else {
+            const int r = q * 16 + (lane >> 2);
+            c = min(c0 + r, valid - 1);
+            k = ((lane & 3) ^ swz_a(r)) * 8;
+          }
+          u32x4_t v = {0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int ce = kmajor ? c + e : c, ke = kmajor ? k : k + e;
+            if (ce < valid && k0 + ke < P.Kv) {
+              const int64_t at = kmajor ? static_cast<int64_t>(ke) * ld + (ce - c0) : static_cast<int64_t>(ce - c0) * ld + ke;
+              const uint32_t bits = ((__attribute__((address_space(1))) const bf16_bits*)base)[at];
+              v[e >> 1] |= bits << ((e & 1) * 16);
+            }
+          }
+          return v;
+        };
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          ta[j] = chunk(AKM, ab, j, m0, m_end, P.lda);
+          asm volatile("" ::: "memory");
+          tb[j] = chunk(!BKC, bb, j, n0, P.Nv, P.ldb);
+          asm volatile("" ::: "memory");
+        }
+      };
+      auto put = [&](int kt, int stage, u32x4_t (&ta)[4], u32x4_t (&tb)[4]) {
+        if ((kt + 1) * kMfmaBK <= P.Kv && !tiny) {
+          if (a_moves)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ta[j] = move_down(ta[j], (a_shift >> (j * 4)) & 7);
+          if (b_moves)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) tb[j] = move_down(tb[j], (b_shift >> (j * 4)) & 7);
+        }
+        store_tail(stage, ta, tb);
+      };
       const int ntiles = (P.Kv + kMfmaBK - 1) / kMfmaBK;
       u32x4_t ta[4], tb[4];
-      if (wm < ntiles) fetch_tail(wm, ta, tb);
-      for (int kt = 0; kt < ntiles; kt += 2) {
-        const int here = min(2, ntiles - kt);
-        if (wm < here) store_tail(wm, ta, tb);
-        __syncthreads();
-        if (kt + 2 + wm < ntiles) fetch_tail(kt + 2 + wm, ta, tb);
-        read_frags(0);
+      timeline_stamp(rec, 1, t);
+      if (wm < ntiles) {
+        fetch(wm, ta, tb);
+        put(wm, wm, ta, tb);
+      }
+      if (2 + wm < ntiles) fetch(2 + wm, ta, tb);
+      timeline_stamp(rec, 2, t);
+      __syncthreads();
+      timeline_stamp(rec, 3, t);
+      int buf = 0;
+      for (int kt = 0; kt < ntiles; kt += 2, buf ^= 2) {
+        read_frags(buf);
         mma_all();
-        if (here > 1) {
-          read_frags(1);
+        if (kt + 2 + wm < ntiles) put(kt + 2 + wm, (buf ^ 2) + wm, ta, tb);
+        if (kt + 4 + wm < ntiles) fetch(kt + 4 + wm, ta, tb);
+        if (kt + 1 < ntiles) {
+          read_frags(buf + 1);
           mma_all();
         }
         __syncthreads();
       }
+      timeline_stamp(rec, 4, t);
     } else {
     timeline_stamp(rec, 1, t);
     if (nk64 > 0) {
