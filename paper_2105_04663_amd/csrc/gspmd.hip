@@ -123,12 +123,16 @@ int64_t tiles_of(const Problem& p, int bm, int bn) {
 //   32 x 8192 x 8192: 101 / 43, 51, 54     64 x 8192 x 8192: 105 / 62, 47, 65     256 x 8192 x 8192: 135 / 222, 140, 97
 //   32 x 2048 x 16384: 31 / 26, 19, 20     256 x 2048 x 2048: 39 / 22, 13, 17     64 x 1024 x 1024: 14 / 6, 7, 10
 // a workgroup of dot_mfma_kernel takes about 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step, one of dot_split_kernel 4 us
-// and 1.0, 1.3, 1.7 us per round of eight 32-wide steps; rounds of 256 workgroups follow each other.
+// and 1.0, 1.3, 1.7 us per round of eight 32-wide steps; rounds of 256 workgroups follow each other.  Operands that are
+// not 16-byte aligned cost the address unit four times as much: 20 us and 3 us a step in the staged tiles (a few of them
+// on a mostly idle chip), 1.5, 2.0, 2.8 us a round here, whatever the number of rows:
+//   601 x 2001 x 601: 102 / 32, 20, 25     2001 x 1003 x 2001: 75 / 139, 92, 65     301 x 1001 x 301: 54 / 10, 11, 15
 // Partial sums along a contracting mesh dimension keep dot_mfma_kernel's order of summation (`ordered`): the joined sum,
 // the two-launch sum and partials that a caller sums agree bit for bit.
 constexpr int kSplitMaxRows = 256;
 int split_row_blocks(const std::vector<Problem>& ps, KernelPath path, int32_t in_dtype, bool ordered) {
-  if (in_dtype != GSPMD_BF16 || ordered || path != kPathMfmaDirect) return 0;
+  if (in_dtype != GSPMD_BF16 || ordered || path == kPathFallback) return 0;
+  const bool staged = path == kPathMfmaStaged;
   int64_t rows = 0, k = 0, big = 0;
   for (const auto& p : ps) {
     if (p.lda > (1 << 24) || p.ldb > (1 << 24)) return 0;        // 32-bit offsets of 64 rows
@@ -136,15 +140,15 @@ int split_row_blocks(const std::vector<Problem>& ps, KernelPath path, int32_t in
     k = std::max<int64_t>(k, p.Kv);
     big += tiles_of(p, kMfmaBM, kMfmaBN);
   }
-  if (rows == 0 || rows > kSplitMaxRows) return 0;
+  if (rows == 0 || (rows > kSplitMaxRows && !staged)) return 0;
   const double steps64 = static_cast<double>((k + 63) / 64), rounds8 = static_cast<double>((k + 255) / 256);
-  double best = static_cast<double>((big + 255) / 256) * (9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95));
+  double best = static_cast<double>((big + 255) / 256) * (staged ? 20.0 + steps64 * 3.0 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95));
   int blocks = 0;
-  const struct { int blocks; double per_round; } kinds[] = {{1, 1.0}, {2, 1.3}, {4, 1.7}};
+  const struct { int blocks; double aligned, unaligned; } kinds[] = {{1, 1.0, 1.5}, {2, 1.3, 2.0}, {4, 1.7, 2.8}};
   for (const auto& kind : kinds) {
     int64_t tiles = 0;
     for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
-    const double us = static_cast<double>((tiles + 255) / 256) * (4.0 + rounds8 * kind.per_round);
+    const double us = static_cast<double>((tiles + 255) / 256) * (4.0 + rounds8 * (staged ? kind.unaligned : kind.aligned));
     if (us < best) { best = us; blocks = kind.blocks; }
   }
   return blocks;

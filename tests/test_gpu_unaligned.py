@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 SIZES = [   # M, K, N: widths 1..7 past a multiple of 8, below 8, one to three tiles, K around 32- and 64-wide tiles
     (257, 33, 259), (300, 97, 261), (513, 64, 265), (270, 127, 515), (299, 160, 7), (5, 321, 300), (3, 1, 2), (258, 31, 263), (511, 1001, 254),
-    (264, 200, 271),
+    (264, 200, 271), (300, 198, 262), (258, 130, 514), (100, 66, 1026),
 ]
 
 
@@ -25,17 +25,23 @@ def on_device(bits, rows, cols, shift):
     return t, g.ShardBuf(t.data_ptr() + 2 * shift, g.BF16, 0)
 
 
+@pytest.mark.parametrize("partial", [False, True])
 @pytest.mark.parametrize("layout", [0, 1, 2, 3])
-@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("shift", [0, 1, 2])
 @pytest.mark.parametrize("M,K,N", SIZES)
-def test_dense_rows_of_any_width(M, K, N, shift, layout):
+def test_dense_rows_of_any_width(M, K, N, shift, layout, partial):
+    # `partial`: the product as partition 0's partial sum of a contracting dimension of twice the size, which is never
+    # left to the few-row kernel
     ls, rs = ((K, M) if layout & 1 else (M, K)), ((N, K) if layout & 2 else (K, N))
     lc, rc = ((0,) if layout & 1 else (1,)), ((1,) if layout & 2 else (0,))
     lhs, rhs = wl.draw_small_int_bf16(3, ls), wl.draw_small_int_bf16(4, rs)
     ta, a = on_device(lhs, *ls, shift)
     tb, b = on_device(rhs, *rs, (shift * 3) % 8)
-    mesh, dims = g.Mesh((1,), (0,)), g.DotDims((), (), lc, rc)
-    sh = [g.Sharding(s, (-1, -1)) for s in (ls, rs, (M, N))]
+    P = 2 if partial else 1
+    mesh, dims = g.Mesh((P,), tuple(range(P))), g.DotDims((), (), lc, rc)
+    def split(shape, dim):
+        return g.Sharding(tuple(n * P if i == dim else n for i, n in enumerate(shape)), tuple(0 if i == dim and partial else -1 for i in (0, 1)))
+    sh = [split(ls, lc[0]), split(rs, rc[0]), g.Sharding((M, N), (-1, -1))]
     n = g.dot_workspace_bytes(mesh, dims, *sh, 0)
     ws = torch.empty(n + 256, dtype=torch.uint8, device="cuda")
     out = torch.full((M * N + 8,), float("nan"), dtype=torch.float32, device="cuda")
