@@ -11,11 +11,14 @@
 
 #include "../../include/gspmd.h"
 #include "kernels_basic.h"
+#include "kernels_f32.h"
 #include "launch.h"
 #include "plan.h"
 #include "tile_index.h"
 
 using namespace gspmd;
+
+static_assert(kF32Tile == kGenTile && kF32Threads == 256, "dot_f32_kernel and dot_fallback_kernel share their tiles and launch");
 
 namespace {
 
@@ -225,9 +228,14 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       if (!launch_dot_mfma(l, layout, out_dtype, path == kPathMfmaStaged, stream)) return GSPMD_ERR_DEVICE;
     } else {
       const dim3 grid(static_cast<unsigned>(tiles)), block(256);
-      if (in_dtype == GSPMD_F32)
-        hipLaunchKernelGGL((dot_fallback_kernel<float, float>), grid, block, 0, stream, inl, tab, n, layout, epilogue);
-      else if (out_dtype == GSPMD_F32)
+      if (in_dtype == GSPMD_F32) {
+        switch (layout & 3) {
+          case 0: hipLaunchKernelGGL(dot_f32_kernel<0>, grid, block, 0, stream, inl, tab, n, epilogue); break;
+          case 1: hipLaunchKernelGGL(dot_f32_kernel<1>, grid, block, 0, stream, inl, tab, n, epilogue); break;
+          case 2: hipLaunchKernelGGL(dot_f32_kernel<2>, grid, block, 0, stream, inl, tab, n, epilogue); break;
+          default: hipLaunchKernelGGL(dot_f32_kernel<3>, grid, block, 0, stream, inl, tab, n, epilogue);
+        }
+      } else if (out_dtype == GSPMD_F32)
         hipLaunchKernelGGL((dot_fallback_kernel<bf16_bits, float>), grid, block, 0, stream, inl, tab, n, layout, epilogue);
       else
         hipLaunchKernelGGL((dot_fallback_kernel<bf16_bits, bf16_bits>), grid, block, 0, stream, inl, tab, n, layout, epilogue);

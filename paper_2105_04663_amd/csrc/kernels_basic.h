@@ -1,6 +1,5 @@
-// Device kernels that are not MFMA-shaped: the any-layout fallback contraction (fp32 inputs,
-// or bf16 inputs whose pointers/strides do not allow 16-byte loads), the K-partial sum and the
-// shard <-> global copies.  gfx950 only.
+// Device kernels that are not MFMA-shaped: the any-layout fallback contraction (bf16 operands with rows too long for
+// 32-bit offsets inside a tile, or at odd byte addresses), the K-partial sum and the shard <-> global copies.  gfx950 only.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

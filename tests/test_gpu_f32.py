@@ -1,0 +1,62 @@
+"""dot_f32_kernel at the edges of its tiles and K steps, in all four operand layouts, dense and padded rows: small
+integers (exact, compared bit for bit), and random values against float64 with the bound of a float32 sum:
+|error| <= (K + 2) * 2^-24 * sum |a b| for any order of summation."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle import dot as od
+from tests.harness import Staged
+from tests.test_gpu_split import workload
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(1, 1, 1), (3, 31, 5), (64, 32, 64), (65, 33, 63), (63, 64, 65), (8, 64, 23), (130, 100, 67), (200, 5, 129), (128, 257, 192), (70, 1000, 300)]
+
+
+@pytest.mark.parametrize("align", [0, 8])
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,K,N", SIZES)
+def test_f32_tiles(M, K, N, layout, align):
+    w = workload(M, K, N, layout)
+    w.dtype = "f32"
+    rng = np.random.default_rng(5)
+    for exact in (True, False):
+        if exact:
+            lhs, rhs = (rng.integers(-50, 51, size=s).astype(np.float32) for s in (w.lhs_shape, w.rhs_shape))
+        else:
+            lhs, rhs = (rng.uniform(-1, 1, size=s).astype(np.float32) for s in (w.lhs_shape, w.rhs_shape))
+        st = Staged(w, lhs, rhs, row_align=align)                # row padding holds NaN
+        st.run_local(0)
+        got = st.out_shard(0)
+        dims = (w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+        a, b = lhs.astype(np.float64), rhs.astype(np.float64)
+        ref = od.dot_general(a, b, *dims)
+        if exact:
+            assert np.array_equal(got, ref)
+        else:
+            assert (np.abs(got - ref) <= (K + 2) * 2.0 ** -24 * od.dot_general(np.abs(a), np.abs(b), *dims)).all()
+        if align and N % 8:
+            assert bool(torch.isnan(st.out[0][1].view(M, -1)[:, N:]).all())
+
+
+def test_f32_special_values():
+    # infinities and NaNs of the data reach exactly the outputs they belong to; denormal products and operands are kept
+    w = workload(20, 37, 40, 0)
+    w.dtype = "f32"
+    lhs, rhs = np.ones(w.lhs_shape, np.float32), np.ones(w.rhs_shape, np.float32)
+    rhs[36, 3], rhs[0, 39], lhs[7, 36] = np.inf, np.nan, -np.inf
+    st = Staged(w, lhs, rhs, row_align=8)
+    st.run_local(0)
+    got = st.out_shard(0)
+    with np.errstate(invalid="ignore"):
+        ref = np.array([[np.sum(lhs[m].astype(np.float64) * rhs[:, n].astype(np.float64)) for n in range(40)] for m in range(20)])
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[~np.isnan(ref)], ref[~np.isnan(ref)])
+    tiny = np.float32(2.0 ** -140)
+    lhs, rhs = np.zeros(w.lhs_shape, np.float32), np.zeros(w.rhs_shape, np.float32)
+    lhs[:, 0], rhs[0, :] = tiny, 1.0
+    lhs[:, 1], rhs[1, :] = 2.0 ** -70, 2.0 ** -75
+    st = Staged(w, lhs, rhs, row_align=8)
+    st.run_local(0)
+    assert (st.out_shard(0) == float(tiny) + 2.0 ** -145).all()
