@@ -56,14 +56,16 @@ int32_t check_buf(const gspmd_shard_buf* b) {
   return GSPMD_OK;
 }
 
-// Assign tile ids for tile edge (bm, bn) over the VALID extents; returns total tiles or -1 on overflow.
-int64_t assign_tiles(std::vector<Problem>& ps, int bm, int bn) {
+// Assign tile ids for tile edge (bm, bn) over the VALID extents; returns total tiles or -1 on overflow.  `chain`: of joined
+// problems only the first has tiles (the ids after it start where its own end, so a search for the last entry that begins at
+// or before an id never ends at the others).
+int64_t assign_tiles(std::vector<Problem>& ps, int bm, int bn, bool chain = false) {
   int64_t t = 0;
   for (auto& p : ps) {
     const int64_t tm = (static_cast<int64_t>(p.Mv) + bm - 1) / bm, tn = (static_cast<int64_t>(p.Nv) + bn - 1) / bn;
     p.tile_begin = static_cast<int32_t>(t);
     p.tiles_n = static_cast<int32_t>(tn);
-    t += tm * tn;
+    if (!(chain && p.join_count > 1 && p.join_slot > 0)) t += tm * tn;
     if (t > INT32_MAX) return -1;
   }
   return t;
@@ -88,10 +90,6 @@ KernelPath kernel_path(const std::vector<Problem>& ps, int32_t in_dtype, int32_t
   return path;
 }
 
-bool mfma_eligible(const std::vector<Problem>& ps, int32_t in_dtype, int32_t layout) {
-  return kernel_path(ps, in_dtype, layout) != kPathFallback;
-}
-
 // Run the contraction over all live tiles, then the zero fill of what the tiles do not cover.  Output tiles cover
 // the valid extents only (rounded up to whole tiles, the kernel writes zeros inside a partly valid tile): tiles that
 // would only write zeros are not interleaved with live ones, which would leave compute units idle (workgroups are
@@ -109,6 +107,7 @@ struct JoinSpace {
   uint32_t* counters = nullptr;
   float* partials = nullptr;
   int64_t tiles = 0;          // joined output tiles
+  bool chain = false;         // dot_mid_kernel adds the members up in its registers: no counters, no slots
 };
 
 constexpr int64_t kJoinSlack = int64_t(64) << 20;
@@ -119,42 +118,71 @@ int64_t tiles_of(const Problem& p, int bm, int bn) {
   return ((static_cast<int64_t>(p.Mv) + bm - 1) / bm) * ((static_cast<int64_t>(p.Nv) + bn - 1) / bn);
 }
 
-// Row blocks (of 16) per tile if the launch goes to dot_split_kernel, 0 if not.  That kernel splits K over a workgroup's
-// waves, so it suits launches whose time is one workgroup's chain of K steps on a chip that 256 x 256 tiles leave mostly
-// idle: products of at most kSplitMaxRows rows.  The estimates are straight lines through measured times (one problem,
-// bf16, rows x K x N, us; dot_mfma_kernel / dot_split_kernel with 1, 2, 4 row blocks):
-//   32 x 8192 x 8192: 101 / 43, 51, 54     64 x 8192 x 8192: 105 / 62, 47, 65     256 x 8192 x 8192: 135 / 222, 140, 97
-//   32 x 2048 x 16384: 31 / 26, 19, 20     256 x 2048 x 2048: 39 / 22, 13, 17     64 x 1024 x 1024: 14 / 6, 7, 10
-// a workgroup of dot_mfma_kernel takes about 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step, one of dot_split_kernel 4 us
-// and 1.0, 1.3, 1.7 us per round of eight 32-wide steps; rounds of 256 workgroups follow each other.  Operands that are
-// not 16-byte aligned cost the address unit four times as much: 20 us and 3 us a step in the staged tiles (a few of them
-// on a mostly idle chip), 1.5, 2.0, 2.8 us a round here, whatever the number of rows:
+// Which bf16 MFMA kernel a launch takes, and dot_split_kernel's row blocks (of 16) per tile.
+enum MfmaKernel { kMfmaBig, kMfmaMid, kMfmaSplit };
+struct MfmaChoice {
+  MfmaKernel kernel;
+  int row_blocks;
+};
+
+// The three kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
+// a workgroup draws from L2 per flop (a compute unit takes in 50 to 60 GB/s whatever the kernel), so the choice compares
+// estimates: straight lines through measured times (one problem, bf16, rows x K x N, us;
+// dot_mfma_kernel / dot_mid_kernel / dot_split_kernel with 1, 2, 4 row blocks):
+//   32 x 8192 x 8192: 101 / - / 43, 51, 54        64 x 8192 x 8192: 105 / - / 62, 47, 65      256 x 8192 x 8192: 135 / - / 222, 140, 97
+//   32 x 2048 x 16384: 31 / - / 26, 19, 20        64 x 1024 x 1024: 14 / - / 6, 7, 10         256 x 2048 x 2048: 39 / 29 / 22, 13, 17
+//   512 x 2048 x 2048: 39 / 27 / 41, 24, 16       1024 x 1024 x 4096: 23 / 19 / 89, 59, 40    512 x 512 x 512: 13 / 9
+//   1024 x 4096 x 1024: 69 / 49    2048 x 2048 x 2048: 40 / 29    2048 x 2048 x 4096: 41 / 49    1024 x 8192 x 8192: 140 / 177
+// dot_mfma_kernel: rounds of 256 workgroups of 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step; the slots of joined problems add
+//   8 us and 0.08 us per contribution to an output tile (2048 x 8192 x 2048 over 4 members, 256 contributions: 78 us, of which the K
+//   loops are 30; 299 x 4032 x 2112 over 4 members, 96 contributions: 42 us).
+// dot_mid_kernel: 8 us and 0.28 us per 32-wide step while a compute unit has one workgroup, 0.62 us with two, then rounds of 512; the members
+//   of a joined sum follow each other in one workgroup, 1 us apart (the sums above: 75 and 48 us; 828 x 6464 x 3648 over 8 members: 82 instead of 109).  Two K-contiguous operands come in half lines:
+//   a quarter more per step (two members of 1024 x 4096 x 2048 on 2 partitions: 105 us against 91).
+// dot_split_kernel: rounds of 256 workgroups of 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  Its order of summation is another one:
+//   partial sums along a contracting mesh dimension (`ordered`) stay with the first two, so that the joined sum, the two-launch sum and
+//   partials that a caller sums agree bit for bit; and beyond 256 rows it is taken from K = 1024 on (below, dot_mid_kernel is within 4 us).
+// Operands that are not 16-byte aligned take the first or the third, and cost the address unit four times as much: 20 us
+// and 3 us a step in the staged tiles (a few of them on a mostly idle chip), 1.5, 2.0, 2.8 us a round in the split kernel:
 //   601 x 2001 x 601: 102 / 32, 20, 25     2001 x 1003 x 2001: 75 / 139, 92, 65     301 x 1001 x 301: 54 / 10, 11, 15
-// Partial sums along a contracting mesh dimension keep dot_mfma_kernel's order of summation (`ordered`): the joined sum,
-// the two-launch sum and partials that a caller sums agree bit for bit.
-constexpr int kSplitMaxRows = 256;
-int split_row_blocks(const std::vector<Problem>& ps, KernelPath path, int32_t in_dtype, bool ordered) {
-  if (in_dtype != GSPMD_BF16 || ordered || path == kPathFallback) return 0;
+// While a timeline is recorded launches that dot_mid_kernel would take stay with dot_mfma_kernel (same results).
+constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
+MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
+  MfmaChoice choice{kMfmaBig, 0};
   const bool staged = path == kPathMfmaStaged;
-  int64_t rows = 0, k = 0, big = 0;
+  int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1, chain_k = 0;
+  bool short_ld = true;
   for (const auto& p : ps) {
-    if (p.lda > (1 << 24) || p.ldb > (1 << 24)) return 0;        // 32-bit offsets of 64 rows
+    short_ld = short_ld && p.lda <= (1 << 24) && p.ldb <= (1 << 24);      // 32-bit offsets of 64 rows
     rows = std::max<int64_t>(rows, p.Mv);
     k = std::max<int64_t>(k, p.Kv);
     big += tiles_of(p, kMfmaBM, kMfmaBN);
+    if (p.join_slot == 0) {
+      mid += tiles_of(p, kMidTile, kMidTile);
+      members = std::max<int64_t>(members, p.join_count);
+    }
   }
-  if (rows == 0 || (rows > kSplitMaxRows && !staged)) return 0;
-  const double steps64 = static_cast<double>((k + 63) / 64), rounds8 = static_cast<double>((k + 255) / 256);
-  double best = static_cast<double>((big + 255) / 256) * (staged ? 20.0 + steps64 * 3.0 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95));
-  int blocks = 0;
-  const struct { int blocks; double aligned, unaligned; } kinds[] = {{1, 1.0, 1.5}, {2, 1.3, 2.0}, {4, 1.7, 2.8}};
-  for (const auto& kind : kinds) {
-    int64_t tiles = 0;
-    for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
-    const double us = static_cast<double>((tiles + 255) / 256) * (4.0 + rounds8 * (staged ? kind.unaligned : kind.aligned));
-    if (us < best) { best = us; blocks = kind.blocks; }
+  if (rows == 0) return choice;
+  chain_k = k * members;
+  const double rounds = static_cast<double>((big + 255) / 256), steps64 = static_cast<double>((k + 63) / 64);
+  double best = rounds * (staged ? 20.0 + steps64 * 3.0 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) + (members > 1 ? 8.0 + 0.08 * static_cast<double>(big) : 0.0);
+  if (!staged && g_timeline.load(std::memory_order_acquire) == nullptr) {
+    const double steps32 = static_cast<double>((chain_k + 31) / 32);
+    const bool half_lines = !(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
+    const double us = static_cast<double>((mid + 511) / 512) * (8.0 + static_cast<double>(members) + steps32 * (mid <= 256 ? 0.28 : 0.62) * (half_lines ? 1.25 : 1.0));
+    if (us < 0.95 * best) { best = us; choice.kernel = kMfmaMid; }
   }
-  return blocks;
+  if (!ordered && short_ld && (staged || rows <= kSplitAnyKRows || k >= kSplitMinK)) {
+    const double rounds8 = static_cast<double>((k + 255) / 256);
+    const struct { int blocks; double aligned, unaligned; } kinds[] = {{1, 1.0, 1.5}, {2, 1.3, 2.0}, {4, 1.7, 2.8}};
+    for (const auto& kind : kinds) {
+      int64_t tiles = 0;
+      for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
+      const double us = static_cast<double>((tiles + 255) / 256) * (4.0 + rounds8 * (staged ? kind.unaligned : kind.aligned));
+      if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks}; }
+    }
+  }
+  return choice;
 }
 
 int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dtype, int32_t out_dtype, int32_t epilogue,
@@ -168,13 +196,17 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   const KernelPath path = kernel_path(ps, in_dtype, layout);
   const bool mfma = path != kPathFallback;
   if (join && !mfma) return GSPMD_ERR_UNSUPPORTED;              // the caller checks before it joins problems
-  const int split = join ? 0 : split_row_blocks(ps, path, in_dtype, ordered);
-  const int bm = split ? 16 * split : mfma ? kMfmaBM : kGenTile, bn = split ? kSplitBN : mfma ? kMfmaBN : kGenTile;
+  // joined problems come with the caller's choice between the two kernels that keep the order of summation
+  const MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : mfma ? choose_mfma(ps, path, layout, ordered) : MfmaChoice{kMfmaBig, 0};
+  const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
+  const bool mid = choice.kernel == kMfmaMid;
+  const int bm = split ? 16 * split : mid ? kMidTile : mfma ? kMfmaBM : kGenTile;
+  const int bn = split ? kSplitBN : mid ? kMidTile : mfma ? kMfmaBN : kGenTile;
   // Workgroups start in tile order and the launch ends when the last one does: problems whose tiles take longest
   // (the most K steps) go first, so that the compute units that are still busy at the end are busy with short tiles.
   if (!join)
     std::stable_sort(ps.begin(), ps.end(), [](const Problem& a, const Problem& b) { return a.Kv > b.Kv; });
-  const int64_t tiles = assign_tiles(ps, bm, bn);
+  const int64_t tiles = assign_tiles(ps, bm, bn, mid);
   if (tiles < 0) return GSPMD_ERR_UNSUPPORTED;
   std::vector<ZeroRect> rects;
   for (const auto& p : all) {
@@ -217,6 +249,9 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, g_timeline.load(std::memory_order_acquire),
                          g_timeline_records.load(std::memory_order_acquire)};
       if (!launch_dot_split(l, layout, out_dtype, split, stream)) return GSPMD_ERR_DEVICE;
+    } else if (mid) {
+      const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
+      if (!launch_dot_mid(l, layout, out_dtype, join != nullptr, stream)) return GSPMD_ERR_DEVICE;
     } else if (mfma) {
       if (join && join->tiles > 0) {
         const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((join->tiles + 255) / 256, 1024));
@@ -778,14 +813,16 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
       }
       if (!ok) break;
     }
+    JoinSpace js;
     if (ok) {
       std::vector<Problem> live;
       for (const auto& q : joined) if (q.Mv > 0) live.push_back(q);
-      ok = mfma_eligible(live, in_dtype, jlayout);
+      const KernelPath path = kernel_path(live, in_dtype, jlayout);
+      ok = path != kPathFallback;
+      js.chain = path == kPathMfmaDirect && choose_mfma(live, path, jlayout, true).kernel == kMfmaMid;
     }
     const int64_t table_area = partial_base - static_cast<char*>(workspace);
-    if (ok && table_area + joined_bytes(jtiles, jslots) <= workspace_bytes) {
-      JoinSpace js;
+    if (ok && (js.chain || table_area + joined_bytes(jtiles, jslots) <= workspace_bytes)) {
       js.counters = reinterpret_cast<uint32_t*>(partial_base);
       js.partials = reinterpret_cast<float*>(partial_base + round_up(jtiles * 4, kWsAlign));
       js.tiles = jtiles;

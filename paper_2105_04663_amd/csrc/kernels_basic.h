@@ -88,17 +88,23 @@ __device__ __forceinline__ T copy_from_kernarg(const GSPMD_KERNARG T* p) {
   return out;
 }
 
-// The problem that owns output tile `tile`, from the table in device memory if there is one, else from the table in
-// the kernel arguments (an InlineProblems as first parameter).
-__device__ __forceinline__ Problem lookup_problem(const Problem* __restrict__ tab, int n_prob, int tile) {
-  if (tab) return tab[find_problem(tab, n_prob, tile)];
+// The problem that owns output tile `tile`: its place in the table in device memory if there is one, else in the table in
+// the kernel arguments (an InlineProblems as first parameter), and an entry of whichever table that is.
+__device__ __forceinline__ int lookup_problem_index(const Problem* __restrict__ tab, int n_prob, int tile) {
+  if (tab) return find_problem(tab, n_prob, tile);
   const GSPMD_KERNARG Problem* inl = first_kernel_argument<Problem>();
   int lo = 0, hi = n_prob - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (inl[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
   }
-  return copy_from_kernarg(inl + lo);
+  return lo;
+}
+__device__ __forceinline__ Problem problem_at(const Problem* __restrict__ tab, int i) {
+  return tab ? tab[i] : copy_from_kernarg(first_kernel_argument<Problem>() + i);
+}
+__device__ __forceinline__ Problem lookup_problem(const Problem* __restrict__ tab, int n_prob, int tile) {
+  return problem_at(tab, lookup_problem_index(tab, n_prob, tile));
 }
 
 // Profiling aid (gspmd_set_tile_timeline): one record of eight 64-bit words per workgroup, written by its thread 0.

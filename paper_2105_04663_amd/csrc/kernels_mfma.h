@@ -34,38 +34,11 @@
 #include "kernels_basic.h"
 #include "launch.h"
 #include "mainloop_asm.h"
+#include "mfma_common.h"
 #include "plan.h"
 #include "tile_index.h"
 
 namespace gspmd {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) short short4_t;
-typedef __attribute__((ext_vector_type(8))) short short8_t;
-typedef __attribute__((ext_vector_type(16))) float float16_t;
-typedef __attribute__((ext_vector_type(4))) float float4_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
-typedef __attribute__((address_space(3))) short4_t lds_short4_t;
-
-// s_waitcnt immediate for gfx9: vmcnt [3:0]+[15:14], expcnt [6:4], lgkmcnt [11:8]
-constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | ((lgkm & 15) << 8); }
-#define GSPMD_WAIT_ALL() __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0))
-
-// 16 bytes per lane from sbase + voff (bytes) straight into LDS at lds_addr + lane*16.  The compiler
-// does not see this as an LDS write: every consumer is ordered by an explicit s_waitcnt vmcnt + barrier.
-__device__ __forceinline__ void global_to_lds16(const void* sbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
-}
-
-__device__ __forceinline__ u32x4_t mask_tail8(u32x4_t v, int keep) {   // keep first `keep` of 8 bf16
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const uint32_t m = (2 * d + 1 < keep) ? 0xffffffffu : ((2 * d < keep) ? 0x0000ffffu : 0u);
-    v[d] &= m;
-  }
-  return v;
-}
 
 // 16 bytes from an address that is only 4-byte aligned
 typedef uint32_t u32x4_align4_t __attribute__((ext_vector_type(4), aligned(4)));

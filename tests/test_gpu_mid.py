@@ -1,0 +1,66 @@
+"""dot_mid_kernel (128 x 128 tiles) at the edges of its tiles, of its five LDS stages and of the 32-wide K tiles, in all four
+operand layouts, and its sums over a contracting mesh dimension (members one after the other in one workgroup).  Every
+product is given as a partial sum of a contracting dimension, so that the few-row kernel does not take it; small
+integers and float32 output: compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2105_04663_amd as g
+import workloads as wl
+from oracle import dot as od
+from tests.harness import Staged, out_tensor
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [   # M, K, N: K of 0 to 13 whole tiles with and without a partial one
+    (128, 32, 128), (129, 31, 127), (1, 33, 300), (130, 64, 8), (200, 95, 136), (257, 128, 129), (127, 160, 384), (300, 161, 260), (140, 192, 64),
+    (260, 200, 70), (64, 224, 500), (384, 416, 256), (100, 500, 100),
+]
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,K,N", SIZES)
+def test_partial_product(M, K, N, layout):
+    lhs_shape, rhs_shape = ((2 * K, M) if layout & 1 else (M, 2 * K)), ((N, 2 * K) if layout & 2 else (2 * K, N))
+    lc, rc = ((0,) if layout & 1 else (1,)), ((1,) if layout & 2 else (0,))
+    w = wl.DotWorkload(name="mid", cfg=7, dtype="bf16", out_dtype="f32", lhs_shape=lhs_shape, rhs_shape=rhs_shape, lhs_batch=(), rhs_batch=(),
+                       lhs_contract=lc, rhs_contract=rc, mesh_shape=(2,), device_ids=(1, 0),
+                       lhs_map=(0, -1) if layout & 1 else (-1, 0), rhs_map=(-1, 0) if layout & 2 else (0, -1), out_map=(-1, -1))
+    lhs, rhs = wl.draw_small_int_bf16(3, lhs_shape), wl.draw_small_int_bf16(4, rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=8, share_replicas=False)       # row padding holds NaN
+    a, b = wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs)
+    dims = (w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    for pid in range(2):
+        st.run_local(pid)
+        assert np.array_equal(st.out_shard(pid), od.expected_partial(a, b, dims, w.mesh_shape, w.device_ids, w.lhs_map, w.rhs_map, pid))
+        assert bool(torch.isnan(st.out[pid][1].view(M, -1)[:, N:]).all())
+
+
+@pytest.mark.parametrize("scatter", [False, True])
+@pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,K,N,P", [(300, 999, 264, 3), (129, 2048, 520, 8), (500, 70, 130, 4), (257, 33, 200, 5)])
+def test_sums_of_members(M, K, N, P, out_dtype, scatter):
+    # K split unevenly (with (257, 33, .., 5) the last member has 5 of 7 positions, with (500, 70, .., 4) 16 of 18)
+    w = wl.ksplit(M=M, K=K, N=N, P=P)
+    w.out_map = (-1, 0) if scatter else (-1, -1)
+    lhs, rhs = wl.draw_normal_bf16(5, w.lhs_shape), wl.draw_normal_bf16(6, w.rhs_shape)
+    whole = wl.ksplit(M=M, K=K, N=N, P=P)
+    st = Staged(whole, lhs, rhs, row_align=8, out_dtype="f32", share_replicas=True)
+    total = None
+    for pid in range(P):                                              # ((p0 + p1) + p2) + .. of the members' own products
+        tmp = torch.full((M * st.out[pid][2],), float("nan"), device="cuda")
+        st.run_local(pid, out_override=g.ShardBuf.of(tmp, st.out[pid][2]))
+        part = tmp.view(M, -1)[:, :N].clone()
+        total = part if total is None else total + part
+    total = total.clamp_min(0)
+    st2 = Staged(w, lhs, rhs, row_align=8, out_dtype=out_dtype)
+    st2.run_grouped(epilogue=1)
+    torch.cuda.synchronize()
+    per = -(-N // P)
+    for pid in range(P):
+        got = out_tensor(st2, pid)
+        want = torch.zeros(got.shape, device="cuda")
+        cols = total[:, pid * per:(pid + 1) * per] if scatter else total
+        want[:, :cols.shape[1]] = cols
+        assert torch.equal(got, want.to(got.dtype)), f"partition {pid}"
