@@ -4,6 +4,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 from dataclasses import dataclass
+from operator import is_ as _same
 from typing import List, Optional, Sequence, Tuple
 
 F32, BF16 = 0, 1
@@ -74,21 +75,22 @@ def load_library():
     lib.gspmd_status_string.argtypes = [C.c_int32]
     pm, ps, pd, pb = C.POINTER(_CMesh), C.POINTER(_CSharding), C.POINTER(_CDotDims), C.POINTER(_CShardBuf)
     pi64, pi32 = C.POINTER(C.c_int64), C.POINTER(C.c_int32)
+    pbs = C.c_void_p       # array of shard buffers (_bufs)
     lib.gspmd_shard_bounds.argtypes = [pm, ps, C.c_int64, pi64, pi64, pi64]
     lib.gspmd_classify_dot.argtypes = [pm, pd, ps, ps, ps, pi32]
     lib.gspmd_dot_workspace_bytes.argtypes = [pm, pd, ps, ps, ps, C.c_int64, C.c_int32, pi64]
     lib.gspmd_local_dot.argtypes = [pm, pd, pb, ps, pb, ps, pb, ps, C.c_int64, pi64, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
-    lib.gspmd_grouped_dot.argtypes = [pm, pd, pb, ps, pb, ps, pb, ps, pi64, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
-    lib.gspmd_grouped_dot_noalloc.argtypes = [pm, pd, pb, ps, pb, ps, pb, ps, pi64, C.c_int32, C.c_void_p]
+    lib.gspmd_grouped_dot.argtypes = [pm, pd, pbs, ps, pbs, ps, pbs, ps, pi64, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
+    lib.gspmd_grouped_dot_noalloc.argtypes = [pm, pd, pbs, ps, pbs, ps, pbs, ps, pi64, C.c_int32, C.c_void_p]
     lib.gspmd_reduce_partials.argtypes = [C.POINTER(C.c_void_p), C.c_int32, C.c_int64, C.c_void_p, C.c_int32, C.c_void_p]
     lib.gspmd_shard_extract.argtypes = [pm, ps, C.c_int64, C.c_void_p, pb, C.c_uint32, C.c_void_p]
     lib.gspmd_shard_assemble.argtypes = [pm, ps, C.c_int64, pb, C.c_void_p, C.c_void_p]
     lib.gspmd_infer_out_sharding.argtypes = [pm, pd, ps, ps, pi32, pi64, pi32]
     lib.gspmd_reshard_workspace_bytes.argtypes = [pm, pi64]
-    lib.gspmd_reshard.argtypes = [pm, ps, pb, ps, pb, C.c_void_p, C.c_int64, C.c_void_p]
+    lib.gspmd_reshard.argtypes = [pm, ps, pbs, ps, pbs, C.c_void_p, C.c_int64, C.c_void_p]
     lib.gspmd_compatible_operand_shardings.argtypes = [pm, pd, ps, ps, ps, pi32, pi32]
     lib.gspmd_resharded_dot_workspace_bytes.argtypes = [pm, pd, ps, ps, ps, C.c_int32, pi64]
-    lib.gspmd_resharded_dot.argtypes = [pm, pd, pb, ps, pb, ps, pb, ps, pi64, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
+    lib.gspmd_resharded_dot.argtypes = [pm, pd, pbs, ps, pbs, ps, pbs, ps, pi64, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
     lib.gspmd_plan_dot.argtypes = [pm, pd, ps, ps, ps, C.c_int64, C.c_int64, C.c_int64, C.c_int64, pi64,
                                    C.POINTER(_CGemmDesc), C.c_int64, pi64]
     lib.gspmd_set_tile_timeline.argtypes = [C.c_void_p, C.c_int64]
@@ -115,15 +117,46 @@ def _i32(vals: Sequence[int]):
     return (C.c_int32 * max(1, len(vals)))(*[int(v) for v in vals])
 
 
+class _Marshalled:
+    """Keeps the C form of an object's fields, which is most of what a small call costs (13 of 23 us for a Dot over 4
+    partitions), for as long as the fields are the very tuples of plain ints it was made from: those cannot change, and
+    are held here.  Anything else (lists, other integer types) is marshalled anew for every call."""
+
+    def _fields(self):
+        raise NotImplementedError
+
+    def _make(self):
+        raise NotImplementedError
+
+    def _c(self):
+        fields = self._fields()
+        held = self.__dict__.get("_held")
+        if held is not None and all(map(_same, held[0], fields)):
+            return held[1]
+        made = self._make()          # (C structure, the arrays it points to)
+        if all(type(f) is tuple and all(type(v) is int for v in f) for f in fields):
+            self._held = (fields, made[0], made[1])
+        else:
+            self._keep = made[1]
+            self.__dict__.pop("_held", None)
+        return made[0]
+
+    def __getstate__(self):          # copies and pickles leave the C form behind
+        return {k: v for k, v in self.__dict__.items() if k not in ("_held", "_keep")}
+
+
 @dataclass
-class Mesh:
+class Mesh(_Marshalled):
     """Device mesh: shape and the row-major tensor of partition ids."""
     shape: Tuple[int, ...]
     device_ids: Tuple[int, ...]
 
-    def _c(self):
-        self._keep = (_i64(self.shape), _i64(self.device_ids))
-        return _CMesh(len(self.shape), self._keep[0], self._keep[1])
+    def _fields(self):
+        return (self.shape, self.device_ids)
+
+    def _make(self):
+        keep = (_i64(self.shape), _i64(self.device_ids))
+        return _CMesh(len(self.shape), keep[0], keep[1]), keep
 
     @property
     def n_partitions(self) -> int:
@@ -134,29 +167,35 @@ class Mesh:
 
 
 @dataclass
-class Sharding:
+class Sharding(_Marshalled):
     """mesh_split annotation: unpartitioned shape and dims_mapping (-1 = not split)."""
     global_shape: Tuple[int, ...]
     dims_mapping: Tuple[int, ...]
 
-    def _c(self):
-        self._keep = (_i64(self.global_shape), _i32(self.dims_mapping))
+    def _fields(self):
+        return (self.global_shape, self.dims_mapping)
+
+    def _make(self):
+        keep = (_i64(self.global_shape), _i32(self.dims_mapping))
         rank = len(self.global_shape) if len(self.global_shape) == len(self.dims_mapping) else -1
-        return _CSharding(rank, self._keep[0], self._keep[1])
+        return _CSharding(rank, keep[0], keep[1]), keep
 
 
 @dataclass
-class DotDims:
+class DotDims(_Marshalled):
     lhs_batch: Tuple[int, ...]
     rhs_batch: Tuple[int, ...]
     lhs_contract: Tuple[int, ...]
     rhs_contract: Tuple[int, ...]
 
-    def _c(self):
-        self._keep = (_i32(self.lhs_batch), _i32(self.rhs_batch), _i32(self.lhs_contract), _i32(self.rhs_contract))
+    def _fields(self):
+        return (self.lhs_batch, self.rhs_batch, self.lhs_contract, self.rhs_contract)
+
+    def _make(self):
+        keep = tuple(_i32(f) for f in self._fields())
         nb = len(self.lhs_batch) if len(self.lhs_batch) == len(self.rhs_batch) else -1
         nc = len(self.lhs_contract) if len(self.lhs_contract) == len(self.rhs_contract) else -1
-        return _CDotDims(nb, self._keep[0], self._keep[1], nc, self._keep[2], self._keep[3])
+        return _CDotDims(nb, keep[0], keep[1], nc, keep[2], keep[3]), keep
 
 
 @dataclass
@@ -183,10 +222,11 @@ class ShardBuf:
 
 
 def _bufs(bufs: Sequence[ShardBuf]):
-    arr = (_CShardBuf * max(1, len(bufs)))()
-    for i, b in enumerate(bufs):
-        arr[i] = b._c()
-    return arr
+    """Array of _CShardBuf, written as the three 64-bit words of each (little endian: the dtype is the low half of its word)."""
+    words = []
+    for b in bufs:
+        words += (b.data or 0, b.dtype, b.row_stride)
+    return (C.c_int64 * max(3, len(words)))(*words)
 
 
 def shard_bounds(mesh: Mesh, sharding: Sharding, partition_id: int):
