@@ -620,6 +620,8 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
     } else {
       // fp32: a row of the wave's block is 256 bytes, of which a lane holds 16 per 16-column block.  Staged through the
       // wave's LDS slice in two passes of 64 rows (rows padded to 272 bytes) and stored 16 lanes per row: whole rows.
+      // Whole tiles without the hint: fp32 outputs are mostly partial sums that the next kernel reads (four partials of
+      // 2048 x 4096 and their sum: 127.1 -> 125.2 us).
       constexpr int kPitch = 272;
       unsigned char* slice = smem + wave * (128 * 144);
       global_u32x4_t* c0 = (global_u32x4_t*)(Cg + static_cast<int64_t>(m0 + wm * 128 + (lane >> 4)) * P.ldc + n0 + wn * 64 + (lane & 15) * 4);
@@ -646,13 +648,13 @@ __global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProb
         for (int i = 0; i < 16; ++i) v[i] = *reinterpret_cast<const u32x4_t*>(slice + (i * 4 + (lane >> 4)) * kPitch + (lane & 15) * 16);
         if (whole) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) __builtin_nontemporal_store(v[i], &c0[(pass * 16 + i) * pitch4]);
+          for (int i = 0; i < 16; ++i) c0[(pass * 16 + i) * pitch4] = v[i];
         } else if (all_cols) {
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int row = wm * 128 + pass * 64 + i * 4 + (lane >> 4);
             if (row >= rows_own) v[i] = u32x4_t{0u, 0u, 0u, 0u};
-            if (row < rows_write) __builtin_nontemporal_store(v[i], &c0[(pass * 16 + i) * pitch4]);
+            if (row < rows_write) c0[(pass * 16 + i) * pitch4] = v[i];
           }
         } else {
           const int col = n0 + wn * 64 + (lane & 15) * 4;                      // this lane's 4 columns
