@@ -27,10 +27,10 @@
  *   - Tensors are row-major.  A shard buffer has the STATIC shard shape (ceil(D/n) per split dimension,
  *     Section 4.1), whatever the partition's valid length.  Padding may hold anything, including NaN: no value at
  *     an index >= the valid length of any dimension reaches a result.  Reads stay inside the rows of the valid
- *     region: the MFMA kernels load 16 bytes at a time, so when a row's valid length is not a multiple of 8 elements
- *     the chunk that holds its last valid elements is loaded whole (from inside the row's own allocation, which the
- *     required row stride of a multiple of 8 elements guarantees) and the excess is discarded or zeroed in
- *     registers.  The padded part of outputs is written as zeros.
+ *     region: where row strides are multiples of 8 elements the bf16 MFMA kernels load 16 bytes at a time, so when a row's
+ *     valid length is not a multiple of 8 the chunk that holds its last valid elements is loaded whole (from inside the
+ *     row's own allocation, which that row stride guarantees) and the excess is discarded or zeroed in registers; other
+ *     operands, and float32 ones, are read up to their last valid element and no further.  The padded part of outputs is written as zeros.
  */
 #ifndef GSPMD_H_
 #define GSPMD_H_
@@ -109,8 +109,8 @@ typedef struct {
  * row_stride: distance in elements between consecutive indices of the second-to-last
  * dimension; 0 means dense (= static size of the last dimension).  Outer dimensions are
  * dense on top of it.  A row_stride that is a multiple of 8 elements together with a
- * 16-byte aligned pointer selects the fastest MFMA kernel for bf16 (an even row_stride with a 4-byte aligned pointer
- * its register-staged variant, see gspmd_kernel_path); an operand whose contiguous dimension
+ * 16-byte aligned pointer selects the fastest MFMA kernels for bf16; rows of any other width take kernels that load at
+ * element alignment (a third of the rate on large products); an operand whose contiguous dimension
  * is contracted runs fastest when its rows start on 128-byte lines (row_stride a multiple of 64
  * elements: 9 % faster than a multiple of 8 that is not, at 8200 against 8256).  data may be NULL only for a
  * tensor with a zero-size dimension (no elements: nothing is read or written). */
@@ -173,13 +173,13 @@ typedef struct {
   int32_t reserved;
 } gspmd_gemm_desc;
 
-/* Which contraction kernel the leading dimensions allow (the slowest one any GEMM of a launch needs is used for
- * the whole launch).  bf16 operands whose rows are not even 4-byte aligned, and fp32 operands, take the scalar kernel,
- * which is a correctness path many times slower than the other two. */
+/* What the leading dimensions of bf16 operands allow the contraction (the least that any GEMM of a launch allows holds for
+ * the whole launch).  Within each class the library chooses kernel and tile by size. */
 typedef enum {
-  GSPMD_KERNEL_SCALAR = 0,       /* 64 x 64 tiles, fp32 FMA */
+  GSPMD_KERNEL_SCALAR = 0,       /* rows only 2-byte aligned (odd lda or ldb): MFMA at element alignment, slowest per flop;
+                                    leading dimensions too long for 32-bit offsets inside a tile: 64 x 64 tiles, fp32 FMA */
   GSPMD_KERNEL_MFMA_STAGED = 1,  /* MFMA, operand tiles through registers: lda and ldb even (rows 4-byte aligned) */
-  GSPMD_KERNEL_MFMA = 2          /* MFMA, direct global->LDS loads: lda and ldb multiples of 8 elements */
+  GSPMD_KERNEL_MFMA = 2          /* MFMA, 16-byte aligned operand loads: lda and ldb multiples of 8 elements */
 } gspmd_kernel_path;
 
 /* Utility for inspection and tests: the per-partition program of Section 4 made explicit.

@@ -401,8 +401,8 @@ template <> struct ElementVec<uint32_t> { typedef uint32_t type __attribute__((e
 // Measured, one box, against kernels that moved such rows element by element with divisions: 6000 x 10000 bf16 between
 // two shardings on a 2 x 4 mesh (240 MB, rows of 2500 and 5000) 1.7 -> 6.8 TB/s; 1000000 x 24 0.2 -> 2.3; aligned AllGather of 537 MB
 // 5.8 -> 8.2 (repeated calls, partly from the memory-side cache); cutting a 16384 x 8192 shard 1.6 -> 8.2; cutting
-// 3000 x 2500 of 6000 x 10000 (30 MB) 20.3 -> 9 us.
-constexpr int kMoveUnroll = 4;
+// 3000 x 2500 of 6000 x 10000 (30 MB) 20.3 -> 7.7 us.
+constexpr int kMoveUnroll = 4;       // (8: 231 us, 2: 209, 1: 212 for the 17 moves that take 196 with 4)
 template <typename T, typename ShapePtr, typename BoxPtr, typename SrcOf>
 __device__ __forceinline__ void move_body(ShapePtr sp, BoxPtr bp, SrcOf src_of) {
   constexpr int V = 16 / static_cast<int>(sizeof(T));
@@ -491,6 +491,7 @@ struct InlineReshard {
   const void* src[kInlineReshardSrc];
   MoveBox d[kInlineReshardDescs];
 };
+static_assert(sizeof(InlineReshard) + 2 * sizeof(void*) <= 4096, "kernel arguments");
 
 template <typename T>
 __global__ __launch_bounds__(256) void reshard_kernel(const InlineReshard inl, const MoveBox* __restrict__ boxes,
