@@ -398,7 +398,7 @@ template <> struct ElementVec<uint32_t> { typedef uint32_t type __attribute__((e
 // takes this path.  A chunk that crosses into another src shard or out of the row or its valid extent goes element by
 // element.  Stores carry the non-temporal hint; loads do not (a misaligned load's line is wanted by the next lane's load
 // too: with the hint 3.8 instead of 5.9 TB/s on the reshard below).
-// Measured, one box, against kernels that moved such rows element by element with divisions: 6000 x 10000 bf16 between
+// Measured on one card against kernels that moved such rows element by element with divisions: 6000 x 10000 bf16 between
 // two shardings on a 2 x 4 mesh (240 MB, rows of 2500 and 5000) 1.7 -> 6.8 TB/s; 1000000 x 24 0.2 -> 2.3; aligned AllGather of 537 MB
 // 5.8 -> 8.2 (repeated calls, partly from the memory-side cache); cutting a 16384 x 8192 shard 1.6 -> 8.2; cutting
 // 3000 x 2500 of 6000 x 10000 (30 MB) 20.3 -> 7.7 us.
