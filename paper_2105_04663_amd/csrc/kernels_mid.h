@@ -243,11 +243,8 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   }
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears)
-  if (m0 + kMidTile >= P.Mv) {
-    const int rows_end = rows_cleared(P.Mv, P.Ms), w = min(n0 + kMidTile, P.Ns) - n0;
-    for (int64_t i = t; w > 0 && i < static_cast<int64_t>(rows_end - P.Mv) * w; i += kMidThreads)
-      C[(P.Mv + i / w) * P.ldc + n0 + i % w] = TOut(0);
-  }
+  if (m0 + kMidTile >= P.Mv)
+    zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n0, min(n0 + kMidTile, P.Ns), t);
 }
 
 template <typename TOut, int LAYOUT, bool CHAIN>

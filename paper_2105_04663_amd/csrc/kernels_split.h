@@ -299,13 +299,8 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
   // down, and whole tile columns of padding, the fill kernel clears)
   const int col_end = min(n_nom + BN, P.Ns);
   const int m_done = min(m_nom + BM, P.Mv);
-  for (int c = n0 + BN, w = col_end - c, i = t; w > 0 && i < (m_done - m_nom) * w; i += kSplitThreads)
-    C[static_cast<int64_t>(m_nom + i / w) * P.ldc + c + i % w] = TOut(0);
-  if (m_done == P.Mv) {
-    const int rows_end = rows_cleared(P.Mv, P.Ms), w = col_end - n_nom;
-    for (int64_t i = t; w > 0 && i < static_cast<int64_t>(rows_end - P.Mv) * w; i += kSplitThreads)
-      C[(P.Mv + i / w) * P.ldc + n_nom + i % w] = TOut(0);
-  }
+  if (n0 < n_nom) zero_block<kSplitThreads, TOut>(C, P.ldc, m_nom, m_done, n0 + BN, col_end, t);
+  if (m_done == P.Mv) zero_block<kSplitThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n_nom, col_end, t);
   if (rec != nullptr) {
     timeline_stamp(rec, 6, t);
     __builtin_amdgcn_s_waitcnt(0);
