@@ -341,7 +341,9 @@ int32_t gspmd_resharded_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
  * aligned, owned by the caller, who clears it and keeps it alive until the launches have finished;
  * NULL or n_records 0 switches the timeline off (the default; the kernel then skips the stamps on one uniform branch).
  * The setting is process-wide, not per stream: launches that overlap write to the same records, and a launch recorded
- * into a HIP graph keeps the buffer it was recorded with.  Results of the Dot are unchanged.  Returns GSPMD_ERR_BAD_BUFFER for a misaligned pointer or a count outside [0, 2^31). */
+ * into a HIP graph keeps the buffer it was recorded with.  Results of the Dot are unchanged.  The kernels of 256 x 256 tiles
+ * and of split K write records; bf16 launches that otherwise run in 128 x 128 tiles run in 256 x 256 tiles, which add up in the
+ * same order, while the timeline is on, and float32 operands leave none.  Returns GSPMD_ERR_BAD_BUFFER for a misaligned pointer or a count outside [0, 2^31). */
 int32_t gspmd_set_tile_timeline(void* device_records, int64_t n_records);
 
 #ifdef __cplusplus

@@ -145,7 +145,8 @@ struct MfmaChoice {
 // Operands that are not 16-byte aligned take the first or the third, and cost the address unit four times as much: 20 us
 // and 3 us a step in the staged tiles (a few of them on a mostly idle chip), 1.5, 2.0, 2.8 us a round in the split kernel:
 //   601 x 2001 x 601: 102 / 32, 20, 25     2001 x 1003 x 2001: 75 / 139, 92, 65     301 x 1001 x 301: 54 / 10, 11, 15
-// While a timeline is recorded launches that dot_mid_kernel would take stay with dot_mfma_kernel (same results).
+// While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
+// (with_records): the choice is the same with and without, so results are.
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   MfmaChoice choice{kMfmaBig, 0};
@@ -166,7 +167,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   chain_k = k * members;
   const double rounds = static_cast<double>((big + 255) / 256), steps64 = static_cast<double>((k + 63) / 64);
   double best = rounds * (staged ? 20.0 + steps64 * 3.0 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) + (members > 1 ? 8.0 + 0.08 * static_cast<double>(big) : 0.0);
-  if (!staged && g_timeline.load(std::memory_order_acquire) == nullptr) {
+  if (!staged) {
     const double steps32 = static_cast<double>((chain_k + 31) / 32);
     const bool half_lines = !(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
     const double us = static_cast<double>((mid + 511) / 512) * (8.0 + static_cast<double>(members) + steps32 * (mid <= 256 ? 0.28 : 0.62) * (half_lines ? 1.25 : 1.0));
@@ -185,6 +186,13 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   return choice;
 }
 
+// dot_mid_kernel's launches while a timeline is recorded: dot_mfma_kernel, which takes whatever dot_mid_kernel takes and adds up
+// in the same order.
+MfmaChoice with_records(MfmaChoice choice) {
+  if (choice.kernel == kMfmaMid && g_timeline.load(std::memory_order_acquire) != nullptr) choice.kernel = kMfmaBig;
+  return choice;
+}
+
 int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dtype, int32_t out_dtype, int32_t epilogue,
                         bool ordered, void* workspace, int64_t workspace_bytes, hipStream_t stream, const JoinSpace* join = nullptr) {
   // problems with an empty static output block write nothing
@@ -197,7 +205,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   const bool mfma = path != kPathFallback;
   if (join && !mfma) return GSPMD_ERR_UNSUPPORTED;              // the caller checks before it joins problems
   // joined problems come with the caller's choice between the two kernels that keep the order of summation
-  const MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : mfma ? choose_mfma(ps, path, layout, ordered) : MfmaChoice{kMfmaBig, 0};
+  const MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : mfma ? with_records(choose_mfma(ps, path, layout, ordered)) : MfmaChoice{kMfmaBig, 0};
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
   const bool mid = choice.kernel == kMfmaMid;
   const int bm = split ? 16 * split : mid ? kMidTile : mfma ? kMfmaBM : kGenTile;
@@ -819,7 +827,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
       for (const auto& q : joined) if (q.Mv > 0) live.push_back(q);
       const KernelPath path = kernel_path(live, in_dtype, jlayout);
       ok = path != kPathFallback;
-      js.chain = path == kPathMfmaDirect && choose_mfma(live, path, jlayout, true).kernel == kMfmaMid;
+      js.chain = path == kPathMfmaDirect && with_records(choose_mfma(live, path, jlayout, true)).kernel == kMfmaMid;
     }
     const int64_t table_area = partial_base - static_cast<char*>(workspace);
     if (ok && (js.chain || table_area + joined_bytes(jtiles, jslots) <= workspace_bytes)) {

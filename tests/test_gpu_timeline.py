@@ -65,6 +65,24 @@ def test_timeline_records_every_workgroup_and_leaves_results_alone(split_k):
     assert int(rec.abs().sum().item()) == 0
 
 
+@pytest.mark.parametrize("M,K,N", [(1024, 2048, 2048), (512, 1100, 4096), (300, 1032, 2000)])
+def test_results_do_not_depend_on_the_timeline(M, K, N):
+    # sizes on either side of where the three kernels meet, K long enough for any of them; N(0, 1) data, so another order
+    # of summation shows in the last bits of a float32 output
+    w = wl.mesh2d(M=M, K=K, N=N, X=1, Y=1, cfg=9)
+    st = Staged(w, wl.draw_normal_bf16(1, (M, K)), wl.draw_normal_bf16(2, (K, N)), row_align=8, out_dtype="f32")
+    plain = _dot(st)
+    rec = torch.zeros(64 * g.TILE_TIMELINE_WORDS, dtype=torch.int64, device="cuda")
+    g.set_tile_timeline(rec.data_ptr(), 64)
+    try:
+        timed = _dot(st)
+    finally:
+        g.set_tile_timeline(0, 0)
+    for a, b in zip(plain, timed):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert int((rec != 0).sum().item()) > 0
+
+
 def test_timeline_rejects_a_misaligned_buffer():
     rec = torch.zeros(64, dtype=torch.int64, device="cuda")
     with pytest.raises(g.GspmdError) as e:
