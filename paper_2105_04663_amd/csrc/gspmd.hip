@@ -14,6 +14,7 @@
 #include "kernels_f32.h"
 #include "launch.h"
 #include "plan.h"
+#include "testing.h"
 #include "tile_index.h"
 
 using namespace gspmd;
@@ -118,12 +119,16 @@ int64_t tiles_of(const Problem& p, int bm, int bn) {
   return ((static_cast<int64_t>(p.Mv) + bm - 1) / bm) * ((static_cast<int64_t>(p.Nv) + bn - 1) / bn);
 }
 
-// Which bf16 MFMA kernel a launch takes, and dot_split_kernel's row blocks (of 16) per tile.
-enum MfmaKernel { kMfmaBig, kMfmaMid, kMfmaSplit };
+// Which kernel a bf16 launch takes, and dot_split_kernel's row blocks (of 16) per tile.
+enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_TESTING_MFMA, kMfmaMid = GSPMD_TESTING_MID, kMfmaSplit = GSPMD_TESTING_SPLIT };
 struct MfmaChoice {
   MfmaKernel kernel;
   int row_blocks;
 };
+
+// What this thread's launches are pinned to, and what its last one took (testing.h).
+thread_local gspmd_testing_launch t_pin{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE};
+thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE};
 
 // The three kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
 // a workgroup draws from L2 per flop (a compute unit takes in 50 to 60 GB/s whatever the kernel), so the choice compares
@@ -146,7 +151,7 @@ struct MfmaChoice {
 // and 3 us a step in the staged tiles (a few of them on a mostly idle chip), 1.5, 2.0, 2.8 us a round in the split kernel:
 //   601 x 2001 x 601: 102 / 32, 20, 25     2001 x 1003 x 2001: 75 / 139, 92, 65     301 x 1001 x 301: 54 / 10, 11, 15
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
-// (with_records): the choice is the same with and without, so results are.
+// (pick_kernel): the choice is the same with and without, so results are.
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   MfmaChoice choice{kMfmaBig, 0};
@@ -186,9 +191,14 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   return choice;
 }
 
-// dot_mid_kernel's launches while a timeline is recorded: dot_mfma_kernel, which takes whatever dot_mid_kernel takes and adds up
-// in the same order.
-MfmaChoice with_records(MfmaChoice choice) {
+// The kernel of a launch of bf16 problems: by the rule above, unless a test has pinned one that may take them.  While a timeline
+// is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
+MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
+  if (path == kPathFallback) return MfmaChoice{kMfmaNone, 0};
+  const MfmaKernel pin = static_cast<MfmaKernel>(t_pin.kernel);
+  if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && path == kPathMfmaDirect) || (pin == kMfmaSplit && !ordered))
+    return MfmaChoice{pin, t_pin.row_blocks};
+  MfmaChoice choice = choose_mfma(ps, path, layout, ordered);
   if (choice.kernel == kMfmaMid && g_timeline.load(std::memory_order_acquire) != nullptr) choice.kernel = kMfmaBig;
   return choice;
 }
@@ -202,10 +212,11 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   std::vector<Problem> ps;
   for (const auto& p : all) if (p.Mv > 0) ps.push_back(p);      // Mv, Nv, Kv are all zero or all positive
   const KernelPath path = kernel_path(ps, in_dtype, layout);
-  const bool mfma = path != kPathFallback;
-  if (join && !mfma) return GSPMD_ERR_UNSUPPORTED;              // the caller checks before it joins problems
+  if (join && path == kPathFallback) return GSPMD_ERR_UNSUPPORTED;      // the caller checks before it joins problems
   // joined problems come with the caller's choice between the two kernels that keep the order of summation
-  const MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : mfma ? with_records(choose_mfma(ps, path, layout, ordered)) : MfmaChoice{kMfmaBig, 0};
+  const MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : pick_kernel(ps, path, layout, ordered);
+  const bool mfma = choice.kernel != kMfmaNone;
+  t_last = gspmd_testing_launch{choice.kernel, choice.row_blocks, join ? 1 : 0};
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
   const bool mid = choice.kernel == kMfmaMid;
   const int bm = split ? 16 * split : mid ? kMidTile : mfma ? kMfmaBM : kGenTile;
@@ -221,7 +232,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
     if (p.join_slot > 0) continue;                              // one of the joined problems speaks for their common output
     // rows that the contraction kernel's tiles write or clear; the MFMA kernel's last tile row also clears up to
     // kRowsBelow rows below its footprint
-    const int32_t rows_done = mfma || split ? rows_cleared(p.Mv, p.Ms)
+    const int32_t rows_done = mfma ? rows_cleared(p.Mv, p.Ms)
                                    : static_cast<int32_t>(std::min<int64_t>(p.Ms, (static_cast<int64_t>(p.Mv) + bm - 1) / bm * bm));
     const int32_t cols_done = static_cast<int32_t>(std::min<int64_t>(p.Ns, (static_cast<int64_t>(p.Nv) + bn - 1) / bn * bn));
     if (rows_done < p.Ms) rects.push_back(ZeroRect{p.C, p.ldc, rows_done, p.Ms, 0, p.Ns, 0});
@@ -825,9 +836,9 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     if (ok) {
       std::vector<Problem> live;
       for (const auto& q : joined) if (q.Mv > 0) live.push_back(q);
-      const KernelPath path = kernel_path(live, in_dtype, jlayout);
-      ok = path != kPathFallback;
-      js.chain = path == kPathMfmaDirect && with_records(choose_mfma(live, path, jlayout, true)).kernel == kMfmaMid;
+      const MfmaKernel kernel = pick_kernel(live, kernel_path(live, in_dtype, jlayout), jlayout, true).kernel;
+      ok = kernel != kMfmaNone && t_pin.one_launch != 0;
+      js.chain = kernel == kMfmaMid;
     }
     const int64_t table_area = partial_base - static_cast<char*>(workspace);
     if (ok && (js.chain || table_area + joined_bytes(jtiles, jslots) <= workspace_bytes)) {
@@ -1307,6 +1318,21 @@ int32_t gspmd_resharded_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
   const int64_t left = workspace_bytes - (ws - static_cast<char*>(workspace));
   return gspmd_grouped_dot(mesh, dims, luse, &l2, ruse, &r2, out_shards, out_sh, lhs_fill, epilogue, ws, left, hip_stream);
 } catch (...) { return GSPMD_ERR_HOST_MEMORY; }
+
+int32_t gspmd_testing_pin(const gspmd_testing_launch* pin) {
+  if (!pin) return GSPMD_ERR_NULL;
+  const bool split = pin->kernel == GSPMD_TESTING_SPLIT;
+  if (pin->kernel < GSPMD_TESTING_BY_RULE || pin->kernel > GSPMD_TESTING_SPLIT || pin->one_launch < GSPMD_TESTING_BY_RULE || pin->one_launch > 1 ||
+      (split ? pin->row_blocks != 1 && pin->row_blocks != 2 && pin->row_blocks != 4 : pin->row_blocks != 0)) return GSPMD_ERR_UNSUPPORTED;
+  t_pin = *pin;
+  return GSPMD_OK;
+}
+
+int32_t gspmd_testing_last(gspmd_testing_launch* last) {
+  if (!last) return GSPMD_ERR_NULL;
+  *last = t_last;
+  return GSPMD_OK;
+}
 
 int32_t gspmd_set_tile_timeline(void* device_records, int64_t n_records) try {
   if (n_records < 0 || n_records > INT32_MAX) return GSPMD_ERR_BAD_BUFFER;
