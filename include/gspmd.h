@@ -176,9 +176,8 @@ typedef struct {
 /* What the leading dimensions of bf16 operands allow the contraction (the least that any GEMM of a launch allows holds for
  * the whole launch).  Within each class the library chooses kernel and tile by size. */
 typedef enum {
-  GSPMD_KERNEL_SCALAR = 0,       /* rows only 2-byte aligned (odd lda or ldb): MFMA at element alignment, slowest per flop;
-                                    leading dimensions too long for 32-bit offsets inside a tile: 64 x 64 tiles, fp32 FMA */
-  GSPMD_KERNEL_MFMA_STAGED = 1,  /* MFMA, operand tiles through registers: lda and ldb even (rows 4-byte aligned) */
+  GSPMD_KERNEL_SCALAR = 0,       /* leading dimensions too long for 32-bit offsets inside a tile: 64 x 64 tiles, fp32 FMA */
+  GSPMD_KERNEL_MFMA_STAGED = 1,  /* MFMA, operands loaded at element alignment: any other lda and ldb */
   GSPMD_KERNEL_MFMA = 2          /* MFMA, 16-byte aligned operand loads: lda and ldb multiples of 8 elements */
 } gspmd_kernel_path;
 

@@ -592,9 +592,7 @@ int32_t gspmd_plan_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
   std::vector<Problem> live;
   for (const auto& p : ps) if (p.Mv > 0) live.push_back(p);
   const KernelPath kp = kernel_path(live, GSPMD_BF16, layout, false);
-  bool odd = false;             // rows that are not 4-byte aligned are reported as what they were before the staged kernel took them
-  for (const auto& p : live) odd = odd || ((p.lda | p.ldb) & 1);
-  const int32_t path = kp == kPathMfmaDirect ? GSPMD_KERNEL_MFMA : kp == kPathMfmaStaged && !odd ? GSPMD_KERNEL_MFMA_STAGED : GSPMD_KERNEL_SCALAR;
+  const int32_t path = kp == kPathMfmaDirect ? GSPMD_KERNEL_MFMA : kp == kPathMfmaStaged ? GSPMD_KERNEL_MFMA_STAGED : GSPMD_KERNEL_SCALAR;
   for (int64_t i = 0; i < std::min<int64_t>(capacity, *count); ++i) {
     const Problem& p = ps[static_cast<size_t>(i)];
     gspmd_gemm_desc& d = descs[i];
