@@ -147,9 +147,11 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 // dot_split_kernel: rounds of 256 workgroups of 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  Its order of summation is another one:
 //   partial sums along a contracting mesh dimension (`ordered`) stay with the first two, so that the joined sum, the two-launch sum and
 //   partials that a caller sums agree bit for bit; and beyond 256 rows it is taken from K = 1024 on (below, dot_mid_kernel is within 4 us).
-// Operands that are not 16-byte aligned take the first or the third, and cost the address unit four times as much: 20 us
-// and 3 us a step in the staged tiles (a few of them on a mostly idle chip), 1.5, 2.0, 2.8 us a round in the split kernel:
-//   601 x 2001 x 601: 102 / 32, 20, 25     2001 x 1003 x 2001: 75 / 139, 92, 65     301 x 1001 x 301: 54 / 10, 11, 15
+// Operands that are not 16-byte aligned take the first or the third, and cost the address unit four times as much: 10.5 us
+// and 2.1 us a step in the staged tiles, 1.5, 2.0, 2.4 us a round in the split kernel (staged / 1, 2, 4 row blocks):
+//   601 x 2001 x 601: 78 / 25, 15, 20     2001 x 1003 x 2001: 45 / 136, 82, 59     301 x 1001 x 301: 45 / 9, 10, 14
+//   3826 x 102 x 538: 14 / 35, 25, 21     482 x 111 x 5292: 14 / 50, 34, 25        2289 x 293 x 885: 21 / 35, 23, 17
+//   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
 // (pick_kernel): the choice is the same with and without, so results are.
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
@@ -171,7 +173,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (rows == 0) return choice;
   chain_k = k * members;
   const double rounds = static_cast<double>((big + 255) / 256), steps64 = static_cast<double>((k + 63) / 64);
-  double best = rounds * (staged ? 20.0 + steps64 * 3.0 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) + (members > 1 ? 8.0 + 0.08 * static_cast<double>(big) : 0.0);
+  double best = rounds * (staged ? 10.5 + steps64 * 2.1 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) + (members > 1 ? 8.0 + 0.08 * static_cast<double>(big) : 0.0);
   if (!staged) {
     const double steps32 = static_cast<double>((chain_k + 31) / 32);
     const bool half_lines = !(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
@@ -180,7 +182,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   }
   if (!ordered && short_ld && (staged || rows <= kSplitAnyKRows || k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((k + 255) / 256);
-    const struct { int blocks; double aligned, unaligned; } kinds[] = {{1, 1.0, 1.5}, {2, 1.3, 2.0}, {4, 1.7, 2.8}};
+    const struct { int blocks; double aligned, unaligned; } kinds[] = {{1, 1.0, 1.5}, {2, 1.3, 2.0}, {4, 1.7, 2.4}};
     for (const auto& kind : kinds) {
       int64_t tiles = 0;
       for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);

@@ -71,6 +71,38 @@ def test_dense_rows_of_any_width(M, K, N, layout, kernel, row_blocks):
 
 @gpu
 @pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,N", [(259, 263), (70, 9)])
+@pytest.mark.parametrize("K", [2, 7, 8, 9, 15, 16, 17, 31, 33, 39, 40, 41, 65, 71, 72, 73, 95, 97, 105])
+def test_staged_tiles_that_k_ends_in(K, M, N, layout):
+    # the last tile's chunks reach up to 31 positions past the valid K and are fetched from before it, below 8 element by element
+    with pinned(MFMA):
+        unaligned.test_dense_rows_of_any_width(M, K, N, 1, layout, False)
+        assert last() == (MFMA, 0, 0)
+
+
+@gpu
+@pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("epilogue", [0, 1])
+def test_staged_tiles_store_rows_of_any_width(epilogue, out_dtype):
+    # shards of 301 x 177 (the last ones 300 x 177, 301 x 175), rows 187 elements apart: 16-byte stores at any element, zeros in the
+    # static block's padding, nothing between the rows
+    w = wl.mesh2d(M=601, K=203, N=529, X=2, Y=3, cfg=7)
+    lhs, rhs = wl.draw_small_int_bf16(5, w.lhs_shape), wl.draw_small_int_bf16(6, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=11, out_dtype=out_dtype)
+    with pinned(MFMA):
+        st.run_grouped(epilogue=epilogue)
+        assert last() == (MFMA, 0, 0)
+    ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    ref = np.maximum(ref, 0.0) if epilogue else ref
+    if out_dtype == "bf16":
+        ref = torch.from_numpy(ref).to(torch.bfloat16).double().numpy()      # integers: exact in fp32, one rounding
+    for pid in range(6):
+        assert np.array_equal(st.out_shard(pid), od.expected_out_shard(ref, w.mesh_shape, w.device_ids, w.out_map, pid))
+        assert bool(torch.isnan(st.out[pid][1].view(301, 187)[:, 177:]).all())
+
+
+@gpu
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
 @pytest.mark.parametrize("M,K,N", mid.SIZES)
 def test_mid_kernel_partial_product(M, K, N, layout):
     with pinned(MID):
