@@ -124,6 +124,7 @@ enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_T
 struct MfmaChoice {
   MfmaKernel kernel;
   int row_blocks;
+  double us = 0.0;            // what the launch is estimated to take
 };
 
 // What this thread's launches are pinned to, and what its last one took (testing.h).
@@ -139,10 +140,12 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   512 x 2048 x 2048: 39 / 27 / 41, 24, 16       1024 x 1024 x 4096: 23 / 19 / 89, 59, 40    512 x 512 x 512: 13 / 9
 //   1024 x 4096 x 1024: 69 / 49    2048 x 2048 x 2048: 40 / 29    2048 x 2048 x 4096: 41 / 49    1024 x 8192 x 8192: 140 / 177
 // dot_mfma_kernel: rounds of 256 workgroups of 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step; the slots of joined problems add
-//   8 us and 0.08 us per contribution to an output tile (2048 x 8192 x 2048 over 4 members, 256 contributions: 78 us, of which the K
-//   loops are 30; 299 x 4032 x 2112 over 4 members, 96 contributions: 42 us).
+//   4.6 us per member (the last arriver at a tile reads the others' contributions one after the other) and 0.05 us per contribution to an
+//   output tile.  Measured beyond the launch without slots: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38;
+//   4, 676: 37; 8, 16: 38; 8, 512: 59; 8, 640: 67.
 // dot_mid_kernel: 8 us and 0.28 us per 32-wide step while a compute unit has one workgroup, 0.62 us with two, then rounds of 512; the members
-//   of a joined sum follow each other in one workgroup, 1 us apart (the sums above: 75 and 48 us; 828 x 6464 x 3648 over 8 members: 82 instead of 109).  Two K-contiguous operands come in half lines:
+//   of a joined sum follow each other in one workgroup, 1 us apart (2048 x 8192 x 2048 over 4 members: 77 us, 299 x 4032 x 2112 over 4: 49, 828 x
+//   6464 x 3648 over 8: 82; with slots 79, 42 and 102).  Two K-contiguous operands come in half lines:
 //   a quarter more per step (two members of 1024 x 4096 x 2048 on 2 partitions: 105 us against 91).
 // dot_split_kernel: rounds of 256 workgroups of 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  Its order of summation is another one:
 //   partial sums along a contracting mesh dimension (`ordered`) stay with the first two, so that the joined sum, the two-launch sum and
@@ -173,7 +176,8 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (rows == 0) return choice;
   chain_k = k * members;
   const double rounds = static_cast<double>((big + 255) / 256), steps64 = static_cast<double>((k + 63) / 64);
-  double best = rounds * (staged ? 10.5 + steps64 * 2.1 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) + (members > 1 ? 8.0 + 0.08 * static_cast<double>(big) : 0.0);
+  double best = rounds * (staged ? 10.5 + steps64 * 2.1 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) +
+                (members > 1 ? 4.6 * static_cast<double>(members) + 0.05 * static_cast<double>(big) : 0.0);
   if (!staged) {
     const double steps32 = static_cast<double>((chain_k + 31) / 32);
     const bool half_lines = !(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
@@ -190,7 +194,19 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
       if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks}; }
     }
   }
+  choice.us = best;
   return choice;
+}
+
+// What forming the members' products by themselves adds to their launch `two` (dense fp32 partials, then a sum kernel per out
+// buffer): 2 us, 3.5 us per kernel and 0.31 us per MB of partials written and read back, 0.9 where rows of partials that are not
+// 16-byte aligned go out element by element.  Sums over a contracting mesh dimension take whichever way is estimated faster; the
+// results are the same.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19; 659 x 4880 x 1316
+// over 2: 51 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x 508 x 4085
+// over 2, unaligned: 36 / 48; 1953 x 409 x 454 over 4: 15 / 20; 828 x 6464 x 3648 over 8: 81 / 74; 4023 x 8430 x 1215 over 8: 142 / 158.
+double apart_us(MfmaKernel two, bool staged, int64_t cols, int64_t partial_bytes, int64_t launches) {
+  const bool by_element = two == kMfmaBig && !staged && (cols & 3);
+  return 2.0 + 3.5 * static_cast<double>(launches) + (by_element ? 0.9e-6 : 0.31e-6) * static_cast<double>(partial_bytes);
 }
 
 // The kernel of a launch of bf16 problems: by the rule above, unless a test has pinned one that may take them.  While a timeline
@@ -753,7 +769,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
   const bool scatter_by_columns = scatter && n_contracting_dims == 1 && r.nrf == 1 && out_sh->dims_mapping[last_out] >= 0 &&
                                   cls[out_sh->dims_mapping[last_out]] == GSPMD_AXIS_CONTRACTING_SCATTER;
   if (contracting && (!scatter || scatter_by_columns) && in_dtype == GSPMD_BF16) {
-    std::vector<Problem> joined;
+    std::vector<Problem> joined, apart;           // the sum in one launch; the members' products by themselves
     int32_t jlayout = 0;
     int64_t jtiles = 0, jslots = 0;
     bool ok = true;
@@ -776,6 +792,8 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
         ok = base[m].size() == base[0].size();
       }
       if (!ok) break;
+      for (const auto& list : base)
+        for (const auto& q : list) if (q.Mv > 0) apart.push_back(q);
       // one round per owner of output columns: the one shared buffer, or every member's own slice
       for (size_t owner = 0; ok && owner < (scatter ? members.size() : 1); ++owner) {
         std::vector<std::vector<Problem>> pm = base;
@@ -836,9 +854,23 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     if (ok) {
       std::vector<Problem> live;
       for (const auto& q : joined) if (q.Mv > 0) live.push_back(q);
-      const MfmaKernel kernel = pick_kernel(live, kernel_path(live, in_dtype, jlayout), jlayout, true).kernel;
-      ok = kernel != kMfmaNone && t_pin.one_launch != 0;
-      js.chain = kernel == kMfmaMid;
+      const MfmaChoice one = pick_kernel(live, kernel_path(live, in_dtype, jlayout), jlayout, true);
+      js.chain = one.kernel == kMfmaMid;
+      ok = one.kernel != kMfmaNone;
+      if (ok && t_pin.one_launch >= 0) {
+        ok = t_pin.one_launch == 1;
+      } else if (ok && !apart.empty()) {
+        const KernelPath path = kernel_path(apart, in_dtype, jlayout);
+        const MfmaChoice two = pick_kernel(apart, path, jlayout, true);
+        int64_t partial_bytes = 0, launches = 0;
+        bool summable = true;       // the sum kernels take so many partials, those of members without any K among them
+        for (int64_t e : elems) partial_bytes += 4 * e;
+        for (const auto& kv : groups) {
+          launches += scatter ? static_cast<int64_t>(kv.second.size()) : 1;
+          summable = summable && kv.second.size() <= static_cast<size_t>(kMaxPartials);
+        }
+        ok = !summable || one.us <= 1.05 * (two.us + apart_us(two.kernel, path == kPathMfmaStaged, apart[0].Ns, partial_bytes, launches));
+      }
     }
     const int64_t table_area = partial_base - static_cast<char*>(workspace);
     if (ok && (js.chain || table_area + joined_bytes(jtiles, jslots) <= workspace_bytes)) {

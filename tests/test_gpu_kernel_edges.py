@@ -224,3 +224,27 @@ def test_sums_of_unaligned_members(one_launch):
     assert torch.equal(st.out[0][1][:300 * 201], total)
     ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
     parity.check(st.out_shard(0), ref)
+
+
+@gpu
+@pytest.mark.parametrize("row_align", [8, 0])
+def test_sum_over_more_members_than_the_sum_kernels_take(row_align):
+    # 40 partitions share 5 positions of K: 35 of them have nothing to add, and only the one-launch sum can leave them out
+    w = wl.ksplit(M=70, K=5, N=75, P=40)
+    lhs, rhs = wl.draw_small_int_bf16(5, w.lhs_shape), wl.draw_small_int_bf16(6, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=row_align, out_dtype="f32")
+    st.run_grouped()
+    ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    assert np.array_equal(st.out_shard(0), ref)
+
+
+@gpu
+@pytest.mark.parametrize("M,K,N,P,row_align,one_launch", [(141, 7248, 463, 8, 8, 0), (659, 4880, 1316, 2, 8, 0), (727, 205, 74, 8, 0, 0),
+                                                          (2048, 8192, 2048, 4, 8, 0), (1953, 409, 454, 4, 8, 1), (4023, 8430, 1215, 8, 8, 1),
+                                                          (1335, 508, 4085, 2, 0, 1)])
+def test_sums_take_the_way_that_measured_faster(M, K, N, P, row_align, one_launch):
+    # sizes at which one way took at most 0.9 of the other's time when the rule was made
+    w = wl.ksplit(M=M, K=K, N=N, P=P)
+    st = Staged(w, np.zeros(w.lhs_shape, dtype=np.uint16), np.zeros(w.rhs_shape, dtype=np.uint16), row_align=row_align)
+    st.run_grouped()
+    assert last()[2] == one_launch
