@@ -225,7 +225,10 @@ def _bufs(bufs: Sequence[ShardBuf]):
     """Array of _CShardBuf, written as the three 64-bit words of each (little endian: the dtype is the low half of its word)."""
     words = []
     for b in bufs:
-        words += (b.data or 0, b.dtype, b.row_stride)
+        data = b.data
+        if data is not None and not isinstance(data, int):       # an address; not whatever turns into an integer, as a tensor does
+            raise TypeError("cannot be converted to pointer")
+        words += (data or 0, b.dtype, b.row_stride)
     return (C.c_int64 * max(3, len(words)))(*words)
 
 

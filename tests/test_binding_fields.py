@@ -1,9 +1,15 @@
 """The binding keeps the C form of meshes, shardings and dimension numbers between calls; whatever happens to the Python
 objects in between, a call sees their present values (host only)."""
 import copy
+import ctypes as C
 import pickle
 
+import numpy as np
+import pytest
+import torch
+
 import paper_2105_04663_amd as g
+from paper_2105_04663_amd import binding
 
 
 def test_present_values_count():
@@ -27,3 +33,17 @@ def test_copies_and_pickles():
     for m, s, d in ((copy.deepcopy(mesh), copy.copy(sh), copy.deepcopy(dims)), pickle.loads(pickle.dumps((mesh, sh, dims)))):
         assert (m, s, d) == (mesh, sh, dims)
         assert g.shard_bounds(m, s, 3) == g.shard_bounds(mesh, sh, 3)
+
+
+@pytest.mark.parametrize("data", [torch.tensor(4096), np.int64(4096), 4096.0, "4096", C.c_void_p(4096)])
+def test_only_an_address_is_an_address(data):
+    # a tensor in place of its data_ptr() must not turn into an address by way of its value; one shard or several
+    mesh, dims = g.Mesh((1,), (0,)), g.DotDims((), (), (1,), (0,))
+    sh = g.Sharding((8, 8), (-1, -1))
+    good, bad = g.ShardBuf(4096, g.BF16), g.ShardBuf(data, g.BF16)
+    with pytest.raises(TypeError):
+        g.grouped_dot(mesh, dims, [good], sh, [bad], sh, [good], sh)
+    with pytest.raises(TypeError):
+        g.local_dot(mesh, dims, good, sh, bad, sh, good, sh, 0)
+    with pytest.raises(TypeError):
+        g.reshard(mesh, sh, [good], sh, [bad])
