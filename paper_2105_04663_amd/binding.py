@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
 from dataclasses import dataclass
 from operator import is_ as _same
 from typing import List, Optional, Sequence, Tuple
@@ -45,6 +46,11 @@ class _CDotDims(C.Structure):
 
 class _CShardBuf(C.Structure):
     _fields_ = [("data", C.c_void_p), ("dtype", C.c_int32), ("row_stride", C.c_int64)]
+
+
+# what _bufs writes its words by
+if (sys.byteorder, C.sizeof(_CShardBuf), _CShardBuf.data.offset, _CShardBuf.dtype.offset, _CShardBuf.row_stride.offset) != ("little", 24, 0, 8, 16):
+    raise ImportError("unexpected layout of gspmd_shard_buf")
 
 
 class _CGemmDesc(C.Structure):

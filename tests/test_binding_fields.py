@@ -47,3 +47,10 @@ def test_only_an_address_is_an_address(data):
         g.local_dot(mesh, dims, good, sh, bad, sh, good, sh, 0)
     with pytest.raises(TypeError):
         g.reshard(mesh, sh, [good], sh, [bad])
+
+
+def test_shard_arrays_have_the_structures_layout():
+    bufs = [g.ShardBuf(2**63 + 5, g.BF16, 8), g.ShardBuf(None, g.F32), g.ShardBuf(4096, g.BF16, 2**40), g.ShardBuf(0, True, 0)]
+    arr = C.cast(binding._bufs(bufs), C.POINTER(binding._CShardBuf))
+    for i, b in enumerate(bufs):
+        assert (arr[i].data, arr[i].dtype, arr[i].row_stride) == (b.data or None, int(b.dtype), b.row_stride)
