@@ -79,7 +79,8 @@ enum KernelPath { kPathFallback = 0, kPathMfmaStaged = 1, kPathMfmaDirect = 2 };
 
 KernelPath kernel_path(const std::vector<Problem>& ps, int32_t in_dtype, int32_t layout, bool check_pointers = true) {
   if (in_dtype != GSPMD_BF16) return kPathFallback;
-  // 32-bit byte offsets inside a tile: 256 rows of a K-contiguous operand, 32 of a K-major one
+  // 32-bit byte offsets inside a tile: 256 rows of a K-contiguous operand (at most 64 in dot_split_kernel, 128 in dot_mid_kernel), 32 of
+  // a K-major one
   const int32_t max_lda = (layout & GSPMD_LAYOUT_LHS_K_MAJOR) ? (1 << 24) : (1 << 22);
   const int32_t max_ldb = (layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) ? (1 << 22) : (1 << 24);
   KernelPath path = kPathMfmaDirect;
@@ -162,9 +163,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   MfmaChoice choice{kMfmaBig, 0};
   const bool staged = path == kPathMfmaStaged;
   int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1, chain_k = 0;
-  bool short_ld = true;
   for (const auto& p : ps) {
-    short_ld = short_ld && p.lda <= (1 << 24) && p.ldb <= (1 << 24);      // 32-bit offsets of 64 rows
     rows = std::max<int64_t>(rows, p.Mv);
     k = std::max<int64_t>(k, p.Kv);
     big += tiles_of(p, kMfmaBM, kMfmaBN);
@@ -184,7 +183,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
     const double us = static_cast<double>((mid + 511) / 512) * (8.0 + static_cast<double>(members) + steps32 * (mid <= 256 ? 0.28 : 0.62) * (half_lines ? 1.25 : 1.0));
     if (us < 0.95 * best) { best = us; choice.kernel = kMfmaMid; }
   }
-  if (!ordered && short_ld && (staged || rows <= kSplitAnyKRows || k >= kSplitMinK)) {
+  if (!ordered && (staged || rows <= kSplitAnyKRows || k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((k + 255) / 256);
     const struct { int blocks; double aligned, unaligned; } kinds[] = {{1, 1.0, 1.5}, {2, 1.3, 2.0}, {4, 1.7, 2.4}};
     for (const auto& kind : kinds) {

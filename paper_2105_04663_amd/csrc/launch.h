@@ -11,7 +11,7 @@ namespace gspmd {
 
 constexpr int kMaxDevices = 64;
 
-// One launch of dot_mfma_kernel over `tiles` workgroups.
+// One launch of a bf16 contraction kernel over `tiles` workgroups.
 struct MfmaLaunch {
   const InlineProblems* inl;             // table that travels in the kernel arguments (tab null), or
   const Problem* tab;                    // table in device memory
@@ -22,7 +22,7 @@ struct MfmaLaunch {
   int timeline_records;
 };
 
-// `staged`: the operands allow 4-byte but not 16-byte aligned chunk loads
+// `staged`: an operand's rows are not 16-byte aligned, both are loaded at element alignment
 template <int LAYOUT>
 bool launch_dot_mfma_layout(const MfmaLaunch& l, int32_t out_dtype, bool staged, hipStream_t stream);
 

@@ -82,3 +82,21 @@ def test_moves_at_any_alignment(shape, mesh_shape, smap, dmap, pitch, shift, dty
     flat = back.float().cpu().numpy()
     assert np.array_equal(flat[at:at + ref.size].reshape(shape), ref)
     assert (flat[:at] == -3.0).all() and (flat[at + ref.size:] == -3.0).all()
+
+
+def test_extents_beyond_the_31_bit_kernel():
+    # more than 2^30 elements in one dimension: element by element in 64-bit indices; shards start at odd elements
+    n, P = (1 << 30) + 5, 3
+    mesh, sh = g.Mesh((P,), (2, 0, 1)), g.Sharding((n,), (0,))
+    whole = torch.empty(n, dtype=torch.int16, device="cuda").random_()
+    back = torch.zeros_like(whole)
+    stream = torch.cuda.current_stream().cuda_stream
+    for pid in range(P):
+        (off,), (valid,), (per,) = g.shard_bounds(mesh, sh, pid)
+        t = torch.zeros(per + 2, dtype=torch.int16, device="cuda")
+        buf = g.ShardBuf(t.data_ptr() + 2, g.BF16, 0)
+        g.shard_extract(mesh, sh, pid, whole.data_ptr(), buf, 0x7FC0, stream)
+        assert torch.equal(t[1:1 + valid], whole[off:off + valid]), f"extract {pid}"
+        assert bool((t[1 + valid:1 + per] == 0x7FC0).all()) and int(t[0]) == 0 and int(t[-1]) == 0, f"extract {pid}"
+        g.shard_assemble(mesh, sh, pid, buf, back.data_ptr(), stream)
+    assert torch.equal(back, whole)
