@@ -144,7 +144,7 @@ def main():
             g.shard_extract(mesh, sh, 0, src.data_ptr(), g.ShardBuf.of(dst, 0), 0, stream)
         torch.cuda.synchronize()
         assert torch.equal(src, dst)
-        print(json.dumps({"calibrate_copy": "shard_copy_kernel", "launches": 5, "bytes_read_per_launch": src.numel() * 2,
+        print(json.dumps({"calibrate_copy": "shard_move_kernel", "launches": 5, "bytes_read_per_launch": src.numel() * 2,
                           "bytes_written_per_launch": src.numel() * 2}), flush=True)
         return
 

@@ -110,7 +110,7 @@ typedef struct {
  * dimension; 0 means dense (= static size of the last dimension).  Outer dimensions are
  * dense on top of it.  A row_stride that is a multiple of 8 elements together with a
  * 16-byte aligned pointer selects the fastest MFMA kernels for bf16; rows of any other width take kernels that load at
- * element alignment (a third of the rate on large products); an operand whose contiguous dimension
+ * element alignment (about two thirds of the rate on large products); an operand whose contiguous dimension
  * is contracted runs fastest when its rows start on 128-byte lines (row_stride a multiple of 64
  * elements: 9 % faster than a multiple of 8 that is not, at 8200 against 8256).  data may be NULL only for a
  * tensor with a zero-size dimension (no elements: nothing is read or written). */
@@ -223,6 +223,11 @@ int32_t gspmd_dot_workspace_bytes(const gspmd_mesh* mesh, const gspmd_dot_dims* 
  * non-contracting lhs dimension: rows at global position >= fill are masked and their out rows are 0.  If it
  * is contracting (the experts' weight gradient) it must be the outermost contracting dimension: positions
  * >= fill take no part in the sum in either operand.
+ * Order of summation: every call with the same arguments, alignments included, gives the same bits, and partial sums of bf16 operands along a
+ * GSPMD_AXIS_CONTRACTING dimension, formed here or in gspmd_grouped_dot, are summed over K in one fixed order.  Other bf16
+ * products, and float32 ones, are not promised one: kernels that order the sum over K differently are chosen by the sizes and
+ * alignment of a whole launch, so that the same element may round differently in a call with more rows, with other fill
+ * counts, or over all partitions instead of one (within fp32 accumulation).
  * workspace: device, 256-byte aligned, >= gspmd_dot_workspace_bytes(); contents are
  * overwritten and must stay untouched until the stream has run the call. */
 int32_t gspmd_local_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,

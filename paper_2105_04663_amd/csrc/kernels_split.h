@@ -18,8 +18,10 @@
 // Measured (us, weights not in cache; before: 256 x 256 tiles on 32 to 128 of the 256 compute units): 32 x 8192 x 8192
 // 101 -> 43 (134 MB of weights at 3.1 TB/s; 36 with rows of 8256 elements, a power of two costs the L2 channels), 64 rows
 // 105 -> 47, 256 rows 135 -> 97, 16 x 8192 x 32768 -> 115 (4.7 TB/s), 256 x 2048 x 2048 39 -> 13, 64 x 1024 x 1024 14 -> 6.
-// Running further ahead (9 instead of 6 steps, or only 2) changes nothing: a compute unit takes in 30 to 40 GB/s
-// whatever is in flight, so what counts is the number of workgroups.  32-column tiles double it but read half lines: no gain.
+// Running further ahead (9 instead of 6 steps, or only 2) changes nothing: a compute unit's L1 keeps about 105 lines of 128 bytes
+// in flight, 608 cycles each at 32 x 8192 x 8192 (256 workgroups: two row tiles draw every weight panel, 268 MB from L2, 144
+// from HBM), and stalls on them for half of its cycles; the matrix cores are busy for 7 %, LDS for 25 %.  32-column tiles read half
+// lines: no gain.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
