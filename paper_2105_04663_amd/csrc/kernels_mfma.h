@@ -79,8 +79,13 @@ __device__ __forceinline__ void zero_rows_below(TOut* __restrict__ C, int ldc, i
 // would reach past the last valid column or the valid K is fetched from before it and moved down in registers.  Stores are
 // 16 bytes at element alignment too.  (The last K tile and the output element by element: 300 x 65 x 301 as a float32 partial
 // 20.8 instead of 13.6 us, 1260 x 7 x 769 30.9 instead of 15.5, 5998 x 3072 x 9999 on 4 x 8 partitions 481 instead of 424.)
+// Placement: where the direct variants' code lies in its 64 KiB decides 1 to 2 % of a launch of few K steps (experts' weight
+// gradient 4 x 512 x 4096 x 8192: 114.6 to 115.7 us with the kernel's start 16 to 48 KiB into them, 116.5 to 117.1 with 0 to 13; four
+// partials of 2048 x 4096 and their sum: 122.3 to 123.0, and 124.3 to 124.8 with 0 or 14).  So they are aligned to 16 KiB and come first
+// in a compiled source (launch_dot_mfma_layout), which puts them 32 KiB into one whatever the sizes of the other kernels.
+constexpr int kMfmaCodeAlign = 16384;
 template <typename TOut, int LAYOUT, bool STAGED>
-__global__ __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue,
+__global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThreads) void dot_mfma_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue,
                                                                 float* __restrict__ join_partials, uint32_t* __restrict__ join_counters,
                                                                 unsigned long long* __restrict__ timeline, int timeline_records) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
@@ -777,8 +782,8 @@ inline bool launch_dot_mfma_as(const MfmaLaunch& l, hipStream_t stream) {
 
 template <int LAYOUT>
 bool launch_dot_mfma_layout(const MfmaLaunch& l, int32_t out_dtype, bool staged, hipStream_t stream) {
-  if (out_dtype == GSPMD_F32) return staged ? launch_dot_mfma_as<float, LAYOUT, true>(l, stream) : launch_dot_mfma_as<float, LAYOUT, false>(l, stream);
-  return staged ? launch_dot_mfma_as<bf16_bits, LAYOUT, true>(l, stream) : launch_dot_mfma_as<bf16_bits, LAYOUT, false>(l, stream);
+  if (!staged) return out_dtype == GSPMD_F32 ? launch_dot_mfma_as<float, LAYOUT, false>(l, stream) : launch_dot_mfma_as<bf16_bits, LAYOUT, false>(l, stream);
+  return out_dtype == GSPMD_F32 ? launch_dot_mfma_as<float, LAYOUT, true>(l, stream) : launch_dot_mfma_as<bf16_bits, LAYOUT, true>(l, stream);
 }
 
 }  // namespace gspmd
