@@ -129,8 +129,8 @@ struct MfmaChoice {
 };
 
 // What this thread's launches are pinned to, and what its last one took (testing.h).
-thread_local gspmd_testing_launch t_pin{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE};
-thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE};
+thread_local gspmd_testing_launch t_pin{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0};
+thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0};
 
 // The three kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
 // a workgroup draws from L2 per flop (a compute unit waits for the 90 to 105 lines its L1 keeps in flight), so the choice compares
@@ -233,7 +233,6 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   // joined problems come with the caller's choice between the two kernels that keep the order of summation
   const MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : pick_kernel(ps, path, layout, ordered);
   const bool mfma = choice.kernel != kMfmaNone;
-  t_last = gspmd_testing_launch{choice.kernel, choice.row_blocks, join ? 1 : 0};
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
   const bool mid = choice.kernel == kMfmaMid;
   const int bm = split ? 16 * split : mid ? kMidTile : mfma ? kMfmaBM : kGenTile;
@@ -261,6 +260,11 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   // the workspace contract does not depend on which way the tables travel
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & (kWsAlign - 1)) || workspace_bytes < table_bytes)
     return GSPMD_ERR_WORKSPACE;
+  t_last.kernel = choice.kernel;
+  t_last.row_blocks = choice.row_blocks;
+  t_last.one_launch = join ? 1 : 0;
+  t_last.table_bytes = inline_tables ? 0 : table_bytes;
+  if (t_pin.dry_run) return GSPMD_OK;
   const Problem* tab = nullptr;
   const ZeroRect* drects = nullptr;
   InlineProblems inl;
@@ -683,6 +687,7 @@ int32_t gspmd_local_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     return st;
   for (const auto& p : ps)
     if ((p.Kv && (!p.A || !p.B)) || !p.C) return GSPMD_ERR_NULL;
+  t_last.sums_begin = t_last.sums_end = 0;
   return launch_problems(ps, layout, lhs->dtype, out->dtype, epilogue, has_contracting(mesh, cls), workspace, workspace_bytes,
                          static_cast<hipStream_t>(hip_stream));
 } catch (...) { return GSPMD_ERR_HOST_MEMORY; }
@@ -871,11 +876,18 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
         ok = !summable || one.us <= 1.05 * (two.us + apart_us(two.kernel, path == kPathMfmaStaged, apart[0].Ns, partial_bytes, launches));
       }
     }
-    const int64_t table_area = partial_base - static_cast<char*>(workspace);
-    if (ok && (js.chain || table_area + joined_bytes(jtiles, jslots) <= workspace_bytes)) {
-      js.counters = reinterpret_cast<uint32_t*>(partial_base);
-      js.partials = reinterpret_cast<float*>(partial_base + round_up(jtiles * 4, kWsAlign));
+    // Behind the launch tables come the counters, then the slots.  A scattered sum has more entries than the query counted (one
+    // per member and owner), so tables too large for the kernel arguments may reach beyond the space it kept for them.
+    int64_t table_area = partial_base - static_cast<char*>(workspace);
+    if (joined.size() > static_cast<size_t>(kInlineProblems))
+      table_area = std::max(table_area, round_up(static_cast<int64_t>(joined.size()) * kTableBytesPerProblem, kWsAlign));
+    if (ok && table_area + (js.chain ? 0 : joined_bytes(jtiles, jslots)) <= workspace_bytes) {
+      char* const counters = static_cast<char*>(workspace) + table_area;
+      js.counters = reinterpret_cast<uint32_t*>(counters);
+      js.partials = reinterpret_cast<float*>(counters + round_up(jtiles * 4, kWsAlign));
       js.tiles = jtiles;
+      t_last.sums_begin = js.chain ? 0 : table_area;
+      t_last.sums_end = js.chain ? 0 : table_area + joined_bytes(jtiles, jslots);
       return launch_problems(joined, jlayout, in_dtype, out_dtype, epilogue, true, workspace, workspace_bytes, stream, &js);
     }
   }
@@ -899,9 +911,15 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     for (size_t i = before; i < ps.size(); ++i)
       if ((ps[i].Kv && (!ps[i].A || !ps[i].B)) || !ps[i].C) return GSPMD_ERR_NULL;
   }
+  t_last.sums_begin = t_last.sums_end = 0;
+  if (contracting) {
+    t_last.sums_begin = partial_base - static_cast<char*>(workspace);
+    t_last.sums_end = t_last.sums_begin;
+    for (int64_t e : elems) t_last.sums_end += round_up(e * 4, kWsAlign);
+  }
   st = launch_problems(ps, layout, in_dtype, contracting ? GSPMD_F32 : out_dtype, contracting ? GSPMD_EPILOGUE_NONE : epilogue,
                        contracting, workspace, workspace_bytes, stream);
-  if (st != GSPMD_OK || !contracting) return st;
+  if (st != GSPMD_OK || !contracting || t_pin.dry_run) return st;
 
   // Sum the partials of each reduce group, ascending in mesh position, into every distinct out buffer of the group.
   for (auto& kv : groups) {
@@ -1355,6 +1373,7 @@ int32_t gspmd_testing_pin(const gspmd_testing_launch* pin) {
   const bool split = pin->kernel == GSPMD_TESTING_SPLIT;
   if (pin->kernel < GSPMD_TESTING_BY_RULE || pin->kernel > GSPMD_TESTING_SPLIT || pin->one_launch < GSPMD_TESTING_BY_RULE || pin->one_launch > 1 ||
       (split ? pin->row_blocks != 1 && pin->row_blocks != 2 && pin->row_blocks != 4 : pin->row_blocks != 0)) return GSPMD_ERR_UNSUPPORTED;
+  if (pin->dry_run != 0 && pin->dry_run != 1) return GSPMD_ERR_UNSUPPORTED;
   t_pin = *pin;
   return GSPMD_OK;
 }

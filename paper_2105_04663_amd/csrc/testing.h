@@ -22,6 +22,10 @@ typedef struct {
   int32_t kernel;       /* GSPMD_TESTING_* */
   int32_t row_blocks;   /* dot_split_kernel: 1, 2 or 4; others 0 */
   int32_t one_launch;   /* sums along a contracting mesh dimension: 1 in one launch where the operands allow, 0 in two; -1 by rule */
+  int32_t dry_run;      /* pin: 1: Dots go no further than their launches, so that host logic can be tested without a GPU */
+  /* last only: bytes of launch tables at the start of the workspace (0: they travel as kernel arguments), and where in the workspace
+   * the partial sums or counters and slots of a sum lie */
+  int64_t table_bytes, sums_begin, sums_end;
 } gspmd_testing_launch;
 
 int32_t gspmd_testing_pin(const gspmd_testing_launch* pin);

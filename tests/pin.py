@@ -8,25 +8,38 @@ BY_RULE, SCALAR, MFMA, MID, SPLIT = -1, 0, 1, 2, 3
 
 
 class _Launch(C.Structure):
-    _fields_ = [("kernel", C.c_int32), ("row_blocks", C.c_int32), ("one_launch", C.c_int32)]
+    _fields_ = [("kernel", C.c_int32), ("row_blocks", C.c_int32), ("one_launch", C.c_int32), ("dry_run", C.c_int32),
+                ("table_bytes", C.c_int64), ("sums_begin", C.c_int64), ("sums_end", C.c_int64)]
 
 
-def _pin(kernel, row_blocks, one_launch):
-    p = _Launch(kernel, row_blocks, one_launch)
+def _pin(kernel, row_blocks, one_launch, dry_run=False):
+    p = _Launch(kernel, row_blocks, one_launch, int(dry_run))
     assert g.load_library().gspmd_testing_pin(C.byref(p)) == 0
 
 
 @contextlib.contextmanager
-def pinned(kernel=BY_RULE, row_blocks=0, one_launch=BY_RULE):
-    _pin(kernel, row_blocks, one_launch)
+def pinned(kernel=BY_RULE, row_blocks=0, one_launch=BY_RULE, dry_run=False):
+    """`dry_run`: Dots stop short of their launches; addresses are not used, so no GPU is needed."""
+    _pin(kernel, row_blocks, one_launch, dry_run)
     try:
         yield
     finally:
         _pin(BY_RULE, 0, BY_RULE)
 
 
-def last():
-    """(kernel, row blocks, one launch for a whole sum) of this thread's last Dot."""
+def _last():
     p = _Launch()
     assert g.load_library().gspmd_testing_last(C.byref(p)) == 0
+    return p
+
+
+def last():
+    """(kernel, row blocks, one launch for a whole sum) of this thread's last Dot."""
+    p = _last()
     return p.kernel, p.row_blocks, p.one_launch
+
+
+def last_workspace():
+    """(bytes of launch tables, begin and end of the partial sums or counters and slots) in the workspace of this thread's last Dot."""
+    p = _last()
+    return p.table_bytes, p.sums_begin, p.sums_end

@@ -13,7 +13,7 @@ from tests import test_gpu_parity as parity
 from tests import test_gpu_split as split
 from tests import test_gpu_unaligned as unaligned
 from tests.harness import Staged
-from tests.pin import MFMA, MID, SCALAR, SPLIT, last, pinned
+from tests.pin import MFMA, MID, SCALAR, SPLIT, last, last_workspace, pinned
 
 gpu = pytest.mark.gpu
 ROW_BLOCKS = [1, 2, 4]
@@ -248,3 +248,28 @@ def test_sums_take_the_way_that_measured_faster(M, K, N, P, row_align, one_launc
     st = Staged(w, np.zeros(w.lhs_shape, dtype=np.uint16), np.zeros(w.rhs_shape, dtype=np.uint16), row_align=row_align)
     st.run_grouped()
     assert last()[2] == one_launch
+
+
+@gpu
+@pytest.mark.parametrize("kernel", [MFMA, MID])
+@pytest.mark.parametrize("row_align", [8, 0])
+@pytest.mark.parametrize("M,K,N,P", [(257, 520, 320, 8), (300, 999, 2051, 6), (70, 1000, 4096, 16)])
+def test_scattered_sums_whose_tables_are_uploaded(M, K, N, P, row_align, kernel):
+    # more pieces than travel as kernel arguments, and a workspace with room for their table beside counters and slots
+    w = wl.ksplit(M=M, K=K, N=N, P=P)
+    w.out_map = (-1, 0)
+    lhs, rhs = wl.draw_small_int_bf16(5, w.lhs_shape), wl.draw_small_int_bf16(6, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=row_align, out_dtype="f32")
+    n = g.dot_workspace_bytes(st.mesh, st.dims, st.lhs_sh, st.rhs_sh, st.out_sh) + P * P * -(-M // 256) * -(-N // (256 * P)) * 270 * 1024
+    ws = torch.full((n + 256,), 255, dtype=torch.uint8, device="cuda")
+    base = (ws.data_ptr() + 255) // 256 * 256
+    ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    for rep in range(3):
+        for _, t, _, _ in st.out:
+            t.fill_(float("nan"))
+        with pinned(kernel, 0, 1):
+            g.grouped_dot(st.mesh, st.dims, [x[0] for x in st.lhs], st.lhs_sh, [x[0] for x in st.rhs], st.rhs_sh, [x[0] for x in st.out], st.out_sh,
+                          None, base, n, torch.cuda.current_stream().cuda_stream)
+            assert last()[2] == 1 and last_workspace()[0] > 0
+        for pid in range(P):
+            assert np.array_equal(st.out_shard(pid), od.expected_out_shard(ref, w.mesh_shape, w.device_ids, w.out_map, pid)), f"rep {rep} pid {pid}"
