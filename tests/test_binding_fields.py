@@ -49,8 +49,15 @@ def test_only_an_address_is_an_address(data):
         g.reshard(mesh, sh, [good], sh, [bad])
 
 
-def test_shard_arrays_have_the_structures_layout():
-    bufs = [g.ShardBuf(2**63 + 5, g.BF16, 8), g.ShardBuf(None, g.F32), g.ShardBuf(4096, g.BF16, 2**40), g.ShardBuf(0, True, 0)]
-    arr = C.cast(binding._bufs(bufs), C.POINTER(binding._CShardBuf))
-    for i, b in enumerate(bufs):
-        assert (arr[i].data, arr[i].dtype, arr[i].row_stride) == (b.data or None, int(b.dtype), b.row_stride)
+@pytest.mark.parametrize("odd", [None, 2**63 + 5])        # an address beyond 63 bits takes another way
+def test_shard_arrays_have_the_structures_layout(odd):
+    bufs = [g.ShardBuf(odd, g.BF16, 8), g.ShardBuf(None, g.F32), g.ShardBuf(4096, np.int32(1), 2**40), g.ShardBuf(0, True, np.int64(3))]
+    arr = (binding._CShardBuf * len(bufs)).from_buffer_copy(binding._bufs(bufs))
+    for a, b in zip(arr, bufs):
+        assert (a.data, a.dtype, a.row_stride) == (b.data or None, int(b.dtype), b.row_stride)
+
+
+@pytest.mark.parametrize("dtype,row_stride", [(1.0, 0), (None, 0), (g.BF16, 8.0), (g.BF16, None), ("1", 0)])
+def test_only_integers_describe_a_shard(dtype, row_stride):
+    with pytest.raises(TypeError):
+        binding._bufs([g.ShardBuf(4096, g.BF16), g.ShardBuf(4096, dtype, row_stride)])
