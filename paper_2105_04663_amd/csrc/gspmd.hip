@@ -125,7 +125,6 @@ enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_T
 struct MfmaChoice {
   MfmaKernel kernel;
   int row_blocks;
-  double us = 0.0;            // what the launch is estimated to take
 };
 
 // What this thread's launches are pinned to, and what its last one took (testing.h).
@@ -140,24 +139,24 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   32 x 2048 x 16384: 31 / - / 26, 19, 20        64 x 1024 x 1024: 14 / - / 6, 7, 10         256 x 2048 x 2048: 39 / 29 / 22, 13, 17
 //   512 x 2048 x 2048: 39 / 27 / 41, 24, 16       1024 x 1024 x 4096: 23 / 19 / 89, 59, 40    512 x 512 x 512: 13 / 9
 //   1024 x 4096 x 1024: 69 / 49    2048 x 2048 x 2048: 40 / 29    2048 x 2048 x 4096: 41 / 49    1024 x 8192 x 8192: 140 / 177
-// dot_mfma_kernel: rounds of 256 workgroups of 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step; the slots of joined problems add
-//   4.6 us per member (the last arriver at a tile reads the others' contributions one after the other) and 0.05 us per contribution to an
-//   output tile.  Measured beyond the launch without slots: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38;
-//   4, 676: 37; 8, 16: 38; 8, 512: 59; 8, 640: 67.
+// dot_mfma_kernel: rounds of 256 workgroups of 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step; slots of joined problems: 8 us and
+//   0.08 us per contribution to an output tile.
 // dot_mid_kernel: 8 us and 0.28 us per 32-wide step while a compute unit has one workgroup, 0.62 us with two, then rounds of 512; the members
-//   of a joined sum follow each other in one workgroup, 1 us apart (2048 x 8192 x 2048 over 4 members: 77 us, 299 x 4032 x 2112 over 4: 49, 828 x
-//   6464 x 3648 over 8: 82; with slots 79, 42 and 102).  Two K-contiguous operands come in half lines:
-//   a quarter more per step (two members of 1024 x 4096 x 2048 on 2 partitions: 105 us against 91).
+//   of a joined sum follow each other in one workgroup, 1 us apart.  Two K-contiguous operands come in half lines: a quarter more per
+//   step (two members of 1024 x 4096 x 2048 on 2 partitions, operands not in cache: 105 us against 91).
+//   These two lines choose between the two forms of a joined sum, measured one after the other / slots: 2048 x 8192 x 2048 over 4 members
+//   77 / 79 us (the line takes the slots), 299 x 4032 x 2112 over 4: 49 / 42, 828 x 6464 x 3648 over 8: 82 / 102, both K-major 1792 x 714 x
+//   3936 over 2, two groups of them (K per member): 54 / 76.  They are coarse as prices of a whole sum: sum_us, below.
 // dot_split_kernel: rounds of 256 workgroups of 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  Its order of summation is another one:
 //   partial sums along a contracting mesh dimension (`ordered`) stay with the first two, so that the joined sum, the two-launch sum and
 //   partials that a caller sums agree bit for bit; and beyond 256 rows it is taken from K = 1024 on (below, dot_mid_kernel is within 4 us).
-// Operands that are not 16-byte aligned take the first or the third, and cost the address unit four times as much: 10.5 us
-// and 2.1 us a step in the staged tiles, 1.5, 2.0, 2.4 us a round in the split kernel (staged / 1, 2, 4 row blocks):
+// Operands that are not 16-byte aligned take the first or the third, and cost the address unit more: 10.5 us and 2.1 us a step in
+// the staged tiles; rounds of 3.2, 4.3, 6.5 us and 1.2, 1.25, 1.55 us per eight steps in the split kernel (staged / 1, 2, 4 row blocks):
 //   601 x 2001 x 601: 78 / 25, 15, 20     2001 x 1003 x 2001: 45 / 136, 82, 59     301 x 1001 x 301: 45 / 9, 10, 14
 //   3826 x 102 x 538: 14 / 35, 25, 21     482 x 111 x 5292: 14 / 50, 34, 25        2289 x 293 x 885: 21 / 35, 23, 17
-//   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46
+//   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46     5990 x 3107 x 555: 117 / -, -, 107
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
-// (pick_kernel): the choice is the same with and without, so results are.
+// (with_records): the choice is the same with and without, so results are.
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   MfmaChoice choice{kMfmaBig, 0};
@@ -176,48 +175,74 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   chain_k = k * members;
   const double rounds = static_cast<double>((big + 255) / 256), steps64 = static_cast<double>((k + 63) / 64);
   double best = rounds * (staged ? 10.5 + steps64 * 2.1 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) +
-                (members > 1 ? 4.6 * static_cast<double>(members) + 0.05 * static_cast<double>(big) : 0.0);
+                (members > 1 ? 8.0 + 0.08 * static_cast<double>(big) : 0.0);
   if (!staged) {
     const double steps32 = static_cast<double>((chain_k + 31) / 32);
-    const bool half_lines = !(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
+    const bool half_lines = (layout & 3) == GSPMD_LAYOUT_RHS_K_CONTIGUOUS;
     const double us = static_cast<double>((mid + 511) / 512) * (8.0 + static_cast<double>(members) + steps32 * (mid <= 256 ? 0.28 : 0.62) * (half_lines ? 1.25 : 1.0));
     if (us < 0.95 * best) { best = us; choice.kernel = kMfmaMid; }
   }
   if (!ordered && (staged || rows <= kSplitAnyKRows || k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((k + 255) / 256);
-    const struct { int blocks; double aligned, unaligned; } kinds[] = {{1, 1.0, 1.5}, {2, 1.3, 2.0}, {4, 1.7, 2.4}};
+    const struct { int blocks; double aligned, beside, unaligned; } kinds[] = {{1, 1.0, 3.2, 1.2}, {2, 1.3, 4.3, 1.25}, {4, 1.7, 6.5, 1.55}};
     for (const auto& kind : kinds) {
       int64_t tiles = 0;
       for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
-      const double us = static_cast<double>((tiles + 255) / 256) * (4.0 + rounds8 * (staged ? kind.unaligned : kind.aligned));
+      const double us = static_cast<double>((tiles + 255) / 256) * (staged ? kind.beside + rounds8 * kind.unaligned : 4.0 + rounds8 * kind.aligned);
       if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks}; }
     }
   }
-  choice.us = best;
   return choice;
 }
 
-// What forming the members' products by themselves adds to their launch `two` (dense fp32 partials, then a sum kernel per out
-// buffer): 2 us, 3.5 us per kernel and 0.31 us per MB of partials written and read back, 0.9 where rows of partials that are not
-// 16-byte aligned go out element by element.  Sums over a contracting mesh dimension take whichever way is estimated faster; the
-// results are the same.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19; 659 x 4880 x 1316
-// over 2: 51 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x 508 x 4085
-// over 2, unaligned: 36 / 48; 1953 x 409 x 454 over 4: 15 / 20; 828 x 6464 x 3648 over 8: 81 / 74; 4023 x 8430 x 1215 over 8: 142 / 158.
+// Sums over a contracting mesh dimension are formed in one launch (joined problems) or in two: the members' products by themselves, in dense
+// fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 20 % faster; the results are the same bits.
+// sum_us prices the contraction launch.  dot_mfma_kernel's slots cost 4.6 us per member, the last arriver at a tile reading the others'
+// contributions one after the other, and 0.05 us per contribution (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17;
+// 4, 24: 19; 4, 84: 25; 4, 256: 38; 4, 676: 37; 8, 16: 38; 8, 512: 59; 8, 640: 67); dot_mid_kernel's members 1.7 us each, and its steps, with
+// one and with two workgroups on a compute unit, as below, by layout.
+double sum_us(const std::vector<Problem>& ps, MfmaKernel kernel, bool staged, int32_t layout) {
+  int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1;
+  for (const auto& p : ps) {
+    rows = std::max<int64_t>(rows, p.Mv);
+    k = std::max<int64_t>(k, p.Kv);
+    big += tiles_of(p, kMfmaBM, kMfmaBN);
+    if (p.join_slot == 0) {
+      mid += tiles_of(p, kMidTile, kMidTile);
+      members = std::max<int64_t>(members, p.join_count);
+    }
+  }
+  const double m = static_cast<double>(members);
+  if (kernel != kMfmaMid) {
+    const double steps = static_cast<double>((k + 63) / 64);
+    return static_cast<double>((big + 255) / 256) * (staged ? 10.5 + 2.1 * steps : 9.0 + steps * (rows <= 96 ? 0.75 : 0.95)) +
+           (members > 1 ? 4.6 * m + 0.05 * static_cast<double>(big) : 0.0);
+  }
+  const double steps = static_cast<double>((k * members + 31) / 32), alone[4] = {0.26, 0.25, 0.30, 0.26}, both[4] = {0.57, 0.41, 0.50, 0.55};
+  const double one = 8.0 + 1.7 * m + steps * alone[layout & 3], two = 8.0 + 1.7 * m + steps * both[layout & 3];
+  return static_cast<double>(mid / 512) * two + (mid % 512 == 0 ? 0.0 : mid % 512 <= 256 ? one : two);
+}
+// What partials cost beside their launch: 1 us, 2.5 us per sum kernel and 0.31 us per MB written and read back, 0.9 where rows that are not
+// 16-byte aligned go out element by element.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
+// 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
+// 508 x 4085 over 2, unaligned: 36 / 48; 1953 x 409 x 454 over 4: 15 / 20; 4023 x 8430 x 1215 over 8: 142 / 158.
 double apart_us(MfmaKernel two, bool staged, int64_t cols, int64_t partial_bytes, int64_t launches) {
   const bool by_element = two == kMfmaBig && !staged && (cols & 3);
-  return 2.0 + 3.5 * static_cast<double>(launches) + (by_element ? 0.9e-6 : 0.31e-6) * static_cast<double>(partial_bytes);
+  return 1.0 + 2.5 * static_cast<double>(launches) + (by_element ? 0.9e-6 : 0.31e-6) * static_cast<double>(partial_bytes);
 }
 
-// The kernel of a launch of bf16 problems: by the rule above, unless a test has pinned one that may take them.  While a timeline
-// is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
+// The kernel of a launch of bf16 problems: by the rule above, unless a test has pinned one that may take them.
 MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   if (path == kPathFallback) return MfmaChoice{kMfmaNone, 0};
   const MfmaKernel pin = static_cast<MfmaKernel>(t_pin.kernel);
   if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && path == kPathMfmaDirect) || (pin == kMfmaSplit && !ordered))
     return MfmaChoice{pin, t_pin.row_blocks};
-  MfmaChoice choice = choose_mfma(ps, path, layout, ordered);
-  if (choice.kernel == kMfmaMid && g_timeline.load(std::memory_order_acquire) != nullptr) choice.kernel = kMfmaBig;
-  return choice;
+  return choose_mfma(ps, path, layout, ordered);
+}
+
+// While a timeline is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
+MfmaKernel with_records(MfmaKernel kernel) {
+  return kernel == kMfmaMid && g_timeline.load(std::memory_order_acquire) != nullptr ? kMfmaBig : kernel;
 }
 
 int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dtype, int32_t out_dtype, int32_t epilogue,
@@ -231,7 +256,8 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   const KernelPath path = kernel_path(ps, in_dtype, layout);
   if (join && path == kPathFallback) return GSPMD_ERR_UNSUPPORTED;      // the caller checks before it joins problems
   // joined problems come with the caller's choice between the two kernels that keep the order of summation
-  const MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : pick_kernel(ps, path, layout, ordered);
+  MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : pick_kernel(ps, path, layout, ordered);
+  if (!join) choice.kernel = with_records(choice.kernel);
   const bool mfma = choice.kernel != kMfmaNone;
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
   const bool mid = choice.kernel == kMfmaMid;
@@ -858,14 +884,15 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     if (ok) {
       std::vector<Problem> live;
       for (const auto& q : joined) if (q.Mv > 0) live.push_back(q);
-      const MfmaChoice one = pick_kernel(live, kernel_path(live, in_dtype, jlayout), jlayout, true);
-      js.chain = one.kernel == kMfmaMid;
-      ok = one.kernel != kMfmaNone;
+      const KernelPath live_path = kernel_path(live, in_dtype, jlayout);
+      const MfmaKernel one = pick_kernel(live, live_path, jlayout, true).kernel;
+      js.chain = with_records(one) == kMfmaMid;
+      ok = one != kMfmaNone;
       if (ok && t_pin.one_launch >= 0) {
         ok = t_pin.one_launch == 1;
       } else if (ok && !apart.empty()) {
         const KernelPath path = kernel_path(apart, in_dtype, jlayout);
-        const MfmaChoice two = pick_kernel(apart, path, jlayout, true);
+        const MfmaKernel two = pick_kernel(apart, path, jlayout, true).kernel;
         int64_t partial_bytes = 0, launches = 0;
         bool summable = true;       // the sum kernels take so many partials, those of members without any K among them
         for (int64_t e : elems) partial_bytes += 4 * e;
@@ -873,7 +900,9 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
           launches += scatter ? static_cast<int64_t>(kv.second.size()) : 1;
           summable = summable && kv.second.size() <= static_cast<size_t>(kMaxPartials);
         }
-        ok = !summable || one.us <= 1.05 * (two.us + apart_us(two.kernel, path == kPathMfmaStaged, apart[0].Ns, partial_bytes, launches));
+        const bool staged = path == kPathMfmaStaged;
+        ok = !summable || sum_us(live, one, live_path == kPathMfmaStaged, jlayout) <=
+                              1.2 * (sum_us(apart, two, staged, jlayout) + apart_us(two, staged, apart[0].Ns, partial_bytes, launches));
       }
     }
     // Behind the launch tables come the counters, then the slots.  A scattered sum has more entries than the query counted (one
