@@ -131,25 +131,61 @@ struct MfmaChoice {
 thread_local gspmd_testing_launch t_pin{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0};
 thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0};
 
+// What a launch of dot_mfma_kernel or dot_mid_kernel takes, in us: straight lines through measured times.
+// dot_mfma_kernel: rounds of 256 workgroups of 9 us and 1.3 us per 64-wide K step, where the chip is full and its clock drops, down to 0.85
+//   in a round of few (short tiles: 0.75), 2 us for what is left of K; staged operands 10.5 and 2.1 us.  Joined problems meet in slots: 4.6 us
+//   per member, the last arriver at a tile reading the others' contributions one after the other, and 0.05 us per contribution to a tile
+//   (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38; 8, 16: 38; 8, 512: 59).
+// dot_mid_kernel: 8 us and 0.205 us per 32-wide step while a compute unit has one workgroup, 0.40 with two, then rounds of 512; the members of
+//   a joined sum follow each other in one workgroup, 1.7 us apart; 1.5 us per 32-wide tile that is left of K; a fifth more per step where
+//   a K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).
+// Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 118 / 60   512 x 8192 x 512: 117 / 47
+//   2048 x 4096 x 4096: 63 / 60   2048 x 1024 x 4096: 25 / 20   4653 x 7168 x 4288: 245 / 281   1456 x 1415 x 3969, two of them: 37 / 48
+//   2178 x 4736 x 1447, two: 75 / 61   1090 x 1333 x 1568, eight: 60 / 52   4 experts' weight gradients of 512 x 4096 x 8192: 122 / 227
+// Sums, slots / one after the other (K over all members): 2048 x 8192 x 2048 over 4: 78 / 66   1024 x 8192 x 2048 over 2, two groups: 75 / 58
+//   both K-major 2085 x 3540 x 1652 over 2, two groups: 64 / 60   1770 x 3303 x 2085 over 2, two groups: 65 / 67   1572 x 4544 x 3328 over 8: 136 / 88
+struct LaunchSize {
+  int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1;      // longest extents, tiles of 256 x 256 and of 128 x 128, most members of a sum
+  bool broken_lines = false;
+};
+LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
+  LaunchSize s;
+  for (const auto& p : ps) {
+    s.rows = std::max<int64_t>(s.rows, p.Mv);
+    s.k = std::max<int64_t>(s.k, p.Kv);
+    s.big += tiles_of(p, kMfmaBM, kMfmaBN);
+    if (p.join_slot == 0) {
+      s.mid += tiles_of(p, kMidTile, kMidTile);
+      s.members = std::max<int64_t>(s.members, p.join_count);
+    }
+    s.broken_lines = s.broken_lines || (!(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (p.lda & 63)) || ((layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && (p.ldb & 63));
+  }
+  return s;
+}
+double big_us(const LaunchSize& s, bool staged) {
+  const double steps = static_cast<double>((s.k + 63) / 64), full = static_cast<double>(s.big / 256), part = static_cast<double>(s.big % 256) / 256.0;
+  const double beside = staged ? 10.5 : 9.0 + (s.k % 64 ? 2.0 : 0.0);
+  auto step = [&](double fill) { return staged ? 2.1 : s.rows <= 96 ? 0.75 : 0.85 + 0.45 * fill * fill; };
+  const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * static_cast<double>(s.big) : 0.0;
+  return full * (beside + steps * step(1.0)) + (part > 0.0 ? beside + steps * step(part) : 0.0) + slots;
+}
+double mid_us(const LaunchSize& s) {
+  const double m = static_cast<double>(s.members), left = static_cast<double>((s.k % 64 + 31) / 32);
+  const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 8.0 + 1.7 * (m - 1.0) + 1.5 * m * left;
+  const int64_t part = s.mid % 512;
+  return static_cast<double>(s.mid / 512) * (beside + steps * 0.40) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? 0.205 : 0.40));
+}
+
 // The three kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
-// a workgroup draws from L2 per flop (a compute unit waits for the 90 to 105 lines its L1 keeps in flight), so the choice compares
-// estimates: straight lines through measured times (one problem, bf16, rows x K x N, us;
-// dot_mfma_kernel / dot_mid_kernel / dot_split_kernel with 1, 2, 4 row blocks):
-//   32 x 8192 x 8192: 101 / - / 43, 51, 54        64 x 8192 x 8192: 105 / - / 62, 47, 65      256 x 8192 x 8192: 135 / - / 222, 140, 97
-//   32 x 2048 x 16384: 31 / - / 26, 19, 20        64 x 1024 x 1024: 14 / - / 6, 7, 10         256 x 2048 x 2048: 39 / 29 / 22, 13, 17
-//   512 x 2048 x 2048: 39 / 27 / 41, 24, 16       1024 x 1024 x 4096: 23 / 19 / 89, 59, 40    512 x 512 x 512: 13 / 9
-//   1024 x 4096 x 1024: 69 / 49    2048 x 2048 x 2048: 40 / 29    2048 x 2048 x 4096: 41 / 49    1024 x 8192 x 8192: 140 / 177
-// dot_mfma_kernel: rounds of 256 workgroups of 9 us and 0.75 (short tiles) to 0.95 us per 64-wide K step; slots of joined problems: 8 us and
-//   0.08 us per contribution to an output tile.
-// dot_mid_kernel: 8 us and 0.28 us per 32-wide step while a compute unit has one workgroup, 0.62 us with two, then rounds of 512; the members
-//   of a joined sum follow each other in one workgroup, 1 us apart.  Two K-contiguous operands come in half lines: a quarter more per
-//   step (two members of 1024 x 4096 x 2048 on 2 partitions, operands not in cache: 105 us against 91).
-//   These two lines choose between the two forms of a joined sum, measured one after the other / slots: 2048 x 8192 x 2048 over 4 members
-//   77 / 79 us (the line takes the slots), 299 x 4032 x 2112 over 4: 49 / 42, 828 x 6464 x 3648 over 8: 82 / 102, both K-major 1792 x 714 x
-//   3936 over 2, two groups of them (K per member): 54 / 76.  They are coarse as prices of a whole sum: sum_us, below.
-// dot_split_kernel: rounds of 256 workgroups of 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  Its order of summation is another one:
-//   partial sums along a contracting mesh dimension (`ordered`) stay with the first two, so that the joined sum, the two-launch sum and
-//   partials that a caller sums agree bit for bit; and beyond 256 rows it is taken from K = 1024 on (below, dot_mid_kernel is within 4 us).
+// a workgroup draws from L2 per flop, so the choice compares estimates: the lines above, and for dot_split_kernel rounds of 256 workgroups of
+// 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  One problem, bf16, rows x K x N, us, dot_mfma_kernel / dot_split_kernel with 1, 2, 4 row
+// blocks:
+//   32 x 8192 x 8192: 101 / 43, 51, 54        64 x 8192 x 8192: 105 / 62, 47, 65      256 x 8192 x 8192: 135 / 222, 140, 97
+//   32 x 2048 x 16384: 31 / 26, 19, 20        64 x 1024 x 1024: 14 / 6, 7, 10         256 x 2048 x 2048: 39 / 22, 13, 17
+//   512 x 2048 x 2048: 39 / 41, 24, 16        1024 x 1024 x 4096: 23 / 89, 59, 40
+// dot_split_kernel's order of summation is another one: partial sums along a contracting mesh dimension (`ordered`) stay with the
+// first two, so that the joined sum, the two-launch sum and partials that a caller sums agree bit for bit; and beyond 256 rows it is taken
+// from K = 1024 on (below, dot_mid_kernel is within 4 us).
 // Operands that are not 16-byte aligned take the first or the third, and cost the address unit more: 10.5 us and 2.1 us a step in
 // the staged tiles; rounds of 3.2, 4.3, 6.5 us and 1.2, 1.25, 1.55 us per eight steps in the split kernel (staged / 1, 2, 4 row blocks):
 //   601 x 2001 x 601: 78 / 25, 15, 20     2001 x 1003 x 2001: 45 / 136, 82, 59     301 x 1001 x 301: 45 / 9, 10, 14
@@ -161,29 +197,15 @@ constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   MfmaChoice choice{kMfmaBig, 0};
   const bool staged = path == kPathMfmaStaged;
-  int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1, chain_k = 0;
-  for (const auto& p : ps) {
-    rows = std::max<int64_t>(rows, p.Mv);
-    k = std::max<int64_t>(k, p.Kv);
-    big += tiles_of(p, kMfmaBM, kMfmaBN);
-    if (p.join_slot == 0) {
-      mid += tiles_of(p, kMidTile, kMidTile);
-      members = std::max<int64_t>(members, p.join_count);
-    }
-  }
-  if (rows == 0) return choice;
-  chain_k = k * members;
-  const double rounds = static_cast<double>((big + 255) / 256), steps64 = static_cast<double>((k + 63) / 64);
-  double best = rounds * (staged ? 10.5 + steps64 * 2.1 : 9.0 + steps64 * (rows <= 96 ? 0.75 : 0.95)) +
-                (members > 1 ? 8.0 + 0.08 * static_cast<double>(big) : 0.0);
+  const LaunchSize size = launch_size(ps, layout);
+  if (size.rows == 0) return choice;
+  double best = big_us(size, staged);
   if (!staged) {
-    const double steps32 = static_cast<double>((chain_k + 31) / 32);
-    const bool half_lines = (layout & 3) == GSPMD_LAYOUT_RHS_K_CONTIGUOUS;
-    const double us = static_cast<double>((mid + 511) / 512) * (8.0 + static_cast<double>(members) + steps32 * (mid <= 256 ? 0.28 : 0.62) * (half_lines ? 1.25 : 1.0));
+    const double us = mid_us(size);
     if (us < 0.95 * best) { best = us; choice.kernel = kMfmaMid; }
   }
-  if (!ordered && (staged || rows <= kSplitAnyKRows || k >= kSplitMinK)) {
-    const double rounds8 = static_cast<double>((k + 255) / 256);
+  if (!ordered && (staged || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
+    const double rounds8 = static_cast<double>((size.k + 255) / 256);
     const struct { int blocks; double aligned, beside, unaligned; } kinds[] = {{1, 1.0, 3.2, 1.2}, {2, 1.3, 4.3, 1.25}, {4, 1.7, 6.5, 1.55}};
     for (const auto& kind : kinds) {
       int64_t tiles = 0;
@@ -197,30 +219,9 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 
 // Sums over a contracting mesh dimension are formed in one launch (joined problems) or in two: the members' products by themselves, in dense
 // fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 20 % faster; the results are the same bits.
-// sum_us prices the contraction launch.  dot_mfma_kernel's slots cost 4.6 us per member, the last arriver at a tile reading the others'
-// contributions one after the other, and 0.05 us per contribution (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17;
-// 4, 24: 19; 4, 84: 25; 4, 256: 38; 4, 676: 37; 8, 16: 38; 8, 512: 59; 8, 640: 67); dot_mid_kernel's members 1.7 us each, and its steps, with
-// one and with two workgroups on a compute unit, as below, by layout.
 double sum_us(const std::vector<Problem>& ps, MfmaKernel kernel, bool staged, int32_t layout) {
-  int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1;
-  for (const auto& p : ps) {
-    rows = std::max<int64_t>(rows, p.Mv);
-    k = std::max<int64_t>(k, p.Kv);
-    big += tiles_of(p, kMfmaBM, kMfmaBN);
-    if (p.join_slot == 0) {
-      mid += tiles_of(p, kMidTile, kMidTile);
-      members = std::max<int64_t>(members, p.join_count);
-    }
-  }
-  const double m = static_cast<double>(members);
-  if (kernel != kMfmaMid) {
-    const double steps = static_cast<double>((k + 63) / 64);
-    return static_cast<double>((big + 255) / 256) * (staged ? 10.5 + 2.1 * steps : 9.0 + steps * (rows <= 96 ? 0.75 : 0.95)) +
-           (members > 1 ? 4.6 * m + 0.05 * static_cast<double>(big) : 0.0);
-  }
-  const double steps = static_cast<double>((k * members + 31) / 32), alone[4] = {0.26, 0.25, 0.30, 0.26}, both[4] = {0.57, 0.41, 0.50, 0.55};
-  const double one = 8.0 + 1.7 * m + steps * alone[layout & 3], two = 8.0 + 1.7 * m + steps * both[layout & 3];
-  return static_cast<double>(mid / 512) * two + (mid % 512 == 0 ? 0.0 : mid % 512 <= 256 ? one : two);
+  const LaunchSize size = launch_size(ps, layout);
+  return kernel == kMfmaMid ? mid_us(size) : big_us(size, staged);
 }
 // What partials cost beside their launch: 1 us, 2.5 us per sum kernel and 0.31 us per MB written and read back, 0.9 where rows that are not
 // 16-byte aligned go out element by element.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;

@@ -16,6 +16,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "kernels_basic.h"
 #include "launch.h"
@@ -26,8 +27,11 @@
 namespace gspmd {
 
 constexpr int kMidPart = kMidTile * kMfmaBK * 2;      // 8 KiB: one operand's 32-wide K tile
-constexpr int kMidStage = 2 * kMidPart, kMidStages = 5;
-constexpr int kMidLds = kMidStages * kMidStage;
+constexpr int kMidStage = 2 * kMidPart;
+// LDS stages with one and with two workgroups on a compute unit, and how many tiles ahead of the multiplication loads are issued
+template <int PER_CU> constexpr int mid_stages() { return PER_CU == 1 ? 10 : 5; }
+template <int PER_CU> constexpr int mid_ahead() { return PER_CU == 1 ? 6 : 4; }
+constexpr int kMidUnroll = 5;                         // K steps after which the stages come round: their places are then constants of the code
 
 // K-major part [32 k][128 columns]: 16 chunks of 16 bytes per k row.  Chunk pairs (one 16-column block) are XOR-swizzled by
 // the row, so that the 4 rows x 32 bytes that a 16-lane group reads and those of the group beside it (8 rows further)
@@ -41,15 +45,27 @@ __device__ __forceinline__ int mid_km_load_offset(int q, int lane, int c0, int c
   if (n >= cols_valid) n = ((cols_valid - 1) >> 3) << 3;
   return (kr * ld + (n - c0)) * 2;
 }
+// K-contiguous operand: load instruction q (0..7) of the part with the tile's rows 64 half .. 64 half + 63, 64 k: 8 rows, 8 lanes per row;
+// rows past the valid extent reuse the last valid row
+__device__ __forceinline__ int mid_kc_load_offset(int q, int lane, int half, int r0, int rows_valid, int ld) {
+  const int r = q * 8 + (lane >> 3);
+  return (min(half * 64 + r, rows_valid - 1 - r0) * ld + ((lane & 7) ^ swz_h(r)) * 8) * 2;
+}
 // fragment of the 16-column block at `base` (block b further at ^ (b << 5) for a base that is a multiple of 64)
 __device__ __forceinline__ int mid_km_frag_offset(int base, int lane) {
   const int i = lane & 15, krow = (lane >> 4) * 8 + (i >> 2), cl = base + (i & 3) * 4;
   return krow * 256 + (((cl >> 3) ^ mid_swz(krow)) << 4) + (cl & 7) * 2;
 }
 
-template <typename TOut, int LAYOUT, bool CHAIN>
+template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU>
 __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
+  constexpr int R = mid_stages<PER_CU>(), L = mid_ahead<PER_CU>();
+  static_assert(2 * kMidUnroll % R == 0, "the loop's stages come round");
+  // A tile's load is issued in the half step L tiles before it is multiplied, into a stage whose last reads every wave has behind it: the
+  // reads of the K step before the current one (those of the step itself too, where the barrier waits for them).
+  constexpr bool kReadsDone = L > R - 3;
+  static_assert(L % 2 == 0 && L >= 4 && L < R, "loads run ahead by whole K steps, and a stage is free before it is filled");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -67,23 +83,35 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   const int members = CHAIN ? max(P.join_count, 1) : 1;
 
   float4_t acc[4][4], sum[CHAIN ? 4 : 1][CHAIN ? 4 : 1];
-  const int a_frag = AKM ? mid_km_frag_offset(wm, lane) : kc_frag_offset(wm, lane);
-  const int b_frag = kMidPart + (BKC ? kc_frag_offset(wn, lane) : mid_km_frag_offset(wn, lane));
-  auto read_kc = [&](const unsigned char* p) { return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(p)); };
-  auto read_km = [&](const unsigned char* p) {
+  // Fragment addresses.  LDS offsets in instructions have 16 bits: stages are addressed from a register per four of them (with five
+  // stages: one for the first four, one for the last).  A K-contiguous operand's register says which half of the rows this wave reads, and
+  // with five stages the second one stands for a step whose second tile is in stage 0 again.
+  constexpr int kGroups = R == 10 ? 3 : 2;
+  const int a_half = wm >> 6, b_half = wn >> 6;
+  uint32_t a_reg[kGroups][AKM ? 4 : 2], b_reg[kGroups][BKC ? 2 : 4];
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    auto half_at = [&](int half) { return R == 5 && g == 1 ? (half ? 0 : 4) : g * 4 + half; };
+#pragma unroll
+    for (int i = 0; i < (AKM ? 4 : 2); ++i) {
+      a_reg[g][i] = lds0 + (AKM ? (mid_km_frag_offset(wm, lane) ^ (i << 5)) + g * 4 * kMidStage : (kc_half_frag_offset(0, lane) ^ (i * 64)) + half_at(a_half) * kMidStage);
+      asm volatile("" : "+v"(a_reg[g][i]));
+    }
+#pragma unroll
+    for (int i = 0; i < (BKC ? 2 : 4); ++i) {
+      b_reg[g][i] = lds0 + kMidPart + (BKC ? (kc_half_frag_offset(0, lane) ^ (i * 64)) + half_at(b_half) * kMidStage : (mid_km_frag_offset(wn, lane) ^ (i << 5)) + g * 4 * kMidStage);
+      asm volatile("" : "+v"(b_reg[g][i]));
+    }
+  }
+  typedef __attribute__((address_space(3))) const u32x4_t lds_u32x4_t;
+  auto read_kc = [&](uint32_t at) { return __builtin_bit_cast(bf16x8_t, *(lds_u32x4_t*)(uintptr_t)at); };
+  auto read_km = [&](uint32_t at) {
     short8_t both;
-    both.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(p));
-    both.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(p + 4 * 256));
+    both.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(uintptr_t)at);
+    both.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)(uintptr_t)(at + 4 * 256));
     return __builtin_bit_cast(bf16x8_t, both);
   };
-  bf16x8_t fa[2][4], fb[2][4];                  // fragments of two tiles: one being multiplied, the next being read
-  auto read_frags = [&](int stage, int set) {
-    const unsigned char* base = smem + stage * kMidStage;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fb[set][i] = BKC ? read_kc(base + b_frag + i * 1024) : read_km(base + (b_frag ^ (i << 5)));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fa[set][i] = AKM ? read_km(base + (a_frag ^ (i << 5))) : read_kc(base + a_frag + i * 1024);
-  };
+  bf16x8_t fa[2][4], fb[2][4];                  // fragments of two 32-wide tiles: one being multiplied, the next being read
   auto multiply = [&](int set) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -103,90 +131,124 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
     const bf16_bits* a_base = static_cast<const bf16_bits*>(P.A) + (AKM ? static_cast<int64_t>(m0) : static_cast<int64_t>(m0) * P.lda);
     const bf16_bits* b_base = static_cast<const bf16_bits*>(P.B) + (BKC ? static_cast<int64_t>(n0) * P.ldb : static_cast<int64_t>(n0));
     const int64_t a_tile = AKM ? static_cast<int64_t>(kMfmaBK) * P.lda : kMfmaBK, b_tile = BKC ? kMfmaBK : static_cast<int64_t>(kMfmaBK) * P.ldb;
-    const int tiles = P.Kv / kMfmaBK, left = P.Kv - tiles * kMfmaBK;
-    int a_off[2], b_off[2];                     // this wave's two load instructions of each operand's part
+    const int tiles = P.Kv / (2 * kMfmaBK) * 2, left = P.Kv - tiles * kMfmaBK;      // tiles of the whole 64-wide K steps
+    int a_off[2][2], b_off[2][2];               // this wave's two load instructions of each operand's part, in even and odd tiles
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int q = wave * 2 + j;
-      a_off[j] = AKM ? mid_km_load_offset(q, lane, m0, P.Mv, P.lda) : kc_load_offset(q, lane, m0, P.Mv, P.lda);
-      b_off[j] = BKC ? kc_load_offset(q, lane, n0, P.Nv, P.ldb) : mid_km_load_offset(q, lane, n0, P.Nv, P.ldb);
-    }
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int q = wave * 2 + j;
+        a_off[h][j] = AKM ? mid_km_load_offset(q, lane, m0, P.Mv, P.lda) : mid_kc_load_offset(q, lane, h, m0, P.Mv, P.lda);
+        b_off[h][j] = BKC ? mid_kc_load_offset(q, lane, h, n0, P.Nv, P.ldb) : mid_km_load_offset(q, lane, n0, P.Nv, P.ldb);
+      }
     const bf16_bits *a_next = a_base, *b_next = b_base;
-    int fill = 0;                               // stage the next load goes to
-    auto issue = [&]() {
-      const uint32_t at = lds0 + fill * kMidStage + wave * 2048;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) global_to_lds16(a_next, a_off[j], at + j * 1024);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) global_to_lds16(b_next, b_off[j], at + kMidPart + j * 1024);
-      a_next += a_tile;
-      b_next += b_tile;
-      fill = fill == kMidStages - 1 ? 0 : fill + 1;
+    const uint32_t lds_wave = lds0 + wave * 2048;
+    // the i-th of this wave's four load instructions of an even (h 0) or odd tile, into stage `at`
+    auto issue_one = [&](int h, int i, int at) {
+      if (i < 2) global_to_lds16(a_next, a_off[h][i & 1], lds_wave + at * kMidStage + (i & 1) * 1024);
+      else global_to_lds16(b_next, b_off[h][i & 1], lds_wave + at * kMidStage + kMidPart + (i & 1) * 1024);
+      if (i == 3) {
+        if (AKM) a_next += a_tile;
+        else if (h == 1) a_next += 2 * kMfmaBK;
+        if (!BKC) b_next += b_tile;
+        else if (h == 1) b_next += 2 * kMfmaBK;
+      }
     };
-    for (int s = 0; s < min(tiles, kMidStages); ++s) issue();
-    int stage = 0;                              // of the tile whose fragments are read next
-    auto next_stage = [&]() { stage = stage == kMidStages - 1 ? 0 : stage + 1; };
-    // Waits until the tile to be read has landed, `after` later tiles being in flight, and every wave has its fragments of
-    // the tile before in registers (lgkmcnt 0): that tile's stage is free.
-    auto arrive = [&](int after) {
+    // Fragment i (rhs 0..3, then lhs 0..3) of half h of a K step whose first tile is in stage s0, into set h.  A K-contiguous operand's
+    // rows are all in the tile of their half of the 128 rows, 64 k each; a K-major operand's k rows in the tile of their half of the step.
+    // `fixed`: s0 is a constant, and so is what is added to the registers.
+    auto read_one = [&](int h, int i, int s0, bool fixed) {
+      const int s_km = s0 + h >= R ? s0 + h - R : s0 + h;
+      auto place = [&](int s, uint32_t (&first), uint32_t (&of_group)) { return fixed ? of_group + (R == 5 && s == 4 ? 0 : (s & 3) * kMidStage) : first + s * kMidStage; };
+      auto km = [&](auto& reg, int x) { return place(s_km, reg[0][x], reg[s_km >> 2][x]); };
+      auto kc = [&](auto& reg, int half) {                 // the tile of this wave's half: the step's second one may be in stage 0 again
+        if (fixed) return place(s0, reg[0][h], reg[s0 >> 2][h]);
+        const int s = s0 + half;
+        return reg[0][h] + (s >= R ? s - R - half : s0) * kMidStage;
+      };
+      if (i < 4) fb[h][i] = BKC ? read_kc(kc(b_reg, b_half) + i * 2048) : read_km(km(b_reg, BKC ? 0 : i));
+      else fa[h][i - 4] = AKM ? read_km(km(a_reg, AKM ? i - 4 : 0)) : read_kc(kc(a_reg, a_half) + (i - 4) * 2048);
+    };
+    // Half a K step: the MFMAs of fragment set `set`, and between them, one at a time, the reads of the next half's fragments (of the
+    // step in stage s0) and the loads of the tile L further on (into stage `to`).
+    auto half_step = [&](auto set_tag, int s0, bool fixed, bool reads, bool loads, int to) {
+      constexpr int set = decltype(set_tag)::value;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        acc[q >> 2][q & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][q & 3], fa[set][q >> 2], acc[q >> 2][q & 3], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if ((q & 1) == 0 && reads) read_one(set ^ 1, q >> 1, s0, fixed);
+        if ((q & 3) == 1 && loads) issue_one(set, q >> 2, to);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // waits until all but the `after` tiles loaded last have landed (and this wave's fragment reads are over)
+    auto landed = [&](int after) {
       if (after >= 4) __builtin_amdgcn_s_waitcnt(waitcnt_imm(16, 0));
-      else if (after == 3) __builtin_amdgcn_s_waitcnt(waitcnt_imm(12, 0));
-      else if (after == 2) __builtin_amdgcn_s_waitcnt(waitcnt_imm(8, 0));
-      else if (after == 1) __builtin_amdgcn_s_waitcnt(waitcnt_imm(4, 0));
+      else if (after >= 3) __builtin_amdgcn_s_waitcnt(waitcnt_imm(12, 0));
+      else if (after >= 2) __builtin_amdgcn_s_waitcnt(waitcnt_imm(8, 0));
+      else if (after >= 1) __builtin_amdgcn_s_waitcnt(waitcnt_imm(4, 0));
       else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
       __builtin_amdgcn_s_barrier();
     };
     if (tiles > 0) {
-      arrive(min(tiles, kMidStages) - 1);
-      read_frags(0, 0);
-      next_stage();
+      const std::integral_constant<int, 0> even{};
+      const std::integral_constant<int, 1> odd{};
+      for (int s = 0; s < min(tiles, L); s += 2)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) issue_one(i >> 2, i & 3, s + (i >> 2));
+      landed(min(tiles, L) - 2);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) read_one(0, i, 0, true);
+      const int full = tiles - L;               // tiles below this one load another while they are multiplied
       int k = 0;                                // tile in fragment set 0
-      for (; k + kMidStages + 2 <= tiles; k += 2) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          __builtin_amdgcn_s_waitcnt(waitcnt_imm(12, 0));        // tile k + h + 1 is there; k + h + 2 .. k + h + 4 on their way
-          __builtin_amdgcn_s_barrier();
-          issue();                                               // tile k + h + 5 into the stage of tile k + h
-          read_frags(stage, h ^ 1);
-          next_stage();
-          __builtin_amdgcn_sched_barrier(0);                     // the reads are under way before the MFMAs, and those do not
-          multiply(h);                                           // move behind the next wait
-          __builtin_amdgcn_sched_barrier(0);
-        }
+      auto step = [&](auto u_tag) {             // a K step whose tiles are in stages 2 u and 2 u + 1 (modulo R)
+        constexpr int s0 = 2 * decltype(u_tag)::value % R, next = (s0 + 2) % R, to = (s0 + L) % R;
+        half_step(even, s0, true, true, true, to);
+        // Both tiles of the next step have landed, L - 3 later ones are on their way
+        __builtin_amdgcn_s_waitcnt(kReadsDone ? waitcnt_imm(4 * (L - 3), 0) : waitcnt_vm(4 * (L - 3)));
+        __builtin_amdgcn_s_barrier();
+        half_step(odd, next, true, true, true, (to + 1) % R);
+        k += 2;
+      };
+      for (; k + 2 * kMidUnroll <= full; ) {
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+        step(std::integral_constant<int, 2>{});
+        step(std::integral_constant<int, 3>{});
+        step(std::integral_constant<int, 4>{});
       }
-      for (; k < tiles; k += 2) {               // at most six tiles left, one of them still to be loaded
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (k + h >= tiles) break;
-          if (k + h + 1 < tiles) {
-            const int loaded = min(tiles, k + h + kMidStages);   // tiles whose loads have been issued
-            arrive(loaded - (k + h + 2));
-            if (loaded < tiles) issue();
-            read_frags(stage, h ^ 1);
-            next_stage();
-          }
-          multiply(h);
-        }
+      int s0 = 0, to = L;                       // the rest with stages that are worked out
+      auto follow = [](int s, int by) { return s + by >= R ? s + by - R : s + by; };
+      for (; k < tiles; k += 2) {
+        const bool load = k < full, more = k + 2 < tiles;
+        half_step(even, s0, false, true, load, to);
+        s0 = follow(s0, 2);
+        if (more) landed(load ? L - 3 : tiles - k - 4);
+        half_step(odd, s0, false, more, load, follow(to, 1));
+        to = follow(to, 2);
       }
     }
-    if (left > 0) {                             // the partial tile, through registers: zeros beyond the valid K in BOTH operands
+    for (int done = 0; done < left; done += kMfmaBK) {      // up to two tiles, the last maybe partial, through registers: zeros beyond the valid K in BOTH operands
       typedef GSPMD_GLOBAL const unsigned char* gbytes;
       u32x4_t ta[2], tb[2];
+      const int64_t at_tile = tiles + done / kMfmaBK;
       auto chunk = [&](bool kmajor, const bf16_bits* base, int off, int q) -> u32x4_t {
         u32x4_t v = {0u, 0u, 0u, 0u};
-        const int kr = kmajor ? q * 4 + (lane >> 4) : ((lane & 3) ^ swz_a(q * 16 + (lane >> 2))) * 8;
-        if (kr < left) {
+        const int kr = kmajor ? q * 4 + (lane >> 4) : ((lane & 3) ^ swz_a(q * 16 + (lane >> 2))) * 8, here = left - done;
+        if (kr < here) {
           v = *(GSPMD_GLOBAL const u32x4_t*)((gbytes)base + off);
-          if (!kmajor && kr + 8 > left) v = mask_tail8(v, left - kr);
+          if (!kmajor && kr + 8 > here) v = mask_tail8(v, here - kr);
         }
         return v;
       };
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        ta[j] = chunk(AKM, a_base + tiles * a_tile, a_off[j], wave * 2 + j);
-        tb[j] = chunk(!BKC, b_base + tiles * b_tile, b_off[j], wave * 2 + j);
+        const int q = wave * 2 + j;
+        ta[j] = chunk(AKM, a_base + at_tile * a_tile, AKM ? a_off[0][j] : kc_load_offset(q, lane, m0, P.Mv, P.lda), q);
+        tb[j] = chunk(!BKC, b_base + at_tile * b_tile, BKC ? kc_load_offset(q, lane, n0, P.Nv, P.ldb) : b_off[0][j], q);
       }
-      __syncthreads();                          // every wave has read the last whole tile
+      __syncthreads();                          // every wave has read the tiles before
       unsigned char* at = smem + wave * 2048 + lane * 16;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
@@ -194,7 +256,11 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         *reinterpret_cast<u32x4_t*>(at + kMidPart + j * 1024) = tb[j];
       }
       __syncthreads();
-      read_frags(0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        fb[0][i] = BKC ? read_kc(lds0 + kMidPart + kc_frag_offset(wn, lane) + i * 1024) : read_km(b_reg[0][BKC ? 0 : i]);
+        fa[0][i] = AKM ? read_km(a_reg[0][AKM ? i : 0]) : read_kc(lds0 + kc_frag_offset(wm, lane) + i * 1024);
+      }
       multiply(0);
     }
     if constexpr (CHAIN) {
@@ -248,26 +314,33 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
     zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n0, min(n0 + kMidTile, P.Ns), t);
 }
 
-template <typename TOut, int LAYOUT, bool CHAIN>
+template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU>
 inline bool launch_dot_mid_as(const MfmaLaunch& l, hipStream_t stream) {
+  constexpr int lds = mid_stages<PER_CU>() * kMidStage;
   static std::once_flag once[kMaxDevices];
   static bool ok[kMaxDevices];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
   std::call_once(once[dev], [dev] {
-    ok[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&dot_mid_kernel<TOut, LAYOUT, CHAIN>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, kMidLds) == hipSuccess;
+    ok[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
   });
   if (!ok[dev]) return false;
-  hipLaunchKernelGGL((dot_mid_kernel<TOut, LAYOUT, CHAIN>), dim3(static_cast<unsigned>(l.tiles)), dim3(kMidThreads), kMidLds, stream, *l.inl, l.tab,
+  hipLaunchKernelGGL((dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU>), dim3(static_cast<unsigned>(l.tiles)), dim3(kMidThreads), lds, stream, *l.inl, l.tab,
                      l.n_prob, l.epilogue);
   return hipGetLastError() == hipSuccess;
 }
 
+template <int LAYOUT, bool CHAIN>
+bool launch_dot_mid_out(const MfmaLaunch& l, int32_t out_dtype, hipStream_t stream) {
+  if (l.tiles <= 256)
+    return out_dtype == GSPMD_F32 ? launch_dot_mid_as<float, LAYOUT, CHAIN, 1>(l, stream) : launch_dot_mid_as<bf16_bits, LAYOUT, CHAIN, 1>(l, stream);
+  return out_dtype == GSPMD_F32 ? launch_dot_mid_as<float, LAYOUT, CHAIN, 2>(l, stream) : launch_dot_mid_as<bf16_bits, LAYOUT, CHAIN, 2>(l, stream);
+}
+
 template <int LAYOUT>
 bool launch_dot_mid_layout(const MfmaLaunch& l, int32_t out_dtype, bool chain, hipStream_t stream) {
-  if (out_dtype == GSPMD_F32) return chain ? launch_dot_mid_as<float, LAYOUT, true>(l, stream) : launch_dot_mid_as<float, LAYOUT, false>(l, stream);
-  return chain ? launch_dot_mid_as<bf16_bits, LAYOUT, true>(l, stream) : launch_dot_mid_as<bf16_bits, LAYOUT, false>(l, stream);
+  return chain ? launch_dot_mid_out<LAYOUT, true>(l, out_dtype, stream) : launch_dot_mid_out<LAYOUT, false>(l, out_dtype, stream);
 }
 
 }  // namespace gspmd

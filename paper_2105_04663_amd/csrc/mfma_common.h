@@ -15,6 +15,7 @@ typedef __attribute__((address_space(3))) short4_t lds_short4_t;
 
 // s_waitcnt immediate for gfx9: vmcnt [3:0]+[15:14], expcnt [6:4], lgkmcnt [11:8]
 constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | ((lgkm & 15) << 8); }
+constexpr int waitcnt_vm(int vm) { return waitcnt_imm(vm, 15); }      // vmcnt alone
 #define GSPMD_WAIT_ALL() __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0))
 
 // 16 bytes per lane from sbase + voff (bytes) straight into LDS at lds_addr + lane*16.  The compiler
