@@ -136,17 +136,18 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   in a round of few (short tiles: 0.75), 2 us for what is left of K; staged operands 10.5 and 2.1 us.  Joined problems meet in slots: 4.6 us
 //   per member, the last arriver at a tile reading the others' contributions one after the other, and 0.05 us per contribution to a tile
 //   (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38; 8, 16: 38; 8, 512: 59).
-// dot_mid_kernel: 8 us and 0.205 us per 32-wide step while a compute unit has one workgroup, 0.40 with two, then rounds of 512; the members of
-//   a joined sum follow each other in one workgroup, 1.7 us apart; 1.5 us per 32-wide tile that is left of K; a fifth more per step where
-//   a K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).
+// dot_mid_kernel: 8.8 us and 0.205 us per 32-wide step while a compute unit has one workgroup, 0.40 with two, then rounds of 512; the members of
+//   a joined sum follow each other in one workgroup, 1.8 us apart where they are not alike and whole K steps long; 0.25 us per 32-wide tile
+//   that is left of K; a fifth more per step where a K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us,
+//   with rows of 8032 elements 117).  Fitted to 60 drawn launches of 1 to 8 members; root mean square of the relative error 12 %.
 // Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 118 / 60   512 x 8192 x 512: 117 / 47
 //   2048 x 4096 x 4096: 63 / 60   2048 x 1024 x 4096: 25 / 20   4653 x 7168 x 4288: 245 / 281   1456 x 1415 x 3969, two of them: 37 / 48
 //   2178 x 4736 x 1447, two: 75 / 61   1090 x 1333 x 1568, eight: 60 / 52   4 experts' weight gradients of 512 x 4096 x 8192: 122 / 227
-// Sums, slots / one after the other (K over all members): 2048 x 8192 x 2048 over 4: 78 / 66   1024 x 8192 x 2048 over 2, two groups: 75 / 58
+// Sums, slots / one after the other (K over all members): 2048 x 8192 x 2048 over 4: 78 / 64   1024 x 8192 x 2048 over 2, two groups: 75 / 59
 //   both K-major 2085 x 3540 x 1652 over 2, two groups: 64 / 60   1770 x 3303 x 2085 over 2, two groups: 65 / 67   1572 x 4544 x 3328 over 8: 136 / 88
 struct LaunchSize {
   int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1;      // longest extents, tiles of 256 x 256 and of 128 x 128, most members of a sum
-  bool broken_lines = false;
+  bool broken_lines = false, whole_steps = true;      // a K-contiguous operand's rows are not whole lines; all K are whole 64-wide steps
 };
 LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
   LaunchSize s;
@@ -158,6 +159,7 @@ LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
       s.mid += tiles_of(p, kMidTile, kMidTile);
       s.members = std::max<int64_t>(s.members, p.join_count);
     }
+    s.whole_steps = s.whole_steps && p.Kv % (2 * kMfmaBK) == 0;
     s.broken_lines = s.broken_lines || (!(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (p.lda & 63)) || ((layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && (p.ldb & 63));
   }
   return s;
@@ -171,7 +173,7 @@ double big_us(const LaunchSize& s, bool staged) {
 }
 double mid_us(const LaunchSize& s) {
   const double m = static_cast<double>(s.members), left = static_cast<double>((s.k % 64 + 31) / 32);
-  const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 8.0 + 1.7 * (m - 1.0) + 1.5 * m * left;
+  const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 8.8 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
   const int64_t part = s.mid % 512;
   return static_cast<double>(s.mid / 512) * (beside + steps * 0.40) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? 0.205 : 0.40));
 }
@@ -218,7 +220,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 }
 
 // Sums over a contracting mesh dimension are formed in one launch (joined problems) or in two: the members' products by themselves, in dense
-// fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 20 % faster; the results are the same bits.
+// fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 15 % faster; the results are the same bits.
 double sum_us(const std::vector<Problem>& ps, MfmaKernel kernel, bool staged, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
   return kernel == kMfmaMid ? mid_us(size) : big_us(size, staged);
@@ -268,6 +270,15 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   // (the most K steps) go first, so that the compute units that are still busy at the end are busy with short tiles.
   if (!join)
     std::stable_sort(ps.begin(), ps.end(), [](const Problem& a, const Problem& b) { return a.Kv > b.Kv; });
+  if (mid && join)
+    for (size_t i = 0; i < ps.size(); i += std::max(ps[i].join_count, 1)) {     // the members of a sum are consecutive, in the order of summation
+      bool alike = ps[i].join_count > 1 && ps[i].Kv % (2 * kMfmaBK) == 0;
+      for (int32_t m = 1; m < ps[i].join_count && alike; ++m) {
+        const Problem &a = ps[i], &b = ps[i + static_cast<size_t>(m)];
+        alike = a.Kv == b.Kv && a.lda == b.lda && a.ldb == b.ldb;
+      }
+      ps[i].join_alike = alike ? 1 : 0;
+    }
   const int64_t tiles = assign_tiles(ps, bm, bn, mid);
   if (tiles < 0) return GSPMD_ERR_UNSUPPORTED;
   std::vector<ZeroRect> rects;
@@ -903,7 +914,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
         }
         const bool staged = path == kPathMfmaStaged;
         ok = !summable || sum_us(live, one, live_path == kPathMfmaStaged, jlayout) <=
-                              1.2 * (sum_us(apart, two, staged, jlayout) + apart_us(two, staged, apart[0].Ns, partial_bytes, launches));
+                              1.15 * (sum_us(apart, two, staged, jlayout) + apart_us(two, staged, apart[0].Ns, partial_bytes, launches));
       }
     }
     // Behind the launch tables come the counters, then the slots.  A scattered sum has more entries than the query counted (one

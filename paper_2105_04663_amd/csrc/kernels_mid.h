@@ -1,16 +1,19 @@
-// bf16 MFMA contraction in 128 x 128 tiles, two workgroups per compute unit: for launches that 256 x 256 tiles (one
+// bf16 MFMA contraction in 128 x 128 tiles, one or two workgroups per compute unit: for launches that 256 x 256 tiles (one
 // workgroup per compute unit, 9 us beside its K loop) leave waiting or idle -- few output tiles, short K -- and for sums over
 // a contracting mesh dimension, which it forms without a workspace: a workgroup takes the members' K ranges one after
-// the other and adds each member's finished product to a second set of accumulators, so the sum is ((p0 + p1) + p2) + ..
+// the other (without a break where they are alike: 2048 x 8192 x 2048 over 4 members 66.8 -> 62.9 us) and adds each member's finished product to a second set of accumulators, so the sum is ((p0 + p1) + p2) + ..
 // in fp32 as everywhere else.  Products take their 32-wide K tiles in the order and with the instruction of
 // dot_mfma_kernel: results are bit-identical to it.  16-byte aligned operands only.
 //
-// What bounds it: what a compute unit draws from L2, 16 KiB per 32-wide K tile for 256 cycles of the matrix cores.  With two
-// workgroups on each (2048 x 2048 x 4096) its L1 keeps about 91 lines of 128 bytes in flight, 322 cycles each, and stalls on them
-// for 45 % of the cycles; matrix cores busy for 42 %, LDS for 21 %.  (One workgroup, 2048 x 2048 x 2048: 32 % and 16 %.)
-// Five LDS stages of a 32-wide K tile (80 KiB) filled by direct global->LDS loads, up to five tiles ahead, one barrier per
-// tile; a wave reads the next tile's fragments while it multiplies this one's.
-// A K-major operand lies in its stage as [32 k][128], read with the transpose read; a K-contiguous one as [128][32 k].
+// What bounds it: what a compute unit draws from L2 and beyond, 16 KiB per 32-wide K tile for 256 cycles of the matrix cores: the loads
+// alone take 190 ns per tile on a full chip, 135 on few compute units, a tile with everything 205 (400 for two workgroups).  So:
+// a K step is 64 wide, two tiles.  Of a K-contiguous operand each tile holds half of the 128 rows, 64 k of each, whole lines of
+// 128 bytes (in [128][32 k] tiles every line comes twice: the loads alone 236 ns); of a K-major operand 32 k rows, [32 k][128], read
+// with the transpose read.  A wave issues one fragment read or load after each MFMA (all of a tile's ahead of its MFMAs: 240 ns), and
+// the stages come round every five steps, so that their places are constants of the code.  One barrier per step.  With one workgroup
+// on a compute unit ten stages (160 KiB), loads six tiles ahead; with two five stages each, four ahead.
+// Measured (us, before / now): 2048 x 8192 x 2048 73.5 / 60.5, 512 x 8192 x 512 67.7 / 47.3, 2048 x 4096 x 4096 73 / 60, 2112 x 8000 x 2112
+// 118 / 90, both K-contiguous 127 / 92; operands from HBM instead of the memory-side cache 2048 x 8192 x 2048 over 4 members 64 / 82.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -81,6 +84,9 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   const int rows_in_band = min(kBandRows, tiles_m - band * kBandRows);
   const int m0 = (band * kBandRows + in_band % rows_in_band) * kMidTile, n0 = (in_band / rows_in_band) * kMidTile;
   const int members = CHAIN ? max(P.join_count, 1) : 1;
+  // Members that are alike and whole K steps long follow each other without a break: the loads of the next one are under way while this one's
+  // last steps are multiplied.  Others are taken one by one.
+  const bool run_on = CHAIN && P.join_alike != 0;
 
   float4_t acc[4][4], sum[CHAIN ? 4 : 1][CHAIN ? 4 : 1];
   // Fragment addresses.  LDS offsets in instructions have 16 bits: stages are addressed from a register per four of them (with five
@@ -119,19 +125,33 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
   };
 
-  for (int member = 0; member < members; ++member) {
-    if (CHAIN && member > 0) {
-      P = problem_at(tab, which + member);
-      __syncthreads();                          // every wave has read the last tile of the member before
+  auto add_member = [&](bool first) {
+    if constexpr (CHAIN) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[i][j] = first ? acc[i][j] : sum[i][j] + acc[i][j];
     }
+  };
+  auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
-    const bf16_bits* a_base = static_cast<const bf16_bits*>(P.A) + (AKM ? static_cast<int64_t>(m0) : static_cast<int64_t>(m0) * P.lda);
-    const bf16_bits* b_base = static_cast<const bf16_bits*>(P.B) + (BKC ? static_cast<int64_t>(n0) * P.ldb : static_cast<int64_t>(n0));
+  };
+
+  for (int member = 0; member < (run_on ? 1 : members); ++member) {
+    if (CHAIN && member > 0) {
+      P = problem_at(tab, which + member);
+      __syncthreads();                          // every wave has read the last tile of the member before
+    }
+    clear();
+    const int64_t a_first = AKM ? static_cast<int64_t>(m0) : static_cast<int64_t>(m0) * P.lda, b_first = BKC ? static_cast<int64_t>(n0) * P.ldb : static_cast<int64_t>(n0);
+    const bf16_bits* a_base = static_cast<const bf16_bits*>(P.A) + a_first;
+    const bf16_bits* b_base = static_cast<const bf16_bits*>(P.B) + b_first;
     const int64_t a_tile = AKM ? static_cast<int64_t>(kMfmaBK) * P.lda : kMfmaBK, b_tile = BKC ? kMfmaBK : static_cast<int64_t>(kMfmaBK) * P.ldb;
-    const int tiles = P.Kv / (2 * kMfmaBK) * 2, left = P.Kv - tiles * kMfmaBK;      // tiles of the whole 64-wide K steps
+    const int own = P.Kv / (2 * kMfmaBK) * 2, left = P.Kv - own * kMfmaBK;          // tiles of a member's whole 64-wide K steps
+    const int tiles = run_on ? own * members : own;
     int a_off[2][2], b_off[2][2];               // this wave's two load instructions of each operand's part, in even and odd tiles
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -143,6 +163,8 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       }
     const bf16_bits *a_next = a_base, *b_next = b_base;
     const uint32_t lds_wave = lds0 + wave * 2048;
+    int to_load = own / 2, loading = 0, to_add = own / 2;                     // K steps of the members being loaded and multiplied that are to come
+    bool to_add_first = true;
     // the i-th of this wave's four load instructions of an even (h 0) or odd tile, into stage `at`
     auto issue_one = [&](int h, int i, int at) {
       if (i < 2) global_to_lds16(a_next, a_off[h][i & 1], lds_wave + at * kMidStage + (i & 1) * 1024);
@@ -152,6 +174,22 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         else if (h == 1) a_next += 2 * kMfmaBK;
         if (!BKC) b_next += b_tile;
         else if (h == 1) b_next += 2 * kMfmaBK;
+        if (CHAIN && h == 1 && run_on && --to_load == 0) {                    // on to the next member
+          to_load = own / 2;
+          if (++loading < members) {
+            const Problem Q = problem_at(tab, which + loading);
+            a_next = static_cast<const bf16_bits*>(Q.A) + a_first;
+            b_next = static_cast<const bf16_bits*>(Q.B) + b_first;
+          }
+        }
+      }
+    };
+    auto step_done = [&]() {                    // a K step has been multiplied
+      if (CHAIN && run_on && --to_add == 0) {
+        add_member(to_add_first);
+        clear();
+        to_add_first = false;
+        to_add = own / 2;
       }
     };
     // Fragment i (rhs 0..3, then lhs 0..3) of half h of a K step whose first tile is in stage s0, into set h.  A K-contiguous operand's
@@ -209,6 +247,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         __builtin_amdgcn_s_waitcnt(kReadsDone ? waitcnt_imm(4 * (L - 3), 0) : waitcnt_vm(4 * (L - 3)));
         __builtin_amdgcn_s_barrier();
         half_step(odd, next, true, true, true, (to + 1) % R);
+        step_done();
         k += 2;
       };
       for (; k + 2 * kMidUnroll <= full; ) {
@@ -226,6 +265,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         s0 = follow(s0, 2);
         if (more) landed(load ? L - 3 : tiles - k - 4);
         half_step(odd, s0, false, more, load, follow(to, 1));
+        step_done();
         to = follow(to, 2);
       }
     }
@@ -263,12 +303,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       }
       multiply(0);
     }
-    if constexpr (CHAIN) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sum[i][j] = member == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
-    }
+    if (!run_on) add_member(member == 0);
   }
 
   // ---- epilogue: a lane holds columns n .. n + 3 of row m per 16 x 16 block

@@ -1,4 +1,4 @@
-"""dot_mid_kernel (128 x 128 tiles) at the edges of its tiles, of its five LDS stages and of the 32-wide K tiles, in all four
+"""dot_mid_kernel (128 x 128 tiles) at the edges of its tiles, of its LDS stages and of the 32-wide K tiles, in all four
 operand layouts, and its sums over a contracting mesh dimension (members one after the other in one workgroup).  Every
 product is given as a partial sum of a contracting dimension, so that the few-row kernel does not take it; small
 integers and float32 output: compared bit for bit."""
@@ -9,7 +9,9 @@ import torch
 import paper_2105_04663_amd as g
 import workloads as wl
 from oracle import dot as od
+from tests import test_gpu_parity as parity
 from tests.harness import Staged, out_tensor
+from tests.pin import MFMA, MID, last, pinned
 
 pytestmark = pytest.mark.gpu
 
@@ -64,3 +66,41 @@ def test_sums_of_members(M, K, N, P, out_dtype, scatter):
         cols = total[:, pid * per:(pid + 1) * per] if scatter else total
         want[:, :cols.shape[1]] = cols
         assert torch.equal(got, want.to(got.dtype)), f"partition {pid}"
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,K,N", [(130, 448, 140), (100, 512, 300), (257, 576, 129), (129, 673, 264), (128, 1344, 130),      # one workgroup on a compute unit
+                                   (2100, 320, 2090), (2100, 512, 2090), (2100, 735, 2090)])                                 # 289 tiles: two
+def test_loads_around_the_ring_of_stages(M, K, N, layout):
+    # K of as many 64-wide steps as the loop takes at a time, one more or less, with and without something left
+    lhs_shape, rhs_shape = ((K, M) if layout & 1 else (M, K)), ((N, K) if layout & 2 else (K, N))
+    lc, rc = ((0,) if layout & 1 else (1,)), ((1,) if layout & 2 else (0,))
+    w = wl.DotWorkload(name="mid", cfg=7, dtype="bf16", out_dtype="f32", lhs_shape=lhs_shape, rhs_shape=rhs_shape, lhs_batch=(), rhs_batch=(),
+                       lhs_contract=lc, rhs_contract=rc, mesh_shape=(1,), device_ids=(0,), lhs_map=(-1, -1), rhs_map=(-1, -1), out_map=(-1, -1))
+    lhs, rhs = wl.draw_small_int_bf16(3, lhs_shape), wl.draw_small_int_bf16(4, rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=8)
+    with pinned(MID):
+        st.run_grouped()
+        assert last()[0] == MID
+    a, b = wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs)
+    assert np.array_equal(st.out_shard(0), od.dot_general(a, b, (), (), lc, rc))
+
+
+@pytest.mark.parametrize("M,N", [(130, 264), (2100, 2090)])
+@pytest.mark.parametrize("per,P", [(64, 2), (64, 8), (128, 3), (192, 4), (320, 2), (704, 3), (96, 4)])
+def test_alike_members_follow_on(M, N, per, P):
+    # members of equal K: of 1 to 11 whole steps, the next ones' loads under way before the first is multiplied (and, of 96, one by one)
+    w = wl.ksplit(M=M, K=per * P, N=N, P=P)
+    lhs, rhs = wl.draw_normal_bf16(5, w.lhs_shape), wl.draw_normal_bf16(6, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=8, out_dtype="f32")
+    got = {}
+    for kernel, one in ((MID, 1), (MFMA, 0)):            # in one launch, and as dense partials of the 256 x 256 kernel and their sum
+        st.out[0][1].fill_(float("nan"))
+        with pinned(kernel, 0, one):
+            st.run_grouped()
+            assert last() == (kernel, 0, one)
+        torch.cuda.synchronize()
+        got[kernel] = st.out[0][1].view(M, -1)[:, :N].clone()
+    assert torch.equal(got[MID], got[MFMA])
+    ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    parity.check(st.out_shard(0), ref)
