@@ -225,13 +225,11 @@ double sum_us(const std::vector<Problem>& ps, MfmaKernel kernel, bool staged, in
   const LaunchSize size = launch_size(ps, layout);
   return kernel == kMfmaMid ? mid_us(size) : big_us(size, staged);
 }
-// What partials cost beside their launch: 1 us, 2.5 us per sum kernel and 0.31 us per MB written and read back, 0.9 where rows that are not
-// 16-byte aligned go out element by element.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
+// What partials cost beside their launch: 1 us, 2.5 us per sum kernel and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
 // 508 x 4085 over 2, unaligned: 36 / 48; 1953 x 409 x 454 over 4: 15 / 20; 4023 x 8430 x 1215 over 8: 142 / 158.
-double apart_us(MfmaKernel two, bool staged, int64_t cols, int64_t partial_bytes, int64_t launches) {
-  const bool by_element = two == kMfmaBig && !staged && (cols & 3);
-  return 1.0 + 2.5 * static_cast<double>(launches) + (by_element ? 0.9e-6 : 0.31e-6) * static_cast<double>(partial_bytes);
+double apart_us(int64_t partial_bytes, int64_t launches) {
+  return 1.0 + 2.5 * static_cast<double>(launches) + 0.31e-6 * static_cast<double>(partial_bytes);
 }
 
 // The kernel of a launch of bf16 problems: by the rule above, unless a test has pinned one that may take them.
@@ -914,7 +912,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
         }
         const bool staged = path == kPathMfmaStaged;
         ok = !summable || sum_us(live, one, live_path == kPathMfmaStaged, jlayout) <=
-                              1.15 * (sum_us(apart, two, staged, jlayout) + apart_us(two, staged, apart[0].Ns, partial_bytes, launches));
+                              1.15 * (sum_us(apart, two, staged, jlayout) + apart_us(partial_bytes, launches));
       }
     }
     // Behind the launch tables come the counters, then the slots.  A scattered sum has more entries than the query counted (one

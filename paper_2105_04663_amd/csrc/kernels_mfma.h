@@ -45,7 +45,6 @@ typedef __attribute__((address_space(1))) u32x4_t global_u32x4_t;
 template <int ALIGN> struct Store16;
 template <> struct Store16<2> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(2))); };
 template <> struct Store16<4> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(4))); };
-template <> struct Store16<16> { typedef u32x4_t type; };
 
 // Zeros over rows [row_begin, row_end) x columns [col_begin, col_end) of an output block, by all kMfmaThreads threads of
 // the workgroup: the rows of the static block below the last tile row's footprint.  `vec`: 16-byte stores are
@@ -575,10 +574,9 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
   timeline_stamp(rec, 5, t);
   // ---- epilogue: lane holds, for row m, columns n .. n+3 of each 16-column block
   TOut* __restrict__ Cg = static_cast<TOut*>(P.C);
-  typedef __attribute__((address_space(1))) typename Store16<STAGED ? static_cast<int>(sizeof(TOut)) : 16>::type out16_t;
-  const bool vec_ok = ((P.ldc & 3) == 0) && ((reinterpret_cast<uintptr_t>(Cg) & 15) == 0);
-  // the whole-tile path stores 16 bytes per lane: rows of 8 bf16 or 4 fp32 elements must keep that alignment
-  const bool rows_16b = (P.ldc & (16 / static_cast<int>(sizeof(TOut)) - 1)) == 0;
+  typedef __attribute__((address_space(1))) typename Store16<static_cast<int>(sizeof(TOut))>::type out16_t;
+  // rows below the tile's own are cleared in 16-byte stores where the output's rows keep that alignment
+  const bool rows_16b = (P.ldc & (16 / static_cast<int>(sizeof(TOut)) - 1)) == 0 && (reinterpret_cast<uintptr_t>(Cg) & 15) == 0;
   const int rows_own = m_end - m0, rows_write = m_write_end - m0;    // of the tile's 256 rows: valid, written (zeros between)
   // the last tile row of a problem also clears what the static block has below its 256-row footprint (an expert with
   // few occupied slots; at most kRowsBelow rows), over this tile's columns; what lies beyond, and the static columns
@@ -586,171 +584,136 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
   if (m_end == P.Mv && m_write_end < P.Ms) {
     const int col_end = min(n0 + kMfmaBN, P.Ns);
     constexpr int kPer = 16 / static_cast<int>(sizeof(TOut));
-    zero_rows_below<TOut>(Cg, P.ldc, m_write_end, rows_cleared(P.Mv, P.Ms), n0, col_end, vec_ok && rows_16b && ((col_end - n0) % kPer) == 0, t);
+    zero_rows_below<TOut>(Cg, P.ldc, m_write_end, rows_cleared(P.Mv, P.Ms), n0, col_end, rows_16b && ((col_end - n0) % kPer) == 0, t);
   }
-  if (STAGED || (vec_ok && rows_16b)) {
-    // 16-byte stores of whole lines; bf16 through the hardware round-to-nearest-even conversion.  A tile with all 256
-    // columns (and rows) valid stores without predicates; in the last tile column a lane's 16 bytes are masked beyond
-    // the valid columns, and the chunk that the static block ends in (if it ends inside one) is stored element by
-    // element, so that nothing is written beyond the block's static width.
-    // Relu or not is decided once per workgroup, not per element: with the test inside the conversion loop the compiler
-    // turns every element into a compare, a select and a repack.  Stores go through global-address-space pointers
-    // (a flat store also counts as an LDS operation, and the waits for the staging reads would wait for it) with the
-    // non-temporal hint (the output is written once and not read again by this launch; with 2 GB of output per launch
-    // the hint is worth 8 %); all of a wave's staging reads are issued before its first store.
-    const bool relu = epilogue == GSPMD_EPILOGUE_RELU;
-    const bool all_cols = n0 + kMfmaBN <= P.Nv;
-    const bool whole = rows_own >= kMfmaBM && all_cols;          // all 256 rows and columns valid: no predicates
-    if constexpr (sizeof(TOut) == 2) {
-      // bf16: the wave's 128 x 64 block is a 128-byte line per row, but a lane holds only 8 bytes of it per 16-column
-      // block.  Stage it through the wave's own slice of LDS (free now: every wave's LDS reads are over and no tile load is in flight;
-      // rows padded to 144 bytes against bank conflicts) and store 16 bytes per lane, 8 lanes per row: whole lines.
-      constexpr int kPitch = 144;
-      unsigned char* slice = smem + wave * (128 * kPitch);
-      typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+  // 16-byte stores of whole lines, at whatever element alignment the output's rows have (element by element, float32 partials of 3456 x 1914 x 698
+  // over 2 members, 349 columns each, and their sum took 57 us; 45); bf16 through the hardware round-to-nearest-even conversion.  A tile with all 256
+  // columns (and rows) valid stores without predicates; in the last tile column a lane's 16 bytes are masked beyond
+  // the valid columns, and the chunk that the static block ends in (if it ends inside one) is stored element by
+  // element, so that nothing is written beyond the block's static width.
+  // Relu or not is decided once per workgroup, not per element: with the test inside the conversion loop the compiler
+  // turns every element into a compare, a select and a repack.  Stores go through global-address-space pointers
+  // (a flat store also counts as an LDS operation, and the waits for the staging reads would wait for it) with the
+  // non-temporal hint (the output is written once and not read again by this launch; with 2 GB of output per launch
+  // the hint is worth 8 %); all of a wave's staging reads are issued before its first store.
+  const bool relu = epilogue == GSPMD_EPILOGUE_RELU;
+  const bool all_cols = n0 + kMfmaBN <= P.Nv;
+  const bool whole = rows_own >= kMfmaBM && all_cols;          // all 256 rows and columns valid: no predicates
+  if constexpr (sizeof(TOut) == 2) {
+    // bf16: the wave's 128 x 64 block is a 128-byte line per row, but a lane holds only 8 bytes of it per 16-column
+    // block.  Stage it through the wave's own slice of LDS (free now: every wave's LDS reads are over and no tile load is in flight;
+    // rows padded to 144 bytes against bank conflicts) and store 16 bytes per lane, 8 lanes per row: whole lines.
+    constexpr int kPitch = 144;
+    unsigned char* slice = smem + wave * (128 * kPitch);
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+    auto stage = [&](auto relu_tag) {
+      constexpr bool kRelu = decltype(relu_tag)::value;
+#pragma unroll
+      for (int bm = 0; bm < 8; ++bm)
+#pragma unroll
+        for (int bn = 0; bn < 4; ++bn) {
+          float v[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = apply_epilogue(acc[bm][bn * 4 + j], kRelu ? GSPMD_EPILOGUE_RELU : GSPMD_EPILOGUE_NONE);
+          bf16x4_t o = {static_cast<__bf16>(v[0]), static_cast<__bf16>(v[1]), static_cast<__bf16>(v[2]), static_cast<__bf16>(v[3])};
+          *reinterpret_cast<bf16x4_t*>(slice + (bm * 16 + (lane & 15)) * kPitch + bn * 32 + (lane >> 4) * 8) = o;
+        }
+    };
+    if (relu) stage(std::true_type{}); else stage(std::false_type{});
+    out16_t* c0 = (out16_t*)(Cg + static_cast<int64_t>(m0 + wm * 128 + (lane >> 3)) * P.ldc + n0 + wn * 64 + (lane & 7) * 8);
+    const int64_t pitch8 = static_cast<int64_t>(P.ldc);      // 8 rows of bf16 in units of 16 bytes
+    const int row0 = wm * 128 + (lane >> 3);
+    u32x4_t v[16];
+#pragma unroll
+    for (int p = 0; p < 16; ++p) v[p] = *reinterpret_cast<const u32x4_t*>(slice + (p * 8 + (lane >> 3)) * kPitch + (lane & 7) * 16);
+    if (whole) {
+#pragma unroll
+      for (int p = 0; p < 16; ++p) __builtin_nontemporal_store(v[p], &c0[p * pitch8]);
+    } else if (all_cols) {
+#pragma unroll
+      for (int p = 0; p < 16; ++p) {
+        const int row = row0 + p * 8;
+        if (row >= rows_own) v[p] = u32x4_t{0u, 0u, 0u, 0u};
+        if (row < rows_write) __builtin_nontemporal_store(v[p], &c0[p * pitch8]);
+      }
+    } else {
+      const int col = n0 + wn * 64 + (lane & 7) * 8;                         // this lane's 8 columns
+      const int keep = max(0, min(8, P.Nv - col)), room = max(0, min(8, P.Ns - col));
+#pragma unroll
+      for (int p = 0; p < 16; ++p) {
+        const int row = row0 + p * 8;
+        const u32x4_t o = row < rows_own ? mask_tail8(v[p], keep) : u32x4_t{0u, 0u, 0u, 0u};
+        if (row >= rows_write) continue;
+        if (room == 8) {
+          __builtin_nontemporal_store(o, &c0[p * pitch8]);
+        } else {
+          bf16_bits* out = reinterpret_cast<bf16_bits*>(Cg) + static_cast<int64_t>(m0 + row) * P.ldc + col;
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (e < room) out[e] = static_cast<bf16_bits>(o[e >> 1] >> ((e & 1) * 16));
+        }
+      }
+    }
+  } else {
+    // fp32: a row of the wave's block is 256 bytes, of which a lane holds 16 per 16-column block.  Staged through the
+    // wave's LDS slice in two passes of 64 rows (rows padded to 272 bytes) and stored 16 lanes per row: whole rows.
+    // Whole tiles without the hint: fp32 outputs are mostly partial sums that the next kernel reads (products and their sum, with the
+    // hint / without: 2048 x 1024 x 4096 four times 127.4 / 123.3 us, 4096 x 1024 x 4096 four times 204 / 191, 8192 x 2048 x 4096 twice
+    // 285 / 267, 2048 x 2048 x 2048 eight times 213 / 213).
+    constexpr int kPitch = 272;
+    unsigned char* slice = smem + wave * (128 * 144);
+    out16_t* c0 = (out16_t*)(Cg + static_cast<int64_t>(m0 + wm * 128 + (lane >> 4)) * P.ldc + n0 + wn * 64 + (lane & 15) * 4);
+    const int64_t pitch4 = static_cast<int64_t>(P.ldc);      // 4 rows of fp32 in units of 16 bytes
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
       auto stage = [&](auto relu_tag) {
         constexpr bool kRelu = decltype(relu_tag)::value;
 #pragma unroll
-        for (int bm = 0; bm < 8; ++bm)
+        for (int b4 = 0; b4 < 4; ++b4) {
+          const int bm = pass * 4 + b4;
 #pragma unroll
           for (int bn = 0; bn < 4; ++bn) {
-            float v[4];
+            float4_t v;
 #pragma unroll
             for (int j = 0; j < 4; ++j) v[j] = apply_epilogue(acc[bm][bn * 4 + j], kRelu ? GSPMD_EPILOGUE_RELU : GSPMD_EPILOGUE_NONE);
-            bf16x4_t o = {static_cast<__bf16>(v[0]), static_cast<__bf16>(v[1]), static_cast<__bf16>(v[2]), static_cast<__bf16>(v[3])};
-            *reinterpret_cast<bf16x4_t*>(slice + (bm * 16 + (lane & 15)) * kPitch + bn * 32 + (lane >> 4) * 8) = o;
+            *reinterpret_cast<float4_t*>(slice + (b4 * 16 + (lane & 15)) * kPitch + bn * 64 + (lane >> 4) * 16) = v;
           }
+        }
       };
       if (relu) stage(std::true_type{}); else stage(std::false_type{});
-      out16_t* c0 = (out16_t*)(Cg + static_cast<int64_t>(m0 + wm * 128 + (lane >> 3)) * P.ldc + n0 + wn * 64 + (lane & 7) * 8);
-      const int64_t pitch8 = static_cast<int64_t>(P.ldc);      // 8 rows of bf16 in units of 16 bytes
-      const int row0 = wm * 128 + (lane >> 3);
       u32x4_t v[16];
 #pragma unroll
-      for (int p = 0; p < 16; ++p) v[p] = *reinterpret_cast<const u32x4_t*>(slice + (p * 8 + (lane >> 3)) * kPitch + (lane & 7) * 16);
+      for (int i = 0; i < 16; ++i) v[i] = *reinterpret_cast<const u32x4_t*>(slice + (i * 4 + (lane >> 4)) * kPitch + (lane & 15) * 16);
       if (whole) {
 #pragma unroll
-        for (int p = 0; p < 16; ++p) __builtin_nontemporal_store(v[p], &c0[p * pitch8]);
+        for (int i = 0; i < 16; ++i) c0[(pass * 16 + i) * pitch4] = v[i];
       } else if (all_cols) {
 #pragma unroll
-        for (int p = 0; p < 16; ++p) {
-          const int row = row0 + p * 8;
-          if (row >= rows_own) v[p] = u32x4_t{0u, 0u, 0u, 0u};
-          if (row < rows_write) __builtin_nontemporal_store(v[p], &c0[p * pitch8]);
+        for (int i = 0; i < 16; ++i) {
+          const int row = wm * 128 + pass * 64 + i * 4 + (lane >> 4);
+          if (row >= rows_own) v[i] = u32x4_t{0u, 0u, 0u, 0u};
+          if (row < rows_write) c0[(pass * 16 + i) * pitch4] = v[i];
         }
       } else {
-        const int col = n0 + wn * 64 + (lane & 7) * 8;                         // this lane's 8 columns
-        const int keep = max(0, min(8, P.Nv - col)), room = max(0, min(8, P.Ns - col));
+        const int col = n0 + wn * 64 + (lane & 15) * 4;                      // this lane's 4 columns
+        const int keep = max(0, min(4, P.Nv - col)), room = max(0, min(4, P.Ns - col));
 #pragma unroll
-        for (int p = 0; p < 16; ++p) {
-          const int row = row0 + p * 8;
-          const u32x4_t o = row < rows_own ? mask_tail8(v[p], keep) : u32x4_t{0u, 0u, 0u, 0u};
+        for (int i = 0; i < 16; ++i) {
+          const int row = wm * 128 + pass * 64 + i * 4 + (lane >> 4);
+          u32x4_t o = v[i];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (row >= rows_own || e >= keep) o[e] = 0u;
           if (row >= rows_write) continue;
-          if (room == 8) {
-            __builtin_nontemporal_store(o, &c0[p * pitch8]);
+          if (room == 4) {
+            __builtin_nontemporal_store(o, &c0[(pass * 16 + i) * pitch4]);
           } else {
-            bf16_bits* out = reinterpret_cast<bf16_bits*>(Cg) + static_cast<int64_t>(m0 + row) * P.ldc + col;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (e < room) out[e] = static_cast<bf16_bits>(o[e >> 1] >> ((e & 1) * 16));
-          }
-        }
-      }
-    } else {
-      // fp32: a row of the wave's block is 256 bytes, of which a lane holds 16 per 16-column block.  Staged through the
-      // wave's LDS slice in two passes of 64 rows (rows padded to 272 bytes) and stored 16 lanes per row: whole rows.
-      // Whole tiles without the hint: fp32 outputs are mostly partial sums that the next kernel reads (products and their sum, with the
-      // hint / without: 2048 x 1024 x 4096 four times 127.4 / 123.3 us, 4096 x 1024 x 4096 four times 204 / 191, 8192 x 2048 x 4096 twice
-      // 285 / 267, 2048 x 2048 x 2048 eight times 213 / 213).
-      constexpr int kPitch = 272;
-      unsigned char* slice = smem + wave * (128 * 144);
-      out16_t* c0 = (out16_t*)(Cg + static_cast<int64_t>(m0 + wm * 128 + (lane >> 4)) * P.ldc + n0 + wn * 64 + (lane & 15) * 4);
-      const int64_t pitch4 = static_cast<int64_t>(P.ldc);      // 4 rows of fp32 in units of 16 bytes
-#pragma unroll
-      for (int pass = 0; pass < 2; ++pass) {
-        auto stage = [&](auto relu_tag) {
-          constexpr bool kRelu = decltype(relu_tag)::value;
-#pragma unroll
-          for (int b4 = 0; b4 < 4; ++b4) {
-            const int bm = pass * 4 + b4;
-#pragma unroll
-            for (int bn = 0; bn < 4; ++bn) {
-              float4_t v;
-#pragma unroll
-              for (int j = 0; j < 4; ++j) v[j] = apply_epilogue(acc[bm][bn * 4 + j], kRelu ? GSPMD_EPILOGUE_RELU : GSPMD_EPILOGUE_NONE);
-              *reinterpret_cast<float4_t*>(slice + (b4 * 16 + (lane & 15)) * kPitch + bn * 64 + (lane >> 4) * 16) = v;
-            }
-          }
-        };
-        if (relu) stage(std::true_type{}); else stage(std::false_type{});
-        u32x4_t v[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = *reinterpret_cast<const u32x4_t*>(slice + (i * 4 + (lane >> 4)) * kPitch + (lane & 15) * 16);
-        if (whole) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) c0[(pass * 16 + i) * pitch4] = v[i];
-        } else if (all_cols) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int row = wm * 128 + pass * 64 + i * 4 + (lane >> 4);
-            if (row >= rows_own) v[i] = u32x4_t{0u, 0u, 0u, 0u};
-            if (row < rows_write) c0[(pass * 16 + i) * pitch4] = v[i];
-          }
-        } else {
-          const int col = n0 + wn * 64 + (lane & 15) * 4;                      // this lane's 4 columns
-          const int keep = max(0, min(4, P.Nv - col)), room = max(0, min(4, P.Ns - col));
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int row = wm * 128 + pass * 64 + i * 4 + (lane >> 4);
-            u32x4_t o = v[i];
+            uint32_t* out = reinterpret_cast<uint32_t*>(Cg) + static_cast<int64_t>(m0 + row) * P.ldc + col;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (row >= rows_own || e >= keep) o[e] = 0u;
-            if (row >= rows_write) continue;
-            if (room == 4) {
-              __builtin_nontemporal_store(o, &c0[(pass * 16 + i) * pitch4]);
-            } else {
-              uint32_t* out = reinterpret_cast<uint32_t*>(Cg) + static_cast<int64_t>(m0 + row) * P.ldc + col;
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (e < room) out[e] = o[e];
-            }
+              if (e < room) out[e] = o[e];
           }
         }
-      }
-    }
-    if (rec != nullptr) {
-      timeline_stamp(rec, 6, t);
-      GSPMD_WAIT_ALL();
-      timeline_stamp(rec, 7, t);
-    }
-    return;
-  }
-#pragma unroll
-  for (int bm = 0; bm < 8; ++bm) {
-    const int m = m0 + wm * 128 + bm * 16 + (lane & 15);
-    if (m >= m_write_end) continue;
-    const bool mrow = m < m_end;
-    TOut* crow = Cg + static_cast<int64_t>(m) * P.ldc;
-#pragma unroll
-    for (int bn = 0; bn < 4; ++bn) {
-      const int n = n0 + wn * 64 + bn * 16 + (lane >> 4) * 4;
-      if (n >= P.Ns) continue;
-      float v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = (mrow && n + j < P.Nv) ? apply_epilogue(acc[bm][bn * 4 + j], epilogue) : 0.f;
-      if (vec_ok && n + 4 <= P.Ns) {
-        if constexpr (sizeof(TOut) == 4) {
-          *reinterpret_cast<float4*>(crow + n) = make_float4(v[0], v[1], v[2], v[3]);
-        } else {
-          ushort4 o;
-          o.x = float_to_bf16(v[0]); o.y = float_to_bf16(v[1]); o.z = float_to_bf16(v[2]); o.w = float_to_bf16(v[3]);
-          *reinterpret_cast<ushort4*>(crow + n) = o;
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (n + j < P.Ns) store_from_float<TOut>(crow + n + j, v[j]);
       }
     }
   }
