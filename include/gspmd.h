@@ -177,7 +177,8 @@ typedef struct {
  * the whole launch).  Within each class the library chooses kernel and tile by size. */
 typedef enum {
   GSPMD_KERNEL_SCALAR = 0,       /* leading dimensions too long for 32-bit offsets inside a tile: 64 x 64 tiles, fp32 FMA */
-  GSPMD_KERNEL_MFMA_STAGED = 1,  /* MFMA, operands loaded at element alignment: any other lda and ldb */
+  GSPMD_KERNEL_MFMA_STAGED = 1,  /* MFMA, operands loaded at element alignment: any other lda and ldb (even ones go straight to LDS
+                                  * too, word by word, where their tiles allow; odd ones through registers) */
   GSPMD_KERNEL_MFMA = 2          /* MFMA, 16-byte aligned operand loads: lda and ldb multiples of 8 elements */
 } gspmd_kernel_path;
 

@@ -72,10 +72,10 @@ int64_t assign_tiles(std::vector<Problem>& ps, int bm, int bn, bool chain = fals
   return t;
 }
 
-// Which contraction kernel a launch can take: the MFMA kernel with direct global->LDS loads needs 16-byte aligned
-// operand pointers and leading dimensions that are multiples of 8 elements; its register-staged variant takes elements
-// at any (even) address; longer rows (and fp32 operands) go to the scalar-FMA kernel.
-enum KernelPath { kPathFallback = 0, kPathMfmaStaged = 1, kPathMfmaDirect = 2 };
+// Which contraction kernels a launch can take: those with direct global->LDS loads take rows of whole 32-bit words (even leading
+// dimensions, pointers at multiples of 4 bytes), where a K-major operand's rows are not padded to 16 bytes only the rhs's and from one tile of
+// columns on; the register-staged variant takes elements at any (even) address; longer rows (and fp32 operands) go to the scalar-FMA kernel.
+enum KernelPath { kPathFallback = 0, kPathMfmaStaged = 1, kPathMfmaWords = 2, kPathMfmaDirect = 3 };
 
 KernelPath kernel_path(const std::vector<Problem>& ps, int32_t in_dtype, int32_t layout, bool check_pointers = true) {
   if (in_dtype != GSPMD_BF16) return kPathFallback;
@@ -87,7 +87,12 @@ KernelPath kernel_path(const std::vector<Problem>& ps, int32_t in_dtype, int32_t
   for (const auto& p : ps) {
     const uintptr_t ptrs = check_pointers ? reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B) : 0;
     if (p.lda > max_lda || p.ldb > max_ldb || (ptrs & 1)) return kPathFallback;
-    if ((ptrs & 15) || ((p.lda | p.ldb) & 7)) path = kPathMfmaStaged;
+    const uintptr_t a = check_pointers ? reinterpret_cast<uintptr_t>(p.A) : 0, b = check_pointers ? reinterpret_cast<uintptr_t>(p.B) : 0;
+    const bool a_loose = (a & 15) || (p.lda & 7), b_loose = (b & 15) || (p.ldb & 7);
+    if (!a_loose && !b_loose) continue;
+    const bool words = !((a | b) & 3) && !((p.lda | p.ldb) & 1) && !(a_loose && (layout & GSPMD_LAYOUT_LHS_K_MAJOR)) &&
+                       !(b_loose && !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && p.Nv < kMidTile);
+    path = std::min(path, words ? kPathMfmaWords : kPathMfmaStaged);
   }
   return path;
 }
@@ -125,6 +130,7 @@ enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_T
 struct MfmaChoice {
   MfmaKernel kernel;
   int row_blocks;
+  bool staged = false;      // dot_mfma_kernel: operands through registers
 };
 
 // What this thread's launches are pinned to, and what its last one took (testing.h).
@@ -147,6 +153,7 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   both K-major 2085 x 3540 x 1652 over 2, two groups: 64 / 60   1770 x 3303 x 2085 over 2, two groups: 65 / 67   1572 x 4544 x 3328 over 8: 136 / 88
 struct LaunchSize {
   int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1;      // longest extents, tiles of 256 x 256 and of 128 x 128, most members of a sum
+  int64_t cols = INT32_MAX;                                    // fewest columns
   bool broken_lines = false, whole_steps = true;      // a K-contiguous operand's rows are not whole lines; all K are whole 64-wide steps
 };
 LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
@@ -154,6 +161,7 @@ LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
   for (const auto& p : ps) {
     s.rows = std::max<int64_t>(s.rows, p.Mv);
     s.k = std::max<int64_t>(s.k, p.Kv);
+    s.cols = std::min<int64_t>(s.cols, p.Nv);
     s.big += tiles_of(p, kMfmaBM, kMfmaBN);
     if (p.join_slot == 0) {
       s.mid += tiles_of(p, kMidTile, kMidTile);
@@ -196,23 +204,27 @@ double mid_us(const LaunchSize& s) {
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
 // (with_records): the choice is the same with and without, so results are.
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
+// dot_mfma_kernel's direct variants take a K-major rhs with loose rows from one of their tiles of columns on
+bool big_staged(const LaunchSize& size, KernelPath path, int32_t layout) {
+  return path == kPathMfmaStaged || (path == kPathMfmaWords && !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && size.cols < kMfmaBN);
+}
 MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   MfmaChoice choice{kMfmaBig, 0};
-  const bool staged = path == kPathMfmaStaged;
+  const bool loose = path == kPathMfmaStaged;
   const LaunchSize size = launch_size(ps, layout);
   if (size.rows == 0) return choice;
-  double best = big_us(size, staged);
-  if (!staged) {
+  double best = big_us(size, choice.staged = big_staged(size, path, layout));
+  if (!loose) {
     const double us = mid_us(size);
-    if (us < 0.95 * best) { best = us; choice.kernel = kMfmaMid; }
+    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0}; }
   }
-  if (!ordered && (staged || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
+  if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((size.k + 255) / 256);
     const struct { int blocks; double aligned, beside, unaligned; } kinds[] = {{1, 1.0, 3.2, 1.2}, {2, 1.3, 4.3, 1.25}, {4, 1.7, 6.5, 1.55}};
     for (const auto& kind : kinds) {
       int64_t tiles = 0;
       for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
-      const double us = static_cast<double>((tiles + 255) / 256) * (staged ? kind.beside + rounds8 * kind.unaligned : 4.0 + rounds8 * kind.aligned);
+      const double us = static_cast<double>((tiles + 255) / 256) * (loose ? kind.beside + rounds8 * kind.unaligned : 4.0 + rounds8 * kind.aligned);
       if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks}; }
     }
   }
@@ -221,9 +233,9 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 
 // Sums over a contracting mesh dimension are formed in one launch (joined problems) or in two: the members' products by themselves, in dense
 // fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 15 % faster; the results are the same bits.
-double sum_us(const std::vector<Problem>& ps, MfmaKernel kernel, bool staged, int32_t layout) {
+double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
-  return kernel == kMfmaMid ? mid_us(size) : big_us(size, staged);
+  return choice.kernel == kMfmaMid ? mid_us(size) : big_us(size, choice.staged);
 }
 // What partials cost beside their launch: 1 us, 2.5 us per sum kernel and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
@@ -236,8 +248,8 @@ double apart_us(int64_t partial_bytes, int64_t launches) {
 MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   if (path == kPathFallback) return MfmaChoice{kMfmaNone, 0};
   const MfmaKernel pin = static_cast<MfmaKernel>(t_pin.kernel);
-  if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && path == kPathMfmaDirect) || (pin == kMfmaSplit && !ordered))
-    return MfmaChoice{pin, t_pin.row_blocks};
+  if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && path != kPathMfmaStaged) || (pin == kMfmaSplit && !ordered))
+    return MfmaChoice{pin, t_pin.row_blocks, pin == kMfmaBig && big_staged(launch_size(ps, layout), path, layout)};
   return choose_mfma(ps, path, layout, ordered);
 }
 
@@ -259,6 +271,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   // joined problems come with the caller's choice between the two kernels that keep the order of summation
   MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : pick_kernel(ps, path, layout, ordered);
   if (!join) choice.kernel = with_records(choice.kernel);
+  choice.staged = choice.kernel == kMfmaBig && big_staged(launch_size(ps, layout), path, layout);
   const bool mfma = choice.kernel != kMfmaNone;
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
   const bool mid = choice.kernel == kMfmaMid;
@@ -336,7 +349,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       }
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, join ? join->partials : nullptr, join ? join->counters : nullptr,
                          g_timeline.load(std::memory_order_acquire), g_timeline_records.load(std::memory_order_acquire)};
-      if (!launch_dot_mfma(l, layout, out_dtype, path == kPathMfmaStaged, stream)) return GSPMD_ERR_DEVICE;
+      if (!launch_dot_mfma(l, layout, out_dtype, choice.staged, stream)) return GSPMD_ERR_DEVICE;
     } else {
       const dim3 grid(static_cast<unsigned>(tiles)), block(256);
       if (in_dtype == GSPMD_F32) {
@@ -649,7 +662,7 @@ int32_t gspmd_plan_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
   std::vector<Problem> live;
   for (const auto& p : ps) if (p.Mv > 0) live.push_back(p);
   const KernelPath kp = kernel_path(live, GSPMD_BF16, layout, false);
-  const int32_t path = kp == kPathMfmaDirect ? GSPMD_KERNEL_MFMA : kp == kPathMfmaStaged ? GSPMD_KERNEL_MFMA_STAGED : GSPMD_KERNEL_SCALAR;
+  const int32_t path = kp == kPathMfmaDirect ? GSPMD_KERNEL_MFMA : kp == kPathFallback ? GSPMD_KERNEL_SCALAR : GSPMD_KERNEL_MFMA_STAGED;
   for (int64_t i = 0; i < std::min<int64_t>(capacity, *count); ++i) {
     const Problem& p = ps[static_cast<size_t>(i)];
     gspmd_gemm_desc& d = descs[i];
@@ -894,15 +907,13 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     if (ok) {
       std::vector<Problem> live;
       for (const auto& q : joined) if (q.Mv > 0) live.push_back(q);
-      const KernelPath live_path = kernel_path(live, in_dtype, jlayout);
-      const MfmaKernel one = pick_kernel(live, live_path, jlayout, true).kernel;
-      js.chain = with_records(one) == kMfmaMid;
-      ok = one != kMfmaNone;
+      const MfmaChoice one = pick_kernel(live, kernel_path(live, in_dtype, jlayout), jlayout, true);
+      js.chain = with_records(one.kernel) == kMfmaMid;
+      ok = one.kernel != kMfmaNone;
       if (ok && t_pin.one_launch >= 0) {
         ok = t_pin.one_launch == 1;
       } else if (ok && !apart.empty()) {
-        const KernelPath path = kernel_path(apart, in_dtype, jlayout);
-        const MfmaKernel two = pick_kernel(apart, path, jlayout, true).kernel;
+        const MfmaChoice two = pick_kernel(apart, kernel_path(apart, in_dtype, jlayout), jlayout, true);
         int64_t partial_bytes = 0, launches = 0;
         bool summable = true;       // the sum kernels take so many partials, those of members without any K among them
         for (int64_t e : elems) partial_bytes += 4 * e;
@@ -910,9 +921,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
           launches += scatter ? static_cast<int64_t>(kv.second.size()) : 1;
           summable = summable && kv.second.size() <= static_cast<size_t>(kMaxPartials);
         }
-        const bool staged = path == kPathMfmaStaged;
-        ok = !summable || sum_us(live, one, live_path == kPathMfmaStaged, jlayout) <=
-                              1.15 * (sum_us(apart, two, staged, jlayout) + apart_us(partial_bytes, launches));
+        ok = !summable || sum_us(live, one, jlayout) <= 1.15 * (sum_us(apart, two, jlayout) + apart_us(partial_bytes, launches));
       }
     }
     // Behind the launch tables come the counters, then the slots.  A scattered sum has more entries than the query counted (one

@@ -47,7 +47,7 @@ template <> struct Store16<2> { typedef uint32_t type __attribute__((ext_vector_
 template <> struct Store16<4> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(4))); };
 
 // Zeros over rows [row_begin, row_end) x columns [col_begin, col_end) of an output block, by all kMfmaThreads threads of
-// the workgroup: the rows of the static block below the last tile row's footprint.  `vec`: 16-byte stores are
+// the workgroup: the rows of the static block below the last tile row's footprint, the columns right of a moved tile.  `vec`: 16-byte stores are
 // aligned (checked by the caller for the block's pointer, row stride and col_begin) and the width is a multiple of them.
 template <typename TOut>
 __device__ __forceinline__ void zero_rows_below(TOut* __restrict__ C, int ldc, int row_begin, int row_end, int col_begin, int col_end,
@@ -72,8 +72,10 @@ __device__ __forceinline__ void zero_rows_below(TOut* __restrict__ C, int ldc, i
   }
 }
 
-// STAGED: the variant for operands that are not 16-byte aligned (a row stride that is not a multiple of 8 elements, e.g.
-// dense shards of 1250 or 697 columns): direct global->LDS loads need 16-byte aligned chunks, so every K tile goes
+// Direct global->LDS loads need addresses that are multiples of 4 bytes, no more: dense rows of an even number of elements take them
+// too (a KiB in 17 to 20 cycles of the address unit where rows are 16-byte aligned, 28 to 37 in rows of 2500 bytes; registers or
+// LDS alike).  An odd element address takes it 64.  5998 x 3072 x 9999 on 4 x 8 partitions, rows of 1250: staged 424 us, direct 284.
+// STAGED: the variant for operands at odd element addresses (dense rows of 697 columns, or an odd first element): every K tile goes
 // through registers instead, in 16-byte loads at element alignment.  No read leaves the rows' valid part: a chunk that
 // would reach past the last valid column or the valid K is fetched from before it and moved down in registers.  Stores are
 // 16 bytes at element alignment too.  (The last K tile and the output element by element: 300 x 65 x 301 as a float32 partial
@@ -105,6 +107,11 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
   const TileRows own = tile_rows(tile_row, P.Mv);
   const int m0 = own.first, m_end = own.first + own.rows;
   const int m_write_end = m_end == P.Mv ? min(P.Ms, m0 + kMfmaBM) : m_end;
+  // A K-major rhs whose rows are whole 32-bit words but not padded to 16 bytes: the last tile column is moved back so that no chunk reaches
+  // past a row's last word.  The columns that it shares with its neighbour are computed and stored by both, with the same bits.
+  const int n_nom = n0;
+  if (!STAGED && !BKC && loose_rows(P.B, P.ldb)) n0 = min(n0, P.Nv - kMfmaBN + (P.Nv & 1));
+  const int n_load_end = n0 < n_nom ? n0 + kMfmaBN : P.Nv;
 
   // acc[bm] holds the four 16x16 tiles (bn = 0..3) of 16-row block bm: element 4*bn + r
   float16_t acc[8];
@@ -130,7 +137,7 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       a_off[j] = AKM ? km_load_offset(wn * 4 + j, lane, m0, m_end, P.lda) : kc_half_load_offset(wn * 4 + j, lane, wm, m0, m_end, P.lda);
-      b_off[j] = BKC ? kc_half_load_offset(wn * 4 + j, lane, wm, n0, P.Nv, P.ldb) : km_load_offset(wn * 4 + j, lane, n0, P.Nv, P.ldb);
+      b_off[j] = BKC ? kc_half_load_offset(wn * 4 + j, lane, wm, n0, P.Nv, P.ldb) : km_load_offset(wn * 4 + j, lane, n0, n_load_end, P.ldb);
     }
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
     // address of what tile kt's part holds: k = 32 kt for a K-major operand, the K step's first k for a K-contiguous one
@@ -158,14 +165,11 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
       gptr_t at = (gptr_t)(reinterpret_cast<const unsigned char*>(base) + off);
       if (kmajor) {         // a whole k row per 32 lanes
         const int kr = k0 + q * 2 + (lane >> 5);
-        if (kr < P.Kv) v = *(__attribute__((address_space(1))) const u32x4_t*)at;
+        if (kr < P.Kv) v = *(__attribute__((address_space(1))) const u32x4_words_t*)at;
       } else {              // 8 consecutive k per lane
         const int r = q * 16 + (lane >> 2);
         const int k = k0 + ((lane & 3) ^ swz_a(r)) * 8;
-        if (k < P.Kv) {
-          v = *(__attribute__((address_space(1))) const u32x4_t*)at;
-          if (k + 8 > P.Kv) v = mask_tail8(v, P.Kv - k);
-        }
+        v = load_k_chunk((GSPMD_GLOBAL const uint32_t*)at, P.Kv - k);
       }
       return v;
     };
@@ -179,7 +183,7 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
       for (int j = 0; j < 4; ++j) {
         const int q = wn * 4 + j;
         const int ao = AKM ? km_load_offset(q, lane, m0, m_end, P.lda) : kc_load_offset(q, lane, m0, m_end, P.lda);
-        const int bo = BKC ? kc_load_offset(q, lane, n0, P.Nv, P.ldb) : km_load_offset(q, lane, n0, P.Nv, P.ldb);
+        const int bo = BKC ? kc_load_offset(q, lane, n0, P.Nv, P.ldb) : km_load_offset(q, lane, n0, n_load_end, P.ldb);
         ta[j] = tail_chunk(AKM, ab, ao, q, k0);
         tb[j] = tail_chunk(!BKC, bb, bo, q, k0);
       }
@@ -582,10 +586,12 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
   // few occupied slots; at most kRowsBelow rows), over this tile's columns; what lies beyond, and the static columns
   // right of the last tile column, are cleared by the fill kernel
   if (m_end == P.Mv && m_write_end < P.Ms) {
-    const int col_end = min(n0 + kMfmaBN, P.Ns);
+    const int col_end = min(n_nom + kMfmaBN, P.Ns);
     constexpr int kPer = 16 / static_cast<int>(sizeof(TOut));
     zero_rows_below<TOut>(Cg, P.ldc, m_write_end, rows_cleared(P.Mv, P.Ms), n0, col_end, rows_16b && ((col_end - n0) % kPer) == 0, t);
   }
+  if (n0 < n_nom && n0 + kMfmaBN < P.Ns)                               // static columns right of a tile that was moved back
+    zero_rows_below<TOut>(Cg, P.ldc, m0, m_write_end, n0 + kMfmaBN, min(n_nom + kMfmaBN, P.Ns), false, t);
   // 16-byte stores of whole lines, at whatever element alignment the output's rows have (element by element, float32 partials of 3456 x 1914 x 698
   // over 2 members, 349 columns each, and their sum took 57 us; 45); bf16 through the hardware round-to-nearest-even conversion.  A tile with all 256
   // columns (and rows) valid stores without predicates; in the last tile column a lane's 16 bytes are masked beyond

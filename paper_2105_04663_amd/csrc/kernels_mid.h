@@ -3,7 +3,7 @@
 // a contracting mesh dimension, which it forms without a workspace: a workgroup takes the members' K ranges one after
 // the other (without a break where they are alike: 2048 x 8192 x 2048 over 4 members 66.8 -> 62.9 us) and adds each member's finished product to a second set of accumulators, so the sum is ((p0 + p1) + p2) + ..
 // in fp32 as everywhere else.  Products take their 32-wide K tiles in the order and with the instruction of
-// dot_mfma_kernel: results are bit-identical to it.  16-byte aligned operands only.
+// dot_mfma_kernel: results are bit-identical to it.  Operands at multiples of 4 bytes (see there).
 //
 // What bounds it: what a compute unit draws from L2 and beyond, 16 KiB per 32-wide K tile for 256 cycles of the matrix cores: the loads
 // alone take 190 ns per tile on a full chip, 135 on few compute units, a tile with everything 205 (400 for two workgroups).  So:
@@ -82,7 +82,10 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   const int tiles_m = (P.Mv + kMidTile - 1) / kMidTile;
   const int band = local / (kBandRows * P.tiles_n), in_band = local - band * kBandRows * P.tiles_n;
   const int rows_in_band = min(kBandRows, tiles_m - band * kBandRows);
-  const int m0 = (band * kBandRows + in_band % rows_in_band) * kMidTile, n0 = (in_band / rows_in_band) * kMidTile;
+  const int m0 = (band * kBandRows + in_band % rows_in_band) * kMidTile, n_nom = (in_band / rows_in_band) * kMidTile;
+  // rhs rows that are not padded to 16 bytes: the last tile column is moved back, as in dot_mfma_kernel
+  const bool loose = !BKC && loose_rows(P.B, P.ldb);
+  const int n0 = loose ? min(n_nom, P.Nv - kMidTile + (P.Nv & 1)) : n_nom, n_load_end = n0 < n_nom ? n0 + kMidTile : P.Nv;
   const int members = CHAIN ? max(P.join_count, 1) : 1;
   // Members that are alike and whole K steps long follow each other without a break: the loads of the next one are under way while this one's
   // last steps are multiplied.  Others are taken one by one.
@@ -159,7 +162,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       for (int j = 0; j < 2; ++j) {
         const int q = wave * 2 + j;
         a_off[h][j] = AKM ? mid_km_load_offset(q, lane, m0, P.Mv, P.lda) : mid_kc_load_offset(q, lane, h, m0, P.Mv, P.lda);
-        b_off[h][j] = BKC ? mid_kc_load_offset(q, lane, h, n0, P.Nv, P.ldb) : mid_km_load_offset(q, lane, n0, P.Nv, P.ldb);
+        b_off[h][j] = BKC ? mid_kc_load_offset(q, lane, h, n0, P.Nv, P.ldb) : mid_km_load_offset(q, lane, n0, n_load_end, P.ldb);
       }
     const bf16_bits *a_next = a_base, *b_next = b_base;
     const uint32_t lds_wave = lds0 + wave * 2048;
@@ -276,10 +279,8 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       auto chunk = [&](bool kmajor, const bf16_bits* base, int off, int q) -> u32x4_t {
         u32x4_t v = {0u, 0u, 0u, 0u};
         const int kr = kmajor ? q * 4 + (lane >> 4) : ((lane & 3) ^ swz_a(q * 16 + (lane >> 2))) * 8, here = left - done;
-        if (kr < here) {
-          v = *(GSPMD_GLOBAL const u32x4_t*)((gbytes)base + off);
-          if (!kmajor && kr + 8 > here) v = mask_tail8(v, here - kr);
-        }
+        if (!kmajor) v = load_k_chunk((GSPMD_GLOBAL const uint32_t*)((gbytes)base + off), here - kr);
+        else if (kr < here) v = *(GSPMD_GLOBAL const u32x4_words_t*)((gbytes)base + off);
         return v;
       };
 #pragma unroll
@@ -345,8 +346,12 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   }
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears)
-  if (m0 + kMidTile >= P.Mv)
-    zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n0, min(n0 + kMidTile, P.Ns), t);
+  const int m_done = min(m0 + kMidTile, P.Mv), moved_end = n0 + kMidTile, col_end = min(n_nom + kMidTile, P.Ns);
+  if (n0 < n_nom) zero_block<kMidThreads, TOut>(C, P.ldc, m0, m_done, moved_end, col_end, t);            // right of a tile that was moved back
+  if (m_done == P.Mv) {
+    zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n0, min(moved_end, P.Ns), t);
+    if (n0 < n_nom) zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), moved_end, col_end, t);
+  }
 }
 
 template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU>

@@ -34,4 +34,24 @@ __device__ __forceinline__ u32x4_t mask_tail8(u32x4_t v, int keep) {   // keep f
   return v;
 }
 
+// 16 bytes at an address that is a multiple of 4
+typedef uint32_t u32x4_words_t __attribute__((ext_vector_type(4), aligned(4)));
+
+// Rows of whole 32-bit words that are not padded to 16 bytes: a 16-byte chunk may reach past a row's end.
+__device__ __forceinline__ bool loose_rows(const void* p, int ld) { return (reinterpret_cast<uintptr_t>(p) & 15) || (ld & 7); }
+
+// Eight consecutive k of a K-contiguous row, of which `valid` (any number) exist: zeros beyond, and no word read that holds no valid element.
+__device__ __forceinline__ u32x4_t load_k_chunk(__attribute__((address_space(1))) const uint32_t* at, int valid) {
+  u32x4_t v = {0u, 0u, 0u, 0u};
+  if (valid >= 8) {
+    v = *(__attribute__((address_space(1))) const u32x4_words_t*)at;
+  } else if (valid > 0) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+      if (2 * d < valid) v[d] = at[d];
+    v = mask_tail8(v, valid);
+  }
+  return v;
+}
+
 }  // namespace gspmd

@@ -1,0 +1,75 @@
+"""Operands whose rows are whole 32-bit words but not padded to 16 bytes (leading dimensions of an even number of elements that is no
+multiple of 8): the direct variants of the 256 x 256 and the 128 x 128 tiles take them, a K-major rhs with its last tile column moved back.
+Small integers and float32 output, compared bit for bit; everything beyond the valid extents holds NaN."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2105_04663_amd as g
+import workloads as wl
+from oracle import dot as od
+from tests.harness import Staged
+from tests.pin import MFMA, MID, last, pinned
+
+pytestmark = pytest.mark.gpu
+
+
+def _workload(M, K, N, layout, Y):
+    lhs_shape, rhs_shape = ((K, M) if layout & 1 else (M, K)), ((N, K) if layout & 2 else (K, N))
+    return wl.DotWorkload(name="words", cfg=7, dtype="bf16", out_dtype="f32", lhs_shape=lhs_shape, rhs_shape=rhs_shape, lhs_batch=(), rhs_batch=(),
+                          lhs_contract=(0,) if layout & 1 else (1,), rhs_contract=(1,) if layout & 2 else (0,), mesh_shape=(1, Y),
+                          device_ids=tuple(range(Y)), lhs_map=(-1, -1), rhs_map=(1, -1) if layout & 2 else (-1, 1), out_map=(-1, 1))
+
+
+@pytest.mark.parametrize("kernel", [MFMA, MID])
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,K,N,Y", [(256, 64, 256, 1), (300, 130, 257, 1), (40, 67, 511, 1), (520, 199, 770, 1), (130, 1000, 2 * 258 - 1, 2),
+                                     (257, 321, 3 * 300 - 4, 3), (129, 33, 131, 1), (128, 31, 129, 1), (300, 70, 2 * 130, 2), (64, 701, 3 * 142 - 11, 3)])
+def test_products(M, K, N, Y, layout, kernel):
+    w = _workload(M, K, N, layout, Y)
+    lhs, rhs = wl.draw_small_int_bf16(3, w.lhs_shape), wl.draw_small_int_bf16(4, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=2)
+    with pinned(kernel):
+        st.run_grouped()
+    ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), (), (), w.lhs_contract, w.rhs_contract)
+    for pid in range(Y):
+        assert np.array_equal(st.out_shard(pid), od.expected_out_shard(ref, w.mesh_shape, w.device_ids, w.out_map, pid)), f"partition {pid}"
+    if layout == 0:
+        assert last()[0] == kernel
+
+
+@pytest.mark.parametrize("kernel,one_launch", [(MFMA, 1), (MFMA, 0), (MID, 1), (MID, 0)])
+@pytest.mark.parametrize("M,K,N,P", [(300, 402, 258, 2), (257, 1302, 770, 3), (130, 512, 334, 4)])
+def test_sums_are_the_same_bits(M, K, N, P, kernel, one_launch):
+    # N(0, 1) data: against the members' products with rows padded to 16 bytes, summed here in ascending order
+    w = wl.ksplit(M=M, K=K, N=N, P=P)
+    lhs, rhs = wl.draw_normal_bf16(5, w.lhs_shape), wl.draw_normal_bf16(6, w.rhs_shape)
+    padded = Staged(w, lhs, rhs, row_align=8, out_dtype="f32")
+    total = None
+    for pid in range(P):
+        tmp = torch.full((M * padded.out[pid][2],), float("nan"), device="cuda")
+        padded.run_local(pid, out_override=g.ShardBuf.of(tmp, padded.out[pid][2]))
+        part = tmp.view(M, -1)[:, :N].clone()
+        total = part if total is None else total + part
+    st = Staged(w, lhs, rhs, row_align=2, out_dtype="f32")
+    with pinned(kernel, 0, one_launch):
+        st.run_grouped()
+        assert last() == (kernel, 0, one_launch)
+    torch.cuda.synchronize()
+    assert torch.equal(st.out[0][1].view(M, -1)[:, :N], total)
+
+
+def test_columns_right_of_a_moved_tile_are_cleared():
+    # 770 columns over 3 partitions of 257: the last one has 256 valid of 257 static ones, with rows of 258
+    w = _workload(300, 96, 770, 0, 3)
+    lhs, rhs = wl.draw_normal_bf16(5, w.lhs_shape), wl.draw_normal_bf16(6, w.rhs_shape)
+    for kernel in (MFMA, MID):
+        st = Staged(w, lhs, rhs, row_align=2)
+        for _, t, _, _ in st.out:
+            t.fill_(float("nan"))
+        with pinned(kernel):
+            st.run_grouped()
+        for pid in range(3):
+            got = st.out_shard(pid)
+            assert np.isfinite(got).all()
+        assert (st.out_shard(2)[:, 256:] == 0).all()
