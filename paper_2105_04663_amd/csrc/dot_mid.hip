@@ -3,6 +3,6 @@
 
 namespace gspmd {
 
-template bool launch_dot_mid_layout<GSPMD_TU_LAYOUT>(const MfmaLaunch& l, int32_t out_dtype, bool chain, hipStream_t stream);
+template bool launch_dot_mid_layout<GSPMD_TU_LAYOUT>(const MfmaLaunch& l, int32_t out_dtype, bool chain, bool staged, hipStream_t stream);
 
 }  // namespace gspmd

@@ -130,7 +130,7 @@ enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_T
 struct MfmaChoice {
   MfmaKernel kernel;
   int row_blocks;
-  bool staged = false;      // dot_mfma_kernel: operands through registers
+  bool staged = false;      // dot_mfma_kernel, dot_mid_kernel: operands through registers
 };
 
 // What this thread's launches are pinned to, and what its last one took (testing.h).
@@ -153,7 +153,8 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   both K-major 2085 x 3540 x 1652 over 2, two groups: 64 / 60   1770 x 3303 x 2085 over 2, two groups: 65 / 67   1572 x 4544 x 3328 over 8: 136 / 88
 struct LaunchSize {
   int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1;      // longest extents, tiles of 256 x 256 and of 128 x 128, most members of a sum
-  int64_t cols = INT32_MAX;                                    // fewest columns
+  int64_t cols = INT32_MAX, fewest_rows = INT32_MAX;
+  bool a_odd = false, b_odd = false;                           // an operand has elements at odd addresses
   bool broken_lines = false, whole_steps = true;      // a K-contiguous operand's rows are not whole lines; all K are whole 64-wide steps
 };
 LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
@@ -162,6 +163,9 @@ LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
     s.rows = std::max<int64_t>(s.rows, p.Mv);
     s.k = std::max<int64_t>(s.k, p.Kv);
     s.cols = std::min<int64_t>(s.cols, p.Nv);
+    s.fewest_rows = std::min<int64_t>(s.fewest_rows, p.Mv);
+    s.a_odd = s.a_odd || (p.lda & 1) || (reinterpret_cast<uintptr_t>(p.A) & 2);
+    s.b_odd = s.b_odd || (p.ldb & 1) || (reinterpret_cast<uintptr_t>(p.B) & 2);
     s.big += tiles_of(p, kMfmaBM, kMfmaBN);
     if (p.join_slot == 0) {
       s.mid += tiles_of(p, kMidTile, kMidTile);
@@ -179,11 +183,12 @@ double big_us(const LaunchSize& s, bool staged) {
   const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * static_cast<double>(s.big) : 0.0;
   return full * (beside + steps * step(1.0)) + (part > 0.0 ? beside + steps * step(part) : 0.0) + slots;
 }
-double mid_us(const LaunchSize& s) {
+double mid_us(const LaunchSize& s, bool staged = false) {
   const double m = static_cast<double>(s.members), left = static_cast<double>((s.k % 64 + 31) / 32);
   const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 8.8 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
   const int64_t part = s.mid % 512;
-  return static_cast<double>(s.mid / 512) * (beside + steps * 0.40) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? 0.205 : 0.40));
+  const double one = staged ? 0.11 + 0.16 * ((s.a_odd ? 1 : 0) + (s.b_odd ? 1 : 0)) : 0.205, two = staged ? 2.0 * one : 0.40;
+  return static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
 }
 
 // The three kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
@@ -208,15 +213,19 @@ constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 bool big_staged(const LaunchSize& size, KernelPath path, int32_t layout) {
   return path == kPathMfmaStaged || (path == kPathMfmaWords && !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && size.cols < kMfmaBN);
 }
+// dot_mid_kernel's staged variant moves the last tiles of K-major operands back: from one of its tiles on, and no joined sums
+bool mid_stages_whole(const LaunchSize& size, int32_t layout) {
+  return ((layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) || size.cols >= kMidTile) && (!(layout & GSPMD_LAYOUT_LHS_K_MAJOR) || size.fewest_rows >= kMidTile);
+}
 MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   MfmaChoice choice{kMfmaBig, 0};
   const bool loose = path == kPathMfmaStaged;
   const LaunchSize size = launch_size(ps, layout);
   if (size.rows == 0) return choice;
   double best = big_us(size, choice.staged = big_staged(size, path, layout));
-  if (!loose) {
-    const double us = mid_us(size);
-    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0}; }
+  if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
+    const double us = mid_us(size, loose);
+    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, loose}; }
   }
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((size.k + 255) / 256);
@@ -235,7 +244,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 // fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 15 % faster; the results are the same bits.
 double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
-  return choice.kernel == kMfmaMid ? mid_us(size) : big_us(size, choice.staged);
+  return choice.kernel == kMfmaMid ? mid_us(size, choice.staged) : big_us(size, choice.staged);
 }
 // What partials cost beside their launch: 1 us, 2.5 us per sum kernel and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
@@ -248,8 +257,10 @@ double apart_us(int64_t partial_bytes, int64_t launches) {
 MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   if (path == kPathFallback) return MfmaChoice{kMfmaNone, 0};
   const MfmaKernel pin = static_cast<MfmaKernel>(t_pin.kernel);
-  if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && path != kPathMfmaStaged) || (pin == kMfmaSplit && !ordered))
-    return MfmaChoice{pin, t_pin.row_blocks, pin == kMfmaBig && big_staged(launch_size(ps, layout), path, layout)};
+  const LaunchSize size = launch_size(ps, layout);
+  if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && (path != kPathMfmaStaged || (size.members == 1 && mid_stages_whole(size, layout)))) ||
+      (pin == kMfmaSplit && !ordered))
+    return MfmaChoice{pin, t_pin.row_blocks, pin == kMfmaBig ? big_staged(size, path, layout) : pin == kMfmaMid && path == kPathMfmaStaged};
   return choose_mfma(ps, path, layout, ordered);
 }
 
@@ -271,7 +282,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   // joined problems come with the caller's choice between the two kernels that keep the order of summation
   MfmaChoice choice = join ? MfmaChoice{join->chain ? kMfmaMid : kMfmaBig, 0} : pick_kernel(ps, path, layout, ordered);
   if (!join) choice.kernel = with_records(choice.kernel);
-  choice.staged = choice.kernel == kMfmaBig && big_staged(launch_size(ps, layout), path, layout);
+  choice.staged = choice.kernel == kMfmaBig ? big_staged(launch_size(ps, layout), path, layout) : choice.kernel == kMfmaMid && path == kPathMfmaStaged;
   const bool mfma = choice.kernel != kMfmaNone;
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
   const bool mid = choice.kernel == kMfmaMid;
@@ -340,7 +351,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       if (!launch_dot_split(l, layout, out_dtype, split, stream)) return GSPMD_ERR_DEVICE;
     } else if (mid) {
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
-      if (!launch_dot_mid(l, layout, out_dtype, join != nullptr, stream)) return GSPMD_ERR_DEVICE;
+      if (!launch_dot_mid(l, layout, out_dtype, join != nullptr, choice.staged, stream)) return GSPMD_ERR_DEVICE;
     } else if (mfma) {
       if (join && join->tiles > 0) {
         const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((join->tiles + 255) / 256, 1024));

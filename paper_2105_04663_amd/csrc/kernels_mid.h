@@ -60,9 +60,15 @@ __device__ __forceinline__ int mid_km_frag_offset(int base, int lane) {
   return krow * 256 + (((cl >> 3) ^ mid_swz(krow)) << 4) + (cl & 7) * 2;
 }
 
-template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU>
+// STAGED: the variant for operands at odd element addresses, which direct loads do not take: a tile's chunks are loaded into registers two
+// half steps before they are put where the direct load would have put them, and K-major operands' last tiles are moved back so that
+// every chunk is whole.  Bound by the address unit, 64 cycles for a KiB at an odd address (both operands: 430 ns per 32-wide
+// tile, one 270).  Measured (us, before in 256 x 256 staged tiles or dot_split_kernel / now): 601 x 1203 x 697, six of them 49.5 / 21.5,
+// 4999 x 576 x 1193 28.1 / 18.5, 152 x 209 x 1094, 32 of them 23.7 / 22.
+template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU, bool STAGED>
 __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
+  static_assert(!(STAGED && CHAIN) && (!STAGED || PER_CU == 2), "");
   constexpr int R = mid_stages<PER_CU>(), L = mid_ahead<PER_CU>();
   static_assert(2 * kMidUnroll % R == 0, "the loop's stages come round");
   // A tile's load is issued in the half step L tiles before it is multiplied, into a stage whose last reads every wave has behind it: the
@@ -82,10 +88,11 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   const int tiles_m = (P.Mv + kMidTile - 1) / kMidTile;
   const int band = local / (kBandRows * P.tiles_n), in_band = local - band * kBandRows * P.tiles_n;
   const int rows_in_band = min(kBandRows, tiles_m - band * kBandRows);
-  const int m0 = (band * kBandRows + in_band % rows_in_band) * kMidTile, n_nom = (in_band / rows_in_band) * kMidTile;
+  const int m_nom = (band * kBandRows + in_band % rows_in_band) * kMidTile, n_nom = (in_band / rows_in_band) * kMidTile;
   // rhs rows that are not padded to 16 bytes: the last tile column is moved back, as in dot_mfma_kernel
-  const bool loose = !BKC && loose_rows(P.B, P.ldb);
-  const int n0 = loose ? min(n_nom, P.Nv - kMidTile + (P.Nv & 1)) : n_nom, n_load_end = n0 < n_nom ? n0 + kMidTile : P.Nv;
+  const bool loose = !BKC && (STAGED || loose_rows(P.B, P.ldb));
+  const int n0 = loose ? min(n_nom, P.Nv - kMidTile + (STAGED ? 0 : P.Nv & 1)) : n_nom, n_load_end = n0 < n_nom ? n0 + kMidTile : P.Nv;
+  const int m0 = STAGED && AKM ? min(m_nom, P.Mv - kMidTile) : m_nom;
   const int members = CHAIN ? max(P.join_count, 1) : 1;
   // Members that are alike and whole K steps long follow each other without a break: the loads of the next one are under way while this one's
   // last steps are multiplied.  Others are taken one by one.
@@ -168,10 +175,18 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
     const uint32_t lds_wave = lds0 + wave * 2048;
     int to_load = own / 2, loading = 0, to_add = own / 2;                     // K steps of the members being loaded and multiplied that are to come
     bool to_add_first = true;
-    // the i-th of this wave's four load instructions of an even (h 0) or odd tile, into stage `at`
+    u32x4_t held[STAGED ? 2 : 1][STAGED ? 4 : 1];                            // STAGED: this wave's chunks of an even and an odd tile on their way
+    // the i-th of this wave's four load instructions of an even (h 0) or odd tile, into stage `at` (STAGED: into registers)
     auto issue_one = [&](int h, int i, int at) {
-      if (i < 2) global_to_lds16(a_next, a_off[h][i & 1], lds_wave + at * kMidStage + (i & 1) * 1024);
-      else global_to_lds16(b_next, b_off[h][i & 1], lds_wave + at * kMidStage + kMidPart + (i & 1) * 1024);
+      if constexpr (STAGED) {
+        typedef uint32_t any_t __attribute__((ext_vector_type(4), aligned(2)));
+        typedef GSPMD_GLOBAL const unsigned char* gbytes;
+        held[h][i] = i < 2 ? *(GSPMD_GLOBAL const any_t*)((gbytes)a_next + static_cast<uint32_t>(a_off[h][i & 1])) : *(GSPMD_GLOBAL const any_t*)((gbytes)b_next + static_cast<uint32_t>(b_off[h][i & 1]));
+      } else if (i < 2) {
+        global_to_lds16(a_next, a_off[h][i & 1], lds_wave + at * kMidStage + (i & 1) * 1024);
+      } else {
+        global_to_lds16(b_next, b_off[h][i & 1], lds_wave + at * kMidStage + kMidPart + (i & 1) * 1024);
+      }
       if (i == 3) {
         if (AKM) a_next += a_tile;
         else if (h == 1) a_next += 2 * kMfmaBK;
@@ -186,6 +201,10 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
           }
         }
       }
+    };
+    auto put_one = [&](int h, int i, int at) {  // STAGED: a chunk that has arrived, into stage `at`
+      if constexpr (STAGED)
+        *(__attribute__((address_space(3))) u32x4_t*)(uintptr_t)(lds_wave + at * kMidStage + (i >> 1) * kMidPart + (i & 1) * 1024 + lane * 16) = held[h][i];
     };
     auto step_done = [&]() {                    // a K step has been multiplied
       if (CHAIN && run_on && --to_add == 0) {
@@ -212,16 +231,26 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
     };
     // Half a K step: the MFMAs of fragment set `set`, and between them, one at a time, the reads of the next half's fragments (of the
     // step in stage s0) and the loads of the tile L further on (into stage `to`).
-    auto half_step = [&](auto set_tag, int s0, bool fixed, bool reads, bool loads, int to) {
+    // STAGED: a tile is put into its stage there, and the one two further on loaded if there is one (`more`).
+    auto half_step = [&](auto set_tag, int s0, bool fixed, bool reads, bool loads, int to, bool more_loads) {
       constexpr int set = decltype(set_tag)::value;
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         acc[q >> 2][q & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][q & 3], fa[set][q >> 2], acc[q >> 2][q & 3], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         if ((q & 1) == 0 && reads) read_one(set ^ 1, q >> 1, s0, fixed);
-        if ((q & 3) == 1 && loads) issue_one(set, q >> 2, to);
+        if ((q & 3) == 1 && loads) {
+          put_one(set, q >> 2, to);
+          if (!STAGED || more_loads) issue_one(set, q >> 2, to);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    // (the compiler moves no LDS access across it)
+    auto barrier = [&]() {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
     };
     // waits until all but the `after` tiles loaded last have landed (and this wave's fragment reads are over)
     auto landed = [&](int after) {
@@ -230,30 +259,50 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       else if (after >= 2) __builtin_amdgcn_s_waitcnt(waitcnt_imm(8, 0));
       else if (after >= 1) __builtin_amdgcn_s_waitcnt(waitcnt_imm(4, 0));
       else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
-      __builtin_amdgcn_s_barrier();
+      barrier();
     };
     if (tiles > 0) {
       const std::integral_constant<int, 0> even{};
       const std::integral_constant<int, 1> odd{};
-      for (int s = 0; s < min(tiles, L); s += 2)
+      for (int s = 0; s < min(tiles, L); s += 2) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) issue_one(i >> 2, i & 3, s + (i >> 2));
-      landed(min(tiles, L) - 2);
+        if constexpr (STAGED)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) put_one(i >> 2, i & 3, s + (i >> 2));
+      }
+      if (STAGED && L < tiles)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) issue_one(i >> 2, i & 3, 0);
+      if (STAGED) __syncthreads();
+      else landed(min(tiles, L) - 2);
 #pragma unroll
       for (int i = 0; i < 8; ++i) read_one(0, i, 0, true);
       const int full = tiles - L;               // tiles below this one load another while they are multiplied
+      // waits until the next step's two tiles are there and this one's fragment reads are over, `after` later tiles being on their way
+      auto arrive = [&](int after) {
+        if (STAGED) {
+          __builtin_amdgcn_s_waitcnt(waitcnt_lgkm(0));
+          barrier();
+        } else {
+          landed(after);
+        }
+      };
       int k = 0;                                // tile in fragment set 0
       auto step = [&](auto u_tag) {             // a K step whose tiles are in stages 2 u and 2 u + 1 (modulo R)
         constexpr int s0 = 2 * decltype(u_tag)::value % R, next = (s0 + 2) % R, to = (s0 + L) % R;
-        half_step(even, s0, true, true, true, to);
-        // Both tiles of the next step have landed, L - 3 later ones are on their way
-        __builtin_amdgcn_s_waitcnt(kReadsDone ? waitcnt_imm(4 * (L - 3), 0) : waitcnt_vm(4 * (L - 3)));
-        __builtin_amdgcn_s_barrier();
-        half_step(odd, next, true, true, true, (to + 1) % R);
+        half_step(even, s0, true, true, true, to, true);
+        if constexpr (STAGED) {
+          arrive(0);
+        } else {                                // both tiles of the next step have landed, L - 3 later ones are on their way
+          __builtin_amdgcn_s_waitcnt(kReadsDone ? waitcnt_imm(4 * (L - 3), 0) : waitcnt_vm(4 * (L - 3)));
+          barrier();
+        }
+        half_step(odd, next, true, true, true, (to + 1) % R, true);
         step_done();
         k += 2;
       };
-      for (; k + 2 * kMidUnroll <= full; ) {
+      for (; k + 2 * kMidUnroll <= (STAGED ? full - 2 : full); ) {
         step(std::integral_constant<int, 0>{});
         step(std::integral_constant<int, 1>{});
         step(std::integral_constant<int, 2>{});
@@ -263,11 +312,11 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       int s0 = 0, to = L;                       // the rest with stages that are worked out
       auto follow = [](int s, int by) { return s + by >= R ? s + by - R : s + by; };
       for (; k < tiles; k += 2) {
-        const bool load = k < full, more = k + 2 < tiles;
-        half_step(even, s0, false, true, load, to);
+        const bool load = k < full, more = k + 2 < tiles, more_loads = k + 2 < full;
+        half_step(even, s0, false, true, load, to, more_loads);
         s0 = follow(s0, 2);
-        if (more) landed(load ? L - 3 : tiles - k - 4);
-        half_step(odd, s0, false, more, load, follow(to, 1));
+        if (more) arrive(load ? L - 3 : tiles - k - 4);
+        half_step(odd, s0, false, more, load, follow(to, 1), more_loads);
         step_done();
         to = follow(to, 2);
       }
@@ -279,8 +328,8 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       auto chunk = [&](bool kmajor, const bf16_bits* base, int off, int q) -> u32x4_t {
         u32x4_t v = {0u, 0u, 0u, 0u};
         const int kr = kmajor ? q * 4 + (lane >> 4) : ((lane & 3) ^ swz_a(q * 16 + (lane >> 2))) * 8, here = left - done;
-        if (!kmajor) v = load_k_chunk((GSPMD_GLOBAL const uint32_t*)((gbytes)base + off), here - kr);
-        else if (kr < here) v = *(GSPMD_GLOBAL const u32x4_words_t*)((gbytes)base + off);
+        if (!kmajor) v = STAGED ? load_k_elements((GSPMD_GLOBAL const uint16_t*)((gbytes)base + off), here - kr) : load_k_chunk((GSPMD_GLOBAL const uint32_t*)((gbytes)base + off), here - kr);
+        else if (kr < here) v = *(GSPMD_GLOBAL const u32x4_elements_t*)((gbytes)base + off);
         return v;
       };
 #pragma unroll
@@ -346,7 +395,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   }
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears)
-  const int m_done = min(m0 + kMidTile, P.Mv), moved_end = n0 + kMidTile, col_end = min(n_nom + kMidTile, P.Ns);
+  const int m_done = min(m_nom + kMidTile, P.Mv), moved_end = n0 + kMidTile, col_end = min(n_nom + kMidTile, P.Ns);
   if (n0 < n_nom) zero_block<kMidThreads, TOut>(C, P.ldc, m0, m_done, moved_end, col_end, t);            // right of a tile that was moved back
   if (m_done == P.Mv) {
     zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n0, min(moved_end, P.Ns), t);
@@ -354,7 +403,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   }
 }
 
-template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU>
+template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU, bool STAGED = false>
 inline bool launch_dot_mid_as(const MfmaLaunch& l, hipStream_t stream) {
   constexpr int lds = mid_stages<PER_CU>() * kMidStage;
   static std::once_flag once[kMaxDevices];
@@ -362,11 +411,11 @@ inline bool launch_dot_mid_as(const MfmaLaunch& l, hipStream_t stream) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
   std::call_once(once[dev], [dev] {
-    ok[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU>),
+    ok[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU, STAGED>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
   });
   if (!ok[dev]) return false;
-  hipLaunchKernelGGL((dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU>), dim3(static_cast<unsigned>(l.tiles)), dim3(kMidThreads), lds, stream, *l.inl, l.tab,
+  hipLaunchKernelGGL((dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU, STAGED>), dim3(static_cast<unsigned>(l.tiles)), dim3(kMidThreads), lds, stream, *l.inl, l.tab,
                      l.n_prob, l.epilogue);
   return hipGetLastError() == hipSuccess;
 }
@@ -379,7 +428,9 @@ bool launch_dot_mid_out(const MfmaLaunch& l, int32_t out_dtype, hipStream_t stre
 }
 
 template <int LAYOUT>
-bool launch_dot_mid_layout(const MfmaLaunch& l, int32_t out_dtype, bool chain, hipStream_t stream) {
+bool launch_dot_mid_layout(const MfmaLaunch& l, int32_t out_dtype, bool chain, bool staged, hipStream_t stream) {
+  if (staged)
+    return out_dtype == GSPMD_F32 ? launch_dot_mid_as<float, LAYOUT, false, 2, true>(l, stream) : launch_dot_mid_as<bf16_bits, LAYOUT, false, 2, true>(l, stream);
   return chain ? launch_dot_mid_out<LAYOUT, true>(l, out_dtype, stream) : launch_dot_mid_out<LAYOUT, false>(l, out_dtype, stream);
 }
 

@@ -56,18 +56,18 @@ inline bool launch_dot_split(const MfmaLaunch& l, int32_t layout, int32_t out_dt
 #endif
 
 // One launch of dot_mid_kernel in 128 x 128 tiles.  `chain`: the launch has joined problems; the members of one output
-// are consecutive in the table, in the order of summation, and only the first of them has tiles.
+// are consecutive in the table, in the order of summation, and only the first of them has tiles.  `staged`: operands through registers (no chain).
 constexpr int kMidTile = 128, kMidThreads = 256;
 template <int LAYOUT>
-bool launch_dot_mid_layout(const MfmaLaunch& l, int32_t out_dtype, bool chain, hipStream_t stream);
+bool launch_dot_mid_layout(const MfmaLaunch& l, int32_t out_dtype, bool chain, bool staged, hipStream_t stream);
 
 #ifndef GSPMD_TU_LAYOUT
-inline bool launch_dot_mid(const MfmaLaunch& l, int32_t layout, int32_t out_dtype, bool chain, hipStream_t stream) {
+inline bool launch_dot_mid(const MfmaLaunch& l, int32_t layout, int32_t out_dtype, bool chain, bool staged, hipStream_t stream) {
   switch (layout & 3) {
-    case 0: return launch_dot_mid_layout<0>(l, out_dtype, chain, stream);
-    case 1: return launch_dot_mid_layout<1>(l, out_dtype, chain, stream);
-    case 2: return launch_dot_mid_layout<2>(l, out_dtype, chain, stream);
-    default: return launch_dot_mid_layout<3>(l, out_dtype, chain, stream);
+    case 0: return launch_dot_mid_layout<0>(l, out_dtype, chain, staged, stream);
+    case 1: return launch_dot_mid_layout<1>(l, out_dtype, chain, staged, stream);
+    case 2: return launch_dot_mid_layout<2>(l, out_dtype, chain, staged, stream);
+    default: return launch_dot_mid_layout<3>(l, out_dtype, chain, staged, stream);
   }
 }
 #endif

@@ -16,6 +16,7 @@ typedef __attribute__((address_space(3))) short4_t lds_short4_t;
 // s_waitcnt immediate for gfx9: vmcnt [3:0]+[15:14], expcnt [6:4], lgkmcnt [11:8]
 constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4) | ((lgkm & 15) << 8); }
 constexpr int waitcnt_vm(int vm) { return waitcnt_imm(vm, 15); }      // vmcnt alone
+constexpr int waitcnt_lgkm(int lgkm) { return waitcnt_imm(63, lgkm); }  // lgkmcnt alone
 #define GSPMD_WAIT_ALL() __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0))
 
 // 16 bytes per lane from sbase + voff (bytes) straight into LDS at lds_addr + lane*16.  The compiler
@@ -37,6 +38,8 @@ __device__ __forceinline__ u32x4_t mask_tail8(u32x4_t v, int keep) {   // keep f
 // 16 bytes at an address that is a multiple of 4
 typedef uint32_t u32x4_words_t __attribute__((ext_vector_type(4), aligned(4)));
 
+typedef uint32_t u32x4_elements_t __attribute__((ext_vector_type(4), aligned(2)));      // at any bf16 element's address
+
 // Rows of whole 32-bit words that are not padded to 16 bytes: a 16-byte chunk may reach past a row's end.
 __device__ __forceinline__ bool loose_rows(const void* p, int ld) { return (reinterpret_cast<uintptr_t>(p) & 15) || (ld & 7); }
 
@@ -50,6 +53,19 @@ __device__ __forceinline__ u32x4_t load_k_chunk(__attribute__((address_space(1))
     for (int d = 0; d < 4; ++d)
       if (2 * d < valid) v[d] = at[d];
     v = mask_tail8(v, valid);
+  }
+  return v;
+}
+
+// the same in rows at any element's address
+__device__ __forceinline__ u32x4_t load_k_elements(__attribute__((address_space(1))) const uint16_t* at, int valid) {
+  u32x4_t v = {0u, 0u, 0u, 0u};
+  if (valid >= 8) {
+    v = *(__attribute__((address_space(1))) const u32x4_elements_t*)at;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+      if (e < valid) v[e >> 1] |= static_cast<uint32_t>(at[e]) << ((e & 1) * 16);
   }
   return v;
 }

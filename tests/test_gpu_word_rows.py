@@ -73,3 +73,20 @@ def test_columns_right_of_a_moved_tile_are_cleared():
             got = st.out_shard(pid)
             assert np.isfinite(got).all()
         assert (st.out_shard(2)[:, 256:] == 0).all()
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,K,N,Y", [(128, 64, 129, 1), (131, 63, 257, 1), (300, 129, 3 * 141 - 1, 3), (129, 449, 2 * 131 - 1, 2), (257, 577, 131, 1), (133, 1345, 129, 1),
+                                     (2101, 321, 2091, 1)])
+def test_dense_odd_rows_through_registers(M, K, N, Y, layout):
+    # every operand at odd element addresses: dot_mid_kernel's staged variant, at the edges of its tiles and of its ring of stages
+    w = _workload(M, K, N, layout, Y)
+    lhs, rhs = wl.draw_small_int_bf16(3, w.lhs_shape), wl.draw_small_int_bf16(4, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=0)
+    with pinned(MID):
+        st.run_grouped()
+        if layout & 1 == 0 or M % 2:
+            assert last()[0] == MID
+    ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), (), (), w.lhs_contract, w.rhs_contract)
+    for pid in range(Y):
+        assert np.array_equal(st.out_shard(pid), od.expected_out_shard(ref, w.mesh_shape, w.device_ids, w.out_map, pid)), f"partition {pid}"
