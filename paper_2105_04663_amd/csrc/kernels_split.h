@@ -18,7 +18,8 @@
 // Measured (us, weights not in cache; before: 256 x 256 tiles on 32 to 128 of the 256 compute units): 32 x 8192 x 8192
 // 101 -> 43 (134 MB of weights at 3.1 TB/s; 36 with rows of 8256 elements, a power of two costs the L2 channels), 64 rows
 // 105 -> 47, 256 rows 135 -> 97, 16 x 8192 x 32768 -> 115 (4.7 TB/s), 256 x 2048 x 2048 39 -> 13, 64 x 1024 x 1024 14 -> 6.
-// Running further ahead (9 instead of 6 steps, or only 2) changes nothing: a compute unit's L1 keeps about 105 lines of 128 bytes
+// Of the 43 us, 40 are the loads alone (36 with the tiles' order below: 32 x 8192 x 8192 42.7 -> 40.1, 16 rows 44.0 -> 42.8, 128 x 4096 x
+// 4096 16.5 -> 15.1).  Running further ahead (9 instead of 6 steps, or only 2) changes nothing: a compute unit's L1 keeps about 105 lines of 128 bytes
 // in flight, 608 cycles each at 32 x 8192 x 8192 (256 workgroups: two row tiles draw every weight panel, 268 MB from L2, 144
 // from HBM), and stalls on them for half of its cycles; the matrix cores are busy for 7 %, LDS for 25 %.  32-column tiles read half
 // lines: no gain.
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   unsigned long long* const rec = timeline_record(timeline, timeline_records);
   if (rec != nullptr) timeline_stamp(rec, 0, t, timeline_where());
-  const int tile = logical_tile(blockIdx.x, gridDim.x);
+  const int tile = spread_tile(blockIdx.x, gridDim.x);
   const Problem P = lookup_problem(tab, n_prob, tile);
   const int local = tile - P.tile_begin;
   // the row index runs fastest: the row tiles that share a weight panel are on one XCD at the same time

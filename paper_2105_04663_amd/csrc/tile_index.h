@@ -37,6 +37,17 @@ GSPMD_INDEX_FN int logical_tile(int b, int total) {
   return base + x * each + (x < extra ? x : extra) + i;
 }
 
+// The same for dot_split_kernel: XCD x takes runs of kSpreadRun consecutive ids, the runs dealt out to the XCDs in turn (what is left
+// after whole rounds of runs keeps its ids).  Row tiles that share a weight panel stay on one XCD, and the panels that an XCD streams at a
+// time lie apart: with the 16 panels of 128 bytes of an eighth side by side, rows of 16 KiB keep to half of its L2's channels.
+constexpr int kSpreadRun = 4;
+GSPMD_INDEX_FN int spread_tile(int b, int total) {
+  constexpr int round = 8 * kSpreadRun;
+  if (b >= total / round * round) return b;
+  const int r = b % round, x = r & 7, i = r >> 3;
+  return b - r + x * kSpreadRun + i;
+}
+
 constexpr int kBandRows = 8;
 
 GSPMD_INDEX_FN int swz_h(int row) { return (row >> 1) & 7; }

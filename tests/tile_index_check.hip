@@ -174,6 +174,17 @@ static void check_tile_order() {
       }
     CHECK(next == base + width, "short window of %d ids not covered", width);
   }
+  // dot_split_kernel's order: a permutation, in whole rounds of eight runs XCD x takes every eighth run
+  for (int total : {1, 31, 32, 33, 64, 100, 256, 1000, 70001}) {
+    std::set<int> seen;
+    for (int b = 0; b < total; ++b) {
+      const int t = spread_tile(b, total);
+      CHECK(t >= 0 && t < total, "spread_tile(%d, %d) = %d", b, total, t);
+      if (b < total / (8 * kSpreadRun) * (8 * kSpreadRun)) CHECK(t / kSpreadRun % 8 == (b & 7), "XCD %d gets tile %d of %d", b & 7, t, total);
+      seen.insert(t);
+    }
+    CHECK(static_cast<int>(seen.size()) == total, "spread_tile is not a permutation for %d workgroups", total);
+  }
 }
 
 int main() {
