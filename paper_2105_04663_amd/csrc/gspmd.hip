@@ -208,6 +208,7 @@ double mid_us(const LaunchSize& s, bool staged = false) {
 //   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46     5990 x 3107 x 555: 117 / -, -, 107
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
 // (with_records): the choice is the same with and without, so results are.
+constexpr int32_t kMidShortK = 384;      // members with something left of K that dot_mid_kernel runs through one loop
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 // dot_mfma_kernel's direct variants take a K-major rhs with loose rows from one of their tiles of columns on
 bool big_staged(const LaunchSize& size, KernelPath path, int32_t layout) {
@@ -292,9 +293,11 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   // (the most K steps) go first, so that the compute units that are still busy at the end are busy with short tiles.
   if (!join)
     std::stable_sort(ps.begin(), ps.end(), [](const Problem& a, const Problem& b) { return a.Kv > b.Kv; });
+  // (where dot_mid_kernel puts two workgroups on a compute unit it has no registers for the other kind)
+  const bool short_members = mid && join && launch_size(ps, layout).mid <= kMidAlone;
   if (mid && join)
     for (size_t i = 0; i < ps.size(); i += std::max(ps[i].join_count, 1)) {     // the members of a sum are consecutive, in the order of summation
-      bool alike = ps[i].join_count > 1 && ps[i].Kv % (2 * kMfmaBK) == 0;
+      bool alike = ps[i].join_count > 1 && (ps[i].Kv % (2 * kMfmaBK) == 0 || (short_members && ps[i].Kv <= kMidShortK && (path == kPathMfmaDirect || ps[i].Kv % 8 == 0)));
       for (int32_t m = 1; m < ps[i].join_count && alike; ++m) {
         const Problem &a = ps[i], &b = ps[i + static_cast<size_t>(m)];
         alike = a.Kv == b.Kv && a.lda == b.lda && a.ldb == b.ldb;
@@ -346,8 +349,11 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   const int n = static_cast<int>(ps.size());
   if (tiles > 0) {
     if (split) {
-      const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, g_timeline.load(std::memory_order_acquire),
-                         g_timeline_records.load(std::memory_order_acquire)};
+      MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, g_timeline.load(std::memory_order_acquire),
+                   g_timeline_records.load(std::memory_order_acquire)};
+      // weights whose rows are whole multiples of what an L2's channels cover (32 x 8192 x 8192: 42.7 us in an eighth of the tiles at a time, 40.1
+      // spread out; other rows gain nothing, 101 x 1793 x 2281 loses: 10.4, 11.2)
+      l.spread = !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && std::all_of(ps.begin(), ps.end(), [](const Problem& p) { return p.ldb % 2048 == 0; });
       if (!launch_dot_split(l, layout, out_dtype, split, stream)) return GSPMD_ERR_DEVICE;
     } else if (mid) {
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};

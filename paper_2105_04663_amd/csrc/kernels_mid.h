@@ -41,18 +41,18 @@ constexpr int kMidUnroll = 5;                         // K steps after which the
 // lie in different banks.
 __device__ __forceinline__ int mid_swz(int krow) { return ((krow & 3) | (((krow >> 3) & 1) << 2)) << 1; }
 // load instruction q (0..7) of a K-major part: k rows 4 q .. 4 q + 3, 16 lanes per row; chunks past the valid extent reuse
-// the last valid chunk
-__device__ __forceinline__ int mid_km_load_offset(int q, int lane, int c0, int cols_valid, int ld) {
+// the last valid chunk, k rows past `k_valid` the last valid row
+__device__ __forceinline__ int mid_km_load_offset(int q, int lane, int c0, int cols_valid, int ld, int k_valid = kMfmaBK) {
   const int kr = q * 4 + (lane >> 4);
   int n = c0 + (((lane & 15) ^ mid_swz(kr)) << 3);
   if (n >= cols_valid) n = ((cols_valid - 1) >> 3) << 3;
-  return (kr * ld + (n - c0)) * 2;
+  return (min(kr, k_valid - 1) * ld + (n - c0)) * 2;
 }
 // K-contiguous operand: load instruction q (0..7) of the part with the tile's rows 64 half .. 64 half + 63, 64 k: 8 rows, 8 lanes per row;
-// rows past the valid extent reuse the last valid row
-__device__ __forceinline__ int mid_kc_load_offset(int q, int lane, int half, int r0, int rows_valid, int ld) {
+// rows past the valid extent reuse the last valid row, chunks past `k_valid` the last valid chunk
+__device__ __forceinline__ int mid_kc_load_offset(int q, int lane, int half, int r0, int rows_valid, int ld, int k_valid = 2 * kMfmaBK) {
   const int r = q * 8 + (lane >> 3);
-  return (min(half * 64 + r, rows_valid - 1 - r0) * ld + ((lane & 7) ^ swz_h(r)) * 8) * 2;
+  return (min(half * 64 + r, rows_valid - 1 - r0) * ld + min((lane & 7) ^ swz_h(r), (k_valid - 1) >> 3) * 8) * 2;
 }
 // fragment of the 16-column block at `base` (block b further at ^ (b << 5) for a base that is a multiple of 64)
 __device__ __forceinline__ int mid_km_frag_offset(int base, int lane) {
@@ -66,7 +66,8 @@ __device__ __forceinline__ int mid_km_frag_offset(int base, int lane) {
 // tile, one 270).  Measured (us, before in 256 x 256 staged tiles or dot_split_kernel / now): 601 x 1203 x 697, six of them 49.5 / 21.5,
 // 4999 x 576 x 1193 28.1 / 18.5, 152 x 209 x 1094, 32 of them 23.7 / 22.
 template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU, bool STAGED>
-__global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
+__global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (one: the sums' accumulators take the other half of the registers)
+ void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
   static_assert(!(STAGED && CHAIN) && (!STAGED || PER_CU == 2), "");
   constexpr int R = mid_stages<PER_CU>(), L = mid_ahead<PER_CU>();
@@ -94,8 +95,8 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
   const int n0 = loose ? min(n_nom, P.Nv - kMidTile + (STAGED ? 0 : P.Nv & 1)) : n_nom, n_load_end = n0 < n_nom ? n0 + kMidTile : P.Nv;
   const int m0 = STAGED && AKM ? min(m_nom, P.Mv - kMidTile) : m_nom;
   const int members = CHAIN ? max(P.join_count, 1) : 1;
-  // Members that are alike and whole K steps long follow each other without a break: the loads of the next one are under way while this one's
-  // last steps are multiplied.  Others are taken one by one.
+  // Members that are alike follow each other without a break: the loads of the next one are under way while this one's last steps are
+  // multiplied (those with something left of K in the loop that is not unrolled, so only short ones).  Others are taken one by one.
   const bool run_on = CHAIN && P.join_alike != 0;
 
   float4_t acc[4][4], sum[CHAIN ? 4 : 1][CHAIN ? 4 : 1];
@@ -160,17 +161,35 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
     const bf16_bits* a_base = static_cast<const bf16_bits*>(P.A) + a_first;
     const bf16_bits* b_base = static_cast<const bf16_bits*>(P.B) + b_first;
     const int64_t a_tile = AKM ? static_cast<int64_t>(kMfmaBK) * P.lda : kMfmaBK, b_tile = BKC ? kMfmaBK : static_cast<int64_t>(kMfmaBK) * P.ldb;
-    const int own = P.Kv / (2 * kMfmaBK) * 2, left = P.Kv - own * kMfmaBK;          // tiles of a member's whole 64-wide K steps
+    const int left = P.Kv % (2 * kMfmaBK);      // of K after the whole 64-wide steps
+    // What is left is one more step, its loads held to the valid K and its fragments cleared beyond; only where a chunk of eight k that is
+    // partly valid may reach past its row's end, and where registers are short, it goes through registers after the loop.
+    const bool masked = !STAGED && !(CHAIN && PER_CU == 2) && left > 0 && (left % 8 == 0 || ((AKM || !loose_rows(P.A, P.lda)) && (!BKC || !loose_rows(P.B, P.ldb))));
+    const int own = (P.Kv / (2 * kMfmaBK) + (masked ? 1 : 0)) * 2;                   // a member's tiles
     const int tiles = run_on ? own * members : own;
     int a_off[2][2], b_off[2][2];               // this wave's two load instructions of each operand's part, in even and odd tiles
+    auto place_loads = [&](int k_valid) {       // in a step of which `k_valid` k exist
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int q = wave * 2 + j;
-        a_off[h][j] = AKM ? mid_km_load_offset(q, lane, m0, P.Mv, P.lda) : mid_kc_load_offset(q, lane, h, m0, P.Mv, P.lda);
-        b_off[h][j] = BKC ? mid_kc_load_offset(q, lane, h, n0, P.Nv, P.ldb) : mid_km_load_offset(q, lane, n0, n_load_end, P.ldb);
-      }
+        for (int j = 0; j < 2; ++j) {
+          const int q = wave * 2 + j, here = h == 0 || k_valid <= kMfmaBK ? min(k_valid, kMfmaBK) : k_valid - kMfmaBK;
+          a_off[h][j] = AKM ? mid_km_load_offset(q, lane, m0, P.Mv, P.lda, here) : mid_kc_load_offset(q, lane, h, m0, P.Mv, P.lda, k_valid);
+          b_off[h][j] = BKC ? mid_kc_load_offset(q, lane, h, n0, P.Nv, P.ldb, k_valid) : mid_km_load_offset(q, lane, n0, n_load_end, P.ldb, here);
+        }
+    };
+    int64_t a_go, b_go;                         // how far a K-major operand's next tile is
+    auto place_whole = [&]() {
+      place_loads(2 * kMfmaBK);
+      a_go = a_tile;
+      b_go = b_tile;
+    };
+    place_whole();
+    // the last step's: of a K-major operand with nothing left in the step's second half, the first half's rows once more
+    auto place_last = [&]() {
+      place_loads(left);
+      if (left <= kMfmaBK) a_go = b_go = 0;
+    };
     const bf16_bits *a_next = a_base, *b_next = b_base;
     const uint32_t lds_wave = lds0 + wave * 2048;
     int to_load = own / 2, loading = 0, to_add = own / 2;                     // K steps of the members being loaded and multiplied that are to come
@@ -188,12 +207,14 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         global_to_lds16(b_next, b_off[h][i & 1], lds_wave + at * kMidStage + kMidPart + (i & 1) * 1024);
       }
       if (i == 3) {
-        if (AKM) a_next += a_tile;
+        if (AKM) a_next += a_go;
         else if (h == 1) a_next += 2 * kMfmaBK;
-        if (!BKC) b_next += b_tile;
+        if (!BKC) b_next += b_go;
         else if (h == 1) b_next += 2 * kMfmaBK;
-        if (CHAIN && h == 1 && run_on && --to_load == 0) {                    // on to the next member
+        if (h == 1) --to_load;
+        if (CHAIN && h == 1 && run_on && to_load == 0) {                      // on to the next member
           to_load = own / 2;
+          if (masked) place_whole();
           if (++loading < members) {
             const Problem Q = problem_at(tab, which + loading);
             a_next = static_cast<const bf16_bits*>(Q.A) + a_first;
@@ -207,7 +228,8 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         *(__attribute__((address_space(3))) u32x4_t*)(uintptr_t)(lds_wave + at * kMidStage + (i >> 1) * kMidPart + (i & 1) * 1024 + lane * 16) = held[h][i];
     };
     auto step_done = [&]() {                    // a K step has been multiplied
-      if (CHAIN && run_on && --to_add == 0) {
+      --to_add;
+      if (CHAIN && run_on && to_add == 0) {
         add_member(to_add_first);
         clear();
         to_add_first = false;
@@ -246,6 +268,14 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         __builtin_amdgcn_sched_barrier(0);
       }
     };
+    auto clear_beyond = [&](int h) {            // in fragments of half h of the last step, in BOTH operands: the padding may hold anything
+      const int valid = left - h * kMfmaBK - (lane >> 4) * 8;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        fa[h][i] = __builtin_bit_cast(bf16x8_t, mask_tail8(__builtin_bit_cast(u32x4_t, fa[h][i]), valid));
+        fb[h][i] = __builtin_bit_cast(bf16x8_t, mask_tail8(__builtin_bit_cast(u32x4_t, fb[h][i]), valid));
+      }
+    };
     // (the compiler moves no LDS access across it)
     auto barrier = [&]() {
       asm volatile("" ::: "memory");
@@ -265,6 +295,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       const std::integral_constant<int, 0> even{};
       const std::integral_constant<int, 1> odd{};
       for (int s = 0; s < min(tiles, L); s += 2) {
+        if (masked && to_load == 1) place_last();
 #pragma unroll
         for (int i = 0; i < 8; ++i) issue_one(i >> 2, i & 3, s + (i >> 2));
         if constexpr (STAGED)
@@ -302,7 +333,8 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
         step_done();
         k += 2;
       };
-      for (; k + 2 * kMidUnroll <= (STAGED ? full - 2 : full); ) {
+      const int unrolled = STAGED || masked ? (run_on ? 0 : full - 2) : full;      // (a step whose loads or fragments are special is not among these)
+      for (; k + 2 * kMidUnroll <= unrolled; ) {
         step(std::integral_constant<int, 0>{});
         step(std::integral_constant<int, 1>{});
         step(std::integral_constant<int, 2>{});
@@ -311,23 +343,41 @@ __global__ __launch_bounds__(kMidThreads, 2) void dot_mid_kernel(const InlinePro
       }
       int s0 = 0, to = L;                       // the rest with stages that are worked out
       auto follow = [](int s, int by) { return s + by >= R ? s + by - R : s + by; };
-      for (; k < tiles; k += 2) {
-        const bool load = k < full, more = k + 2 < tiles, more_loads = k + 2 < full;
-        half_step(even, s0, false, true, load, to, more_loads);
+      for (; k < full; k += 2) {
+        const bool more_loads = k + 2 < full;
+        if (masked && to_load == 1) place_last();
+        if (masked && to_add == 1) clear_beyond(0);
+        half_step(even, s0, false, true, true, to, more_loads);
         s0 = follow(s0, 2);
-        if (more) arrive(load ? L - 3 : tiles - k - 4);
-        half_step(odd, s0, false, more, load, follow(to, 1), more_loads);
+        arrive(L - 3);
+        if (masked && to_add == 1) clear_beyond(1);
+        half_step(odd, s0, false, true, true, follow(to, 1), more_loads);
         step_done();
         to = follow(to, 2);
       }
+      for (; k + 2 < tiles; k += 2) {           // everything is loaded
+        if (masked && to_add == 1) clear_beyond(0);
+        half_step(even, s0, false, true, false, 0, false);
+        s0 = follow(s0, 2);
+        arrive(tiles - k - 4);
+        if (masked && to_add == 1) clear_beyond(1);
+        half_step(odd, s0, false, true, false, 0, false);
+        step_done();
+      }
+      if (masked) clear_beyond(0);
+      half_step(even, s0, false, true, false, 0, false);
+      if (masked) clear_beyond(1);
+      half_step(odd, s0, false, false, false, 0, false);
+      step_done();
     }
-    for (int done = 0; done < left; done += kMfmaBK) {      // up to two tiles, the last maybe partial, through registers: zeros beyond the valid K in BOTH operands
+    for (int done = masked ? left : 0; done < left; done += kMfmaBK) {      // up to two tiles, the last maybe partial, through registers
       typedef GSPMD_GLOBAL const unsigned char* gbytes;
       u32x4_t ta[2], tb[2];
       const int64_t at_tile = tiles + done / kMfmaBK;
+      const int here = left - done;
       auto chunk = [&](bool kmajor, const bf16_bits* base, int off, int q) -> u32x4_t {
         u32x4_t v = {0u, 0u, 0u, 0u};
-        const int kr = kmajor ? q * 4 + (lane >> 4) : ((lane & 3) ^ swz_a(q * 16 + (lane >> 2))) * 8, here = left - done;
+        const int kr = kmajor ? q * 4 + (lane >> 4) : ((lane & 3) ^ swz_a(q * 16 + (lane >> 2))) * 8;
         if (!kmajor) v = STAGED ? load_k_elements((GSPMD_GLOBAL const uint16_t*)((gbytes)base + off), here - kr) : load_k_chunk((GSPMD_GLOBAL const uint32_t*)((gbytes)base + off), here - kr);
         else if (kr < here) v = *(GSPMD_GLOBAL const u32x4_elements_t*)((gbytes)base + off);
         return v;
@@ -422,7 +472,7 @@ inline bool launch_dot_mid_as(const MfmaLaunch& l, hipStream_t stream) {
 
 template <int LAYOUT, bool CHAIN>
 bool launch_dot_mid_out(const MfmaLaunch& l, int32_t out_dtype, hipStream_t stream) {
-  if (l.tiles <= 256)
+  if (l.tiles <= kMidAlone)
     return out_dtype == GSPMD_F32 ? launch_dot_mid_as<float, LAYOUT, CHAIN, 1>(l, stream) : launch_dot_mid_as<bf16_bits, LAYOUT, CHAIN, 1>(l, stream);
   return out_dtype == GSPMD_F32 ? launch_dot_mid_as<float, LAYOUT, CHAIN, 2>(l, stream) : launch_dot_mid_as<bf16_bits, LAYOUT, CHAIN, 2>(l, stream);
 }

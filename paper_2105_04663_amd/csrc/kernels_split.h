@@ -66,7 +66,7 @@ template <int W> __device__ __forceinline__ int split_pair(int block, int krow) 
 }
 
 template <typename TOut, int LAYOUT, int RB, int CB>
-__global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue,
+__global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue, int spread,
                                                                   unsigned long long* __restrict__ timeline, int timeline_records) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
   constexpr int BM = 16 * RB, BN = 16 * CB, D = split_depth<RB, CB>();
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   unsigned long long* const rec = timeline_record(timeline, timeline_records);
   if (rec != nullptr) timeline_stamp(rec, 0, t, timeline_where());
-  const int tile = spread_tile(blockIdx.x, gridDim.x);
+  const int tile = spread ? spread_tile(blockIdx.x, gridDim.x) : logical_tile(blockIdx.x, gridDim.x);
   const Problem P = lookup_problem(tab, n_prob, tile);
   const int local = tile - P.tile_begin;
   // the row index runs fastest: the row tiles that share a weight panel are on one XCD at the same time
@@ -324,7 +324,7 @@ inline bool launch_dot_split_as(const MfmaLaunch& l, hipStream_t stream) {
   });
   if (!ok[dev]) return false;
   hipLaunchKernelGGL((dot_split_kernel<TOut, LAYOUT, RB, CB>), dim3(static_cast<unsigned>(l.tiles)), dim3(kSplitThreads), lds, stream, *l.inl, l.tab,
-                     l.n_prob, l.epilogue, l.timeline, l.timeline_records);
+                     l.n_prob, l.epilogue, l.spread ? 1 : 0, l.timeline, l.timeline_records);
   return hipGetLastError() == hipSuccess;
 }
 

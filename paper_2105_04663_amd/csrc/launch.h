@@ -20,6 +20,7 @@ struct MfmaLaunch {
   uint32_t* join_counters;
   unsigned long long* timeline;
   int timeline_records;
+  bool spread = false;                   // dot_split_kernel: tiles in spread_tile's order
 };
 
 // `staged`: an operand's rows are not 16-byte aligned, both are loaded at element alignment
@@ -58,6 +59,7 @@ inline bool launch_dot_split(const MfmaLaunch& l, int32_t layout, int32_t out_dt
 // One launch of dot_mid_kernel in 128 x 128 tiles.  `chain`: the launch has joined problems; the members of one output
 // are consecutive in the table, in the order of summation, and only the first of them has tiles.  `staged`: operands through registers (no chain).
 constexpr int kMidTile = 128, kMidThreads = 256;
+constexpr int kMidAlone = 256;         // up to so many tiles a compute unit has one workgroup
 template <int LAYOUT>
 bool launch_dot_mid_layout(const MfmaLaunch& l, int32_t out_dtype, bool chain, bool staged, hipStream_t stream);
 
