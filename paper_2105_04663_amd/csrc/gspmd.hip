@@ -208,7 +208,7 @@ double mid_us(const LaunchSize& s, bool staged = false) {
 //   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46     5990 x 3107 x 555: 117 / -, -, 107
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
 // (with_records): the choice is the same with and without, so results are.
-constexpr int32_t kMidShortK = 384;      // members with something left of K that dot_mid_kernel runs through one loop
+constexpr int32_t kMidShortK = 1024;      // members with something left of K that dot_mid_kernel runs through one loop
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 // dot_mfma_kernel's direct variants take a K-major rhs with loose rows from one of their tiles of columns on
 bool big_staged(const LaunchSize& size, KernelPath path, int32_t layout) {
@@ -263,6 +263,15 @@ MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t 
       (pin == kMfmaSplit && !ordered))
     return MfmaChoice{pin, t_pin.row_blocks, pin == kMfmaBig ? big_staged(size, path, layout) : pin == kMfmaMid && path == kPathMfmaStaged};
   return choose_mfma(ps, path, layout, ordered);
+}
+
+// How many workgroups of dot_f32_kernel share a compute unit: two rounds of three of its equal tiles, or rounds of four where three do not come out even (us,
+// registers for three / kept for four): 2048 x 2048 x 3000 on 2 x 4, six tiles each: 231 with three, 222 with three of the latter, 248 with
+// four; four each: 2048 x 2048 x 2048 176 / 144, 1300 x 700 x 3000 on 1 x 4 70 / 58; sixteen: 4096 x 4096 x 4096 1123 / 1097.  Elsewhere the
+// former, whose loop is 1 to 2 % shorter: 2500 x 900 x 2500, 6.25 each: 119, 121; 4000 x 2000 x 3000 on 1 x 4, twelve: 426, 430.
+int f32_per_unit(int64_t tiles) {
+  const int64_t each = (tiles + 255) / 256;
+  return each == 6 ? 3 : each % 4 == 0 && each % 3 != 0 ? 4 : 0;
 }
 
 // While a timeline is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
@@ -370,12 +379,19 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
     } else {
       const dim3 grid(static_cast<unsigned>(tiles)), block(256);
       if (in_dtype == GSPMD_F32) {
-        switch (layout & 3) {
-          case 0: hipLaunchKernelGGL(dot_f32_kernel<0>, grid, block, 0, stream, inl, tab, n, epilogue); break;
-          case 1: hipLaunchKernelGGL(dot_f32_kernel<1>, grid, block, 0, stream, inl, tab, n, epilogue); break;
-          case 2: hipLaunchKernelGGL(dot_f32_kernel<2>, grid, block, 0, stream, inl, tab, n, epilogue); break;
-          default: hipLaunchKernelGGL(dot_f32_kernel<3>, grid, block, 0, stream, inl, tab, n, epilogue);
-        }
+        const int per_unit = f32_per_unit(tiles);
+        auto go = [&](auto lean) {
+          constexpr bool kLean = decltype(lean)::value;
+          const unsigned extra = per_unit == 3 ? kF32LdsForThree - kF32Lds : 0;
+          switch (layout & 3) {
+            case 0: hipLaunchKernelGGL((dot_f32_kernel<0, kLean>), grid, block, extra, stream, inl, tab, n, epilogue); break;
+            case 1: hipLaunchKernelGGL((dot_f32_kernel<1, kLean>), grid, block, extra, stream, inl, tab, n, epilogue); break;
+            case 2: hipLaunchKernelGGL((dot_f32_kernel<2, kLean>), grid, block, extra, stream, inl, tab, n, epilogue); break;
+            default: hipLaunchKernelGGL((dot_f32_kernel<3, kLean>), grid, block, extra, stream, inl, tab, n, epilogue);
+          }
+        };
+        if (per_unit) go(std::true_type{});
+        else go(std::false_type{});
       } else if (out_dtype == GSPMD_F32)
         hipLaunchKernelGGL((dot_fallback_kernel<bf16_bits, float>), grid, block, 0, stream, inl, tab, n, layout, epilogue);
       else

@@ -60,3 +60,16 @@ def test_f32_special_values():
     st = Staged(w, lhs, rhs, row_align=8)
     st.run_local(0)
     assert (st.out_shard(0) == float(tiny) + 2.0 ** -145).all()
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,K,N", [(2001, 37, 2030), (2501, 70, 2390)])          # 1024 and 1520 tiles: four workgroups on a compute unit, three
+def test_f32_workgroups_on_a_compute_unit(M, K, N, layout):
+    w = workload(M, K, N, layout)
+    w.dtype = "f32"
+    rng = np.random.default_rng(5)
+    lhs, rhs = (rng.integers(-50, 51, size=s).astype(np.float32) for s in (w.lhs_shape, w.rhs_shape))
+    st = Staged(w, lhs, rhs, row_align=0)
+    st.run_local(0)
+    dims = (w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    assert np.array_equal(st.out_shard(0), od.dot_general(lhs.astype(np.float64), rhs.astype(np.float64), *dims))
