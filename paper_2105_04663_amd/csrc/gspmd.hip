@@ -729,12 +729,13 @@ int32_t gspmd_dot_workspace_bytes(const gspmd_mesh* mesh, const gspmd_dot_dims* 
   int32_t pmap[kMaxRank];
   partial_mapping(mesh, cls, out_sh, pmap);
   const gspmd_sharding part_sh{out_sh->rank, out_sh->global_shape, pmap};
-  for (int64_t p = (pid < 0 ? 0 : pid); p < (pid < 0 ? P : pid + 1); ++p) {
+  {                              // static shards: what is counted is the same for every partition
+    const int64_t partitions = pid < 0 ? P : 1;
     int64_t n, e, t;
-    if ((st = count_partition(mesh, r, lhs_sh, rhs_sh, &part_sh, p, &n, &e, &t, kMfmaBM)) != GSPMD_OK) return st;
-    n_prob += n;
-    tiles = std::min<int64_t>(tiles + t, int64_t(1) << 40);
-    if (pid < 0 && contracting) partial_bytes += round_up(e * 4, kWsAlign);
+    if ((st = count_partition(mesh, r, lhs_sh, rhs_sh, &part_sh, std::max<int64_t>(pid, 0), &n, &e, &t, kMfmaBM)) != GSPMD_OK) return st;
+    n_prob = n * partitions;
+    tiles = std::min<int64_t>(t * partitions, int64_t(1) << 40);
+    if (pid < 0 && contracting) partial_bytes = round_up(e * 4, kWsAlign) * partitions;
   }
   // A grouped call with a contracting mesh dimension keeps its partial sums either as one dense fp32 array per
   // partition or, when the problems can be joined in one launch, as one slot per output tile and partition plus a
@@ -807,10 +808,11 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
   int32_t pmap[kMaxRank];
   partial_mapping(mesh, cls, out_sh, pmap);
   const gspmd_sharding part_sh{out_sh->rank, out_sh->global_shape, pmap};   // == out_sh unless a sum is scattered
-  for (int64_t p = 0; p < P; ++p) {
-    int64_t n;
-    if ((st = count_partition(mesh, r, lhs_sh, rhs_sh, &part_sh, p, &n, &elems[static_cast<size_t>(p)])) != GSPMD_OK) return st;
-    n_bound += n;
+  if (contracting) {
+    int64_t n, e;
+    if ((st = count_partition(mesh, r, lhs_sh, rhs_sh, &part_sh, 0, &n, &e)) != GSPMD_OK) return st;
+    n_bound = n * P;
+    elems.assign(static_cast<size_t>(P), e);
   }
   char* partial_base = static_cast<char*>(workspace) + round_up(std::max<int64_t>(n_bound, 1) * kTableBytesPerProblem, kWsAlign);
   std::vector<float*> partial(static_cast<size_t>(P), nullptr);

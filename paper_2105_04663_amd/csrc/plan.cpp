@@ -45,9 +45,10 @@ int32_t mesh_coords(const gspmd_mesh* mesh, int64_t pid, int64_t* coords) {
   int64_t p = 1;
   for (int i = 0; i < mesh->rank; ++i) p *= mesh->shape[i];
   if (pid < 0 || pid >= p) return GSPMD_ERR_PARTITION_RANGE;
-  int64_t lin = -1;
-  for (int64_t i = 0; i < p; ++i)
-    if (mesh->device_ids[i] == pid) { lin = i; break; }
+  // ids in order have each its own position: no search
+  int64_t lin = mesh->device_ids[pid] == pid ? pid : -1;
+  for (int64_t i = 0; i < p && lin < 0; ++i)
+    if (mesh->device_ids[i] == pid) lin = i;
   if (lin < 0) return GSPMD_ERR_PARTITION_RANGE;
   for (int i = mesh->rank - 1; i >= 0; --i) {
     coords[i] = lin % mesh->shape[i];
