@@ -247,7 +247,7 @@ double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t 
   const LaunchSize size = launch_size(ps, layout);
   return choice.kernel == kMfmaMid ? mid_us(size, choice.staged) : big_us(size, choice.staged);
 }
-// What partials cost beside their launch: 1 us, 2.5 us per sum kernel and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
+// What partials cost beside their launch: 1 us, 2.5 us per sum kernel (one per reduce group) and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
 // 508 x 4085 over 2, unaligned: 36 / 48; 1953 x 409 x 454 over 4: 15 / 20; 4023 x 8430 x 1215 over 8: 142 / 158.
 double apart_us(int64_t partial_bytes, int64_t launches) {
@@ -501,55 +501,79 @@ void partial_mapping(const gspmd_mesh* mesh, const int32_t* cls, const gspmd_sha
   }
 }
 
-// out shard of partition `pid` = epilogue(sum of the group's partials) restricted to the shard's place in them.
-int32_t launch_reduce_scatter(const gspmd_mesh* mesh, const gspmd_sharding* out_sh, const gspmd_sharding* part_sh, int64_t pid,
-                              const float* const* partials, int n_partials, const gspmd_shard_buf* out, int32_t epilogue,
+// out shard of each of `pids` = epilogue(sum of the group's partials) restricted to the shard's place in them; all in one launch (out buffers
+// whose rows are laid out differently in one each).
+int32_t launch_reduce_scatter(const gspmd_mesh* mesh, const gspmd_sharding* out_sh, const gspmd_sharding* part_sh, const int64_t* pids, int n_out,
+                              const float* const* partials, int n_partials, const gspmd_shard_buf* outs, int32_t epilogue,
                               hipStream_t stream) {
-  Bounds ob, pb;
+  for (int i = 1; i < n_out; ++i)
+    if (outs[pids[i]].row_stride != outs[pids[0]].row_stride) {
+      for (int j = 0; j < n_out; ++j) {
+        const int32_t st = launch_reduce_scatter(mesh, out_sh, part_sh, pids + j, 1, partials, n_partials, outs, epilogue, stream);
+        if (st != GSPMD_OK) return st;
+      }
+      return GSPMD_OK;
+    }
+  ScatterLaunch l;
+  std::memset(&l, 0, sizeof(l));
+  ScatterDesc& d = l.d;
+  uintptr_t bits = 0;
+  bool vec = true;
   int32_t st;
-  if ((st = shard_bounds(mesh, out_sh, pid, &ob)) != GSPMD_OK) return st;
-  if ((st = shard_bounds(mesh, part_sh, pid, &pb)) != GSPMD_OK) return st;
-  ScatterDesc d;
-  std::memset(&d, 0, sizeof(d));
-  const int r = ob.rank, last = r - 1;
-  d.rank = r;
-  int64_t rows = 1, in_stride = 1;
-  for (int i = last; i >= 0; --i) {
-    if (ob.shard[i] > INT32_MAX) return GSPMD_ERR_UNSUPPORTED;
-    d.shard[i] = static_cast<int32_t>(ob.shard[i]);
-    d.valid[i] = static_cast<int32_t>(ob.valid[i]);
-    d.in_off[i] = ob.offset[i] - pb.offset[i];
-    d.in_stride[i] = in_stride;
-    in_stride *= pb.shard[i];
-    if (i < last) rows *= ob.shard[i];
+  for (int i = 0; i < n_out; ++i) {
+    const gspmd_shard_buf& out = outs[pids[i]];
+    Bounds ob, pb;
+    if ((st = shard_bounds(mesh, out_sh, pids[i], &ob)) != GSPMD_OK) return st;
+    if ((st = shard_bounds(mesh, part_sh, pids[i], &pb)) != GSPMD_OK) return st;
+    const int r = ob.rank, last = r - 1;
+    if (i == 0) {                         // static shapes and strides are the same for all
+      d.rank = r;
+      int64_t rows = 1, in_stride = 1;
+      for (int k = last; k >= 0; --k) {
+        if (ob.shard[k] > INT32_MAX) return GSPMD_ERR_UNSUPPORTED;
+        d.shard[k] = static_cast<int32_t>(ob.shard[k]);
+        d.in_stride[k] = in_stride;
+        in_stride *= pb.shard[k];
+        if (k < last) rows *= ob.shard[k];
+      }
+      if (rows > INT32_MAX) return GSPMD_ERR_UNSUPPORTED;
+      d.rows = static_cast<int32_t>(rows);
+      d.out_stride[last] = 1;
+      if (r >= 2) {
+        const int64_t rs = out.row_stride > 0 ? out.row_stride : ob.shard[last];
+        if (rs < ob.shard[last]) return GSPMD_ERR_BAD_BUFFER;
+        d.out_stride[r - 2] = rs;
+        for (int k = r - 3; k >= 0; --k) d.out_stride[k] = d.out_stride[k + 1] * ob.shard[k + 1];
+      }
+      if (rows == 0 || ob.shard[last] == 0) return GSPMD_OK;
+      vec = !(ob.shard[last] & 3) && !(pb.shard[last] & 3);
+      for (int k = 0; k < last; ++k) vec = vec && !(d.in_stride[k] & 3) && !(d.out_stride[k] & 3);
+    }
+    if (!out.data) return GSPMD_ERR_NULL;
+    ScatterOut& o = l.o[i];
+    o.out = out.data;
+    bits |= reinterpret_cast<uintptr_t>(out.data);
+    for (int k = 0; k < r; ++k) {
+      o.valid[k] = static_cast<int32_t>(ob.valid[k]);
+      o.in_off[k] = ob.offset[k] - pb.offset[k];
+    }
+    vec = vec && !(o.in_off[last] & 3);
   }
-  if (rows > INT32_MAX) return GSPMD_ERR_UNSUPPORTED;
-  d.rows = static_cast<int32_t>(rows);
-  d.out_stride[last] = 1;
-  if (r >= 2) {
-    const int64_t rs = out->row_stride > 0 ? out->row_stride : ob.shard[last];
-    if (rs < ob.shard[last]) return GSPMD_ERR_BAD_BUFFER;
-    d.out_stride[r - 2] = rs;
-    for (int i = r - 3; i >= 0; --i) d.out_stride[i] = d.out_stride[i + 1] * ob.shard[i + 1];
-  }
-  if (rows == 0 || ob.shard[last] == 0) return GSPMD_OK;
-  PartialPtrs pp;
-  uintptr_t bits = reinterpret_cast<uintptr_t>(out->data);
-  for (int i = 0; i < kMaxPartials; ++i) pp.p[i] = nullptr;
-  for (int i = 0; i < n_partials; ++i) { pp.p[i] = partials[i]; bits |= reinterpret_cast<uintptr_t>(partials[i]); }
-  bool vec = !(bits & 15) && !(ob.shard[last] & 3) && !(pb.shard[last] & 3) && !(d.in_off[last] & 3);
-  for (int i = 0; i < last; ++i) vec = vec && !(d.in_stride[i] & 3) && !(d.out_stride[i] & 3);
-  const int64_t cols_v = (ob.shard[last] + (vec ? 3 : 0)) / (vec ? 4 : 1);
-  // one vector per thread (a workgroup per 256 vectors of a row) up to the grid limit, beyond that each thread walks
+  for (int i = 0; i < n_partials; ++i) { l.ptrs.p[i] = partials[i]; bits |= reinterpret_cast<uintptr_t>(partials[i]); }
+  vec = vec && !(bits & 15);
+  const int32_t cols = d.shard[d.rank - 1];
+  const int64_t cols_v = (static_cast<int64_t>(cols) + (vec ? 3 : 0)) / (vec ? 4 : 1);
+  // one vector per thread (a workgroup per 256 vectors of a row, or several short rows) up to the grid limit, beyond that each thread walks
   // down its column: measured faster than fewer workgroups with a loop (6.2 against 5.4 TB/s on 2.4 GB)
-  const int64_t gx = (cols_v + 255) / 256;
-  const dim3 block(256), grid(static_cast<unsigned>(gx), static_cast<unsigned>(std::min<int64_t>(rows, 65535)));
-  if (out->dtype == GSPMD_F32) {
-    if (vec) hipLaunchKernelGGL((reduce_scatter_kernel<float, 4>), grid, block, 0, stream, d, pp, n_partials, static_cast<float*>(out->data), epilogue);
-    else hipLaunchKernelGGL((reduce_scatter_kernel<float, 1>), grid, block, 0, stream, d, pp, n_partials, static_cast<float*>(out->data), epilogue);
+  while (d.log_lanes < 8 && (int64_t(1) << d.log_lanes) < cols_v) ++d.log_lanes;
+  const int64_t gx = (cols_v + 255) / 256, rows_side = 256 >> d.log_lanes;
+  const dim3 block(256), grid(static_cast<unsigned>(gx), static_cast<unsigned>(std::min<int64_t>((d.rows + rows_side - 1) / rows_side, 65535)), static_cast<unsigned>(n_out));
+  if (outs[pids[0]].dtype == GSPMD_F32) {
+    if (vec) hipLaunchKernelGGL((reduce_scatter_kernel<float, 4>), grid, block, 0, stream, l, n_partials, epilogue);
+    else hipLaunchKernelGGL((reduce_scatter_kernel<float, 1>), grid, block, 0, stream, l, n_partials, epilogue);
   } else {
-    if (vec) hipLaunchKernelGGL((reduce_scatter_kernel<bf16_bits, 4>), grid, block, 0, stream, d, pp, n_partials, static_cast<bf16_bits*>(out->data), epilogue);
-    else hipLaunchKernelGGL((reduce_scatter_kernel<bf16_bits, 1>), grid, block, 0, stream, d, pp, n_partials, static_cast<bf16_bits*>(out->data), epilogue);
+    if (vec) hipLaunchKernelGGL((reduce_scatter_kernel<bf16_bits, 4>), grid, block, 0, stream, l, n_partials, epilogue);
+    else hipLaunchKernelGGL((reduce_scatter_kernel<bf16_bits, 1>), grid, block, 0, stream, l, n_partials, epilogue);
   }
   return hipGetLastError() == hipSuccess ? GSPMD_OK : GSPMD_ERR_DEVICE;
 }
@@ -953,7 +977,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
         bool summable = true;       // the sum kernels take so many partials, those of members without any K among them
         for (int64_t e : elems) partial_bytes += 4 * e;
         for (const auto& kv : groups) {
-          launches += scatter ? static_cast<int64_t>(kv.second.size()) : 1;
+          ++launches;
           summable = summable && kv.second.size() <= static_cast<size_t>(kMaxPartials);
         }
         ok = !summable || sum_us(live, one, jlayout) <= 1.15 * (sum_us(apart, two, jlayout) + apart_us(partial_bytes, launches));
@@ -1010,15 +1034,15 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
     if (members.size() > static_cast<size_t>(kMaxPartials)) return GSPMD_ERR_UNSUPPORTED;
     std::vector<const float*> ptrs;
     for (auto& m : members) ptrs.push_back(partial[static_cast<size_t>(m.second)]);
-    std::vector<void*> written;
+    std::vector<int64_t> owners;          // one member per distinct out buffer
     for (auto& m : members) {
-      const gspmd_shard_buf& o = out_shards[m.second];
-      if (std::find(written.begin(), written.end(), o.data) != written.end()) continue;
-      written.push_back(o.data);
-      if ((st = launch_reduce_scatter(mesh, out_sh, &part_sh, m.second, ptrs.data(), static_cast<int>(ptrs.size()), &o, epilogue,
-                                      stream)) != GSPMD_OK)
-        return st;
+      bool seen = false;
+      for (int64_t o : owners) seen = seen || out_shards[o].data == out_shards[m.second].data;
+      if (!seen) owners.push_back(m.second);
     }
+    if ((st = launch_reduce_scatter(mesh, out_sh, &part_sh, owners.data(), static_cast<int>(owners.size()), ptrs.data(),
+                                    static_cast<int>(ptrs.size()), out_shards, epilogue, stream)) != GSPMD_OK)
+      return st;
   }
   return GSPMD_OK;
 } catch (...) { return GSPMD_ERR_HOST_MEMORY; }

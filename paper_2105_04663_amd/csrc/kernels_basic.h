@@ -274,53 +274,72 @@ struct ScatterDesc {
   int32_t rank;
   int32_t rows;                  // product of the out shard's static extents except the last
   int32_t shard[kMaxRank];       // out shard, static extents
-  int32_t valid[kMaxRank];       // out shard, valid extents (the rest is written as 0 and never read from the partials)
-  int64_t in_off[kMaxRank];      // where the out shard starts inside the partial, per dimension
+  int32_t log_lanes, unused;     // 2^log_lanes lanes walk along a row of the out shard
   int64_t in_stride[kMaxRank];   // element strides of the (dense) partials
   int64_t out_stride[kMaxRank];  // element strides of the out shard
 };
+struct ScatterOut {              // one per out shard that a launch writes
+  void* out;
+  int32_t valid[kMaxRank];       // valid extents (the rest is written as 0 and never read from the partials)
+  int64_t in_off[kMaxRank];      // where the out shard starts inside the partial, per dimension
+};
+struct ScatterLaunch {
+  ScatterDesc d;
+  PartialPtrs ptrs;
+  ScatterOut o[kMaxPartials];
+};
+static_assert(sizeof(ScatterLaunch) + 2 * sizeof(int) <= 4096 && sizeof(ScatterOut) % 8 == 0, "kernel arguments");
 
-// grid.x covers the last dimension in vectors of VEC, grid.y strides over the rows.  VEC = 4 needs 16-byte aligned
-// pointers and every stride, offset and extent of the last two dimensions a multiple of 4.
+// 2^log_lanes lanes side by side in a row, grid.x covering it in vectors of VEC, the workgroup's other lanes in the next rows; grid.y strides over
+// the rows, grid.z = out shard (the slices of one sum in one launch: eight kernels of 2.5 us each before).  Four partials are loaded before
+// they are added.  VEC = 4 needs 16-byte aligned pointers and every stride, offset and extent of the last two dimensions a multiple of 4.
 template <typename TOut, int VEC>
-__global__ __launch_bounds__(256) void reduce_scatter_kernel(ScatterDesc d, PartialPtrs ptrs, int n_partials,
-                                                             TOut* __restrict__ out, int epilogue) {
-  const int last = d.rank - 1;
-  const int c = (blockIdx.x * blockDim.x + threadIdx.x) * VEC;
+__global__ __launch_bounds__(256) void reduce_scatter_kernel(const ScatterLaunch launch, int n_partials, int epilogue) {
+  const GSPMD_KERNARG ScatterLaunch* const args = first_kernel_argument<ScatterLaunch>();
+  const GSPMD_KERNARG ScatterDesc& d = args->d;
+  const GSPMD_KERNARG ScatterOut& shard = args->o[blockIdx.z];
+  typedef float vec_t __attribute__((ext_vector_type(VEC)));
+  GSPMD_GLOBAL TOut* const out = (GSPMD_GLOBAL TOut*)shard.out;
+  const int last = d.rank - 1, lane = threadIdx.x & ((1 << d.log_lanes) - 1), rows_side = 256 >> d.log_lanes;
+  const int c = ((blockIdx.x << d.log_lanes) + lane) * VEC;
   if (c >= d.shard[last]) return;
-  for (int row = blockIdx.y; row < d.rows; row += gridDim.y) {
-    int rem = row;
-    int64_t in = d.in_off[last] + c, o = c;
+  for (int64_t at = static_cast<int64_t>(blockIdx.y) * rows_side + (threadIdx.x >> d.log_lanes); at < d.rows; at += static_cast<int64_t>(gridDim.y) * rows_side) {
+    int rem = static_cast<int>(at);
+    int64_t in = shard.in_off[last] + c, o = c;
     bool ok = true;
     for (int k = last - 1; k >= 0; --k) {
       const int x = rem % d.shard[k];
       rem /= d.shard[k];
-      in += (x + d.in_off[k]) * d.in_stride[k];
+      in += (x + shard.in_off[k]) * d.in_stride[k];
       o += x * d.out_stride[k];
-      ok = ok && x < d.valid[k];
+      ok = ok && x < shard.valid[k];
     }
-    float acc[VEC];
+    float v[VEC];
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-    if (ok && c < d.valid[last]) {
-      if constexpr (VEC == 4) {
-        f32x4 sum = load_stream4(ptrs.p[0] + in);
-        for (int p = 1; p < n_partials; ++p) sum += load_stream4(ptrs.p[p] + in);   // fixed ascending order: deterministic
-        acc[0] = sum.x; acc[1] = sum.y; acc[2] = sum.z; acc[3] = sum.w;
+    for (int j = 0; j < VEC; ++j) v[j] = 0.f;
+    if (ok && c < shard.valid[last]) {
+      auto part = [&](int p) { return __builtin_nontemporal_load((GSPMD_GLOBAL const vec_t*)((GSPMD_GLOBAL const float*)args->ptrs.p[p] + in)); };
+      vec_t sum;
+      for (int p = 0; p < n_partials; p += 4) {            // fixed ascending order: deterministic
+        vec_t g[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = (c + j < d.valid[last]) ? apply_epilogue(acc[j], epilogue) : 0.f;
-      } else {
-        acc[0] = ptrs.p[0][in];
-        for (int p = 1; p < n_partials; ++p) acc[0] += ptrs.p[p][in];
-        acc[0] = apply_epilogue(acc[0], epilogue);
+        for (int q = 0; q < 4; ++q)
+          if (p + q < n_partials) g[q] = part(p + q);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (p + q < n_partials) sum = p + q == 0 ? g[q] : sum + g[q];
       }
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) v[j] = (c + j < shard.valid[last]) ? apply_epilogue(sum[j], epilogue) : 0.f;
     }
     if constexpr (VEC == 4) {
       f32x4 res;
-      res.x = acc[0]; res.y = acc[1]; res.z = acc[2]; res.w = acc[3];
-      store_stream4(out + o, res);
+      res.x = v[0]; res.y = v[1]; res.z = v[2]; res.w = v[3];
+      store_stream4((TOut*)out + o, res);
+    } else if constexpr (sizeof(TOut) == 2) {
+      out[o] = float_to_bf16(v[0]);
     } else {
-      store_from_float<TOut>(out + o, acc[0]);
+      out[o] = v[0];
     }
   }
 }
