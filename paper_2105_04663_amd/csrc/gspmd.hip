@@ -302,14 +302,17 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   // (the most K steps) go first, so that the compute units that are still busy at the end are busy with short tiles.
   if (!join)
     std::stable_sort(ps.begin(), ps.end(), [](const Problem& a, const Problem& b) { return a.Kv > b.Kv; });
-  // (where dot_mid_kernel puts two workgroups on a compute unit it has no registers for the other kind)
+  // Members of a sum run through one loop where their strides are equal and their K is, too, except that the last one's may be less (the part of
+  // K that does not divide): 303 x 3900 x 7424 over eight members, 488 and 484 of K: 49.5 us, one after another with a drained ring 59.4.
+  // K beyond whole 64-wide steps has to be one that the kernel masks; with two workgroups on a compute unit it has no registers for that.
   const bool short_members = mid && join && launch_size(ps, layout).mid <= kMidAlone;
   if (mid && join)
     for (size_t i = 0; i < ps.size(); i += std::max(ps[i].join_count, 1)) {     // the members of a sum are consecutive, in the order of summation
-      bool alike = ps[i].join_count > 1 && (ps[i].Kv % (2 * kMfmaBK) == 0 || (short_members && ps[i].Kv <= kMidShortK && (path == kPathMfmaDirect || ps[i].Kv % 8 == 0)));
+      const auto fits = [&](int32_t k) { return k % (2 * kMfmaBK) == 0 || (short_members && k <= kMidShortK && (path == kPathMfmaDirect || k % 8 == 0)); };
+      bool alike = ps[i].join_count > 1 && fits(ps[i].Kv);
       for (int32_t m = 1; m < ps[i].join_count && alike; ++m) {
         const Problem &a = ps[i], &b = ps[i + static_cast<size_t>(m)];
-        alike = a.Kv == b.Kv && a.lda == b.lda && a.ldb == b.ldb;
+        alike = a.lda == b.lda && a.ldb == b.ldb && (a.Kv == b.Kv || (m == ps[i].join_count - 1 && b.Kv > 0 && b.Kv < a.Kv && fits(b.Kv)));
       }
       ps[i].join_alike = alike ? 1 : 0;
     }

@@ -161,12 +161,14 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
     const bf16_bits* a_base = static_cast<const bf16_bits*>(P.A) + a_first;
     const bf16_bits* b_base = static_cast<const bf16_bits*>(P.B) + b_first;
     const int64_t a_tile = AKM ? static_cast<int64_t>(kMfmaBK) * P.lda : kMfmaBK, b_tile = BKC ? kMfmaBK : static_cast<int64_t>(kMfmaBK) * P.ldb;
-    const int left = P.Kv % (2 * kMfmaBK);      // of K after the whole 64-wide steps
+    // of K after the whole 64-wide steps; of members that follow on, the last one may have less K than the others
+    const int left = P.Kv % (2 * kMfmaBK), last_k = run_on ? problem_at(tab, which + members - 1).Kv : P.Kv, last_left = last_k % (2 * kMfmaBK);
     // What is left is one more step, its loads held to the valid K and its fragments cleared beyond; only where a chunk of eight k that is
     // partly valid may reach past its row's end, and where registers are short, it goes through registers after the loop.
-    const bool masked = !STAGED && !(CHAIN && PER_CU == 2) && left > 0 && (left % 8 == 0 || ((AKM || !loose_rows(P.A, P.lda)) && (!BKC || !loose_rows(P.B, P.ldb))));
-    const int own = (P.Kv / (2 * kMfmaBK) + (masked ? 1 : 0)) * 2;                   // a member's tiles
-    const int tiles = run_on ? own * members : own;
+    const bool masked = !STAGED && !(CHAIN && PER_CU == 2) && (left | last_left) > 0 && ((left | last_left) % 8 == 0 || ((AKM || !loose_rows(P.A, P.lda)) && (!BKC || !loose_rows(P.B, P.ldb))));
+    const int own = (P.Kv / (2 * kMfmaBK) + (masked && left > 0 ? 1 : 0)) * 2;       // a member's tiles
+    const int last_own = (last_k / (2 * kMfmaBK) + (masked && last_left > 0 ? 1 : 0)) * 2;
+    const int tiles = run_on ? own * (members - 1) + last_own : own;
     int a_off[2][2], b_off[2][2];               // this wave's two load instructions of each operand's part, in even and odd tiles
     auto place_loads = [&](int k_valid) {       // in a step of which `k_valid` k exist
 #pragma unroll
@@ -186,13 +188,15 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
     };
     place_whole();
     // the last step's: of a K-major operand with nothing left in the step's second half, the first half's rows once more
+    int left_loading = left, left_adding = left;          // of the members being loaded and multiplied
     auto place_last = [&]() {
-      place_loads(left);
-      if (left <= kMfmaBK) a_go = b_go = 0;
+      if (left_loading == 0) return;
+      place_loads(left_loading);
+      if (left_loading <= kMfmaBK) a_go = b_go = 0;
     };
     const bf16_bits *a_next = a_base, *b_next = b_base;
     const uint32_t lds_wave = lds0 + wave * 2048;
-    int to_load = own / 2, loading = 0, to_add = own / 2;                     // K steps of the members being loaded and multiplied that are to come
+    int to_load = own / 2, loading = 0, adding = 0, to_add = own / 2;                     // K steps of the members being loaded and multiplied that are to come
     bool to_add_first = true;
     u32x4_t held[STAGED ? 2 : 1][STAGED ? 4 : 1];                            // STAGED: this wave's chunks of an even and an odd tile on their way
     // the i-th of this wave's four load instructions of an even (h 0) or odd tile, into stage `at` (STAGED: into registers)
@@ -213,9 +217,11 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
         else if (h == 1) b_next += 2 * kMfmaBK;
         if (h == 1) --to_load;
         if (CHAIN && h == 1 && run_on && to_load == 0) {                      // on to the next member
-          to_load = own / 2;
           if (masked) place_whole();
-          if (++loading < members) {
+          ++loading;
+          to_load = (loading == members - 1 ? last_own : own) / 2;
+          left_loading = loading == members - 1 ? last_left : left;
+          if (loading < members) {
             const Problem Q = problem_at(tab, which + loading);
             a_next = static_cast<const bf16_bits*>(Q.A) + a_first;
             b_next = static_cast<const bf16_bits*>(Q.B) + b_first;
@@ -233,7 +239,9 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
         add_member(to_add_first);
         clear();
         to_add_first = false;
-        to_add = own / 2;
+        ++adding;
+        to_add = (adding == members - 1 ? last_own : own) / 2;
+        left_adding = adding == members - 1 ? last_left : left;
       }
     };
     // Fragment i (rhs 0..3, then lhs 0..3) of half h of a K step whose first tile is in stage s0, into set h.  A K-contiguous operand's
@@ -269,7 +277,8 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
       }
     };
     auto clear_beyond = [&](int h) {            // in fragments of half h of the last step, in BOTH operands: the padding may hold anything
-      const int valid = left - h * kMfmaBK - (lane >> 4) * 8;
+      if (left_adding == 0) return;
+      const int valid = left_adding - h * kMfmaBK - (lane >> 4) * 8;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         fa[h][i] = __builtin_bit_cast(bf16x8_t, mask_tail8(__builtin_bit_cast(u32x4_t, fa[h][i]), valid));

@@ -30,7 +30,7 @@ struct Problem {
   int32_t join_count; // contributions per output tile; 0 or 1: this problem alone
   int32_t join_slot;  // this problem's place in the order of summation
   int32_t join_first; // index, among all joined output tiles of the launch, of this problem's tile 0
-  int32_t join_alike; // dot_mid_kernel: this and the following members have equal strides and K, and run through one loop
+  int32_t join_alike; // dot_mid_kernel: this and the following members have equal strides and K (the last one maybe less), and run through one loop
 };
 static_assert(sizeof(Problem) == 80, "device layout");
 

@@ -88,9 +88,10 @@ def test_loads_around_the_ring_of_stages(M, K, N, layout):
 
 @pytest.mark.parametrize("M,N", [(130, 264), (2100, 2090)])
 @pytest.mark.parametrize("per,P", [(64, 2), (64, 8), (128, 3), (192, 4), (320, 2), (704, 3), (96, 4), (33, 5), (70, 8), (254, 2), (639, 3)])
-def test_alike_members_follow_on(M, N, per, P):
-    # members of equal K: of 1 to 11 steps, the last one whole or not, the next ones' loads under way before the first is multiplied
-    w = wl.ksplit(M=M, K=per * P, N=N, P=P)
+@pytest.mark.parametrize("short", [0, 1, 30])
+def test_alike_members_follow_on(M, N, per, P, short):
+    # members of equal K, the last one's equal or less: of 1 to 11 steps, the last one whole or not, the next ones' loads under way before the first is multiplied
+    w = wl.ksplit(M=M, K=per * P - short, N=N, P=P)          # K beyond the last member's is padding
     lhs, rhs = wl.draw_normal_bf16(5, w.lhs_shape), wl.draw_normal_bf16(6, w.rhs_shape)
     st = Staged(w, lhs, rhs, row_align=8, out_dtype="f32")
     got = {}
