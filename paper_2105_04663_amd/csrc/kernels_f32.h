@@ -8,7 +8,7 @@
 // better (f32_per_unit).  128-row tiles, three on a compute unit, need more registers than there are: 275 us below.  A lane's four k of a K-contiguous fragment are one 16-byte LDS read; the four MFMAs
 // that use them take k = 4 g + i of every 16 (g = lane / 16), for both operands alike, which only reorders the sum.
 // Measured, 2048 x 2048 x 3000 on a 2 x 4 mesh: 522 us with scalar FMA, 315 with loads one step ahead and conditions inside
-// the loop (every wait then a full one), 229 now: 110 TFLOP/s, MFMA busy for 81 % of the cycles in which a compute unit has
+// the loop (every wait then a full one), 230 with three workgroups on a compute unit, 223 by the rule: 113 TFLOP/s; MFMA busy (at 230) for 81 % of the cycles in which a compute unit has
 // work, which is 86 % of the launch.
 #pragma once
 #include <hip/hip_runtime.h>
