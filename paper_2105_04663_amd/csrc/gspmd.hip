@@ -139,13 +139,14 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 
 // What a launch of dot_mfma_kernel or dot_mid_kernel takes, in us: straight lines through measured times.
 // dot_mfma_kernel: rounds of 256 workgroups of 9 us and 1.3 us per 64-wide K step, where the chip is full and its clock drops, down to 0.85
-//   in a round of few (short tiles: 0.75), 2 us for what is left of K; staged operands 10.5 and 2.1 us.  Joined problems meet in slots: 4.6 us
-//   per member, the last arriver at a tile reading the others' contributions one after the other, and 0.05 us per contribution to a tile
+//   in a round of few (short tiles: 0.75), 2 us for what is left of K; staged operands 10.5 and 2.1 us.  From two full rounds on 1.25 us, and the last
+//   round counts by its share, as the workgroups no longer start together.  Joined problems meet in slots: 4.6 us
+//   per member, the last arriver at a tile reading the others' contributions one after the other, and 0.05 us per contribution to a tile, 0.1 beyond 256
 //   (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38; 8, 16: 38; 8, 512: 59).
 // dot_mid_kernel: 8.8 us and 0.205 us per 32-wide step while a compute unit has one workgroup, 0.40 with two, then rounds of 512; the members of
 //   a joined sum follow each other in one workgroup, 1.8 us apart where they are not alike and whole K steps long; 0.25 us per 32-wide tile
-//   that is left of K; a fifth more per step where a K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us,
-//   with rows of 8032 elements 117).  Fitted to 60 drawn launches of 1 to 8 members; root mean square of the relative error 12 %.
+//   that is left of K; in sums of more than one round of 512 0.44, and 0.30 in a last round of up to 256; a fifth more per step where a
+//   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Fitted to 60 drawn launches of 1 to 8 members; root mean square of the relative error 12 %.
 // Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 118 / 60   512 x 8192 x 512: 117 / 47
 //   2048 x 4096 x 4096: 63 / 60   2048 x 1024 x 4096: 25 / 20   4653 x 7168 x 4288: 245 / 281   1456 x 1415 x 3969, two of them: 37 / 48
 //   2178 x 4736 x 1447, two: 75 / 61   1090 x 1333 x 1568, eight: 60 / 52   4 experts' weight gradients of 512 x 4096 x 8192: 122 / 227
@@ -180,14 +181,18 @@ double big_us(const LaunchSize& s, bool staged) {
   const double steps = static_cast<double>((s.k + 63) / 64), full = static_cast<double>(s.big / 256), part = static_cast<double>(s.big % 256) / 256.0;
   const double beside = staged ? 10.5 : 9.0 + (s.k % 64 ? 2.0 : 0.0);
   auto step = [&](double fill) { return staged ? 2.1 : s.rows <= 96 ? 0.75 : 0.85 + 0.45 * fill * fill; };
-  const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * static_cast<double>(s.big) : 0.0;
+  const double first = static_cast<double>(std::min<int64_t>(s.big, 256)), later = static_cast<double>(s.big) - first;
+  const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * first + 0.1 * later : 0.0;
+  if (!staged && s.rows > 96 && full >= 2.0) return (full + part) * (beside + steps * 1.25) + slots;
   return full * (beside + steps * step(1.0)) + (part > 0.0 ? beside + steps * step(part) : 0.0) + slots;
 }
 double mid_us(const LaunchSize& s, bool staged = false) {
   const double m = static_cast<double>(s.members), left = static_cast<double>((s.k % 64 + 31) / 32);
   const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 8.8 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
   const int64_t part = s.mid % 512;
-  const double one = staged ? 0.11 + 0.16 * ((s.a_odd ? 1 : 0) + (s.b_odd ? 1 : 0)) : 0.205, two = staged ? 2.0 * one : 0.40;
+  const bool long_sum = s.members > 1 && s.mid > 512;
+  const double one = staged ? 0.11 + 0.16 * ((s.a_odd ? 1 : 0) + (s.b_odd ? 1 : 0)) : long_sum ? 0.30 : 0.205;
+  const double two = staged ? 2.0 * one : long_sum ? 0.44 : 0.40;
   return static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
 }
 
@@ -242,7 +247,12 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 }
 
 // Sums over a contracting mesh dimension are formed in one launch (joined problems) or in two: the members' products by themselves, in dense
-// fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 15 % faster; the results are the same bits.
+// fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 15 % faster, or 5 % where one launch would take more than a round
+// of dot_mid_kernel's tiles (kSeveralRounds: what a launch pays once no longer matters, and the lines are closer); the results are the same bits.
+// Scattered over all members, slots / one after the other / two launches (us): 4227 x 13543 x 3328 over 4: - / 410 / 363   4227 x 8192 x 3328
+//   over 4: - / 233 / 249   3000 x 13543 x 3328 over 4: - / 351 / 269   8192 x 8000 x 2048 over 4: 333 / 297 / 290   6000 x 12000 x 4096 over 2: 455 /
+//   649 / 487   4227 x 5000 x 3328 over 4: - / 175 / 211   4096 x 16384 x 4096 over 4: 468 / 507 / 432
+constexpr int64_t kSeveralRounds = 512;
 double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
   return choice.kernel == kMfmaMid ? mid_us(size, choice.staged) : big_us(size, choice.staged);
@@ -983,7 +993,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
           ++launches;
           summable = summable && kv.second.size() <= static_cast<size_t>(kMaxPartials);
         }
-        ok = !summable || sum_us(live, one, jlayout) <= 1.15 * (sum_us(apart, two, jlayout) + apart_us(partial_bytes, launches));
+        ok = !summable || sum_us(live, one, jlayout) <= (launch_size(live, jlayout).mid > kSeveralRounds ? 1.05 : 1.15) * (sum_us(apart, two, jlayout) + apart_us(partial_bytes, launches));
       }
     }
     // Behind the launch tables come the counters, then the slots.  A scattered sum has more entries than the query counted (one
