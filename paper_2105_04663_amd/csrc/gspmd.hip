@@ -13,6 +13,7 @@
 #include "kernels_basic.h"
 #include "kernels_f32.h"
 #include "launch.h"
+#include "mfma_common.h"
 #include "plan.h"
 #include "testing.h"
 #include "tile_index.h"
@@ -134,8 +135,8 @@ struct MfmaChoice {
 };
 
 // What this thread's launches are pinned to, and what its last one took (testing.h).
-thread_local gspmd_testing_launch t_pin{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0};
-thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0};
+thread_local gspmd_testing_launch t_pin{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0, 0, 0};
+thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0, 0, 0};
 
 // What a launch of dot_mfma_kernel or dot_mid_kernel takes, in us: straight lines through measured times.
 // dot_mfma_kernel: rounds of 256 workgroups of 9 us and 1.3 us per 64-wide K step, where the chip is full and its clock drops, down to 0.85
@@ -289,6 +290,24 @@ MfmaKernel with_records(MfmaKernel kernel) {
   return kernel == kMfmaMid && g_timeline.load(std::memory_order_acquire) != nullptr ? kMfmaBig : kernel;
 }
 
+// Problems whose last tile column is moved back: those with loose rhs rows, and with one member of a sum all of them (the members are
+// consecutive).  2048 x 8192 x 2050 over two members with rhs rows of 2056 and 2050 elements: both take columns 1794 .. 2049 for their last tile.
+// Returns how many.
+int32_t mark_moved_back(std::vector<Problem>& ps) {
+  int32_t moved = 0;
+  for (size_t i = 0; i < ps.size();) {
+    const size_t end = i + static_cast<size_t>(std::max(ps[i].join_count, 1));
+    bool loose = false;
+    for (size_t m = i; m < end; ++m) loose = loose || loose_rows(ps[m].B, ps[m].ldb);
+    for (; i < end; ++i)
+      if (loose) {
+        ps[i].flags |= kProblemMovesBack;
+        ++moved;
+      }
+  }
+  return moved;
+}
+
 int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dtype, int32_t out_dtype, int32_t epilogue,
                         bool ordered, void* workspace, int64_t workspace_bytes, hipStream_t stream, const JoinSpace* join = nullptr) {
   // problems with an empty static output block write nothing
@@ -324,8 +343,10 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
         const Problem &a = ps[i], &b = ps[i + static_cast<size_t>(m)];
         alike = a.lda == b.lda && a.ldb == b.ldb && (a.Kv == b.Kv || (m == ps[i].join_count - 1 && b.Kv > 0 && b.Kv < a.Kv && fits(b.Kv)));
       }
-      ps[i].join_alike = alike ? 1 : 0;
+      if (alike) ps[i].flags |= kProblemRunsOn;
     }
+  const bool moves = choice.kernel == kMfmaBig && !choice.staged && path == kPathMfmaWords && !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
+  t_last.moved_back = moves ? mark_moved_back(ps) : 0;
   const int64_t tiles = assign_tiles(ps, bm, bn, mid);
   if (tiles < 0) return GSPMD_ERR_UNSUPPORTED;
   std::vector<ZeroRect> rects;

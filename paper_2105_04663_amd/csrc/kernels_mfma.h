@@ -107,11 +107,9 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
   const TileRows own = tile_rows(tile_row, P.Mv);
   const int m0 = own.first, m_end = own.first + own.rows;
   const int m_write_end = m_end == P.Mv ? min(P.Ms, m0 + kMfmaBM) : m_end;
-  // A K-major rhs whose rows are whole 32-bit words but not padded to 16 bytes: the last tile column is moved back so that no chunk reaches
-  // past a row's last word.  The columns that it shares with its neighbour are computed and stored by both, with the same bits.
   const int n_nom = n0;
-  if (!STAGED && !BKC && loose_rows(P.B, P.ldb)) n0 = min(n0, P.Nv - kMfmaBN + (P.Nv & 1));
-  const int n_load_end = n0 < n_nom ? n0 + kMfmaBN : P.Nv;
+  if (!STAGED && !BKC) n0 = tile_first_column(n_nom, P.Nv, kMfmaBN, (P.flags & kProblemMovesBack) != 0);
+  const int n_load_end = tile_load_end(n0, n_nom, P.Nv, kMfmaBN);
 
   // acc[bm] holds the four 16x16 tiles (bn = 0..3) of 16-row block bm: element 4*bn + r
   float16_t acc[8];

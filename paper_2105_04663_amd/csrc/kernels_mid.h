@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   const int members = CHAIN ? max(P.join_count, 1) : 1;
   // Members that are alike follow each other without a break: the loads of the next one are under way while this one's last steps are
   // multiplied (those with something left of K in the loop that is not unrolled, so only short ones).  Others are taken one by one.
-  const bool run_on = CHAIN && P.join_alike != 0;
+  const bool run_on = CHAIN && (P.flags & kProblemRunsOn) != 0;
 
   float4_t acc[4][4], sum[CHAIN ? 4 : 1][CHAIN ? 4 : 1];
   // Fragment addresses.  LDS offsets in instructions have 16 bits: stages are addressed from a register per four of them (with five

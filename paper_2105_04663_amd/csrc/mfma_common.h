@@ -41,7 +41,7 @@ typedef uint32_t u32x4_words_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_elements_t __attribute__((ext_vector_type(4), aligned(2)));      // at any bf16 element's address
 
 // Rows of whole 32-bit words that are not padded to 16 bytes: a 16-byte chunk may reach past a row's end.
-__device__ __forceinline__ bool loose_rows(const void* p, int ld) { return (reinterpret_cast<uintptr_t>(p) & 15) || (ld & 7); }
+__host__ __device__ __forceinline__ bool loose_rows(const void* p, int ld) { return (reinterpret_cast<uintptr_t>(p) & 15) || (ld & 7); }
 
 // Eight consecutive k of a K-contiguous row, of which `valid` (any number) exist: zeros beyond, and no word read that holds no valid element.
 __device__ __forceinline__ u32x4_t load_k_chunk(__attribute__((address_space(1))) const uint32_t* at, int valid) {

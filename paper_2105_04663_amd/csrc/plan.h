@@ -30,9 +30,14 @@ struct Problem {
   int32_t join_count; // contributions per output tile; 0 or 1: this problem alone
   int32_t join_slot;  // this problem's place in the order of summation
   int32_t join_first; // index, among all joined output tiles of the launch, of this problem's tile 0
-  int32_t join_alike; // dot_mid_kernel: this and the following members have equal strides and K (the last one maybe less), and run through one loop
+  int32_t flags;      // kProblem*
 };
 static_assert(sizeof(Problem) == 80, "device layout");
+
+// dot_mid_kernel: this and the following members have equal strides and K (the last one maybe less), and run through one loop
+constexpr int32_t kProblemRunsOn = 1;
+// dot_mfma_kernel, dot_mid_kernel, direct loads of a K-major rhs: the last tile column is moved back (tile_first_column)
+constexpr int32_t kProblemMovesBack = 2;
 
 // A rectangle of a problem's static output block that no output tile covers (whole tile rows / columns beyond the
 // valid extents): written as 0 by a fill kernel, so that the contraction kernel is launched over live tiles only.

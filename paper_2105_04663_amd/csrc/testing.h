@@ -26,6 +26,8 @@ typedef struct {
   /* last only: bytes of launch tables at the start of the workspace (0: they travel as kernel arguments), and where in the workspace
    * the partial sums or counters and slots of a sum lie */
   int64_t table_bytes, sums_begin, sums_end;
+  int32_t moved_back;   /* last only: problems whose last tile column is moved back (all members of a sum, or none) */
+  int32_t reserved;
 } gspmd_testing_launch;
 
 int32_t gspmd_testing_pin(const gspmd_testing_launch* pin);

@@ -50,6 +50,16 @@ GSPMD_INDEX_FN int spread_tile(int b, int total) {
 
 constexpr int kBandRows = 8;
 
+// A K-major rhs whose rows are whole 32-bit words but not padded to 16 bytes: the last tile column is moved back so that no chunk
+// reaches past a row's last word.  The columns that it shares with its neighbour are computed and stored by both, with the same bits.
+// Contributions to one output meet by tile and lane, not by column, so `moved` is the same for all of them.
+GSPMD_INDEX_FN int tile_first_column(int nominal, int cols_valid, int tile, bool moved) {
+  const int last = cols_valid - tile + (cols_valid & 1);
+  return moved && last < nominal ? last : nominal;
+}
+// The end of the columns that such a tile loads.
+GSPMD_INDEX_FN int tile_load_end(int first, int nominal, int cols_valid, int tile) { return first < nominal ? first + tile : cols_valid; }
+
 GSPMD_INDEX_FN int swz_h(int row) { return (row >> 1) & 7; }
 
 // Main loop, K-contiguous operand: part `half` (0/1) of a 64-wide K step is [128 rows][64 k] with 128-byte rows.

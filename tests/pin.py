@@ -9,7 +9,8 @@ BY_RULE, SCALAR, MFMA, MID, SPLIT = -1, 0, 1, 2, 3
 
 class _Launch(C.Structure):
     _fields_ = [("kernel", C.c_int32), ("row_blocks", C.c_int32), ("one_launch", C.c_int32), ("dry_run", C.c_int32),
-                ("table_bytes", C.c_int64), ("sums_begin", C.c_int64), ("sums_end", C.c_int64)]
+                ("table_bytes", C.c_int64), ("sums_begin", C.c_int64), ("sums_end", C.c_int64),
+                ("moved_back", C.c_int32), ("reserved", C.c_int32)]
 
 
 def _pin(kernel, row_blocks, one_launch, dry_run=False):
@@ -43,3 +44,8 @@ def last_workspace():
     """(bytes of launch tables, begin and end of the partial sums or counters and slots) in the workspace of this thread's last Dot."""
     p = _last()
     return p.table_bytes, p.sums_begin, p.sums_end
+
+
+def last_moved_back():
+    """How many problems (members of a sum one by one) of this thread's last launch have their last tile column moved back."""
+    return _last().moved_back

@@ -59,6 +59,38 @@ def test_sums_are_the_same_bits(M, K, N, P, kernel, one_launch):
     assert torch.equal(st.out[0][1].view(M, -1)[:, :N], total)
 
 
+def _restride(st, pid, ld, first):
+    """Partition `pid`'s rhs shard in rows of `ld` elements from element `first` of a buffer that ends with the last row's valid words."""
+    _, old, old_ld, shard = st.rhs[pid]
+    rows, cols = shard
+    t = torch.full((first + (rows - 1) * ld + (cols + 1) // 2 * 2,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    torch.as_strided(t, (rows, cols), (ld, 1), first).copy_(old.view(rows, old_ld)[:, :cols])
+    st.keep.append(t)
+    st.rhs[pid] = (g.ShardBuf.of(t[first:], ld), t, ld, shard)
+
+
+@pytest.mark.parametrize("kernel,one_launch", [(MFMA, 1), (MFMA, 0)])
+@pytest.mark.parametrize("scatter", [False, True])
+@pytest.mark.parametrize("strides,firsts", [((2056, 2052), (0, 0)), ((2052, 2056), (0, 0)), ((2056, 2056), (0, 2)), ((2056, 2056, 2058), (4, 0, 0)), ((2056, 2056), (0, 0))])
+def test_members_with_rows_of_their_own(strides, firsts, scatter, kernel, one_launch):
+    # one member's rhs rows are padded to 16 bytes, another's are not: all take the same columns for their last tile
+    P, M, N = len(strides), 300, 2051             # scattered: 1026 and 1025 columns, 684, 684 and 683
+    w = wl.ksplit(M=M, K=P * 256, N=N, P=P)
+    lhs, rhs = wl.draw_small_int_bf16(5, w.lhs_shape), wl.draw_small_int_bf16(6, w.rhs_shape)
+    w.out_map = (-1, 0) if scatter else (-1, -1)
+    st = Staged(w, lhs, rhs, row_align=8, out_dtype="f32")
+    for pid in range(P):
+        _restride(st, pid, strides[pid], firsts[pid])
+    room = torch.empty(1 << 26, dtype=torch.uint8, device="cuda")       # scattered pieces take more slots than the query has room for
+    st.workspace = lambda *_: (room.data_ptr(), room.numel())
+    with pinned(kernel, 0, one_launch):
+        st.run_grouped()
+        assert last() == (kernel, 0, one_launch)
+    ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    for pid in range(P):
+        assert np.array_equal(st.out_shard(pid), od.expected_out_shard(ref, w.mesh_shape, w.device_ids, w.out_map, pid)), f"partition {pid}"
+
+
 def test_columns_right_of_a_moved_tile_are_cleared():
     # 770 columns over 3 partitions of 257: the last one has 256 valid of 257 static ones, with rows of 258
     w = _workload(300, 96, 770, 0, 3)

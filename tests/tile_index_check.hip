@@ -111,6 +111,25 @@ static void check_km(int c0, int cols_valid, int ld) {
         }
 }
 
+// ---- tile columns of a K-major rhs in loose rows (even ld, not padded to 16 bytes): the columns that the tiles load reach no further
+// than the last valid word, and their stored columns cover the valid ones; whether a tile is moved depends on nothing but `moved`
+template <class Offset> static void check_moved_columns(int tile, int cols_valid, int loads, Offset offset) {
+  const int ld = (cols_valid + 1) & ~1, words_end = ld;       // a word's second half may be beyond the last valid column
+  int next = 0;
+  for (int nominal = 0; nominal < cols_valid; nominal += tile) {
+    const int first = tile_first_column(nominal, cols_valid, tile, true), load_end = tile_load_end(first, nominal, cols_valid, tile);
+    CHECK(first >= 0 && first % 2 == 0 && first <= nominal && first <= next, "tile of %d at %d of %d columns moved to %d", tile, nominal, cols_valid, first);
+    next = first + tile;
+    CHECK(tile_first_column(nominal, cols_valid, tile, false) == nominal, "a tile that is not moved");
+    for (int q = 0; q < loads; ++q)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int elem = offset(q, lane, first, load_end, ld) / 2 + first;      // counted from column 0 of k row 0
+        CHECK(elem >= 0 && elem % ld + 8 <= words_end, "tile of %d at %d of %d columns: a chunk at column %d", tile, first, cols_valid, elem % ld);
+      }
+  }
+  CHECK(next >= cols_valid, "tiles of %d columns end at %d of %d", tile, next, cols_valid);
+}
+
 static void check_tile_order() {
   for (int rows_valid : {1, 15, 16, 17, 128, 255, 256, 257, 734, 745, 959, 967, 1024, 1500, 2049, 5000, 16384})
     for (int tiles_n : {1, 2, 5, 32, 128}) {
@@ -198,6 +217,8 @@ int main() {
     for (int c0 : {0, 256, 1024})
       for (int cols_valid : {c0 + 1, c0 + 7, c0 + 8, c0 + 9, c0 + 226, c0 + 255, c0 + 256, c0 + 9999})
         if (((cols_valid + 7) & ~7) <= ld) check_km(c0, cols_valid, ld);
+  for (int cols_valid : {256, 257, 258, 259, 300, 511, 512, 513, 514, 770, 1025, 2049, 2050, 2056})
+    check_moved_columns(kMfmaBN, cols_valid, 16, [](int q, int lane, int c0, int end, int ld) { return km_load_offset(q, lane, c0, end, ld); });
   check_tile_order();
   if (failures) { printf("%d failures\n", failures); return 1; }
   printf("tile index ok\n");
