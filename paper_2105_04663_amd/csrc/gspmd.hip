@@ -345,7 +345,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       }
       if (alike) ps[i].flags |= kProblemRunsOn;
     }
-  const bool moves = choice.kernel == kMfmaBig && !choice.staged && path == kPathMfmaWords && !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
+  const bool moves = mfma && !split && !choice.staged && path == kPathMfmaWords && !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
   t_last.moved_back = moves ? mark_moved_back(ps) : 0;
   const int64_t tiles = assign_tiles(ps, bm, bn, mid);
   if (tiles < 0) return GSPMD_ERR_UNSUPPORTED;

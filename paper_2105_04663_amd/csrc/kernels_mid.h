@@ -36,30 +36,6 @@ template <int PER_CU> constexpr int mid_stages() { return PER_CU == 1 ? 10 : 5; 
 template <int PER_CU> constexpr int mid_ahead() { return PER_CU == 1 ? 6 : 4; }
 constexpr int kMidUnroll = 5;                         // K steps after which the stages come round: their places are then constants of the code
 
-// K-major part [32 k][128 columns]: 16 chunks of 16 bytes per k row.  Chunk pairs (one 16-column block) are XOR-swizzled by
-// the row, so that the 4 rows x 32 bytes that a 16-lane group reads and those of the group beside it (8 rows further)
-// lie in different banks.
-__device__ __forceinline__ int mid_swz(int krow) { return ((krow & 3) | (((krow >> 3) & 1) << 2)) << 1; }
-// load instruction q (0..7) of a K-major part: k rows 4 q .. 4 q + 3, 16 lanes per row; chunks past the valid extent reuse
-// the last valid chunk, k rows past `k_valid` the last valid row
-__device__ __forceinline__ int mid_km_load_offset(int q, int lane, int c0, int cols_valid, int ld, int k_valid = kMfmaBK) {
-  const int kr = q * 4 + (lane >> 4);
-  int n = c0 + (((lane & 15) ^ mid_swz(kr)) << 3);
-  if (n >= cols_valid) n = ((cols_valid - 1) >> 3) << 3;
-  return (min(kr, k_valid - 1) * ld + (n - c0)) * 2;
-}
-// K-contiguous operand: load instruction q (0..7) of the part with the tile's rows 64 half .. 64 half + 63, 64 k: 8 rows, 8 lanes per row;
-// rows past the valid extent reuse the last valid row, chunks past `k_valid` the last valid chunk
-__device__ __forceinline__ int mid_kc_load_offset(int q, int lane, int half, int r0, int rows_valid, int ld, int k_valid = 2 * kMfmaBK) {
-  const int r = q * 8 + (lane >> 3);
-  return (min(half * 64 + r, rows_valid - 1 - r0) * ld + min((lane & 7) ^ swz_h(r), (k_valid - 1) >> 3) * 8) * 2;
-}
-// fragment of the 16-column block at `base` (block b further at ^ (b << 5) for a base that is a multiple of 64)
-__device__ __forceinline__ int mid_km_frag_offset(int base, int lane) {
-  const int i = lane & 15, krow = (lane >> 4) * 8 + (i >> 2), cl = base + (i & 3) * 4;
-  return krow * 256 + (((cl >> 3) ^ mid_swz(krow)) << 4) + (cl & 7) * 2;
-}
-
 // STAGED: the variant for operands at odd element addresses, which direct loads do not take: a tile's chunks are loaded into registers two
 // half steps before they are put where the direct load would have put them, and K-major operands' last tiles are moved back so that
 // every chunk is whole.  Bound by the address unit, 64 cycles for a KiB at an odd address (both operands: 430 ns per 32-wide
@@ -90,9 +66,8 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   const int band = local / (kBandRows * P.tiles_n), in_band = local - band * kBandRows * P.tiles_n;
   const int rows_in_band = min(kBandRows, tiles_m - band * kBandRows);
   const int m_nom = (band * kBandRows + in_band % rows_in_band) * kMidTile, n_nom = (in_band / rows_in_band) * kMidTile;
-  // rhs rows that are not padded to 16 bytes: the last tile column is moved back, as in dot_mfma_kernel
-  const bool loose = !BKC && (STAGED || loose_rows(P.B, P.ldb));
-  const int n0 = loose ? min(n_nom, P.Nv - kMidTile + (STAGED ? 0 : P.Nv & 1)) : n_nom, n_load_end = n0 < n_nom ? n0 + kMidTile : P.Nv;
+  const int n0 = BKC ? n_nom : STAGED ? min(n_nom, P.Nv - kMidTile) : tile_first_column(n_nom, P.Nv, kMidTile, (P.flags & kProblemMovesBack) != 0);
+  const int n_load_end = tile_load_end(n0, n_nom, P.Nv, kMidTile);
   const int m0 = STAGED && AKM ? min(m_nom, P.Mv - kMidTile) : m_nom;
   const int members = CHAIN ? max(P.join_count, 1) : 1;
   // Members that are alike follow each other without a break: the loads of the next one are under way while this one's last steps are

@@ -114,6 +114,32 @@ GSPMD_INDEX_FN int km_frag_offset(int base, int lane) {
   return krow * 512 + (((cl >> 3) ^ swz_b(krow)) << 4) + (cl & 7) * 2;
 }
 
+// ---- dot_mid_kernel's tiles of 128 x 128
+// K-major part [32 k][128 columns]: 16 chunks of 16 bytes per k row.  Chunk pairs (one 16-column block) are XOR-swizzled by
+// the row, so that the 4 rows x 32 bytes that a 16-lane group reads and those of the group beside it (8 rows further)
+// lie in different banks.
+GSPMD_INDEX_FN int mid_swz(int krow) { return ((krow & 3) | (((krow >> 3) & 1) << 2)) << 1; }
+// load instruction q (0..7) of a K-major part: k rows 4 q .. 4 q + 3, 16 lanes per row; chunks past the valid extent reuse
+// the last valid chunk, k rows past `k_valid` the last valid row
+GSPMD_INDEX_FN int mid_km_load_offset(int q, int lane, int c0, int cols_valid, int ld, int k_valid = kMfmaBK) {
+  const int kr = q * 4 + (lane >> 4);
+  int n = c0 + (((lane & 15) ^ mid_swz(kr)) << 3);
+  if (n >= cols_valid) n = ((cols_valid - 1) >> 3) << 3;
+  return ((kr < k_valid ? kr : k_valid - 1) * ld + (n - c0)) * 2;
+}
+// K-contiguous operand: load instruction q (0..7) of the part with the tile's rows 64 half .. 64 half + 63, 64 k: 8 rows, 8 lanes per row;
+// rows past the valid extent reuse the last valid row, chunks past `k_valid` the last valid chunk
+GSPMD_INDEX_FN int mid_kc_load_offset(int q, int lane, int half, int r0, int rows_valid, int ld, int k_valid = 2 * kMfmaBK) {
+  const int r = q * 8 + (lane >> 3);
+  const int last = rows_valid - 1 - r0, row = half * 64 + r, c = (lane & 7) ^ swz_h(r), last_c = (k_valid - 1) >> 3;
+  return ((row < last ? row : last) * ld + (c < last_c ? c : last_c) * 8) * 2;
+}
+// fragment of the 16-column block at `base` (block b further at ^ (b << 5) for a base that is a multiple of 64)
+GSPMD_INDEX_FN int mid_km_frag_offset(int base, int lane) {
+  const int i = lane & 15, krow = (lane >> 4) * 8 + (i >> 2), cl = base + (i & 3) * 4;
+  return krow * 256 + (((cl >> 3) ^ mid_swz(krow)) << 4) + (cl & 7) * 2;
+}
+
 // How the valid rows of a problem are divided among its tile rows.  The work of a tile is proportional to the
 // 16-row blocks it multiplies, and workgroups are handed to compute units in id order, so a launch finishes soonest
 // when its tiles cost about the same: the ceil(rows / 16) blocks are split as evenly as possible over the

@@ -69,7 +69,7 @@ def _restride(st, pid, ld, first):
     st.rhs[pid] = (g.ShardBuf.of(t[first:], ld), t, ld, shard)
 
 
-@pytest.mark.parametrize("kernel,one_launch", [(MFMA, 1), (MFMA, 0)])
+@pytest.mark.parametrize("kernel,one_launch", [(MFMA, 1), (MFMA, 0), (MID, 1), (MID, 0)])
 @pytest.mark.parametrize("scatter", [False, True])
 @pytest.mark.parametrize("strides,firsts", [((2056, 2052), (0, 0)), ((2052, 2056), (0, 0)), ((2056, 2056), (0, 2)), ((2056, 2056, 2058), (4, 0, 0)), ((2056, 2056), (0, 0))])
 def test_members_with_rows_of_their_own(strides, firsts, scatter, kernel, one_launch):

@@ -3,7 +3,7 @@ row strides and base addresses of each (host only: Dots stop short of their laun
 import pytest
 
 import paper_2105_04663_amd as g
-from tests.pin import BY_RULE, MFMA, last, last_moved_back, pinned
+from tests.pin import BY_RULE, MFMA, MID, last, last_moved_back, pinned
 
 
 def _moved(M, K, N, strides, offsets, out_map, kernel, one_launch):
@@ -19,7 +19,7 @@ def _moved(M, K, N, strides, offsets, out_map, kernel, one_launch):
     return last_moved_back()
 
 
-@pytest.mark.parametrize("kernel", [MFMA])
+@pytest.mark.parametrize("kernel", [MFMA, MID])
 @pytest.mark.parametrize("strides,offsets", [((2056, 2050), (0, 0)), ((2050, 2056), (0, 0)), ((2056, 2056), (0, 4)), ((2056, 2056), (8, 0)),
                                              ((2056, 2056, 2058), (0, 0, 0)), ((2056, 2056), (0, 0)), ((2050, 2050), (0, 0))])
 def test_all_members_or_none(strides, offsets, kernel):
@@ -32,11 +32,12 @@ def test_all_members_or_none(strides, offsets, kernel):
     assert last() == (kernel, 0, 0)
 
 
-def test_pieces_of_a_scattered_sum():
+@pytest.mark.parametrize("kernel", [MFMA, MID])
+def test_pieces_of_a_scattered_sum(kernel):
     # owner 0's columns start at a multiple of 16 bytes, owner 1's 2050 elements further: with padded rows only the latter's pieces move
-    assert _moved(300, 1024, 4100, (4104, 4104), (0, 0), (-1, 0), MFMA, 1) == 2
-    assert _moved(300, 1024, 4100, (4104, 4100), (0, 0), (-1, 0), MFMA, 1) == 4
-    assert last() == (MFMA, 0, 1)
+    assert _moved(300, 1024, 4100, (4104, 4104), (0, 0), (-1, 0), kernel, 1) == 2
+    assert _moved(300, 1024, 4100, (4104, 4100), (0, 0), (-1, 0), kernel, 1) == 4
+    assert last() == (kernel, 0, 1)
 
 
 @pytest.mark.parametrize("M,K,N,strides,offsets", [(2048, 8192, 2050, (2056, 2050), (0, 0)), (4096, 4096, 4098, (4104, 4098), (0, 0)),

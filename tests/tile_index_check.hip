@@ -219,6 +219,8 @@ int main() {
         if (((cols_valid + 7) & ~7) <= ld) check_km(c0, cols_valid, ld);
   for (int cols_valid : {256, 257, 258, 259, 300, 511, 512, 513, 514, 770, 1025, 2049, 2050, 2056})
     check_moved_columns(kMfmaBN, cols_valid, 16, [](int q, int lane, int c0, int end, int ld) { return km_load_offset(q, lane, c0, end, ld); });
+  for (int cols_valid : {128, 129, 130, 131, 140, 255, 256, 257, 258, 385, 770, 1025, 2049, 2050, 2056})
+    check_moved_columns(128, cols_valid, 8, [](int q, int lane, int c0, int end, int ld) { return mid_km_load_offset(q, lane, c0, end, ld); });
   check_tile_order();
   if (failures) { printf("%d failures\n", failures); return 1; }
   printf("tile index ok\n");
