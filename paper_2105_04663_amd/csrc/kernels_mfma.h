@@ -586,7 +586,8 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
   if (m_end == P.Mv && m_write_end < P.Ms) {
     const int col_end = min(n_nom + kMfmaBN, P.Ns);
     constexpr int kPer = 16 / static_cast<int>(sizeof(TOut));
-    zero_rows_below<TOut>(Cg, P.ldc, m_write_end, rows_cleared(P.Mv, P.Ms), n0, col_end, rows_16b && ((col_end - n0) % kPer) == 0, t);
+    // from n_nom, a multiple of 16 bytes, on: what a moved tile shares with its neighbour the neighbour clears
+    zero_rows_below<TOut>(Cg, P.ldc, m_write_end, rows_cleared(P.Mv, P.Ms), n_nom, col_end, rows_16b && ((col_end - n_nom) % kPer) == 0, t);
   }
   if (n0 < n_nom && n0 + kMfmaBN < P.Ns)                               // static columns right of a tile that was moved back
     zero_rows_below<TOut>(Cg, P.ldc, m0, m_write_end, n0 + kMfmaBN, min(n_nom + kMfmaBN, P.Ns), false, t);

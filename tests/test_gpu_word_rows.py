@@ -62,7 +62,7 @@ def test_sums_are_the_same_bits(M, K, N, P, kernel, one_launch):
 def _restride(st, pid, ld, first):
     """Partition `pid`'s rhs shard in rows of `ld` elements from element `first` of a buffer that ends with the last row's valid words."""
     _, old, old_ld, shard = st.rhs[pid]
-    rows, cols = shard
+    rows, cols = int(np.prod(shard[:-1])), shard[-1]
     t = torch.full((first + (rows - 1) * ld + (cols + 1) // 2 * 2,), float("nan"), dtype=torch.bfloat16, device="cuda")
     torch.as_strided(t, (rows, cols), (ld, 1), first).copy_(old.view(rows, old_ld)[:, :cols])
     st.keep.append(t)
@@ -89,6 +89,24 @@ def test_members_with_rows_of_their_own(strides, firsts, scatter, kernel, one_la
     ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
     for pid in range(P):
         assert np.array_equal(st.out_shard(pid), od.expected_out_shard(ref, w.mesh_shape, w.device_ids, w.out_map, pid)), f"partition {pid}"
+
+
+@pytest.mark.parametrize("H", [300, 301, 512, 770])
+@pytest.mark.parametrize("fill", [(10, 0, 257), (600, 17, 511)])
+def test_rows_below_a_moved_tile_are_cleared(H, fill):
+    # few occupied slots of 600; the output's rows are padded to 16 bytes, the rhs's are not
+    w = wl.moe(E=3, C=600, M=64, H=H)
+    lhs, rhs = wl.draw_small_int_bf16(5, w.lhs_shape), wl.draw_small_int_bf16(6, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=8, out_dtype="bf16")
+    _restride(st, 0, (H + 1) // 2 * 2, 0)
+    with pinned(MFMA):
+        st.run_grouped(fill=list(fill))
+        assert last()[0] == MFMA
+    got = st.out_shard(0)
+    for e, f in enumerate(fill):
+        want = wl.bf16_bits_to_f64(lhs)[e, :f] @ wl.bf16_bits_to_f64(rhs)[e]
+        want = torch.from_numpy(want).to(torch.bfloat16).double().numpy()
+        assert np.array_equal(got[e, :f], want) and not got[e, f:].any(), f"expert {e}"
 
 
 def test_columns_right_of_a_moved_tile_are_cleared():
