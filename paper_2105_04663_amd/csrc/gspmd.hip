@@ -276,13 +276,16 @@ MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t 
   return choose_mfma(ps, path, layout, ordered);
 }
 
-// How many workgroups of dot_f32_kernel share a compute unit: two rounds of three of its equal tiles, or rounds of four where three do not come out even (us,
-// registers for three / kept for four): 2048 x 2048 x 3000 on 2 x 4, six tiles each: 231 with three, 222 with three of the latter, 248 with
-// four; four each: 2048 x 2048 x 2048 176 / 144, 1300 x 700 x 3000 on 1 x 4 70 / 58; sixteen: 4096 x 4096 x 4096 1123 / 1097.  Elsewhere the
-// former, whose loop is 1 to 2 % shorter: 2500 x 900 x 2500, 6.25 each: 119, 121; 4000 x 2000 x 3000 on 1 x 4, twelve: 426, 430.
-int f32_per_unit(int64_t tiles) {
+// Whether four workgroups of dot_f32_kernel share a compute unit, not three: where its equal tiles come out even that way, and not in threes (us,
+// three / four): four each, 2048 x 2048 x 2048 176 / 144, 2040 x 500 x 2040 52.8 / 44.4, 1300 x 700 x 3000 on 1 x 4 70 / 58; 3.75 each, 2048 x 2000 x
+// 1920 176 / 145; beyond that the matrix cores are nearly full either way: eight each, 2048 x 1024 x 4096 150 / 147, 2040 x 2000 x 4090
+// 289 / 290; sixteen, 4096 x 4096 x 4096 1123 / 1097, 4090 x 2000 x 4090 568 / 576.  Elsewhere three, whose loop is 1 to 2 % shorter: five each, 2040 x
+// 2000 x 2550 194 / 216; six, 1530 x 2000 x 4090 219 / 242, 2048 x 2048 x 3000 on 2 x 4 227 / 247; nine, 3060 x 2000 x 3060 318 / 322; 2500 x 900 x
+// 2500, 6.25 each, 119 / 121.  The registers of four with LDS for three: 3 % shorter to 5 % longer over 71 shapes of six
+// tiles each and more, by no size that tells which.
+bool f32_four(int64_t tiles) {
   const int64_t each = (tiles + 255) / 256;
-  return each == 6 ? 3 : each % 4 == 0 && each % 3 != 0 ? 4 : 0;
+  return each % 4 == 0 && each % 3 != 0;
 }
 
 // While a timeline is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
@@ -413,18 +416,16 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
     } else {
       const dim3 grid(static_cast<unsigned>(tiles)), block(256);
       if (in_dtype == GSPMD_F32) {
-        const int per_unit = f32_per_unit(tiles);
         auto go = [&](auto lean) {
           constexpr bool kLean = decltype(lean)::value;
-          const unsigned extra = per_unit == 3 ? kF32LdsForThree - kF32Lds : 0;
           switch (layout & 3) {
-            case 0: hipLaunchKernelGGL((dot_f32_kernel<0, kLean>), grid, block, extra, stream, inl, tab, n, epilogue); break;
-            case 1: hipLaunchKernelGGL((dot_f32_kernel<1, kLean>), grid, block, extra, stream, inl, tab, n, epilogue); break;
-            case 2: hipLaunchKernelGGL((dot_f32_kernel<2, kLean>), grid, block, extra, stream, inl, tab, n, epilogue); break;
-            default: hipLaunchKernelGGL((dot_f32_kernel<3, kLean>), grid, block, extra, stream, inl, tab, n, epilogue);
+            case 0: hipLaunchKernelGGL((dot_f32_kernel<0, kLean>), grid, block, 0, stream, inl, tab, n, epilogue); break;
+            case 1: hipLaunchKernelGGL((dot_f32_kernel<1, kLean>), grid, block, 0, stream, inl, tab, n, epilogue); break;
+            case 2: hipLaunchKernelGGL((dot_f32_kernel<2, kLean>), grid, block, 0, stream, inl, tab, n, epilogue); break;
+            default: hipLaunchKernelGGL((dot_f32_kernel<3, kLean>), grid, block, 0, stream, inl, tab, n, epilogue);
           }
         };
-        if (per_unit) go(std::true_type{});
+        if (f32_four(tiles)) go(std::true_type{});
         else go(std::false_type{});
       } else if (out_dtype == GSPMD_F32)
         hipLaunchKernelGGL((dot_fallback_kernel<bf16_bits, float>), grid, block, 0, stream, inl, tab, n, layout, epilogue);

@@ -4,11 +4,11 @@
 // Matrix-core bound: 256 flop per clock and compute unit, a sixteenth of the bf16 rate, so one 64 x 64 tile per workgroup
 // feeds the cores from L2 at 16 bytes per clock, and small tiles are what keeps all compute units equally busy (2048 x
 // 2048 x 3000 on 8 partitions: 1536 tiles, six per compute unit).  Four waves of 32 x 32; K in steps of 32 through two
-// LDS buffers, loads two steps ahead, one barrier per step, four workgroups on a compute unit, or three where that shares its tiles out
-// better (f32_per_unit).  128-row tiles, three on a compute unit, need more registers than there are: 275 us below.  A lane's four k of a K-contiguous fragment are one 16-byte LDS read; the four MFMAs
+// LDS buffers, loads two steps ahead, one barrier per step, three workgroups on a compute unit, or four where that shares its tiles out
+// better (f32_four).  128-row tiles, three on a compute unit, need more registers than there are: 275 us below.  A lane's four k of a K-contiguous fragment are one 16-byte LDS read; the four MFMAs
 // that use them take k = 4 g + i of every 16 (g = lane / 16), for both operands alike, which only reorders the sum.
 // Measured, 2048 x 2048 x 3000 on a 2 x 4 mesh: 522 us with scalar FMA, 315 with loads one step ahead and conditions inside
-// the loop (every wait then a full one), 230 with three workgroups on a compute unit, 223 by the rule: 113 TFLOP/s; MFMA busy (at 230) for 81 % of the cycles in which a compute unit has
+// the loop (every wait then a full one), 229 now: 110 TFLOP/s; MFMA busy for 81 % of the cycles in which a compute unit has
 // work, which is 86 % of the launch.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -24,8 +24,6 @@ constexpr int kF32Tile = 64, kF32BK = 32, kF32Threads = 256;
 constexpr int kF32PitchKC = kF32BK + 4;       // K-contiguous operand in LDS: [64][32 k], rows 16 bytes apart in banks
 constexpr int kF32PitchKM = kF32Tile + 4;     // K-major operand: [32 k][64], rows 4 k apart 16 banks apart
 constexpr int kF32PartFloats = kF32Tile * kF32PitchKC;         // the larger of the two formats (2304; K-major 2176)
-constexpr int kF32Lds = 4 * kF32PartFloats * 4;                // two buffers of two operands
-constexpr int kF32LdsForThree = 160 * 1024 / 4 + 1024;         // too much for a fourth workgroup on a compute unit, not for a third
 
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 

@@ -63,7 +63,7 @@ def test_f32_special_values():
 
 
 @pytest.mark.parametrize("layout", [0, 1, 2, 3])
-@pytest.mark.parametrize("M,K,N", [(2001, 37, 2030), (2501, 70, 2390)])          # 1024 and 1520 tiles: four workgroups on a compute unit, three
+@pytest.mark.parametrize("M,K,N", [(2001, 37, 2030), (2501, 70, 2390)])          # 1024 tiles: four workgroups on a compute unit; 1520: three
 def test_f32_workgroups_on_a_compute_unit(M, K, N, layout):
     w = workload(M, K, N, layout)
     w.dtype = "f32"
