@@ -105,3 +105,23 @@ def test_alike_members_follow_on(M, N, per, P, short):
     assert torch.equal(got[MID], got[MFMA])
     ref = od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
     parity.check(st.out_shard(0), ref)
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,N,row_align", [(2100, 2090, 8), (2100, 2090, 2), (200, 300, 2)])       # two workgroups on a compute unit, one
+@pytest.mark.parametrize("per", [33, 55, 64 + 40, 64 + 63, 128 + 31])
+def test_what_is_left_of_members(M, N, row_align, per, layout):
+    # one or two 32-wide tiles after each member's 64-wide steps, and no step before them
+    K, P = 2 * per, 2
+    lhs_shape, rhs_shape = ((K, M) if layout & 1 else (M, K)), ((N, K) if layout & 2 else (K, N))
+    w = wl.DotWorkload(name="mid", cfg=7, dtype="bf16", out_dtype="f32", lhs_shape=lhs_shape, rhs_shape=rhs_shape, lhs_batch=(), rhs_batch=(),
+                       lhs_contract=(0,) if layout & 1 else (1,), rhs_contract=(1,) if layout & 2 else (0,), mesh_shape=(P,), device_ids=(0, 1),
+                       lhs_map=(0, -1) if layout & 1 else (-1, 0), rhs_map=(-1, 0) if layout & 2 else (0, -1), out_map=(-1, -1))
+    lhs, rhs = wl.draw_small_int_bf16(5, lhs_shape), wl.draw_small_int_bf16(6, rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=row_align)
+    with pinned(MID, 0, 1):
+        st.run_grouped()
+        if row_align == 8 or not layout & 1:          # (a K-major lhs takes 16-byte aligned rows only)
+            assert last() == (MID, 0, 1)
+    a, b = wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs)
+    assert np.array_equal(st.out_shard(0), od.dot_general(a, b, (), (), w.lhs_contract, w.rhs_contract))
