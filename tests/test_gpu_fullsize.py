@@ -97,7 +97,7 @@ def test_config4_moe_full_size():
 @pytest.mark.parametrize("make,row_align", [(wl.mesh2d, 8), (wl.mesh2d_uneven, 8), (wl.mesh2d, 0)],
                          ids=["config5", "config5_uneven", "config5_dense_rows"])
 def test_config5_nested_mesh_full_size(make, row_align):
-    # row_align 0: the 1250-column shards stored densely, rows 4-byte aligned only -> the register-staged MFMA kernel
+    # row_align 0: the 1250-column shards stored densely, rows 4-byte aligned only -> direct loads at multiples of 4 bytes (reported in the staged class)
     import paper_2105_04663_amd as g
     w = make()
     lhs, rhs = w.draw_lhs(), w.draw_rhs()

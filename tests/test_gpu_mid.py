@@ -125,3 +125,30 @@ def test_what_is_left_of_members(M, N, row_align, per, layout):
             assert last() == (MID, 0, 1)
     a, b = wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs)
     assert np.array_equal(st.out_shard(0), od.dot_general(a, b, (), (), w.lhs_contract, w.rhs_contract))
+
+
+@pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("scatter", [False, True])
+@pytest.mark.parametrize("N", [264, 301])
+def test_sum_into_shards_of_different_strides(N, scatter, out_dtype):
+    # a sum in two launches into every member's own out buffer, each with rows of its own
+    M, K, P = 70, 96, 3
+    w = wl.ksplit(M=M, K=K, N=N, P=P)
+    w.out_map = (-1, 0) if scatter else (-1, -1)
+    lhs, rhs = wl.draw_small_int_bf16(5, w.lhs_shape), wl.draw_small_int_bf16(6, w.rhs_shape)
+    st = Staged(w, lhs, rhs, row_align=8, out_dtype=out_dtype, share_replicas=False)
+    cols = st.out[0][3][-1]
+    for pid, ld in enumerate(((cols + 7) // 8 * 8, cols, cols + 5)):
+        t = torch.full((M * ld,), float("nan"), dtype=st.out[pid][1].dtype, device="cuda")
+        st.out[pid] = (g.ShardBuf.of(t, ld), t, ld, st.out[pid][3])
+    with pinned(one_launch=0):
+        st.run_grouped(epilogue=1)
+        assert last()[2] == 0
+    ref = np.maximum(od.dot_general(wl.bf16_bits_to_f64(lhs), wl.bf16_bits_to_f64(rhs), w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract), 0)
+    for pid in range(P):
+        want = od.expected_out_shard(ref, w.mesh_shape, w.device_ids, w.out_map, pid)
+        if out_dtype == "bf16":
+            want = torch.from_numpy(want).to(torch.bfloat16).double().numpy()
+        assert np.array_equal(st.out_shard(pid), want), f"partition {pid}"
+        _, t, ld, _ = st.out[pid]
+        assert bool(torch.isnan(t.view(M, ld)[:, cols:]).all()), f"partition {pid}: beyond its rows"
