@@ -108,11 +108,12 @@ typedef struct {
 /* One partition's shard: device pointer to a row-major array of the static shard shape.
  * row_stride: distance in elements between consecutive indices of the second-to-last
  * dimension; 0 means dense (= static size of the last dimension).  Outer dimensions are
- * dense on top of it.  A row_stride that is a multiple of 8 elements together with a
- * 16-byte aligned pointer selects the fastest MFMA kernels for bf16; rows of any other width take kernels that load at
- * element alignment (about two thirds of the rate on large products); an operand whose contiguous dimension
- * is contracted runs fastest when its rows start on 128-byte lines (row_stride a multiple of 64
- * elements: 9 % faster than a multiple of 8 that is not, at 8200 against 8256).  data may be NULL only for a
+ * dense on top of it.  bf16 operands are fastest with a row_stride that is a multiple of 8 elements and a 16-byte
+ * aligned pointer; an even row_stride and a pointer at a multiple of 4 bytes is nearly as fast where the rows are long
+ * enough and, for a lhs, its contracted dimension is the contiguous one; everything else goes through registers at element
+ * alignment (5998 x 3072 x 9999 on a 4 x 8 mesh: rhs rows of 1256 elements 280 us, 1250 283, and 1249 at 9992 columns 422).
+ * An operand whose contiguous dimension is contracted runs fastest when its rows start on 128-byte lines (row_stride a
+ * multiple of 64 elements: 9 % faster than a multiple of 8 that is not, at 8200 against 8256).  data may be NULL only for a
  * tensor with a zero-size dimension (no elements: nothing is read or written). */
 typedef struct {
   void* data;          /* device */
@@ -177,8 +178,8 @@ typedef struct {
  * the whole launch).  Within each class the library chooses kernel and tile by size. */
 typedef enum {
   GSPMD_KERNEL_SCALAR = 0,       /* leading dimensions too long for 32-bit offsets inside a tile: 64 x 64 tiles, fp32 FMA */
-  GSPMD_KERNEL_MFMA_STAGED = 1,  /* MFMA, operands loaded at element alignment: any other lda and ldb (even ones go straight to LDS
-                                  * too, word by word, where their tiles allow; odd ones through registers) */
+  GSPMD_KERNEL_MFMA_STAGED = 1,  /* MFMA at any other lda and ldb: through registers at element alignment, or, where all are even
+                                  * and the tiles allow, straight to LDS like the next class */
   GSPMD_KERNEL_MFMA = 2          /* MFMA, 16-byte aligned operand loads: lda and ldb multiples of 8 elements */
 } gspmd_kernel_path;
 
@@ -186,7 +187,8 @@ typedef enum {
  * How gspmd_local_dot lowers partition `partition_id`'s Dot (shard bounds -> flattened batch / free / contracting
  * extents -> one GEMM per batch entry and per index of a free dimension that padding keeps from flattening), without
  * touching the GPU.  *_row_stride as in gspmd_shard_buf: 0 = dense.  Writes min(count, capacity) descriptors to
- * `descs` (may be NULL when capacity is 0) and the total to `count`.  Pure host work; for inspection and tests. */
+ * `descs` (may be NULL when capacity is 0) and the total to `count`.  A descriptor's `kernel` names the class that the leading
+ * dimensions allow, not the kernel that runs: GSPMD_KERNEL_MFMA_STAGED covers launches that load straight to LDS.  Pure host work; for inspection and tests. */
 int32_t gspmd_plan_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
                        const gspmd_sharding* lhs_sh, const gspmd_sharding* rhs_sh, const gspmd_sharding* out_sh,
                        int64_t lhs_row_stride, int64_t rhs_row_stride, int64_t out_row_stride,

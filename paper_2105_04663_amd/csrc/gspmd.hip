@@ -250,9 +250,10 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 // Sums over a contracting mesh dimension are formed in one launch (joined problems) or in two: the members' products by themselves, in dense
 // fp32 partials, then a sum kernel per out buffer.  Two, where that is estimated 15 % faster, or 5 % where one launch would take more than a round
 // of dot_mid_kernel's tiles (kSeveralRounds: what a launch pays once no longer matters, and the lines are closer); the results are the same bits.
-// Scattered over all members, slots / one after the other / two launches (us): 4227 x 13543 x 3328 over 4: - / 410 / 363   4227 x 8192 x 3328
-//   over 4: - / 233 / 249   3000 x 13543 x 3328 over 4: - / 351 / 269   8192 x 8000 x 2048 over 4: 333 / 297 / 290   6000 x 12000 x 4096 over 2: 455 /
-//   649 / 487   4227 x 5000 x 3328 over 4: - / 175 / 211   4096 x 16384 x 4096 over 4: 468 / 507 / 432
+// Scattered over all members, slots / one after the other / two launches (us, all on one card): 4227 x 13543 x 3328 over 4: - / 416 / 371   4227 x
+//   8192 x 3328 over 4: - / 238 / 250   3000 x 13543 x 3328 over 4: - / 348 / 272   8192 x 8000 x 2048 over 4: 328 / 299 / 290   6000 x 12000 x 4096
+//   over 2: 461 / 660 / 490   4227 x 5000 x 3328 over 4: - / 180 / 211   4096 x 16384 x 4096 over 4: 461 / 513 / 448.  The rule takes the least in
+//   all but the last, where it stays with the slots: its estimates are 4 % apart.
 constexpr int64_t kSeveralRounds = 512;
 double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);

@@ -12,8 +12,8 @@
 // with the transpose read.  A wave issues one fragment read or load after each MFMA (all of a tile's ahead of its MFMAs: 240 ns), and
 // the stages come round every five steps, so that their places are constants of the code.  One barrier per step.  With one workgroup
 // on a compute unit ten stages (160 KiB), loads six tiles ahead; with two five stages each, four ahead.
-// Measured (us, before / now): 2048 x 8192 x 2048 73.5 / 60.5, 512 x 8192 x 512 67.7 / 47.3, 2048 x 4096 x 4096 73 / 60, 2112 x 8000 x 2112
-// 118 / 90, both K-contiguous 127 / 92; operands from HBM instead of the memory-side cache 2048 x 8192 x 2048 over 4 members 64 / 82.
+// Measured (us, with 32-wide steps / now): 2048 x 8192 x 2048 73.5 / 60.5, 512 x 8192 x 512 67.7 / 47.3, 2048 x 4096 x 4096 73 / 60, 2112 x 8000 x
+// 2112 118 / 90, both K-contiguous 127 / 92.  2048 x 8192 x 2048 over 4 members: 64 with operands in the memory-side cache, 82 from HBM.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

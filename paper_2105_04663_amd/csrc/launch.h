@@ -23,7 +23,7 @@ struct MfmaLaunch {
   bool spread = false;                   // dot_split_kernel: tiles in spread_tile's order
 };
 
-// `staged`: an operand's rows are not 16-byte aligned, both are loaded at element alignment
+// `staged`: an operand does not take direct loads, both are loaded at element alignment through registers
 template <int LAYOUT>
 bool launch_dot_mfma_layout(const MfmaLaunch& l, int32_t out_dtype, bool staged, hipStream_t stream);
 
