@@ -207,8 +207,8 @@ double mid_us(const LaunchSize& s, bool staged = false) {
 // dot_split_kernel's order of summation is another one: partial sums along a contracting mesh dimension (`ordered`) stay with the
 // first two, so that the joined sum, the two-launch sum and partials that a caller sums agree bit for bit; and beyond 256 rows it is taken
 // from K = 1024 on (below, dot_mid_kernel is within 4 us).
-// Operands that are not 16-byte aligned take the first or the third, and cost the address unit more: 10.5 us and 2.1 us a step in
-// the staged tiles; rounds of 3.2, 4.3, 6.5 us and 1.2, 1.25, 1.55 us per eight steps in the split kernel (staged / 1, 2, 4 row blocks):
+// Operands that take no direct loads (kPathMfmaStaged) cost the address unit more: 10.5 us and 2.1 us a step in
+// dot_mfma_kernel's staged tiles; in dot_mid_kernel's 0.11 us and 0.16 per odd operand a 32-wide step; rounds of 3.2, 4.3, 6.5 us and 1.2, 1.25, 1.55 us per eight steps in the split kernel (staged / 1, 2, 4 row blocks):
 //   601 x 2001 x 601: 78 / 25, 15, 20     2001 x 1003 x 2001: 45 / 136, 82, 59     301 x 1001 x 301: 45 / 9, 10, 14
 //   3826 x 102 x 538: 14 / 35, 25, 21     482 x 111 x 5292: 14 / 50, 34, 25        2289 x 293 x 885: 21 / 35, 23, 17
 //   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46     5990 x 3107 x 555: 117 / -, -, 107
