@@ -277,16 +277,15 @@ MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t 
   return choose_mfma(ps, path, layout, ordered);
 }
 
-// Whether four workgroups of dot_f32_kernel share a compute unit, not three: where its equal tiles come out even that way, and not in threes (us,
-// three / four): four each, 2048 x 2048 x 2048 176 / 144, 2040 x 500 x 2040 52.8 / 44.4, 1300 x 700 x 3000 on 1 x 4 70 / 58; 3.75 each, 2048 x 2000 x
-// 1920 176 / 145; beyond that the matrix cores are nearly full either way: eight each, 2048 x 1024 x 4096 150 / 147, 2040 x 2000 x 4090
-// 289 / 290; sixteen, 4096 x 4096 x 4096 1123 / 1097, 4090 x 2000 x 4090 568 / 576.  Elsewhere three, whose loop is 1 to 2 % shorter: five each, 2040 x
-// 2000 x 2550 194 / 216; six, 1530 x 2000 x 4090 219 / 242, 2048 x 2048 x 3000 on 2 x 4 227 / 247; nine, 3060 x 2000 x 3060 318 / 322; 2500 x 900 x
-// 2500, 6.25 each, 119 / 121.  The registers of four with LDS for three: 3 % shorter to 5 % longer over 71 shapes of six
-// tiles each and more, by no size that tells which.
-bool f32_four(int64_t tiles) {
+// Whether four workgroups of dot_f32_kernel share a compute unit with two LDS stages each, not three with three: where its equal tiles come out
+// even that way.  With four tiles each, three workgroups leave the fourth to itself (us, three / four): 2048 x 2048 x 2048 147 / 119, 2048 x 1500 x 2000
+// 112 / 91, 2048 x 100 x 2000 16.5 / 15.0.  With more of them, where K is short and a round's start and end count: K = 300, seven each 47.8 /
+// 43.0, eight 49.6 / 47.4, ten 63.8 / 60.5, thirteen 80.4 / 77.2, sixteen 97.1 / 90.7.  Elsewhere three: five each, K = 600 51.8 / 59.9; six 61.3 / 68.1,
+// 2048 x 2048 x 3000 on 2 x 4 180 / 202; nine 90.6 / 96.4; eight, K = 1024 123 / 134, K = 1500 180 / 183.  Up to three each they are alike.
+constexpr int64_t kF32ShortK = 512;
+bool f32_four(int64_t tiles, int64_t k) {
   const int64_t each = (tiles + 255) / 256;
-  return each % 4 == 0 && each % 3 != 0;
+  return each == 4 || (each > 4 && k <= kF32ShortK && (each % 4 == 0 || each % 3 == 1));
 }
 
 // While a timeline is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
@@ -426,7 +425,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
             default: hipLaunchKernelGGL((dot_f32_kernel<3, kLean>), grid, block, 0, stream, inl, tab, n, epilogue);
           }
         };
-        if (f32_four(tiles)) go(std::true_type{});
+        if (f32_four(tiles, launch_size(ps, layout).k)) go(std::true_type{});
         else go(std::false_type{});
       } else if (out_dtype == GSPMD_F32)
         hipLaunchKernelGGL((dot_fallback_kernel<bf16_bits, float>), grid, block, 0, stream, inl, tab, n, layout, epilogue);

@@ -3,38 +3,51 @@
 //
 // Matrix-core bound: 256 flop per clock and compute unit, a sixteenth of the bf16 rate, so one 64 x 64 tile per workgroup
 // feeds the cores from L2 at 16 bytes per clock, and small tiles are what keeps all compute units equally busy (2048 x
-// 2048 x 3000 on 8 partitions: 1536 tiles, six per compute unit).  Four waves of 32 x 32; K in steps of 32 through two
-// LDS buffers, loads two steps ahead, one barrier per step, three workgroups on a compute unit, or four where that shares its tiles out
-// better (f32_four).  128-row tiles, three on a compute unit, need more registers than there are: 275 us below.  A lane's four k of a K-contiguous fragment are one 16-byte LDS read; the four MFMAs
-// that use them take k = 4 g + i of every 16 (g = lane / 16), for both operands alike, which only reorders the sum.
-// Measured, 2048 x 2048 x 3000 on a 2 x 4 mesh: 522 us with scalar FMA, 315 with loads one step ahead and conditions inside
-// the loop (every wait then a full one), 229 now: 110 TFLOP/s; MFMA busy for 81 % of the cycles in which a compute unit has
-// work, which is 86 % of the launch.
+// 2048 x 3000 on 8 partitions: 1536 tiles, six per compute unit).  Four waves of 32 x 32.
+//
+// What the matrix cores lose they lose to vector instructions between the MFMAs, however many workgroups are resident: an address
+// worked out per load and per LDS read (12 instructions beside 32 MFMAs) costs 13 % (2048 x 2048 x 3000: 201 us, now 180; 4096^3: 1060, 916).
+// So the loop has none: 16-byte loads go straight into LDS from bases in scalar registers and constant offsets of a lane, and the stages come round
+// in unrolled code, so that LDS addresses are constants.  K in steps of 32 through three stages (two where four workgroups share a
+// compute unit), one barrier per step; the reads of the next 16 k's fragments and the loads of the step three further on are issued one at a
+// time between the MFMAs, so that a workgroup that is left alone on a compute unit keeps its matrix cores busy too.
+// A lane's four k of a K-contiguous fragment are one 16-byte LDS read; the four MFMAs that use them take k = 4 g + i of every 16 (g =
+// lane / 16), for both operands alike, which only reorders the sum.
+// Measured (us; operands through registers and ds_write, reads ahead of a step's MFMAs / now): 2048 x 2048 x 3000 on a 2 x 4 mesh 230 / 180 (140
+// TFLOP/s), 4096^3 1097 / 916 (150; 155 is what the cores reach without memory), 2048^3 144 / 118, 1024 x 4096 x 1024 86 / 62, 94 x 1790 x 491 on a 2 x 4 mesh 43 / 31.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kernels_basic.h"
+#include "mfma_common.h"
 #include "plan.h"
 #include "tile_index.h"
 
 namespace gspmd {
 
 constexpr int kF32Tile = 64, kF32BK = 32, kF32Threads = 256;
-constexpr int kF32PitchKC = kF32BK + 4;       // K-contiguous operand in LDS: [64][32 k], rows 16 bytes apart in banks
-constexpr int kF32PitchKM = kF32Tile + 4;     // K-major operand: [32 k][64], rows 4 k apart 16 banks apart
-constexpr int kF32PartFloats = kF32Tile * kF32PitchKC;         // the larger of the two formats (2304; K-major 2176)
+constexpr int kF32MaxStride = 1 << 27;                  // elements: a load instruction's rows stay within 32-bit offsets (of bytes)
+constexpr int kF32Part = kF32Tile * kF32BK * 4;        // 8 KiB: one operand's share of a K step
+template <bool LEAN> constexpr int f32_stages() { return LEAN ? 2 : 3; }
 
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-// LEAN: registers for four workgroups on a compute unit.
+// LEAN: LDS for four workgroups on a compute unit (f32_four).
 template <int LAYOUT, bool LEAN>
-__global__ __launch_bounds__(kF32Threads, LEAN ? 4 : 1) void dot_f32_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
+__global__ __launch_bounds__(kF32Threads, LEAN ? 4 : 3) void dot_f32_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
-  __shared__ __attribute__((aligned(16))) float lds[2][2][kF32PartFloats];      // [buffer][operand]
+  constexpr int R = f32_stages<LEAN>();
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[R * 2 * kF32Part];        // [stage][operand]
   typedef GSPMD_GLOBAL const float* gfloats;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
+  typedef __attribute__((address_space(3))) const float lds_float;
+  const int t = threadIdx.x, lane = t & 63, group = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   const int tile = logical_tile(blockIdx.x, gridDim.x);
   const Problem P = lookup_problem(tab, n_prob, tile);
   const int local = tile - P.tile_begin;
@@ -49,145 +62,159 @@ __global__ __launch_bounds__(kF32Threads, LEAN ? 4 : 1) void dot_f32_kernel(cons
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // this thread's two 16-byte chunks of an operand's [64][32 k] or [32 k][64] part of a K step: index along m or n, along k
-  auto place = [&](bool kmajor, int j, int& x, int& k) {
-    const int c = j * kF32Threads + t;
-    if (kmajor) { k = c >> 4; x = (c & 15) * 4; } else { x = c >> 3; k = (c & 7) * 4; }
-  };
-  auto put = [&](bool kmajor, float* part, const f32x4 (&r)[2]) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      int x, k;
-      place(kmajor, j, x, k);
-      *reinterpret_cast<f32x4*>(part + (kmajor ? k * kF32PitchKM + x : x * kF32PitchKC + k)) = r[j];
-    }
-  };
-  // four k of the 16-wide fragment that starts at row / column x and k = kb
-  auto frag = [&](bool kmajor, const float* part, int x, int kb) -> f32x4 {
-    const int xr = x + (lane & 15), kr = kb + (lane >> 4) * 4;
-    if (!kmajor) return *reinterpret_cast<const f32x4*>(part + xr * kF32PitchKC + kr);
-    f32x4 v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = part[(kr + i) * kF32PitchKM + xr];
-    return v;
-  };
-
   const gfloats A = (gfloats)P.A, B = (gfloats)P.B;
-  // Where a chunk's index along m / n lies beyond the valid extent the last valid row (K-contiguous) or the last four
-  // columns (K-major) are loaded in its place: those results are not stored.  A K-major chunk that straddles the end is
-  // fetched from the last four columns as well and moved down by `shift` elements.
-  gfloats a_at[2], b_at[2];
-  int a_shift[2], b_shift[2];
-  auto start = [&](bool kmajor, gfloats base, int64_t ld, int x0, int valid, gfloats (&at)[2], int (&shift)[2]) {
+  // Where the j-th of its wave's two loads of an operand's part begins at K step 0: a base in scalar registers, which moves on from step to step, and
+  // this lane's offset.  An index along m or n beyond the valid extent becomes the last valid row (K-contiguous) or the last four columns
+  // (K-major): those results are not stored.  A K-major chunk that straddles the end is the last four columns as well; its columns' readers
+  // find them there (f32_km_column).
+  auto load_base = [&](bool kmajor, gfloats base, int64_t ld, int x0, int valid, int j) {
+    const int q = wave * 2 + j;
+    return reinterpret_cast<uint64_t>(base + (kmajor ? q * 4 : min(x0 + q * 8, valid - 1)) * ld);
+  };
+  auto load_offset = [&](bool kmajor, int64_t ld, int x0, int valid, int j) -> uint32_t {
+    const int q = wave * 2 + j, row = x0 + q * 8;
+    if (kmajor) return static_cast<uint32_t>((lane >> 4) * ld + f32_km_first(x0 + f32_km_chunk(q, lane) * 4, valid)) * 4;
+    return static_cast<uint32_t>((min(row + (lane >> 3), valid - 1) - min(row, valid - 1)) * ld + f32_kc_chunk(q, lane) * 4) * 4;
+  };
+  uint64_t a_at[2], b_at[2];
+  uint32_t a_off[2], b_off[2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      int x, k;
-      place(kmajor, j, x, k);
-      x += x0;
-      const int xs = max(0, min(x, kmajor ? valid - 4 : valid - 1));
-      shift[j] = kmajor && x < valid ? x - xs : 0;
-      at[j] = base + (kmajor ? k * ld + xs : xs * ld + k);
+  for (int j = 0; j < 2; ++j) {
+    a_at[j] = load_base(AKM, A, P.lda, m0, P.Mv, j);
+    b_at[j] = load_base(!BKC, B, P.ldb, n0, P.Nv, j);
+    a_off[j] = load_offset(AKM, P.lda, m0, P.Mv, j);
+    b_off[j] = load_offset(!BKC, P.ldb, n0, P.Nv, j);
+  }
+  // no whole chunk along m or n, or rows beyond 32-bit offsets
+  const bool slow = (AKM && P.Mv < 4) || (!BKC && P.Nv < 4) || max(P.lda, P.ldb) >= kF32MaxStride;
+  const int64_t a_step = (AKM ? static_cast<int64_t>(P.lda) * kF32BK : kF32BK) * 4, b_step = (BKC ? kF32BK : static_cast<int64_t>(P.ldb) * kF32BK) * 4;
+  // the i-th of this wave's four loads of the next K step
+  auto load_one = [&](int i, uint32_t stage_at) {
+    const uint32_t to = stage_at + (i >> 1) * kF32Part + (wave * 2 + (i & 1)) * 1024;
+    if (i < 2) {
+      global_to_lds16(reinterpret_cast<const void*>(a_at[i & 1]), a_off[i & 1], to);
+      a_at[i & 1] += a_step;
+    } else {
+      global_to_lds16(reinterpret_cast<const void*>(b_at[i & 1]), b_off[i & 1], to);
+      b_at[i & 1] += b_step;
     }
   };
-  start(AKM, A, P.lda, m0, P.Mv, a_at, a_shift);
-  start(!BKC, B, P.ldb, n0, P.Nv, b_at, b_shift);
-  const bool a_moves = AKM && (P.Mv & 3) && m0 + kF32Tile > P.Mv, b_moves = !BKC && (P.Nv & 3) && n0 + kF32Tile > P.Nv;
-  const bool tiny = (AKM && P.Mv < 4) || (!BKC && P.Nv < 4);          // no whole chunk along m or n
-  const int64_t a_step = AKM ? static_cast<int64_t>(P.lda) * kF32BK : kF32BK, b_step = BKC ? kF32BK : static_cast<int64_t>(P.ldb) * kF32BK;
-  auto load = [&](f32x4 (&ra)[2], f32x4 (&rb)[2]) {                   // the next whole step
+  // Where this lane's fragments are in an operand's part: K-contiguous, four k of a row in one read (halves of the step 64 bytes apart by
+  // XOR); K-major, one column of each of two 16-column blocks.
+  uint32_t a_from[2], b_from[2];
+  auto place = [&](bool shifted) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      ra[j] = *(GSPMD_GLOBAL const f32x4_any*)a_at[j];
-      rb[j] = *(GSPMD_GLOBAL const f32x4_any*)b_at[j];
-      a_at[j] += a_step;
-      b_at[j] += b_step;
+    for (int i = 0; i < 2; ++i) {
+      const int x = wm + 16 * i + (lane & 15), y = wn + 16 * i + (lane & 15);
+      a_from[i] = lds0 + (AKM ? f32_km_place(shifted ? f32_km_column(x, P.Mv - m0) : x, group) : f32_kc_place(wm + (lane & 15), group) ^ (i * 64));
+      b_from[i] = lds0 + kF32Part + (!BKC ? f32_km_place(shifted ? f32_km_column(y, P.Nv - n0) : y, group) : f32_kc_place(wn + (lane & 15), group) ^ (i * 64));
     }
   };
-  auto move_down = [](f32x4& v, int s) {
-    if (s & 2) v = f32x4{v[2], v[3], 0.f, 0.f};
-    if (s & 1) v = f32x4{v[1], v[2], v[3], 0.f};
+  place(true);
+  f32x4 fa[2][2], fb[2][2];                     // fragments of two 16-wide halves: one being multiplied, the next being read
+  // fragment i (lhs 0, 1, rhs 0, 1) of half h of the step whose stage is at `stage_at` (from the first one)
+  auto read_one = [&](int h, int i, uint32_t stage_at) {
+    auto four = [&](bool kmajor, const uint32_t (&from)[2], int b) -> f32x4 {
+      if (!kmajor) return *(lds_f32x4*)(uintptr_t)(stage_at + from[h] + b * 16 * 128);
+      f32x4 v;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = *(lds_float*)(uintptr_t)(stage_at + from[b] + (h * 16 + q) * 256);
+      return v;
+    };
+    if (i < 2) fa[h][i] = four(AKM, a_from, i);
+    else fb[h][i & 1] = four(!BKC, b_from, i & 1);
   };
-  // a step that ends beyond the valid K (or an extent below a chunk): element by element, zeros beyond in BOTH operands
-  auto load_slow = [&](bool kmajor, gfloats base, int64_t ld, int x0, int valid, int k0, f32x4 (&r)[2]) {
+  // Half a step: sixteen MFMAs, and between them the reads of the next half's fragments and the loads of a step further on.
+  auto half_step = [&](auto half, bool reads, uint32_t read_at, bool loads, uint32_t load_at) {
+    constexpr int h = decltype(half)::value;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      int x, k;
-      place(kmajor, j, x, k);
-      x += x0; k += k0;
-      r[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int xe = kmajor ? x + e : x, ke = kmajor ? k : k + e;
-        if (xe < valid && ke < P.Kv) r[j][e] = base[kmajor ? ke * ld + xe : xe * ld + ke];
-      }
+    for (int q = 0; q < 16; ++q) {
+      const int i = (q >> 1) & 1, j = q & 1;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[h][j][q >> 2], fa[h][i][q >> 2], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (reads && (q & 1) == 0 && q < 8) read_one(h ^ 1, q >> 1, read_at);
+      if (loads && q % 3 == 2 && q < 12) load_one(q / 3, load_at);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto publish = [&](int s, const f32x4 (&ra)[2], const f32x4 (&rb)[2]) {
-    put(AKM, lds[s][0], ra);
-    put(!BKC, lds[s][1], rb);
-    __syncthreads();       // (a buffer is written again two steps later, after the barrier of the step between)
+  const std::integral_constant<int, 0> first{};
+  const std::integral_constant<int, 1> second{};
+  auto barrier = [&]() {                        // (the compiler moves no LDS access across it)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
   };
-  auto multiply = [&](int s) {
-    f32x4 fa[2][2], fb[2][2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) fa[h][i] = frag(AKM, lds[s][0], wm + 16 * i, 16 * h);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) fb[h][j] = frag(!BKC, lds[s][1], wn + 16 * j, 16 * h);
-    }
-    __builtin_amdgcn_sched_barrier(0);          // all of a step's LDS reads are under way before its first MFMA
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[h][j][q], fa[h][i][q], acc[i][j], 0, 0, 0);
-  };
-  auto settle = [&](f32x4 (&ra)[2], f32x4 (&rb)[2]) {
-    if (a_moves)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) move_down(ra[j], a_shift[j]);
-    if (b_moves)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) move_down(rb[j], b_shift[j]);
+  // waits until all but the `after` steps loaded last have landed, and this wave's fragment reads are over
+  auto landed = [&](int after) {
+    if (after >= 2) __builtin_amdgcn_s_waitcnt(waitcnt_imm(8, 0));
+    else if (after == 1) __builtin_amdgcn_s_waitcnt(waitcnt_imm(4, 0));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 0));
+    barrier();
   };
 
-  const int steps = (P.Kv + kF32BK - 1) / kF32BK, whole = tiny ? 0 : P.Kv / kF32BK;
-  f32x4 ra[2][2], rb[2][2];                     // loads run two steps ahead
-  int s = 0;
-  if (whole >= 4) {                             // pairs of steps, their loads without conditions (the waits then count exactly)
-    load(ra[0], rb[0]);
-    load(ra[1], rb[1]);
-    for (; s + 4 <= whole; s += 2) {
+  const int whole = slow ? 0 : P.Kv / kF32BK;
+  if (whole > 0) {
+    constexpr uint32_t kStage = 2 * kF32Part;
+    for (int s = 0; s < min(whole, R); ++s)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        settle(ra[h], rb[h]);
-        publish(h, ra[h], rb[h]);
-        load(ra[h], rb[h]);
-        multiply(h);
-      }
-    }
+      for (int i = 0; i < 4; ++i) load_one(i, lds0 + s * kStage);
+    landed(min(whole, R) - 1);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      settle(ra[h], rb[h]);
-      publish(h, ra[h], rb[h]);
-      multiply(h);
+    for (int i = 0; i < 4; ++i) read_one(0, i, 0);
+    int s = 0;
+    // a step's stage is free when its second half's fragments are read, before that half is multiplied
+    auto step = [&](uint32_t here, uint32_t next) {
+      half_step(first, true, here, false, 0);
+      landed(R - 2);
+      half_step(second, true, next, true, lds0 + here);
+    };
+    for (; s + 2 * R <= whole; s += R)          // the stages are constants of the code
+#pragma unroll
+      for (int u = 0; u < R; ++u) step(u * kStage, (u + 1) % R * kStage);
+    uint32_t here = 0;                          // the stage of step s
+    auto after = [&](uint32_t at) { return at == (R - 1) * kStage ? 0 : at + kStage; };
+    for (; s + R < whole; ++s) {
+      step(here, after(here));
+      here = after(here);
     }
-    s += 2;
+    for (; s + 1 < whole; ++s) {                // everything is loaded
+      half_step(first, true, here, false, 0);
+      landed(min(whole - s, R) - 2);
+      half_step(second, true, after(here), false, 0);
+      here = after(here);
+    }
+    half_step(first, true, here, false, 0);
+    half_step(second, false, 0, false, 0);
   }
-  for (; s < steps; ++s) {                      // what is left: at most three whole steps and a partial one
-    if (s < whole) {
-      load(ra[0], rb[0]);
-      settle(ra[0], rb[0]);
-    } else {
-      load_slow(AKM, A, P.lda, m0, P.Mv, s * kF32BK, ra[0]);
-      load_slow(!BKC, B, P.ldb, n0, P.Nv, s * kF32BK, rb[0]);
+  if (whole * kF32BK < P.Kv) {                  // what is left of K, or an extent below a chunk: element by element, zeros beyond in BOTH operands
+    place(false);
+    for (int k0 = whole * kF32BK; k0 < P.Kv; k0 += kF32BK) {
+      auto fetch = [&](bool kmajor, gfloats base, int64_t ld, int x0, int valid, int j) -> f32x4 {
+        const int q = wave * 2 + j;
+        const int x = x0 + (kmajor ? f32_km_chunk(q, lane) * 4 : q * 8 + (lane >> 3)), k = k0 + (kmajor ? q * 4 + (lane >> 4) : f32_kc_chunk(q, lane) * 4);
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int xe = kmajor ? x + e : x, ke = kmajor ? k : k + e;
+          if (xe < valid && ke < P.Kv) v[e] = base[kmajor ? ke * ld + xe : xe * ld + ke];
+        }
+        return v;
+      };
+      f32x4 v[4];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        v[j] = fetch(AKM, A, P.lda, m0, P.Mv, j);
+        v[2 + j] = fetch(!BKC, B, P.ldb, n0, P.Nv, j);
+      }
+      __syncthreads();                          // every wave has read the step before
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(lds + (i >> 1) * kF32Part + (wave * 2 + (i & 1)) * 1024 + lane * 16) = v[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) read_one(i >> 2, i & 3, 0);
+      half_step(first, false, 0, false, 0);
+      half_step(second, false, 0, false, 0);
     }
-    publish(s & 1, ra[0], rb[0]);
-    multiply(s & 1);
   }
 
   // a lane holds four consecutive columns of a row per 16 x 16 block; the static block's part of this tile is written

@@ -191,4 +191,20 @@ GSPMD_INDEX_FN void tile_origin(int local, int rows_valid, int tiles_n, int* til
   *n0 = (in_band / rows_in_band) * kMfmaBN;
 }
 
+// ---- dot_f32_kernel's tiles of 64 x 64, 32 k a step: which 16-byte chunk of its row (in a part's own order) lane `lane` of load instruction q (0..7,
+// 1 KiB each) brings, and where a fragment's first k is in the part.
+// K-contiguous part [64 rows][32 k]: 8 rows an instruction, 8 lanes per row; chunks swizzled as in the bf16 kernels' parts of 128-byte rows.
+GSPMD_INDEX_FN int f32_kc_chunk(int q, int lane) { return (lane & 7) ^ swz_h(q * 8 + (lane >> 3)); }
+// four k (4 group .. 4 group + 3) of a row; the second 16 k at ^ 64, 16 rows further at + 2048
+GSPMD_INDEX_FN uint32_t f32_kc_place(int row, int group) { return static_cast<uint32_t>(row * 128 + ((group ^ swz_h(row)) << 4)); }
+// K-major part [32 k][64 columns]: 4 k rows an instruction, 16 lanes per row.  The four groups of 16 lanes read rows 4 apart: their
+// 64-byte blocks are spread over the banks.
+GSPMD_INDEX_FN int f32_km_chunk(int q, int lane) { return (lane & 15) ^ ((q & 3) << 2); }
+// Which column such a chunk begins at, `want` by its place: past the valid extent (at least 4) the last four columns.
+GSPMD_INDEX_FN int f32_km_first(int want, int cols_valid) { return want < cols_valid - 4 ? want : cols_valid - 4 > 0 ? cols_valid - 4 : 0; }
+// Where in the tile column x of `cols_valid` from the tile's first one on is found: a chunk that straddles the end holds the last four.
+GSPMD_INDEX_FN int f32_km_column(int x, int cols_valid) { return x >= (cols_valid & ~3) && x < cols_valid ? x + 4 - (cols_valid & 3) : x; }
+// row 4 group of a column; row 4 group + i at + i * 256, the second 16 k at + 4096
+GSPMD_INDEX_FN uint32_t f32_km_place(int col, int group) { return static_cast<uint32_t>(group * 4 * 256 + (((col >> 2) ^ (group << 2)) << 4) + (col & 3) * 4); }
+
 }  // namespace gspmd

@@ -73,3 +73,35 @@ def test_f32_workgroups_on_a_compute_unit(M, K, N, layout):
     st.run_local(0)
     dims = (w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
     assert np.array_equal(st.out_shard(0), od.dot_general(lhs.astype(np.float64), rhs.astype(np.float64), *dims))
+
+
+# K steps around the stages' count and the unrolled loop (three and two stages), with a part of a step left or not; columns that end inside a chunk
+@pytest.mark.parametrize("layout", [0, 3])
+@pytest.mark.parametrize("M,N", [(66, 129), (1985, 2047)])          # 6 tiles; 1024: four workgroups on a compute unit
+@pytest.mark.parametrize("K", [96, 128, 130, 160, 192, 224, 255, 288])
+def test_f32_steps(M, N, K, layout):
+    w = workload(M, K, N, layout)
+    w.dtype = "f32"
+    rng = np.random.default_rng(K)
+    lhs, rhs = (rng.integers(-50, 51, size=s).astype(np.float32) for s in (w.lhs_shape, w.rhs_shape))
+    st = Staged(w, lhs, rhs, row_align=0)
+    st.run_local(0)
+    dims = (w.lhs_batch, w.rhs_batch, w.lhs_contract, w.rhs_contract)
+    assert np.array_equal(st.out_shard(0), od.dot_general(lhs.astype(np.float64), rhs.astype(np.float64), *dims))
+
+
+def test_f32_rows_beyond_32_bit_offsets():
+    import paper_2105_04663_amd as g
+    stride, M, K, N = 1 << 27, 3, 70, 9                              # rows of 512 MiB: element by element
+    rng = np.random.default_rng(1)
+    lhs, rhs = rng.integers(-50, 51, size=(M, K)).astype(np.float32), rng.integers(-50, 51, size=(K, N)).astype(np.float32)
+    a = torch.empty((M - 1) * stride + K, dtype=torch.float32, device="cuda")
+    for m in range(M):
+        a[m * stride:m * stride + K] = torch.from_numpy(lhs[m])
+    b, out = torch.from_numpy(rhs).cuda(), torch.empty(M, N, dtype=torch.float32, device="cuda")
+    mesh, dims = g.Mesh((1,), (0,)), g.DotDims((), (), (1,), (0,))
+    lsh, rsh, osh = (g.Sharding(s, (-1, -1)) for s in ((M, K), (K, N), (M, N)))
+    ws = torch.empty(g.dot_workspace_bytes(mesh, dims, lsh, rsh, osh, 0, False) + 256, dtype=torch.uint8, device="cuda")
+    g.local_dot(mesh, dims, g.ShardBuf(a.data_ptr(), g.F32, stride), lsh, g.ShardBuf(b.data_ptr(), g.F32, 0), rsh, g.ShardBuf(out.data_ptr(), g.F32, 0), osh,
+                0, None, (ws.data_ptr() + 255) // 256 * 256, ws.numel() - 256, torch.cuda.current_stream().cuda_stream)
+    assert np.array_equal(out.cpu().numpy(), lhs.astype(np.float64) @ rhs.astype(np.float64))

@@ -206,7 +206,41 @@ static void check_tile_order() {
   }
 }
 
+// ---- dot_f32_kernel: both parts of a step of 32 k, 64 rows or columns from x0 of `valid`; lane l of a fragment read takes row or column l & 15
+// of its block and k = 4 (l >> 4) .. + 3 of each half of 16.
+static void check_f32(int x0, int valid, int ld) {
+  std::map<int, RC> kc, km;                     // byte offset in the part -> (row, k), (k, column)
+  for (int q = 0; q < 8; ++q)
+    for (int lane = 0; lane < 64; ++lane) {
+      const int row = q * 8 + (lane >> 3), last = valid - 1, got = x0 + row < last ? x0 + row : last, chunk = f32_kc_chunk(q, lane);
+      CHECK(chunk >= 0 && chunk < 8, "f32 kc: chunk %d", chunk);
+      for (int e = 0; e < 4; ++e) kc[q * 1024 + lane * 16 + 4 * e] = RC(got - x0, chunk * 4 + e);
+      if (valid < 4) continue;
+      const int at = f32_km_chunk(q, lane), first = f32_km_first(x0 + at * 4, valid);
+      CHECK(at >= 0 && at < 16 && first >= 0 && first + 4 <= valid && first + 4 <= ld, "f32 km: columns %d .. %d of %d", first, first + 3, valid);
+      for (int e = 0; e < 4; ++e) km[q * 1024 + lane * 16 + 4 * e] = RC(q * 4 + (lane >> 4), first + e - x0);
+    }
+  CHECK(kc.size() == 64 * 32 && (valid < 4 || km.size() == 64 * 32), "f32: %zu, %zu elements", kc.size(), km.size());
+  for (int block = 0; block < 4; ++block)
+    for (int half = 0; half < 2; ++half)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int x = block * 16 + (lane & 15), group = lane >> 4;
+        const uint32_t row_at = (f32_kc_place((block & 2) * 16 + (lane & 15), group) ^ (half * 64)) + (block & 1) * 2048;
+        for (int e = 0; e < 4; ++e) {
+          const int k = half * 16 + group * 4 + e;
+          const RC a = kc.at(static_cast<int>(row_at) + 4 * e);
+          CHECK(a.second == k && (x0 + x >= valid || a.first == x), "f32 kc read: (%d, %d) instead of (%d, %d)", a.first, a.second, x, k);
+          if (valid < 4) continue;
+          const RC b = km.at(static_cast<int>(f32_km_place(f32_km_column(x, valid - x0), group)) + (half * 16 + e) * 256);
+          CHECK(b.first == k && (x0 + x >= valid || b.second == x), "f32 km read: (%d, %d) instead of (%d, %d)", b.first, b.second, k, x);
+        }
+      }
+}
+
 int main() {
+  for (int valid = 1; valid <= 200; ++valid)
+    for (int x0 = 0; x0 < valid; x0 += 64) check_f32(x0, valid, valid);
+
   for (int ld : {64, 72, 8192, 1 << 21})
     for (int r0 : {0, 256, 1024})
       for (int rows_valid : {r0 + 1, r0 + 2, r0 + 17, r0 + 127, r0 + 128, r0 + 129, r0 + 200, r0 + 255, r0 + 256, r0 + 10000}) {
