@@ -12,7 +12,7 @@ OBJ = os.path.join(HERE, "build")
 LIB = os.path.join(HERE, "libgspmd.so")
 # (source, object, extra flags); the MFMA kernels' sources are compiled once per operand layout
 UNITS = [(os.path.join(CSRC, f"{name}.hip"), f"{name}_l{n}.o", [f"-DGSPMD_TU_LAYOUT={n}"])
-         for name in ("dot_mfma", "dot_split", "dot_mid") for n in range(4)] + [
+         for name in ("dot_mfma", "dot_split", "dot_mid", "dot_pair") for n in range(4)] + [
     (os.path.join(CSRC, "gspmd.hip"), "gspmd.o", []),
     (os.path.join(CSRC, "plan.cpp"), "plan.o", []),
 ]

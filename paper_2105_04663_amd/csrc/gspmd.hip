@@ -127,11 +127,12 @@ int64_t tiles_of(const Problem& p, int bm, int bn) {
 }
 
 // Which kernel a bf16 launch takes, and dot_split_kernel's row blocks (of 16) per tile.
-enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_TESTING_MFMA, kMfmaMid = GSPMD_TESTING_MID, kMfmaSplit = GSPMD_TESTING_SPLIT };
+enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_TESTING_MFMA, kMfmaMid = GSPMD_TESTING_MID, kMfmaSplit = GSPMD_TESTING_SPLIT, kMfmaPair = GSPMD_TESTING_PAIR };
 struct MfmaChoice {
   MfmaKernel kernel;
   int row_blocks;
   bool staged = false;      // dot_mfma_kernel, dot_mid_kernel: operands through registers
+  bool loose = false;       // dot_pair_kernel: rows that are not padded to 16 bytes
 };
 
 // What this thread's launches are pinned to, and what its last one took (testing.h).
@@ -154,10 +155,10 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 // Sums, slots / one after the other (K over all members): 2048 x 8192 x 2048 over 4: 78 / 64   1024 x 8192 x 2048 over 2, two groups: 75 / 59
 //   both K-major 2085 x 3540 x 1652 over 2, two groups: 64 / 60   1770 x 3303 x 2085 over 2, two groups: 65 / 67   1572 x 4544 x 3328 over 8: 136 / 88
 struct LaunchSize {
-  int64_t rows = 0, k = 0, big = 0, mid = 0, members = 1;      // longest extents, tiles of 256 x 256 and of 128 x 128, most members of a sum
+  int64_t rows = 0, k = 0, big = 0, mid = 0, pair = 0, members = 1;      // longest extents, tiles of 256 x 256, 128 x 128 and 256 x 128, most members of a sum
   int64_t cols = INT32_MAX, fewest_rows = INT32_MAX;
   bool a_odd = false, b_odd = false;                           // an operand has elements at odd addresses
-  bool broken_lines = false, whole_steps = true;      // a K-contiguous operand's rows are not whole lines; all K are whole 64-wide steps
+  bool broken_lines = false, whole_steps = true, whole_chunks = true;      // a K-contiguous operand's rows are not whole lines; all K are whole 64-wide steps
 };
 LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
   LaunchSize s;
@@ -169,11 +170,13 @@ LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
     s.a_odd = s.a_odd || (p.lda & 1) || (reinterpret_cast<uintptr_t>(p.A) & 2);
     s.b_odd = s.b_odd || (p.ldb & 1) || (reinterpret_cast<uintptr_t>(p.B) & 2);
     s.big += tiles_of(p, kMfmaBM, kMfmaBN);
+    s.pair += tiles_of(p, kPairRows, kPairCols);
     if (p.join_slot == 0) {
       s.mid += tiles_of(p, kMidTile, kMidTile);
       s.members = std::max<int64_t>(s.members, p.join_count);
     }
     s.whole_steps = s.whole_steps && p.Kv % (2 * kMfmaBK) == 0;
+    s.whole_chunks = s.whole_chunks && p.Kv % 8 == 0;
     s.broken_lines = s.broken_lines || (!(layout & GSPMD_LAYOUT_LHS_K_MAJOR) && (p.lda & 63)) || ((layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && (p.ldb & 63));
   }
   return s;
@@ -197,7 +200,28 @@ double mid_us(const LaunchSize& s, bool staged = false) {
   return static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
 }
 
-// The three kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
+// dot_pair_kernel: 6.5 us, and rounds of 512 workgroups of 5.2 us and 0.70 us per 32-wide step, two of them on a compute unit, more where an operand is
+//   K-contiguous (its half lines come twice from L2; the lhs is the larger part); in a last round about half of that per step
+//   where every compute unit has one, 2.3 us and three quarters of it where only half of them have; 0.1 and 0.2 us more where rows are not padded to 16 bytes (six of 356 x
+//   2088 x 2142: 34.9 / 40.0 / 38.9).  Measured (us, dot_mfma_kernel / dot_mid_kernel / dot_pair_kernel;
+//   both K-major, then lhs K-contiguous): M x N = 2048 x 4096, K = 512 14.4 / 15.6 / 12.4, 14.5 / 15.4 / 12.9; 1024 21.3 / 22.8 / 19.0, 21.7 / 22.3 / 19.7; 2048 35.5 / 36.9 /
+//   30.6, 35.7 / 34.9 / 33.1   4096 x 4096, K = 200 13.8 / 19.7 / 12.3, 14.8 / 20.8 / 14.4; 512 20.4 / 28.5 / 20.6, 20.4 / 28.8 / 21.5; 2048 51 / 69 / 55, 50 / 68 / 64
+//   4096 x 8192, four of them, K = 64 70 / 100 / 53, 67 / 98 / 52; 200 102 / 150 / 83, 105 / 149 / 90; 512 142 / 238 / 133, 140 / 225 / 145; 1024 223 / 346 / 225, 221 / 336 / 256
+double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
+  const double steps = static_cast<double>((s.k + 31) / 32);
+  const bool a_lines = layout & GSPMD_LAYOUT_LHS_K_MAJOR, b_lines = !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
+  const double rows = loose ? 0.1 : 0.0;
+  const double two = 0.70 + (a_lines ? 0.0 : 0.13) + (b_lines ? 0.0 : a_lines ? 0.035 : 0.08) + 2.0 * rows, one = (a_lines ? 0.38 : b_lines ? 0.42 : 0.45) + rows;
+  const int64_t part = s.pair % 512;
+  const double fill = static_cast<double>(part) / 512.0, round = 5.2 + steps * two;
+  double last = 0.0;
+  if (part > 256) last = 5.2 + steps * two * (0.6 + 0.4 * fill);
+  else if (part > 128) last = steps * one;
+  else if (part > 0) last = 2.3 + steps * one * 0.75;
+  return 6.5 + static_cast<double>(s.pair / 512) * round + std::max(last, fill * round);
+}
+
+// The kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
 // a workgroup draws from L2 per flop, so the choice compares estimates: the lines above, and for dot_split_kernel rounds of 256 workgroups of
 // 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  One problem, bf16, rows x K x N, us, dot_mfma_kernel / dot_split_kernel with 1, 2, 4 row
 // blocks:
@@ -224,6 +248,11 @@ bool big_staged(const LaunchSize& size, KernelPath path, int32_t layout) {
 bool mid_stages_whole(const LaunchSize& size, int32_t layout) {
   return ((layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) || size.cols >= kMidTile) && (!(layout & GSPMD_LAYOUT_LHS_K_MAJOR) || size.fewest_rows >= kMidTile);
 }
+// dot_pair_kernel's direct loads take what is left of K in chunks of eight, which reach into the padding of a K-contiguous operand's rows
+bool pair_takes(const LaunchSize& size, KernelPath path, int32_t layout) {
+  const bool kmajor = (layout & GSPMD_LAYOUT_LHS_K_MAJOR) && !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);
+  return size.members == 1 && (path == kPathMfmaDirect || (path == kPathMfmaWords && (size.whole_chunks || kmajor)));
+}
 MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t layout, bool ordered) {
   MfmaChoice choice{kMfmaBig, 0};
   const bool loose = path == kPathMfmaStaged;
@@ -233,6 +262,10 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
     const double us = mid_us(size, loose);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, loose}; }
+  }
+  if (pair_takes(size, path, layout)) {
+    const double us = pair_us(size, layout, path == kPathMfmaWords);
+    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaPair, 0, false, path == kPathMfmaWords}; }
   }
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((size.k + 255) / 256);
@@ -257,7 +290,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 constexpr int64_t kSeveralRounds = 512;
 double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
-  return choice.kernel == kMfmaMid ? mid_us(size, choice.staged) : big_us(size, choice.staged);
+  return choice.kernel == kMfmaMid ? mid_us(size, choice.staged) : choice.kernel == kMfmaPair ? pair_us(size, layout, choice.loose) : big_us(size, choice.staged);
 }
 // What partials cost beside their launch: 1 us, 2.5 us per sum kernel (one per reduce group) and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
@@ -272,7 +305,7 @@ MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t 
   const MfmaKernel pin = static_cast<MfmaKernel>(t_pin.kernel);
   const LaunchSize size = launch_size(ps, layout);
   if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && (path != kPathMfmaStaged || (size.members == 1 && mid_stages_whole(size, layout)))) ||
-      (pin == kMfmaSplit && !ordered))
+      (pin == kMfmaSplit && !ordered) || (pin == kMfmaPair && pair_takes(size, path, layout)))
     return MfmaChoice{pin, t_pin.row_blocks, pin == kMfmaBig ? big_staged(size, path, layout) : pin == kMfmaMid && path == kPathMfmaStaged};
   return choose_mfma(ps, path, layout, ordered);
 }
@@ -290,7 +323,7 @@ bool f32_four(int64_t tiles, int64_t k) {
 
 // While a timeline is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
 MfmaKernel with_records(MfmaKernel kernel) {
-  return kernel == kMfmaMid && g_timeline.load(std::memory_order_acquire) != nullptr ? kMfmaBig : kernel;
+  return (kernel == kMfmaMid || kernel == kMfmaPair) && g_timeline.load(std::memory_order_acquire) != nullptr ? kMfmaBig : kernel;
 }
 
 // Problems whose last tile column is moved back: those with loose rhs rows, and with one member of a sum all of them (the members are
@@ -327,9 +360,9 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   choice.staged = choice.kernel == kMfmaBig ? big_staged(launch_size(ps, layout), path, layout) : choice.kernel == kMfmaMid && path == kPathMfmaStaged;
   const bool mfma = choice.kernel != kMfmaNone;
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
-  const bool mid = choice.kernel == kMfmaMid;
-  const int bm = split ? 16 * split : mid ? kMidTile : mfma ? kMfmaBM : kGenTile;
-  const int bn = split ? kSplitBN : mid ? kMidTile : mfma ? kMfmaBN : kGenTile;
+  const bool mid = choice.kernel == kMfmaMid, pair = choice.kernel == kMfmaPair;
+  const int bm = split ? 16 * split : mid ? kMidTile : pair ? kPairRows : mfma ? kMfmaBM : kGenTile;
+  const int bn = split ? kSplitBN : mid ? kMidTile : pair ? kPairCols : mfma ? kMfmaBN : kGenTile;
   // Workgroups start in tile order and the launch ends when the last one does: problems whose tiles take longest
   // (the most K steps) go first, so that the compute units that are still busy at the end are busy with short tiles.
   if (!join)
@@ -404,6 +437,9 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
     } else if (mid) {
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
       if (!launch_dot_mid(l, layout, out_dtype, join != nullptr, choice.staged, stream)) return GSPMD_ERR_DEVICE;
+    } else if (pair) {
+      const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
+      if (!launch_dot_pair(l, layout, out_dtype, stream)) return GSPMD_ERR_DEVICE;
     } else if (mfma) {
       if (join && join->tiles > 0) {
         const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((join->tiles + 255) / 256, 1024));
@@ -1513,7 +1549,7 @@ int32_t gspmd_resharded_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
 int32_t gspmd_testing_pin(const gspmd_testing_launch* pin) {
   if (!pin) return GSPMD_ERR_NULL;
   const bool split = pin->kernel == GSPMD_TESTING_SPLIT;
-  if (pin->kernel < GSPMD_TESTING_BY_RULE || pin->kernel > GSPMD_TESTING_SPLIT || pin->one_launch < GSPMD_TESTING_BY_RULE || pin->one_launch > 1 ||
+  if (pin->kernel < GSPMD_TESTING_BY_RULE || pin->kernel > GSPMD_TESTING_PAIR || pin->one_launch < GSPMD_TESTING_BY_RULE || pin->one_launch > 1 ||
       (split ? pin->row_blocks != 1 && pin->row_blocks != 2 && pin->row_blocks != 4 : pin->row_blocks != 0)) return GSPMD_ERR_UNSUPPORTED;
   if (pin->dry_run != 0 && pin->dry_run != 1) return GSPMD_ERR_UNSUPPORTED;
   t_pin = *pin;

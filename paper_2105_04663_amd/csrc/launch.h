@@ -74,4 +74,20 @@ inline bool launch_dot_mid(const MfmaLaunch& l, int32_t layout, int32_t out_dtyp
 }
 #endif
 
+// One launch of dot_pair_kernel in 256 x 128 tiles (no joined problems, direct loads, what is left of K in whole chunks).
+constexpr int kPairRows = 256, kPairCols = 128;
+template <int LAYOUT>
+bool launch_dot_pair_layout(const MfmaLaunch& l, int32_t out_dtype, hipStream_t stream);
+
+#ifndef GSPMD_TU_LAYOUT
+inline bool launch_dot_pair(const MfmaLaunch& l, int32_t layout, int32_t out_dtype, hipStream_t stream) {
+  switch (layout & 3) {
+    case 0: return launch_dot_pair_layout<0>(l, out_dtype, stream);
+    case 1: return launch_dot_pair_layout<1>(l, out_dtype, stream);
+    case 2: return launch_dot_pair_layout<2>(l, out_dtype, stream);
+    default: return launch_dot_pair_layout<3>(l, out_dtype, stream);
+  }
+}
+#endif
+
 }  // namespace gspmd

@@ -83,13 +83,13 @@ GSPMD_INDEX_FN int kc_half_frag_offset(int base, int lane) {
 // What is left of K after the main loop uses [256 rows][32 k] parts for a K-contiguous operand:
 // per-lane byte offset, relative to the tile's base, of load instruction q (0..15) of a K-contiguous operand tile
 // ([256 rows][32 k]: instruction q covers rows 16q..16q+15, 4 lanes per row).  Rows past the valid extent reuse the
-// last valid row (their results are never stored).
-GSPMD_INDEX_FN int kc_load_offset(int q, int lane, int r0, int rows_valid, int ld) {
+// last valid row (their results are never stored), chunks past `k_valid` the last valid chunk.
+GSPMD_INDEX_FN int kc_load_offset(int q, int lane, int r0, int rows_valid, int ld, int k_valid = kMfmaBK) {
   const int r = q * 16 + (lane >> 2);
-  const int c = (lane & 3) ^ swz_a(r);
+  const int c = (lane & 3) ^ swz_a(r), last_c = (k_valid - 1) >> 3;
   const int last = rows_valid - 1, want = r0 + r;
   const int rr = (want < last ? want : last) - r0;
-  return (rr * ld + c * 8) * 2;
+  return (rr * ld + (c < last_c ? c : last_c) * 8) * 2;
 }
 // Same for a K-major operand tile ([32 k][256 columns]: instruction q covers k rows 2q, 2q+1, 32 lanes per row).
 // 16-byte chunks past the valid extent reuse the last valid chunk.
@@ -119,11 +119,14 @@ GSPMD_INDEX_FN int km_frag_offset(int base, int lane) {
 // the row, so that the 4 rows x 32 bytes that a 16-lane group reads and those of the group beside it (8 rows further)
 // lie in different banks.
 GSPMD_INDEX_FN int mid_swz(int krow) { return ((krow & 3) | (((krow >> 3) & 1) << 2)) << 1; }
-// load instruction q (0..7) of a K-major part: k rows 4 q .. 4 q + 3, 16 lanes per row; chunks past the valid extent reuse
-// the last valid chunk, k rows past `k_valid` the last valid row
+// Parts of 256 columns (COLS = 256, dot_pair_kernel) have rows of 512 bytes and km_load_offset's swizzle.
+// load instruction q (0..7, 0..15 of 256 columns) of a K-major part: k rows 4 q .. 4 q + 3, 16 lanes per row (two rows, 32 lanes); chunks past the valid
+// extent reuse the last valid chunk, k rows past `k_valid` the last valid row
+template <int COLS = 128>
 GSPMD_INDEX_FN int mid_km_load_offset(int q, int lane, int c0, int cols_valid, int ld, int k_valid = kMfmaBK) {
-  const int kr = q * 4 + (lane >> 4);
-  int n = c0 + (((lane & 15) ^ mid_swz(kr)) << 3);
+  constexpr int lanes = COLS / 8;
+  const int kr = q * (64 / lanes) + lane / lanes;
+  int n = c0 + (((lane & (lanes - 1)) ^ (COLS == 256 ? swz_b(kr) : mid_swz(kr))) << 3);
   if (n >= cols_valid) n = ((cols_valid - 1) >> 3) << 3;
   return ((kr < k_valid ? kr : k_valid - 1) * ld + (n - c0)) * 2;
 }
@@ -134,10 +137,11 @@ GSPMD_INDEX_FN int mid_kc_load_offset(int q, int lane, int half, int r0, int row
   const int last = rows_valid - 1 - r0, row = half * 64 + r, c = (lane & 7) ^ swz_h(r), last_c = (k_valid - 1) >> 3;
   return ((row < last ? row : last) * ld + (c < last_c ? c : last_c) * 8) * 2;
 }
-// fragment of the 16-column block at `base` (block b further at ^ (b << 5) for a base that is a multiple of 64)
+// fragment of the 16-column block at `base` (block b further at ^ (b << 5) for a base that is a multiple of 64), its second half 4 rows further
+template <int COLS = 128>
 GSPMD_INDEX_FN int mid_km_frag_offset(int base, int lane) {
   const int i = lane & 15, krow = (lane >> 4) * 8 + (i >> 2), cl = base + (i & 3) * 4;
-  return krow * 256 + (((cl >> 3) ^ mid_swz(krow)) << 4) + (cl & 7) * 2;
+  return krow * COLS * 2 + (((cl >> 3) ^ (COLS == 256 ? swz_b(krow) : mid_swz(krow))) << 4) + (cl & 7) * 2;
 }
 
 // How the valid rows of a problem are divided among its tile rows.  The work of a tile is proportional to the

@@ -5,6 +5,7 @@
 // lane receives with the operand layout of v_mfma_f32_16x16x32_bf16 (lane l: row or column l & 15, k = 8 (l >> 4) .. + 7).
 // It also checks that no load offset leaves the valid rows / 16-byte chunks, and that the tile order visits every tile
 // of a problem, and every workgroup id of a launch, exactly once.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -206,6 +207,46 @@ static void check_tile_order() {
   }
 }
 
+// ---- dot_mid_kernel's and dot_pair_kernel's K-major parts of SIZE columns, 32 k, loads held to `k_valid` of them, and every 64 columns' fragment reads;
+// the transpose read hands lane j of 16 column j of a 4 x 16 block, 4 lanes to a row.
+template <int SIZE>
+static void check_km_part(int x0, int valid, int ld, int k_valid) {
+  std::map<int, RC> km;
+  for (int q = 0; q < SIZE / 16; ++q)
+    for (int lane = 0; lane < 64; ++lane) {
+      const int at = mid_km_load_offset<SIZE>(q, lane, x0, valid, ld, k_valid) / 2 + x0, kr = at / ld, col = at % ld;
+      CHECK(kr < k_valid && col + 8 <= (valid + 7) / 8 * 8, "km part: k %d, column %d", kr, col);
+      for (int e = 0; e < 8; ++e) km[q * 1024 + lane * 16 + 2 * e] = RC(kr, col + e - x0);
+    }
+  CHECK(km.size() == SIZE * 32, "km part: %zu elements", km.size());
+  for (int wave = 0; wave < SIZE; wave += 64)
+    for (int block = 0; block < 4; ++block)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int second = 0; second < 2; ++second)
+          for (int e = 0; e < 4; ++e) {
+            const int j = lane & 15, group = lane >> 4, source = group * 16 + e * 4 + (j >> 2);
+            const RC got = km.at((mid_km_frag_offset<SIZE>(wave, source) ^ (block << 5)) + second * 4 * 2 * SIZE + (j & 3) * 2);
+            const int k = group * 8 + second * 4 + e, col = wave + block * 16 + j;
+            if (k < k_valid && x0 + col < valid) CHECK(got.first == k && got.second == col, "km part read: (%d, %d) instead of (%d, %d)", got.first, got.second, k, col);
+          }
+}
+// the 128-row halves of 256 columns, whose eight blocks dot_pair_kernel reads from one address
+static void check_km_blocks() {
+  for (int base : {0, 128})
+    for (int block = 0; block < 8; ++block)
+      for (int lane = 0; lane < 64; ++lane)
+        CHECK((mid_km_frag_offset<256>(base, lane) ^ (block << 5)) == mid_km_frag_offset<256>(base + block * 16, lane), "km blocks: base %d block %d", base, block);
+}
+// K-contiguous [rows][32 k] parts held to `k_valid`: no chunk beyond the last valid one, the others where they belong
+static void check_kc_held(int r0, int rows_valid, int ld, int k_valid) {
+  for (int q = 0; q < 16; ++q)
+    for (int lane = 0; lane < 64; ++lane) {
+      const int off = kc_load_offset(q, lane, r0, rows_valid, ld, k_valid) / 2, row = off / ld, k = off % ld, whole = kc_load_offset(q, lane, r0, rows_valid, ld) / 2;
+      CHECK(r0 + row < rows_valid && k < k_valid && k % 8 == 0, "kc held: row %d, k %d", row, k);
+      if (whole % ld < k_valid) CHECK(off == whole, "kc held: offset %d instead of %d", off, whole);
+    }
+}
+
 // ---- dot_f32_kernel: both parts of a step of 32 k, 64 rows or columns from x0 of `valid`; lane l of a fragment read takes row or column l & 15
 // of its block and k = 4 (l >> 4) .. + 3 of each half of 16.
 static void check_f32(int x0, int valid, int ld) {
@@ -240,6 +281,16 @@ static void check_f32(int x0, int valid, int ld) {
 int main() {
   for (int valid = 1; valid <= 200; ++valid)
     for (int x0 = 0; x0 < valid; x0 += 64) check_f32(x0, valid, valid);
+  check_km_blocks();
+  for (int valid : {1, 8, 100, 128, 129, 255, 256, 300, 511, 600})
+    for (int k_valid : {1, 7, 8, 24, 31, 32})
+      for (int x0 = 0; x0 < valid; x0 += 128) {
+        check_km_part<128>(x0, valid, 1000, k_valid);
+        if (x0 % 256 == 0) {
+          check_km_part<256>(x0, valid, 1000, k_valid);
+          check_kc_held(x0, valid, 1000, k_valid);
+        }
+      }
 
   for (int ld : {64, 72, 8192, 1 << 21})
     for (int r0 : {0, 256, 1024})
