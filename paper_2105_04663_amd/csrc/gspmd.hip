@@ -1549,7 +1549,8 @@ int32_t gspmd_resharded_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
 int32_t gspmd_testing_pin(const gspmd_testing_launch* pin) {
   if (!pin) return GSPMD_ERR_NULL;
   const bool split = pin->kernel == GSPMD_TESTING_SPLIT;
-  if (pin->kernel < GSPMD_TESTING_BY_RULE || pin->kernel > GSPMD_TESTING_PAIR || pin->one_launch < GSPMD_TESTING_BY_RULE || pin->one_launch > 1 ||
+  const bool known = (pin->kernel >= GSPMD_TESTING_BY_RULE && pin->kernel <= GSPMD_TESTING_SPLIT) || pin->kernel == GSPMD_TESTING_PAIR;
+  if (!known || pin->one_launch < GSPMD_TESTING_BY_RULE || pin->one_launch > 1 ||
       (split ? pin->row_blocks != 1 && pin->row_blocks != 2 && pin->row_blocks != 4 : pin->row_blocks != 0)) return GSPMD_ERR_UNSUPPORTED;
   if (pin->dry_run != 0 && pin->dry_run != 1) return GSPMD_ERR_UNSUPPORTED;
   t_pin = *pin;

@@ -16,7 +16,7 @@ enum {
   GSPMD_TESTING_MFMA = 1,       /* dot_mfma_kernel */
   GSPMD_TESTING_MID = 2,        /* dot_mid_kernel: what dot_mfma_kernel takes with direct loads; others where nothing is summed and K-major operands have a tile of rows, columns */
   GSPMD_TESTING_SPLIT = 3,      /* dot_split_kernel: no partial sums along a contracting mesh dimension */
-  GSPMD_TESTING_PAIR = 4        /* dot_pair_kernel: what dot_mfma_kernel takes with direct loads, nothing summed, K-contiguous operands in whole chunks of eight or padded rows */
+  GSPMD_TESTING_PAIR = 5        /* dot_pair_kernel: what dot_mfma_kernel takes with direct loads, nothing summed, K-contiguous operands in whole chunks of eight or padded rows */
 };
 
 typedef struct {

@@ -4,7 +4,7 @@ import ctypes as C
 
 import paper_2105_04663_amd as g
 
-BY_RULE, SCALAR, MFMA, MID, SPLIT, PAIR = -1, 0, 1, 2, 3, 4
+BY_RULE, SCALAR, MFMA, MID, SPLIT, PAIR = -1, 0, 1, 2, 3, 5
 
 
 class _Launch(C.Structure):
