@@ -141,7 +141,7 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 
 // What a launch of dot_mfma_kernel or dot_mid_kernel takes, in us: straight lines through measured times.
 // dot_mfma_kernel: rounds of 256 workgroups of 9 us and 1.3 us per 64-wide K step, where the chip is full and its clock drops, down to 0.85
-//   in a round of few (short tiles: 0.75), 2 us for what is left of K; staged operands 10.5 and 2.1 us.  From two full rounds on 1.25 us, and the last
+//   in a round of few (short tiles: 0.75), 2 us for what is left of K.  From two full rounds on 1.25 us, and the last
 //   round counts by its share, as the workgroups no longer start together.  Joined problems meet in slots: 4.6 us
 //   per member, the last arriver at a tile reading the others' contributions one after the other, and 0.05 us per contribution to a tile, 0.1 beyond 256
 //   (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38; 8, 16: 38; 8, 512: 59).
@@ -157,6 +157,7 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 struct LaunchSize {
   int64_t rows = 0, k = 0, big = 0, mid = 0, pair = 0, members = 1;      // longest extents, tiles of 256 x 256, 128 x 128 and 256 x 128, most members of a sum
   int64_t cols = INT32_MAX, fewest_rows = INT32_MAX;
+  int64_t loose_cols = INT32_MAX, loose_rows_of_lhs = INT32_MAX;      // fewest of a K-major operand whose rows are not padded to 16 bytes
   bool a_odd = false, b_odd = false;                           // an operand has elements at odd addresses
   bool broken_lines = false, whole_steps = true, whole_chunks = true;      // a K-contiguous operand's rows are not whole lines; all K are whole 64-wide steps
 };
@@ -167,6 +168,8 @@ LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
     s.k = std::max<int64_t>(s.k, p.Kv);
     s.cols = std::min<int64_t>(s.cols, p.Nv);
     s.fewest_rows = std::min<int64_t>(s.fewest_rows, p.Mv);
+    if (!(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && loose_rows(p.B, p.ldb)) s.loose_cols = std::min<int64_t>(s.loose_cols, p.Nv);
+    if ((layout & GSPMD_LAYOUT_LHS_K_MAJOR) && loose_rows(p.A, p.lda)) s.loose_rows_of_lhs = std::min<int64_t>(s.loose_rows_of_lhs, p.Mv);
     s.a_odd = s.a_odd || (p.lda & 1) || (reinterpret_cast<uintptr_t>(p.A) & 2);
     s.b_odd = s.b_odd || (p.ldb & 1) || (reinterpret_cast<uintptr_t>(p.B) & 2);
     s.big += tiles_of(p, kMfmaBM, kMfmaBN);
@@ -183,21 +186,33 @@ LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
 }
 double big_us(const LaunchSize& s, bool staged) {
   const double steps = static_cast<double>((s.k + 63) / 64), full = static_cast<double>(s.big / 256), part = static_cast<double>(s.big % 256) / 256.0;
-  const double beside = staged ? 10.5 : 9.0 + (s.k % 64 ? 2.0 : 0.0);
-  auto step = [&](double fill) { return staged ? 2.1 : s.rows <= 96 ? 0.75 : 0.85 + 0.45 * fill * fill; };
+  const double beside = 9.0 + (s.k % 64 ? 2.0 : 0.0);
+  auto step = [&](double fill) { return s.rows <= 96 ? 0.75 : 0.85 + 0.45 * fill * fill; };
   const double first = static_cast<double>(std::min<int64_t>(s.big, 256)), later = static_cast<double>(s.big) - first;
   const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * first + 0.1 * later : 0.0;
-  if (!staged && s.rows > 96 && full >= 2.0) return (full + part) * (beside + steps * 1.25) + slots;
+  if (staged) return (14.0 + steps * 2.0) * (full + (part == 0.0 ? 0.0 : full == 0.0 ? 1.0 : 0.6 + 0.4 * part)) + slots;
+  if (s.rows > 96 && full >= 2.0) return (full + part) * (beside + steps * 1.25) + slots;
   return full * (beside + steps * step(1.0)) + (part > 0.0 ? beside + steps * step(part) : 0.0) + slots;
 }
-double mid_us(const LaunchSize& s, bool staged = false) {
+double mid_us(const LaunchSize& s) {
   const double m = static_cast<double>(s.members), left = static_cast<double>((s.k % 64 + 31) / 32);
   const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 8.8 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
   const int64_t part = s.mid % 512;
   const bool long_sum = s.members > 1 && s.mid > 512;
-  const double one = staged ? 0.11 + 0.16 * ((s.a_odd ? 1 : 0) + (s.b_odd ? 1 : 0)) : long_sum ? 0.30 : 0.205;
-  const double two = staged ? 2.0 * one : long_sum ? 0.44 : 0.40;
+  const double one = long_sum ? 0.30 : 0.205, two = long_sum ? 0.44 : 0.40;
   return static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
+}
+// Operands that take no direct loads, through registers.  dot_mfma_kernel: 14 us and 2.0 us per 64-wide step, a last round that is not full between 0.6 and 1 of
+// that.  dot_mid_kernel: 8.8 us (7 from the second round on) and per 32-wide step 0.27 us with one operand at odd addresses and 0.31 with both while a compute
+// unit has one workgroup, 0.54 and 0.69 with two, a last round of more than 256 again in part.  Fitted to 40 drawn launches (us, 256 x 256 / 128 x 128 tiles;
+// M x K x N): 5995 x 2709 x 877 104 / 63   six of 1432 x 2183 x 775 85 / 57   six of 354 x 817 x 2307 39 / 28   4330 x 146 x 4633 40 / 28   32 of 324 x 753 x 325
+//   38 / 27   32 of 554 x 840 x 669 72 / 46   six of 1083 x 1389 x 1844 55 / 65   six of 975 x 889 x 2316 45 / 47   32 of 716 x 411 x 281 26 / 30
+double mid_staged_us(const LaunchSize& s) {
+  const bool both = s.a_odd && s.b_odd, any = s.a_odd || s.b_odd;
+  const double steps = static_cast<double>((s.k + 31) / 32), one = both ? 0.31 : any ? 0.27 : 0.16, two = both ? 0.69 : any ? 0.54 : 0.32;
+  const int64_t full = s.mid / 512, part = s.mid % 512;
+  const double last = part == 0 ? 0.0 : 8.8 + steps * (part <= 256 ? one : two * (0.6 + 0.4 * static_cast<double>(part) / 512.0));
+  return static_cast<double>(full) * ((full >= 2 ? 7.0 : 8.8) + steps * two) + last;
 }
 
 // dot_pair_kernel: 6.5 us, and rounds of 512 workgroups of 5.2 us and 0.70 us per 32-wide step, two of them on a compute unit, more where an operand is
@@ -231,11 +246,13 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 // dot_split_kernel's order of summation is another one: partial sums along a contracting mesh dimension (`ordered`) stay with the
 // first two, so that the joined sum, the two-launch sum and partials that a caller sums agree bit for bit; and beyond 256 rows it is taken
 // from K = 1024 on (below, dot_mid_kernel is within 4 us).
-// Operands that take no direct loads (kPathMfmaStaged) cost the address unit more: 10.5 us and 2.1 us a step in
-// dot_mfma_kernel's staged tiles; in dot_mid_kernel's 0.11 us and 0.16 per odd operand a 32-wide step; rounds of 3.2, 4.3, 6.5 us and 1.2, 1.25, 1.55 us per eight steps in the split kernel (staged / 1, 2, 4 row blocks):
+// Operands that take no direct loads (kPathMfmaStaged) cost the address unit more: big_us, mid_staged_us; rounds of 3.2, 4.3, 6.5 us and 1.2, 1.25, 1.55 us
+// per eight steps in the split kernel (256 x 256 staged tiles / 1, 2, 4 row blocks):
 //   601 x 2001 x 601: 78 / 25, 15, 20     2001 x 1003 x 2001: 45 / 136, 82, 59     301 x 1001 x 301: 45 / 9, 10, 14
 //   3826 x 102 x 538: 14 / 35, 25, 21     482 x 111 x 5292: 14 / 50, 34, 25        2289 x 293 x 885: 21 / 35, 23, 17
 //   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46     5990 x 3107 x 555: 117 / -, -, 107
+// Where such a K-major operand has fewer columns (rows) than a tile of it, that kernel loads element by element, 5.0, 5.5, 9.5 us per eight steps:
+//   32 of 834 x 1827 x 22: 68 / 303, 225, 172     32 of 738 x 657 x 39: 35 / -, -, 63     six of 459 x 2633 x 29: 99 / 65, 86, 125     32 of 56 x 1562 x 9: 164 / 33, 40, 55
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
 // (with_records): the choice is the same with and without, so results are.
 constexpr int32_t kMidShortK = 1024;      // members with something left of K that dot_mid_kernel runs through one loop
@@ -260,7 +277,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (size.rows == 0) return choice;
   double best = big_us(size, choice.staged = big_staged(size, path, layout));
   if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
-    const double us = mid_us(size, loose);
+    const double us = loose ? mid_staged_us(size) : mid_us(size);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, loose}; }
   }
   if (pair_takes(size, path, layout)) {
@@ -269,11 +286,12 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   }
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((size.k + 255) / 256);
-    const struct { int blocks; double aligned, beside, unaligned; } kinds[] = {{1, 1.0, 3.2, 1.2}, {2, 1.3, 4.3, 1.25}, {4, 1.7, 6.5, 1.55}};
+    const struct { int blocks; double aligned, beside, unaligned, elements; } kinds[] = {{1, 1.0, 3.2, 1.2, 5.0}, {2, 1.3, 4.3, 1.25, 5.5}, {4, 1.7, 6.5, 1.55, 9.5}};
     for (const auto& kind : kinds) {
       int64_t tiles = 0;
       for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
-      const double us = static_cast<double>((tiles + 255) / 256) * (loose ? kind.beside + rounds8 * kind.unaligned : 4.0 + rounds8 * kind.aligned);
+      const bool elements = size.loose_cols < kSplitBN || size.loose_rows_of_lhs < 16 * kind.blocks;
+      const double us = static_cast<double>((tiles + 255) / 256) * (loose ? kind.beside + rounds8 * (elements ? kind.elements : kind.unaligned) : 4.0 + rounds8 * kind.aligned);
       if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks}; }
     }
   }
@@ -290,7 +308,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 constexpr int64_t kSeveralRounds = 512;
 double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
-  return choice.kernel == kMfmaMid ? mid_us(size, choice.staged) : choice.kernel == kMfmaPair ? pair_us(size, layout, choice.loose) : big_us(size, choice.staged);
+  return choice.kernel == kMfmaMid ? choice.staged ? mid_staged_us(size) : mid_us(size) : choice.kernel == kMfmaPair ? pair_us(size, layout, choice.loose) : big_us(size, choice.staged);
 }
 // What partials cost beside their launch: 1 us, 2.5 us per sum kernel (one per reduce group) and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
