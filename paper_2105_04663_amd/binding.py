@@ -63,6 +63,7 @@ class _CGemmDesc(C.Structure):
 
 
 _LIB = None
+_CALL = None           # the native entry (csrc/call.c): Dots whose arguments are in their plain form
 
 
 def library_path() -> str:
@@ -71,7 +72,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libgspmd.so (built in-tree by paper_2105_04663_amd.build); raises if absent."""
-    global _LIB
+    global _LIB, _CALL
     if _LIB is not None:
         return _LIB
     path = library_path()
@@ -103,6 +104,13 @@ def load_library():
     lib.gspmd_set_tile_timeline.argtypes = [C.c_void_p, C.c_int64]
     for name in EXPORTED_SYMBOLS[1:]:
         getattr(lib, name).restype = C.c_int32
+    try:
+        from . import _call
+    except ImportError:      # a library built without it, or by another Python: every argument goes through ctypes
+        _call = None
+    if _call is not None:
+        _call.bind(C.cast(lib.gspmd_grouped_dot, C.c_void_p).value, C.cast(lib.gspmd_local_dot, C.c_void_p).value, Mesh, DotDims, Sharding, ShardBuf)
+        _CALL = _call
     _LIB = lib
     return lib
 
@@ -142,7 +150,7 @@ class _Marshalled:
             return held[1]
         made = self._make()          # (C structure, the arrays it points to)
         if all(type(f) is tuple and all(type(v) is int for v in f) for f in fields):
-            self._held = (fields, made[0], made[1])
+            self._held = (fields, made[0], made[1], C.addressof(made[0]))
         else:
             self._keep = made[1]
             self.__dict__.pop("_held", None)
@@ -303,6 +311,11 @@ def _fill(fill):
 def local_dot(mesh: Mesh, dims: DotDims, lhs: ShardBuf, lhs_sh: Sharding, rhs: ShardBuf, rhs_sh: Sharding,
               out: ShardBuf, out_sh: Sharding, partition_id: int, lhs_fill=None,
               workspace: int = 0, workspace_bytes: int = 0, stream: int = 0, epilogue: int = EPILOGUE_NONE) -> None:
+    if _CALL is not None:
+        status = _CALL.local_dot(mesh, dims, lhs, lhs_sh, rhs, rhs_sh, out, out_sh, partition_id, lhs_fill, epilogue, workspace,
+                                 workspace_bytes, stream)
+        if status is not None:
+            return _check(status, "gspmd_local_dot")
     m, d, a, b, o = mesh._c(), dims._c(), lhs_sh._c(), rhs_sh._c(), out_sh._c()
     la, rb, ob = lhs._c(), rhs._c(), out._c()
     _check(load_library().gspmd_local_dot(C.byref(m), C.byref(d), C.byref(la), C.byref(a), C.byref(rb), C.byref(b),
@@ -314,6 +327,11 @@ def grouped_dot(mesh: Mesh, dims: DotDims, lhs_shards: Sequence[ShardBuf], lhs_s
                 rhs_shards: Sequence[ShardBuf], rhs_sh: Sharding, out_shards: Sequence[ShardBuf], out_sh: Sharding,
                 lhs_fill=None, workspace: int = 0, workspace_bytes: int = 0, stream: int = 0,
                 epilogue: int = EPILOGUE_NONE) -> None:
+    if _CALL is not None:
+        status = _CALL.grouped_dot(mesh, dims, lhs_shards, lhs_sh, rhs_shards, rhs_sh, out_shards, out_sh, lhs_fill, epilogue, workspace,
+                                   workspace_bytes, stream)
+        if status is not None:
+            return _check(status, "gspmd_grouped_dot")
     P = mesh.n_partitions
     if not (len(lhs_shards) == len(rhs_shards) == len(out_shards) == P):
         raise ValueError("one shard buffer per partition is required")

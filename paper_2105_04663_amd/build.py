@@ -4,12 +4,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "build")
 LIB = os.path.join(HERE, "libgspmd.so")
+CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 # (source, object, extra flags); the MFMA kernels' sources are compiled once per operand layout
 UNITS = [(os.path.join(CSRC, f"{name}.hip"), f"{name}_l{n}.o", [f"-DGSPMD_TU_LAYOUT={n}"])
          for name in ("dot_mfma", "dot_split", "dot_mid", "dot_pair") for n in range(4)] + [
@@ -28,7 +30,7 @@ def _run(cmd, verbose: bool) -> None:
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libgspmd.so")
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed building {os.path.basename(cmd[-1])}")
     if verbose and res.stderr:
         sys.stderr.write(res.stderr)
 
@@ -44,7 +46,17 @@ def build(verbose: bool = False, only=None) -> str:
         list(pool.map(lambda c: _run(c, verbose), cmds))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", LIB + ".tmp"], verbose)
     os.replace(LIB + ".tmp", LIB)
+    if only is None or "call" in only:
+        build_call(verbose)
     return LIB
+
+
+def build_call(verbose: bool = False) -> str:
+    """The native entry of the binding, for the Python that runs this."""
+    cc = os.environ.get("CC", "gcc")
+    _run([cc, "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "call.c"), "-o", CALL + ".tmp"], verbose)
+    os.replace(CALL + ".tmp", CALL)
+    return CALL
 
 
 if __name__ == "__main__":
