@@ -92,13 +92,13 @@ __device__ __forceinline__ T copy_from_kernarg(const GSPMD_KERNARG T* p) {
 // the kernel arguments (an InlineProblems as first parameter), and an entry of whichever table that is.
 __device__ __forceinline__ int lookup_problem_index(const Problem* __restrict__ tab, int n_prob, int tile) {
   if (tab) return find_problem(tab, n_prob, tile);
-  const GSPMD_KERNARG Problem* inl = first_kernel_argument<Problem>();
-  int lo = 0, hi = n_prob - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (inl[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
-  }
-  return lo;
+  if (n_prob == 1) return 0;
+  // One load and a ballot: a search takes five dependent ones in a table of 32, a microsecond before every tile (4 x 8 mesh of 5998 x 3072 x 9999, 3.75 tiles
+  // a compute unit: 295 -> 289 us; six of 601 x 1203 x 697 20.2 -> 19.9).
+  static_assert(kInlineProblems <= 64, "a lane for every problem");
+  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int begin = first_kernel_argument<Problem>()[min(lane, n_prob - 1)].tile_begin;
+  return __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_prob && begin <= tile)) - 1;
 }
 __device__ __forceinline__ Problem problem_at(const Problem* __restrict__ tab, int i) {
   return tab ? tab[i] : copy_from_kernarg(first_kernel_argument<Problem>() + i);
