@@ -3,6 +3,6 @@
 
 namespace gspmd {
 
-template bool launch_dot_split_layout<GSPMD_TU_LAYOUT>(const MfmaLaunch& l, int32_t out_dtype, int row_blocks, hipStream_t stream);
+template bool launch_dot_split_layout<GSPMD_TU_LAYOUT>(const MfmaLaunch& l, int32_t out_dtype, int row_blocks, int col_blocks, hipStream_t stream);
 
 }  // namespace gspmd

@@ -130,7 +130,7 @@ int64_t tiles_of(const Problem& p, int bm, int bn) {
 enum MfmaKernel : int32_t { kMfmaNone = GSPMD_TESTING_SCALAR, kMfmaBig = GSPMD_TESTING_MFMA, kMfmaMid = GSPMD_TESTING_MID, kMfmaSplit = GSPMD_TESTING_SPLIT, kMfmaPair = GSPMD_TESTING_PAIR };
 struct MfmaChoice {
   MfmaKernel kernel;
-  int row_blocks;
+  int row_blocks, col_blocks = 0;
   bool staged = false;      // dot_mfma_kernel, dot_mid_kernel: operands through registers
   bool loose = false;       // dot_pair_kernel: rows that are not padded to 16 bytes
 };
@@ -190,7 +190,7 @@ double big_us(const LaunchSize& s, bool staged) {
   auto step = [&](double fill) { return s.rows <= 96 ? 0.75 : 0.85 + 0.45 * fill * fill; };
   const double first = static_cast<double>(std::min<int64_t>(s.big, 256)), later = static_cast<double>(s.big) - first;
   const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * first + 0.1 * later : 0.0;
-  if (staged) return (14.0 + steps * 2.0) * (full + (part == 0.0 ? 0.0 : full == 0.0 ? 1.0 : 0.6 + 0.4 * part)) + slots;
+  if (staged) return (14.0 + steps * (std::min(s.loose_cols, s.loose_rows_of_lhs) < 8 ? 7.0 : 2.0)) * (full + (part == 0.0 ? 0.0 : full == 0.0 ? 1.0 : 0.6 + 0.4 * part)) + slots;
   if (s.rows > 96 && full >= 2.0) return (full + part) * (beside + steps * 1.25) + slots;
   return full * (beside + steps * step(1.0)) + (part > 0.0 ? beside + steps * step(part) : 0.0) + slots;
 }
@@ -243,6 +243,11 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 //   32 x 8192 x 8192: 101 / 43, 51, 54        64 x 8192 x 8192: 105 / 62, 47, 65      256 x 8192 x 8192: 135 / 222, 140, 97
 //   32 x 2048 x 16384: 31 / 26, 19, 20        64 x 1024 x 1024: 14 / 6, 7, 10         256 x 2048 x 2048: 39 / 22, 13, 17
 //   512 x 2048 x 2048: 39 / 41, 24, 16        1024 x 1024 x 4096: 23 / 89, 59, 40
+// In tiles of 32 columns (1 and 2 row blocks; 0.75 and 1.05 us per eight steps, staged 0.8 and 0.9), where 64 leave compute units without a tile, or are more than
+// an operand has (64 columns with 1, 2, 4 row blocks / 32 with 1, 2):
+//   16 x 3648 x 2081: 13.9, 14.4, 16.2 / 11.4, 11.6     8 x 4096 x 1024: 10.3, 11.9, 15.2 / 7.6, 8.9      100 x 4096 x 1024: 11.9, 13.3, 17.7 / 10.5, 11.3
+//   16 x 8192 x 8192: 41.7, 42.6, 44.9 / 38.4, 38.8     32 x 8192 x 8192: 39.5, 48.4, 51 / 65, 43         128 x 2048 x 2048: 8.9, 9.5, 12.5 / 12.7, 8.8
+//   172 x 2361 x 559: 14.7, 17.7, 23.4 / 10.9, 13.1     300 x 1000 x 500: 7.9, 9.0, 11.8 / 8.5, 7.8       32 of 261 x 1486 x 59: 102, 86, 61 / 25, 26
 // dot_split_kernel's order of summation is another one: partial sums along a contracting mesh dimension (`ordered`) stay with the
 // first two, so that the joined sum, the two-launch sum and partials that a caller sums agree bit for bit; and beyond 256 rows it is taken
 // from K = 1024 on (below, dot_mid_kernel is within 4 us).
@@ -251,8 +256,9 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 //   601 x 2001 x 601: 78 / 25, 15, 20     2001 x 1003 x 2001: 45 / 136, 82, 59     301 x 1001 x 301: 45 / 9, 10, 14
 //   3826 x 102 x 538: 14 / 35, 25, 21     482 x 111 x 5292: 14 / 50, 34, 25        2289 x 293 x 885: 21 / 35, 23, 17
 //   601 x 1203 x 697, six of them: 52 / -, -, 50     1083 x 1400 x 2367: 50 / 104, 60, 46     5990 x 3107 x 555: 117 / -, -, 107
-// Where such a K-major operand has fewer columns (rows) than a tile of it, that kernel loads element by element, 5.0, 5.5, 9.5 us per eight steps:
-//   32 of 834 x 1827 x 22: 68 / 303, 225, 172     32 of 738 x 657 x 39: 35 / -, -, 63     six of 459 x 2633 x 29: 99 / 65, 86, 125     32 of 56 x 1562 x 9: 164 / 33, 40, 55
+// Where such a K-major operand has fewer columns (rows) than a tile of 64 columns, or fewer than 8 in one of 32, that kernel loads element by element (2.2 to 8.5 us per
+// eight steps); 256 x 256 staged tiles below 8 columns too, 7 us a step.  32 of 268 x 2185 x N (256 x 256 / 64 columns with 1, 2, 4 row blocks / 32 columns with 1, 2):
+//   N = 3: 236 / 98, 96, 60 / 57, 78     7: 270 / 134, 120, 69 / 74, 92     9: 88 / 148, 130, 72 / 24, 24     10: 79 / 148, 130, 73 / 17, 20     31: 88 / 148, 130, 76 / 24, 24
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
 // (with_records): the choice is the same with and without, so results are.
 constexpr int32_t kMidShortK = 1024;      // members with something left of K that dot_mid_kernel runs through one loop
@@ -278,21 +284,23 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   double best = big_us(size, choice.staged = big_staged(size, path, layout));
   if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
     const double us = loose ? mid_staged_us(size) : mid_us(size);
-    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, loose}; }
+    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, 0, loose}; }
   }
   if (pair_takes(size, path, layout)) {
     const double us = pair_us(size, layout, path == kPathMfmaWords);
-    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaPair, 0, false, path == kPathMfmaWords}; }
+    if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaPair, 0, 0, false, path == kPathMfmaWords}; }
   }
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((size.k + 255) / 256);
-    const struct { int blocks; double aligned, beside, unaligned, elements; } kinds[] = {{1, 1.0, 3.2, 1.2, 5.0}, {2, 1.3, 4.3, 1.25, 5.5}, {4, 1.7, 6.5, 1.55, 9.5}};
+    const struct { int blocks, cols; double aligned, beside, unaligned, elements; } kinds[] = {
+        {1, 4, 1.0, 3.2, 1.2, 5.0}, {2, 4, 1.3, 4.3, 1.25, 5.5}, {4, 4, 1.7, 6.5, 1.55, 8.5}, {1, 2, 0.75, 3.2, 0.8, 2.2}, {2, 2, 1.05, 4.3, 0.9, 4.5}};
     for (const auto& kind : kinds) {
       int64_t tiles = 0;
-      for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, kSplitBN);
-      const bool elements = size.loose_cols < kSplitBN || size.loose_rows_of_lhs < 16 * kind.blocks;
+      for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, 16 * kind.cols);
+      const bool whole = kind.cols == 4;
+      const bool elements = size.loose_cols < (whole ? 16 * kind.cols : 8) || size.loose_rows_of_lhs < (whole ? 16 * kind.blocks : 8);
       const double us = static_cast<double>((tiles + 255) / 256) * (loose ? kind.beside + rounds8 * (elements ? kind.elements : kind.unaligned) : 4.0 + rounds8 * kind.aligned);
-      if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks}; }
+      if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks, kind.cols}; }
     }
   }
   return choice;
@@ -324,7 +332,7 @@ MfmaChoice pick_kernel(const std::vector<Problem>& ps, KernelPath path, int32_t 
   const LaunchSize size = launch_size(ps, layout);
   if (pin == kMfmaNone || pin == kMfmaBig || (pin == kMfmaMid && (path != kPathMfmaStaged || (size.members == 1 && mid_stages_whole(size, layout)))) ||
       (pin == kMfmaSplit && !ordered) || (pin == kMfmaPair && pair_takes(size, path, layout)))
-    return MfmaChoice{pin, t_pin.row_blocks, pin == kMfmaBig ? big_staged(size, path, layout) : pin == kMfmaMid && path == kPathMfmaStaged};
+    return MfmaChoice{pin, t_pin.row_blocks, t_pin.col_blocks ? t_pin.col_blocks : 4, pin == kMfmaBig ? big_staged(size, path, layout) : pin == kMfmaMid && path == kPathMfmaStaged};
   return choose_mfma(ps, path, layout, ordered);
 }
 
@@ -380,7 +388,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
   const int split = choice.kernel == kMfmaSplit ? choice.row_blocks : 0;
   const bool mid = choice.kernel == kMfmaMid, pair = choice.kernel == kMfmaPair;
   const int bm = split ? 16 * split : mid ? kMidTile : pair ? kPairRows : mfma ? kMfmaBM : kGenTile;
-  const int bn = split ? kSplitBN : mid ? kMidTile : pair ? kPairCols : mfma ? kMfmaBN : kGenTile;
+  const int bn = split ? 16 * choice.col_blocks : mid ? kMidTile : pair ? kPairCols : mfma ? kMfmaBN : kGenTile;
   // Workgroups start in tile order and the launch ends when the last one does: problems whose tiles take longest
   // (the most K steps) go first, so that the compute units that are still busy at the end are busy with short tiles.
   if (!join)
@@ -422,6 +430,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
     return GSPMD_ERR_WORKSPACE;
   t_last.kernel = choice.kernel;
   t_last.row_blocks = choice.row_blocks;
+  t_last.col_blocks = split ? choice.col_blocks : 0;
   t_last.one_launch = join ? 1 : 0;
   t_last.table_bytes = inline_tables ? 0 : table_bytes;
   if (t_pin.dry_run) return GSPMD_OK;
@@ -451,7 +460,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       // weights whose rows are whole multiples of what an L2's channels cover (32 x 8192 x 8192: 42.7 us in an eighth of the tiles at a time, 40.1
       // spread out; other rows gain nothing, 101 x 1793 x 2281 loses: 10.4, 11.2)
       l.spread = !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && std::all_of(ps.begin(), ps.end(), [](const Problem& p) { return p.ldb % 2048 == 0; });
-      if (!launch_dot_split(l, layout, out_dtype, split, stream)) return GSPMD_ERR_DEVICE;
+      if (!launch_dot_split(l, layout, out_dtype, split, choice.col_blocks, stream)) return GSPMD_ERR_DEVICE;
     } else if (mid) {
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
       if (!launch_dot_mid(l, layout, out_dtype, join != nullptr, choice.staged, stream)) return GSPMD_ERR_DEVICE;
@@ -1571,6 +1580,7 @@ int32_t gspmd_testing_pin(const gspmd_testing_launch* pin) {
   if (!known || pin->one_launch < GSPMD_TESTING_BY_RULE || pin->one_launch > 1 ||
       (split ? pin->row_blocks != 1 && pin->row_blocks != 2 && pin->row_blocks != 4 : pin->row_blocks != 0)) return GSPMD_ERR_UNSUPPORTED;
   if (pin->dry_run != 0 && pin->dry_run != 1) return GSPMD_ERR_UNSUPPORTED;
+  if (pin->col_blocks != 0 && !(split && (pin->col_blocks == 4 || (pin->col_blocks == 2 && pin->row_blocks <= 2)))) return GSPMD_ERR_UNSUPPORTED;
   t_pin = *pin;
   return GSPMD_OK;
 }

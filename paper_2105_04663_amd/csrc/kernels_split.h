@@ -12,8 +12,9 @@
 //
 // Loads are 16 bytes at any element alignment.  An operand chunk never reaches past a row's valid end unless rows are
 // padded to 8 elements: the last tile of an unpadded K-major operand is moved back so that it ends at the last valid
-// column (the columns that it shares with its neighbour are computed twice, in the same order), and what is left of K
-// after the 32-wide steps, or an extent shorter than a tile, goes element by element.
+// column (the columns that it shares with its neighbour are computed twice, in the same order); of one narrower than a tile the
+// last chunk is fetched early and moved down in registers (element by element: 32 of 268 x 2185 x 11 73 us, now 24; of 56 x 1562 x 13 33, now 13).  What is left of K
+// after the 32-wide steps, or an extent of fewer than 8, goes element by element.
 //
 // Measured (us, weights not in cache; before: 256 x 256 tiles on 32 to 128 of the 256 compute units): 32 x 8192 x 8192
 // 101 -> 43 (134 MB of weights at 3.1 TB/s; 36 with rows of 8256 elements, a power of two costs the L2 channels), 64 rows
@@ -21,8 +22,10 @@
 // Of the 43 us, 40 are the loads alone (36 with the tiles' order below: 32 x 8192 x 8192 42.7 -> 40.1, 16 rows 44.0 -> 42.8, 128 x 4096 x
 // 4096 16.5 -> 15.1).  Running further ahead (9 instead of 6 steps, or only 2) changes nothing: a compute unit's L1 keeps about 105 lines of 128 bytes
 // in flight, 608 cycles each at 32 x 8192 x 8192 (256 workgroups: two row tiles draw every weight panel, 268 MB from L2, 144
-// from HBM), and stalls on them for half of its cycles; the matrix cores are busy for 7 %, LDS for 25 %.  32-column tiles read half
-// lines: no gain.
+// from HBM), and stalls on them for half of its cycles; the matrix cores are busy for 7 %, LDS for 25 %.
+// Tiles of 32 columns read half lines, but are twice as many: where 64 columns leave compute units without a tile they are a fifth to a quarter
+// faster (16 x 3648 x 2081 13.9 -> 11.4, 18 x 2944 x 1306 10.6 -> 8.2, 8 x 4096 x 1024 10.3 -> 7.6, 16 x 8192 x 8192 41.7 -> 38.4, 172 x 2361 x 559 14.7 -> 10.9).  16 columns
+// gain another 4 to 9 % with few dozen tiles only, sixteen waves nothing.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -86,9 +89,12 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
   // rows padded to 8 elements may be read up to there
   const bool a_pad = !((reinterpret_cast<uintptr_t>(P.A) & 15) | (P.lda & 7)), b_pad = !((reinterpret_cast<uintptr_t>(P.B) & 15) | (P.ldb & 7));
   int m0 = m_nom, n0 = n_nom;
-  bool slow = false;                                                  // an extent too short for whole chunks
-  if (AKM && !a_pad && m0 + BM > P.Mv) { m0 = max(0, P.Mv - BM); slow = P.Mv < BM; }
-  if (!BKC && !b_pad && n0 + BN > P.Nv) { n0 = max(0, P.Nv - BN); slow = slow || P.Nv < BN; }
+  // an extent too short for whole chunks, or one that ends inside a chunk (in tiles of 32 columns only: 64 x 64 have no registers for it, and the
+  // others would be 1 to 3 % slower for every operand)
+  constexpr bool kMoves = CB == 2;
+  bool slow = false, a_moves = false, b_moves = false;
+  if (AKM && !a_pad && m0 + BM > P.Mv) { m0 = max(0, P.Mv - BM); slow = P.Mv < (kMoves ? 8 : BM); a_moves = P.Mv < BM && (P.Mv & 7); }
+  if (!BKC && !b_pad && n0 + BN > P.Nv) { n0 = max(0, P.Nv - BN); slow = slow || P.Nv < (kMoves ? 8 : BN); b_moves = P.Nv < BN && (P.Nv & 7); }
 
   split_f32x4 acc[RB][CB];
 #pragma unroll
@@ -106,7 +112,8 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
     if constexpr (AKM) {
       const int idx = j * 64 + lane, kr = idx / (2 * RB);
       int m = m0 + (idx - kr * (2 * RB)) * 8;
-      if (m >= P.Mv) m = ((P.Mv - 1) >> 3) << 3;                      // only where rows are padded: the last chunk again
+      if (m >= P.Mv) m = ((P.Mv - 1) >> 3) << 3;                      // only where rows are padded, or few: the last chunk again
+      if (kMoves && !a_pad) m = min(m, max(0, P.Mv - 8));             // fetched early
       a_off[j] = (static_cast<uint32_t>(kr) * P.lda + m) * 2;
     } else {
       a_off[j] = static_cast<uint32_t>(min(j * 16 + (lane >> 2), P.Mv - 1 - m0)) * static_cast<uint32_t>(P.lda) * 2 + (lane & 3) * 16;
@@ -118,6 +125,7 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
       const int idx = j * 64 + lane, kr = idx / (2 * CB);
       int n = n0 + (idx - kr * (2 * CB)) * 8;
       if (n >= P.Nv) n = ((P.Nv - 1) >> 3) << 3;
+      if (kMoves && !b_pad) n = min(n, max(0, P.Nv - 8));
       b_off[j] = (static_cast<uint32_t>(kr) * P.ldb + n) * 2;
     } else {
       b_off[j] = static_cast<uint32_t>(min(j * 16 + (lane >> 2), P.Nv - 1 - n0)) * static_cast<uint32_t>(P.ldb) * 2 + (lane & 3) * 16;
@@ -210,8 +218,26 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
       frags[j] = __builtin_bit_cast(split_bf16x8, *reinterpret_cast<const split_u32x4*>(piece + j * 1024 + rr * 64 + (((lane >> 4) ^ swz_a(rr)) << 4)));
     asm volatile("" ::: "memory");
   };
-  auto compute = [&](const split_u32x4 (&ra)[RB], const split_u32x4 (&rb)[CB]) {
+  // Chunks of a K-major operand narrower than the tile, the last of them fetched early because it would have reached past the valid extent:
+  // moved down to where its elements belong.
+  auto move_down = [&](auto width_tag, auto& regs, int valid) {
+    constexpr int W = decltype(width_tag)::value;
+    int l = lane;
+    asm volatile("" : "+v"(l));                                         // (worked out here, not kept in registers through the loop)
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const int x = ((j * 64 + l) & (2 * W - 1)) * 8, by = x < valid ? max(0, x + 8 - valid) : 0;
+      split_u32x4 v = regs[j];
+      if (by & 4) v = split_u32x4{v[2], v[3], 0u, 0u};
+      if (by & 2) v = split_u32x4{v[1], v[2], v[3], 0u};
+      if (by & 1) v = split_u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+      regs[j] = v;
+    }
+  };
+  auto compute = [&](split_u32x4 (&ra)[RB], split_u32x4 (&rb)[CB], bool whole_step) {
     split_bf16x8 fa[RB], fb[CB];
+    if (kMoves && AKM && a_moves && whole_step) move_down(std::integral_constant<int, RB>{}, ra, P.Mv);
+    if (kMoves && !BKC && b_moves && whole_step) move_down(std::integral_constant<int, CB>{}, rb, P.Nv);
     if constexpr (BKC) relane(std::integral_constant<int, CB>{}, piece_b, rb, fb);
     else transpose(std::integral_constant<int, CB>{}, piece_b, rb, fb);
     if constexpr (AKM) transpose(std::integral_constant<int, RB>{}, piece_a, ra, fa);
@@ -239,7 +265,7 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
       for (; i + 2 * D <= mine; i += D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-          compute(ra[d], rb[d]);
+          compute(ra[d], rb[d], true);
           load_step(ra[d], rb[d]);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -252,13 +278,13 @@ __global__ __launch_bounds__(kSplitThreads) void dot_split_kernel(const InlinePr
     for (; i < mine; i += D) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        if (i + d < mine) compute(ra[d], rb[d]);
+        if (i + d < mine) compute(ra[d], rb[d], true);
         if (i + d + D < mine) load_step(ra[d], rb[d]);
       }
     }
     for (int s = whole + ((wave - whole) & (kSplitWaves - 1)); s < steps; s += kSplitWaves) {    // the rest of this wave's steps
       load_step_slow(s, ra[0], rb[0]);
-      compute(ra[0], rb[0]);
+      compute(ra[0], rb[0], false);
     }
   }
 
@@ -329,7 +355,8 @@ inline bool launch_dot_split_as(const MfmaLaunch& l, hipStream_t stream) {
 }
 
 template <int LAYOUT, typename TOut>
-bool launch_dot_split_out(const MfmaLaunch& l, int row_blocks, hipStream_t stream) {
+bool launch_dot_split_out(const MfmaLaunch& l, int row_blocks, int col_blocks, hipStream_t stream) {
+  if (col_blocks == 2) return row_blocks == 1 ? launch_dot_split_as<TOut, LAYOUT, 1, 2>(l, stream) : launch_dot_split_as<TOut, LAYOUT, 2, 2>(l, stream);
   switch (row_blocks) {
     case 1: return launch_dot_split_as<TOut, LAYOUT, 1, 4>(l, stream);
     case 2: return launch_dot_split_as<TOut, LAYOUT, 2, 4>(l, stream);
@@ -337,8 +364,9 @@ bool launch_dot_split_out(const MfmaLaunch& l, int row_blocks, hipStream_t strea
   }
 }
 template <int LAYOUT>
-bool launch_dot_split_layout(const MfmaLaunch& l, int32_t out_dtype, int row_blocks, hipStream_t stream) {
-  return out_dtype == GSPMD_F32 ? launch_dot_split_out<LAYOUT, float>(l, row_blocks, stream) : launch_dot_split_out<LAYOUT, bf16_bits>(l, row_blocks, stream);
+bool launch_dot_split_layout(const MfmaLaunch& l, int32_t out_dtype, int row_blocks, int col_blocks, hipStream_t stream) {
+  return out_dtype == GSPMD_F32 ? launch_dot_split_out<LAYOUT, float>(l, row_blocks, col_blocks, stream)
+                                : launch_dot_split_out<LAYOUT, bf16_bits>(l, row_blocks, col_blocks, stream);
 }
 
 }  // namespace gspmd

@@ -38,20 +38,19 @@ inline bool launch_dot_mfma(const MfmaLaunch& l, int32_t layout, int32_t out_dty
 }
 #endif
 
-// One launch of dot_split_kernel in tiles of 16 * row_blocks rows (1, 2 or 4 blocks) x kSplitBN columns (no joined
+// One launch of dot_split_kernel in tiles of 16 * row_blocks rows (1, 2 or 4 blocks) x 16 * col_blocks columns (4; 2 with 1 or 2 row blocks; no joined
 // problems).
 constexpr int kSplitWaves = 8, kSplitThreads = 64 * kSplitWaves;
-constexpr int kSplitBN = 64;
 template <int LAYOUT>
-bool launch_dot_split_layout(const MfmaLaunch& l, int32_t out_dtype, int row_blocks, hipStream_t stream);
+bool launch_dot_split_layout(const MfmaLaunch& l, int32_t out_dtype, int row_blocks, int col_blocks, hipStream_t stream);
 
 #ifndef GSPMD_TU_LAYOUT
-inline bool launch_dot_split(const MfmaLaunch& l, int32_t layout, int32_t out_dtype, int row_blocks, hipStream_t stream) {
+inline bool launch_dot_split(const MfmaLaunch& l, int32_t layout, int32_t out_dtype, int row_blocks, int col_blocks, hipStream_t stream) {
   switch (layout & 3) {
-    case 0: return launch_dot_split_layout<0>(l, out_dtype, row_blocks, stream);
-    case 1: return launch_dot_split_layout<1>(l, out_dtype, row_blocks, stream);
-    case 2: return launch_dot_split_layout<2>(l, out_dtype, row_blocks, stream);
-    default: return launch_dot_split_layout<3>(l, out_dtype, row_blocks, stream);
+    case 0: return launch_dot_split_layout<0>(l, out_dtype, row_blocks, col_blocks, stream);
+    case 1: return launch_dot_split_layout<1>(l, out_dtype, row_blocks, col_blocks, stream);
+    case 2: return launch_dot_split_layout<2>(l, out_dtype, row_blocks, col_blocks, stream);
+    default: return launch_dot_split_layout<3>(l, out_dtype, row_blocks, col_blocks, stream);
   }
 }
 #endif

@@ -28,7 +28,7 @@ typedef struct {
    * the partial sums or counters and slots of a sum lie */
   int64_t table_bytes, sums_begin, sums_end;
   int32_t moved_back;   /* last only: problems whose last tile column is moved back (all members of a sum, or none) */
-  int32_t reserved;
+  int32_t col_blocks;   /* dot_split_kernel: 2 (with 1 or 2 row blocks) or 4; pin: 0 is 4 */
 } gspmd_testing_launch;
 
 int32_t gspmd_testing_pin(const gspmd_testing_launch* pin);
