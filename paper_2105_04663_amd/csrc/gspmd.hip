@@ -190,7 +190,8 @@ double big_us(const LaunchSize& s, bool staged) {
   auto step = [&](double fill) { return s.rows <= 96 ? 0.75 : 0.85 + 0.45 * fill * fill; };
   const double first = static_cast<double>(std::min<int64_t>(s.big, 256)), later = static_cast<double>(s.big) - first;
   const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * first + 0.1 * later : 0.0;
-  if (staged) return (14.0 + steps * (std::min(s.loose_cols, s.loose_rows_of_lhs) < 8 ? 7.0 : 2.0)) * (full + (part == 0.0 ? 0.0 : full == 0.0 ? 1.0 : 0.6 + 0.4 * part)) + slots;
+  const double tile = std::min(s.loose_cols, s.loose_rows_of_lhs) < 8 ? 14.0 + steps * 7.0 : std::min(8.0 + steps * 3.4, 14.0 + steps * 2.0);
+  if (staged) return tile * (full + (part == 0.0 ? 0.0 : full == 0.0 ? 1.0 : 0.8 + 0.2 * part)) + slots;
   if (s.rows > 96 && full >= 2.0) return (full + part) * (beside + steps * 1.25) + slots;
   return full * (beside + steps * step(1.0)) + (part > 0.0 ? beside + steps * step(part) : 0.0) + slots;
 }
@@ -202,8 +203,8 @@ double mid_us(const LaunchSize& s) {
   const double one = long_sum ? 0.30 : 0.205, two = long_sum ? 0.44 : 0.40;
   return static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
 }
-// Operands that take no direct loads, through registers.  dot_mfma_kernel: 14 us and 2.0 us per 64-wide step, a last round that is not full between 0.6 and 1 of
-// that.  dot_mid_kernel: 8.8 us (7 from the second round on) and per 32-wide step 0.27 us with one operand at odd addresses and 0.31 with both while a compute
+// Operands that take no direct loads, through registers.  dot_mfma_kernel: 14 us and 2.0 us per 64-wide step (8 and 3.4 up to four), a last round that is not full between 0.8 and 1 of
+// that.  dot_mid_kernel: 7 us and per 32-wide step 0.27 us with one operand at odd addresses and 0.31 with both while a compute
 // unit has one workgroup, 0.54 and 0.69 with two, a last round of more than 256 again in part.  Fitted to 40 drawn launches (us, 256 x 256 / 128 x 128 tiles;
 // M x K x N): 5995 x 2709 x 877 104 / 63   six of 1432 x 2183 x 775 85 / 57   six of 354 x 817 x 2307 39 / 28   4330 x 146 x 4633 40 / 28   32 of 324 x 753 x 325
 //   38 / 27   32 of 554 x 840 x 669 72 / 46   six of 1083 x 1389 x 1844 55 / 65   six of 975 x 889 x 2316 45 / 47   32 of 716 x 411 x 281 26 / 30
@@ -211,8 +212,8 @@ double mid_staged_us(const LaunchSize& s) {
   const bool both = s.a_odd && s.b_odd, any = s.a_odd || s.b_odd;
   const double steps = static_cast<double>((s.k + 31) / 32), one = both ? 0.31 : any ? 0.27 : 0.16, two = both ? 0.69 : any ? 0.54 : 0.32;
   const int64_t full = s.mid / 512, part = s.mid % 512;
-  const double last = part == 0 ? 0.0 : 8.8 + steps * (part <= 256 ? one : two * (0.6 + 0.4 * static_cast<double>(part) / 512.0));
-  return static_cast<double>(full) * ((full >= 2 ? 7.0 : 8.8) + steps * two) + last;
+  const double last = part == 0 ? 0.0 : 7.0 + steps * (part <= 256 ? one : two * (0.6 + 0.4 * static_cast<double>(part) / 512.0));
+  return static_cast<double>(full) * (7.0 + steps * two) + last;
 }
 
 // dot_pair_kernel: 6.5 us, and rounds of 512 workgroups of 5.2 us and 0.70 us per 32-wide step, two of them on a compute unit, more where an operand is
@@ -251,7 +252,7 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 // dot_split_kernel's order of summation is another one: partial sums along a contracting mesh dimension (`ordered`) stay with the
 // first two, so that the joined sum, the two-launch sum and partials that a caller sums agree bit for bit; and beyond 256 rows it is taken
 // from K = 1024 on (below, dot_mid_kernel is within 4 us).
-// Operands that take no direct loads (kPathMfmaStaged) cost the address unit more: big_us, mid_staged_us; rounds of 3.2, 4.3, 6.5 us and 1.2, 1.25, 1.55 us
+// Operands that take no direct loads (kPathMfmaStaged) cost the address unit more: big_us, mid_staged_us; rounds of 3.2, 4.3, 8 us and 1.2, 1.25, 1.55 us
 // per eight steps in the split kernel (256 x 256 staged tiles / 1, 2, 4 row blocks):
 //   601 x 2001 x 601: 78 / 25, 15, 20     2001 x 1003 x 2001: 45 / 136, 82, 59     301 x 1001 x 301: 45 / 9, 10, 14
 //   3826 x 102 x 538: 14 / 35, 25, 21     482 x 111 x 5292: 14 / 50, 34, 25        2289 x 293 x 885: 21 / 35, 23, 17
@@ -293,7 +294,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
     const double rounds8 = static_cast<double>((size.k + 255) / 256);
     const struct { int blocks, cols; double aligned, beside, unaligned, elements; } kinds[] = {
-        {1, 4, 1.0, 3.2, 1.2, 5.0}, {2, 4, 1.3, 4.3, 1.25, 5.5}, {4, 4, 1.7, 6.5, 1.55, 8.5}, {1, 2, 0.75, 3.2, 0.8, 2.2}, {2, 2, 1.05, 4.3, 0.9, 4.5}};
+        {1, 4, 1.0, 3.2, 1.2, 5.0}, {2, 4, 1.3, 4.3, 1.25, 5.5}, {4, 4, 1.7, 8.0, 1.55, 8.5}, {1, 2, 0.75, 3.2, 0.8, 2.2}, {2, 2, 1.05, 4.3, 0.9, 4.5}};
     for (const auto& kind : kinds) {
       int64_t tiles = 0;
       for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, 16 * kind.cols);
