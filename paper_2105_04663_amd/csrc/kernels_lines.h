@@ -1,0 +1,82 @@
+// The end of a bf16 MFMA kernel: a wave's 16 x 16 accumulator blocks, 64 columns wide, out to global memory in whole lines.  In the accumulators'
+// own order (a lane holds columns n .. n + 3 of row m of a block) an instruction stores 32 bytes (bf16) or 64 (float32) of each of 16 rows;
+// staged through the wave's own slice of LDS it stores 16 bytes per lane, lines of 128 or 256 bytes, at the output's element alignment.
+// dot_mid_kernel's tiles all end at about the same time, so what their stores take is time that nothing hides.  Measured there (us, in the accumulators' order / whole lines):
+// 2048 x 1024 x 2048 12.3 / 10.5, 1500 x 512 x 3000 13.4 / 11.3, four of 1000 x 768 x 1024 11.8 / 9.7, six of 601 x 1203 x 697 19.9 / 18.0, 32 of 152 x 209 x 1094 19.3 / 15.7, sums of
+// 2048 x 8192 x 2048 over 4 members 61.0 / 59.7 and over 2, two groups, 63.7 / 60.8; float32 outputs 2048 x 1024 x 4096, four times with their sum, 105.8 / 102.6.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "kernels_basic.h"
+#include "mfma_common.h"
+#include "plan.h"
+
+namespace gspmd {
+
+template <typename TOut> constexpr int line_pitch() { return 64 * static_cast<int>(sizeof(TOut)) + 16; }
+// LDS bytes of a wave that stages `blocks` rows of blocks at once
+template <typename TOut> constexpr int line_slice(int blocks) { return blocks * 16 * line_pitch<TOut>(); }
+
+// Block (i, j) of BLOCKS x 4 is value(i, j); the wave's first row and column are row0 and col0.  `inside`: all of the workgroup's tile is valid.
+// STREAMED: non-temporal stores, for bf16 outputs, which the launch does not read again: four experts' weight gradients of 4096 x 8192 107 us, without the hint 139; 1500 x 512 x
+// 3000 11.3, 11.7.  Not where rows start at odd addresses and lines are stored in two parts (601 x 1203 x 697 18.4 with it, 17.9 without), nor float32
+// ones, mostly partial sums that the next kernel reads (4096 x 512 x 2048, four times with their sum, 81.2, 79.2).
+template <typename TOut, int BLOCKS, int AT_ONCE, bool STREAMED, typename Value>
+__device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL TOut* C, const Problem& P, int row0, int col0, bool inside, int epilogue, int lane, Value value) {
+  constexpr int V = 16 / static_cast<int>(sizeof(TOut)), kLanes = 64 / V, kRowsAt = 64 / kLanes;       // columns of a lane, lanes of a row, rows of a store
+  constexpr int kPitch = line_pitch<TOut>();
+  typedef TOut out_vec __attribute__((ext_vector_type(V), aligned(sizeof(TOut))));
+  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+#pragma unroll
+  for (int pass = 0; pass < BLOCKS / AT_ONCE; ++pass) {
+    auto stage = [&](auto relu_tag) {           // (Relu or not is decided once: inside the loop it becomes a compare and a select per element)
+      constexpr int32_t kEpilogue = decltype(relu_tag)::value ? GSPMD_EPILOGUE_RELU : GSPMD_EPILOGUE_NONE;
+#pragma unroll
+      for (int b = 0; b < AT_ONCE; ++b)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float4_t x = value(pass * AT_ONCE + b, j);
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = apply_epilogue(x[e], kEpilogue);
+          unsigned char* at = slice + (b * 16 + (lane & 15)) * kPitch + (j * 16 + (lane >> 4) * 4) * sizeof(TOut);
+          if constexpr (sizeof(TOut) == 2)
+            *reinterpret_cast<bf16x4_t*>(at) = bf16x4_t{static_cast<__bf16>(v[0]), static_cast<__bf16>(v[1]), static_cast<__bf16>(v[2]), static_cast<__bf16>(v[3])};
+          else
+            *reinterpret_cast<float4_t*>(at) = float4_t{v[0], v[1], v[2], v[3]};
+        }
+    };
+    if (epilogue == GSPMD_EPILOGUE_RELU) stage(std::true_type{}); else stage(std::false_type{});
+    const int row = row0 + pass * AT_ONCE * 16 + lane / kLanes, col = col0 + lane % kLanes * V;
+    GSPMD_GLOBAL TOut* const c0 = C + static_cast<int64_t>(row) * P.ldc + col;
+    const int keep = min(V, P.Nv - col), room = min(V, P.Ns - col);
+#pragma unroll
+    for (int p = 0; p < AT_ONCE * 16 / kRowsAt; ++p) {
+      u32x4_t v = *reinterpret_cast<const u32x4_t*>(slice + (p * kRowsAt + lane / kLanes) * kPitch + lane % kLanes * 16);
+      GSPMD_GLOBAL TOut* const c = c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc;
+      if (inside) {
+        if constexpr (STREAMED) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)c);
+        else *(GSPMD_GLOBAL out_vec*)c = __builtin_bit_cast(out_vec, v);
+        continue;
+      }
+      if (row + p * kRowsAt >= P.Mv || room <= 0) continue;
+      if constexpr (sizeof(TOut) == 2) {
+        v = mask_tail8(v, keep);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e >= keep) v[e] = 0u;
+      }
+      const out_vec o = __builtin_bit_cast(out_vec, v);
+      if (room == V) *(GSPMD_GLOBAL out_vec*)c = o;
+      else
+#pragma unroll
+        for (int e = 0; e < V; ++e) if (e < room) c[e] = o[e];
+    }
+  }
+}
+
+}  // namespace gspmd

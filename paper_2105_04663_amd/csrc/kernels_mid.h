@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "kernels_basic.h"
+#include "kernels_lines.h"
 #include "launch.h"
 #include "mfma_common.h"
 #include "plan.h"
@@ -414,43 +415,14 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
     if (!run_on) add_member(member == 0);
   }
 
-  // ---- epilogue: a lane holds columns n .. n + 3 of row m per 16 x 16 block
+  // ---- epilogue
   GSPMD_GLOBAL TOut* const C = (GSPMD_GLOBAL TOut*)P.C;
-  typedef TOut out4 __attribute__((ext_vector_type(4), aligned(sizeof(TOut))));
-  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-  const bool inside = m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + wm + i * 16 + (lane & 15);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + wn + j * 16 + (lane >> 4) * 4;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float x;
-        if constexpr (CHAIN) x = sum[i][j][e]; else x = acc[i][j][e];
-        v[e] = apply_epilogue(x, epilogue);
-      }
-      if (!inside) {
-        if (m >= P.Mv || n >= P.Ns) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) if (n + e >= P.Nv) v[e] = 0.f;
-      }
-      out4 o;
-      if constexpr (sizeof(TOut) == 2) {
-        const bf16x4_t h = {static_cast<__bf16>(v[0]), static_cast<__bf16>(v[1]), static_cast<__bf16>(v[2]), static_cast<__bf16>(v[3])};
-        o = __builtin_bit_cast(out4, h);
-      } else {
-        o = out4{v[0], v[1], v[2], v[3]};
-      }
-      GSPMD_GLOBAL TOut* c = C + static_cast<int64_t>(m) * P.ldc + n;
-      if (inside || n + 4 <= P.Ns) *(GSPMD_GLOBAL out4*)c = o;
-      else
-#pragma unroll
-        for (int e = 0; e < 4; ++e) if (n + e < P.Ns) c[e] = o[e];
-    }
-  }
+  constexpr int kAtOnce = sizeof(TOut) == 2 ? 4 : 2;
+  static_assert(4 * line_slice<TOut>(kAtOnce) <= R * kMidStage, "");
+  __syncthreads();                              // every wave's fragment reads are over
+  store_lines<TOut, 4, kAtOnce, !STAGED && sizeof(TOut) == 2>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, epilogue, lane, [&](int i, int j) {
+    if constexpr (CHAIN) return sum[i][j]; else return acc[i][j];
+  });
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears)
   const int m_done = min(m_nom + kMidTile, P.Mv), moved_end = n0 + kMidTile, col_end = min(n_nom + kMidTile, P.Ns);

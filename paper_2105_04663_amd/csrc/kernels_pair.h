@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "kernels_basic.h"
+#include "kernels_lines.h"
 #include "launch.h"
 #include "mfma_common.h"
 #include "plan.h"
@@ -187,64 +188,13 @@ __global__ __launch_bounds__(kPairThreads, 2) void dot_pair_kernel(const InlineP
     ending(std::integral_constant<int, 0>{}, ending);
   }
 
-  // ---- epilogue: a lane holds columns n .. n + 3 of row m per 16 x 16 block; staged through the wave's own slice of LDS and stored in whole
-  // lines, 16 bytes per lane at the output's element alignment.
+  // ---- epilogue
   GSPMD_GLOBAL TOut* const C = (GSPMD_GLOBAL TOut*)P.C;
-  constexpr int V = 16 / static_cast<int>(sizeof(TOut)), kLanes = 64 / V, kRowsAt = 64 / kLanes;       // columns of a lane, lanes of a row, rows of a store
-  constexpr int kPasses = sizeof(TOut) == 2 ? 1 : 2, kBlocks = 8 / kPasses, kPitch = 64 * static_cast<int>(sizeof(TOut)) + 16;
-  static_assert(4 * kBlocks * 16 * kPitch <= kPairLds, "");
-  typedef TOut out_vec __attribute__((ext_vector_type(V), aligned(sizeof(TOut))));
-  typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-  unsigned char* const slice = smem + wave * (kBlocks * 16 * kPitch);
-  const bool inside = m0 + kPairRows <= P.Mv && n0 + kPairCols <= P.Nv;
+  constexpr int kAtOnce = sizeof(TOut) == 2 ? 8 : 4;
+  static_assert(4 * line_slice<TOut>(kAtOnce) <= kPairLds, "");
   __syncthreads();                              // every wave's fragment reads are over
-#pragma unroll
-  for (int pass = 0; pass < kPasses; ++pass) {
-    auto stage = [&](auto relu_tag) {           // (Relu or not is decided once: inside the loop it becomes a compare and a select per element)
-      constexpr int32_t kEpilogue = decltype(relu_tag)::value ? GSPMD_EPILOGUE_RELU : GSPMD_EPILOGUE_NONE;
-#pragma unroll
-      for (int b = 0; b < kBlocks; ++b)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = apply_epilogue(acc[pass * kBlocks + b][j][e], kEpilogue);
-          unsigned char* at = slice + (b * 16 + (lane & 15)) * kPitch + (j * 16 + (lane >> 4) * 4) * sizeof(TOut);
-          if constexpr (sizeof(TOut) == 2)
-            *reinterpret_cast<bf16x4_t*>(at) = bf16x4_t{static_cast<__bf16>(v[0]), static_cast<__bf16>(v[1]), static_cast<__bf16>(v[2]), static_cast<__bf16>(v[3])};
-          else
-            *reinterpret_cast<float4_t*>(at) = float4_t{v[0], v[1], v[2], v[3]};
-        }
-    };
-    if (epilogue == GSPMD_EPILOGUE_RELU) stage(std::true_type{}); else stage(std::false_type{});
-    const int row0 = m0 + wm + pass * kBlocks * 16 + lane / kLanes, col = n0 + wn + lane % kLanes * V;
-    GSPMD_GLOBAL TOut* const c0 = C + static_cast<int64_t>(row0) * P.ldc + col;
-    const int keep = min(V, P.Nv - col), room = min(V, P.Ns - col);
-#pragma unroll
-    for (int p = 0; p < kBlocks * 16 / kRowsAt; ++p) {
-      u32x4_t v = *reinterpret_cast<const u32x4_t*>(slice + (p * kRowsAt + lane / kLanes) * kPitch + lane % kLanes * 16);
-      GSPMD_GLOBAL TOut* const c = c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc;
-      if (inside) {
-        // bf16 outputs are not read again by the launch; float32 ones are mostly partial sums that the next kernel reads
-        if constexpr (sizeof(TOut) == 2) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)c);
-        else *(GSPMD_GLOBAL out_vec*)c = __builtin_bit_cast(out_vec, v);
-        continue;
-      }
-      if (row0 + p * kRowsAt >= P.Mv || room <= 0) continue;
-      if constexpr (sizeof(TOut) == 2) {
-        v = mask_tail8(v, keep);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (e >= keep) v[e] = 0u;
-      }
-      const out_vec o = __builtin_bit_cast(out_vec, v);
-      if (room == V) *(GSPMD_GLOBAL out_vec*)c = o;
-      else
-#pragma unroll
-        for (int e = 0; e < V; ++e) if (e < room) c[e] = o[e];
-    }
-  }
+  store_lines<TOut, 8, kAtOnce, sizeof(TOut) == 2>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kPairRows <= P.Mv && n0 + kPairCols <= P.Nv, epilogue, lane,
+                                [&](int i, int j) { return acc[i][j]; });
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears), and right of a tile that was moved back
   const int m_done = min(m0 + kPairRows, P.Mv), moved_end = n0 + kPairCols, col_end = min(n_nom + kPairCols, P.Ns);
