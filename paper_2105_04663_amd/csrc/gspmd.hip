@@ -140,15 +140,16 @@ thread_local gspmd_testing_launch t_pin{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_
 thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING_BY_RULE, 0, 0, 0, 0, 0, 0};
 
 // What a launch of dot_mfma_kernel or dot_mid_kernel takes, in us: straight lines through measured times.
-// dot_mfma_kernel: rounds of 256 workgroups of 9 us and 1.3 us per 64-wide K step, where the chip is full and its clock drops, down to 0.85
+// dot_mfma_kernel: rounds of 256 workgroups of 10 us and 1.3 us per 64-wide K step, where the chip is full and its clock drops, down to 0.85
 //   in a round of few (short tiles: 0.75), 2 us for what is left of K.  From two full rounds on 1.25 us, and the last
 //   round counts by its share, as the workgroups no longer start together.  Joined problems meet in slots: 4.6 us
 //   per member, the last arriver at a tile reading the others' contributions one after the other, and 0.05 us per contribution to a tile, 0.1 beyond 256
 //   (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38; 8, 16: 38; 8, 512: 59).
-// dot_mid_kernel: 8.8 us and 0.205 us per 32-wide step while a compute unit has one workgroup, 0.40 with two, then rounds of 512; the members of
+// dot_mid_kernel: 6.8 us and 0.205 us per 32-wide step while a compute unit has one workgroup, 0.37 with two, then rounds of 512; the members of
 //   a joined sum follow each other in one workgroup, 1.8 us apart where they are not alike and whole K steps long; 0.25 us per 32-wide tile
 //   that is left of K; in sums of more than one round of 512 0.44, and 0.30 in a last round of up to 256; a fifth more per step where a
-//   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Fitted to 60 drawn launches of 1 to 8 members; root mean square of the relative error 12 %.
+//   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Lines fitted to drawn launches, this kernel's share, dot_pair_kernel's and the
+//   256 x 256 tiles' 10 us again since outputs leave in whole lines: over 650 drawn products without a sum the choice takes 0.7 % more than the best of all kernels, 1.1 % before.
 // Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 118 / 60   512 x 8192 x 512: 117 / 47
 //   2048 x 4096 x 4096: 63 / 60   2048 x 1024 x 4096: 25 / 20   4653 x 7168 x 4288: 245 / 281   1456 x 1415 x 3969, two of them: 37 / 48
 //   2178 x 4736 x 1447, two: 75 / 61   1090 x 1333 x 1568, eight: 60 / 52   4 experts' weight gradients of 512 x 4096 x 8192: 122 / 227
@@ -186,7 +187,7 @@ LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
 }
 double big_us(const LaunchSize& s, bool staged) {
   const double steps = static_cast<double>((s.k + 63) / 64), full = static_cast<double>(s.big / 256), part = static_cast<double>(s.big % 256) / 256.0;
-  const double beside = 9.0 + (s.k % 64 ? 2.0 : 0.0);
+  const double beside = 10.0 + (s.k % 64 ? 2.0 : 0.0);
   auto step = [&](double fill) { return s.rows <= 96 ? 0.75 : 0.85 + 0.45 * fill * fill; };
   const double first = static_cast<double>(std::min<int64_t>(s.big, 256)), later = static_cast<double>(s.big) - first;
   const double slots = s.members > 1 ? 4.6 * static_cast<double>(s.members) + 0.05 * first + 0.1 * later : 0.0;
@@ -197,26 +198,26 @@ double big_us(const LaunchSize& s, bool staged) {
 }
 double mid_us(const LaunchSize& s) {
   const double m = static_cast<double>(s.members), left = static_cast<double>((s.k % 64 + 31) / 32);
-  const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 8.8 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
+  const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 6.8 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
   const int64_t part = s.mid % 512;
   const bool long_sum = s.members > 1 && s.mid > 512;
-  const double one = long_sum ? 0.30 : 0.205, two = long_sum ? 0.44 : 0.40;
+  const double one = long_sum ? 0.30 : 0.205, two = long_sum ? 0.44 : 0.37;
   return static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
 }
 // Operands that take no direct loads, through registers.  dot_mfma_kernel: 14 us and 2.0 us per 64-wide step (8 and 3.4 up to four), a last round that is not full between 0.8 and 1 of
-// that.  dot_mid_kernel: 7 us and per 32-wide step 0.27 us with one operand at odd addresses and 0.31 with both while a compute
+// that.  dot_mid_kernel: 4.7 us and per 32-wide step 0.27 us with one operand at odd addresses and 0.31 with both while a compute
 // unit has one workgroup, 0.54 and 0.69 with two, a last round of more than 256 again in part.  Fitted to 40 drawn launches (us, 256 x 256 / 128 x 128 tiles;
 // M x K x N): 5995 x 2709 x 877 104 / 63   six of 1432 x 2183 x 775 85 / 57   six of 354 x 817 x 2307 39 / 28   4330 x 146 x 4633 40 / 28   32 of 324 x 753 x 325
 //   38 / 27   32 of 554 x 840 x 669 72 / 46   six of 1083 x 1389 x 1844 55 / 65   six of 975 x 889 x 2316 45 / 47   32 of 716 x 411 x 281 26 / 30
-double mid_staged_us(const LaunchSize& s) {
+double mid_staged_us(const LaunchSize& s, double beside = 4.7) {
   const bool both = s.a_odd && s.b_odd, any = s.a_odd || s.b_odd;
   const double steps = static_cast<double>((s.k + 31) / 32), one = both ? 0.31 : any ? 0.27 : 0.16, two = both ? 0.69 : any ? 0.54 : 0.32;
   const int64_t full = s.mid / 512, part = s.mid % 512;
-  const double last = part == 0 ? 0.0 : 7.0 + steps * (part <= 256 ? one : two * (0.6 + 0.4 * static_cast<double>(part) / 512.0));
-  return static_cast<double>(full) * (7.0 + steps * two) + last;
+  const double last = part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two * (0.6 + 0.4 * static_cast<double>(part) / 512.0));
+  return static_cast<double>(full) * (beside + steps * two) + last;
 }
 
-// dot_pair_kernel: 6.5 us, and rounds of 512 workgroups of 5.2 us and 0.70 us per 32-wide step, two of them on a compute unit, more where an operand is
+// dot_pair_kernel: 5.8 us, and rounds of 512 workgroups of 5.2 us and 0.70 us per 32-wide step, two of them on a compute unit, more where an operand is
 //   K-contiguous (its half lines come twice from L2; the lhs is the larger part); in a last round about half of that per step
 //   where every compute unit has one, 2.3 us and three quarters of it where only half of them have; 0.1 and 0.2 us more where rows are not padded to 16 bytes (six of 356 x
 //   2088 x 2142: 34.9 / 40.0 / 38.9).  Measured (us, dot_mfma_kernel / dot_mid_kernel / dot_pair_kernel;
@@ -234,12 +235,12 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
   if (part > 256) last = 5.2 + steps * two * (0.6 + 0.4 * fill);
   else if (part > 128) last = steps * one;
   else if (part > 0) last = 2.3 + steps * one * 0.75;
-  return 6.5 + static_cast<double>(s.pair / 512) * round + std::max(last, fill * round);
+  return 5.8 + static_cast<double>(s.pair / 512) * round + std::max(last, fill * round);
 }
 
 // The kernels differ in what a launch pays beside its K loop, in how many workgroups it gives the chip, and in what
 // a workgroup draws from L2 per flop, so the choice compares estimates: the lines above, and for dot_split_kernel rounds of 256 workgroups of
-// 4 us and 1.0, 1.3, 1.7 us per eight 32-wide steps.  One problem, bf16, rows x K x N, us, dot_mfma_kernel / dot_split_kernel with 1, 2, 4 row
+// 4 us (8.5 with 4 row blocks where rows are not padded to 16 bytes: six of 98 x 154 x 1092 11.3, dot_mid_kernel 7.8) and 1.0, 1.3, 1.7 us per eight 32-wide steps.  One problem, bf16, rows x K x N, us, dot_mfma_kernel / dot_split_kernel with 1, 2, 4 row
 // blocks:
 //   32 x 8192 x 8192: 101 / 43, 51, 54        64 x 8192 x 8192: 105 / 62, 47, 65      256 x 8192 x 8192: 135 / 222, 140, 97
 //   32 x 2048 x 16384: 31 / 26, 19, 20        64 x 1024 x 1024: 14 / 6, 7, 10         256 x 2048 x 2048: 39 / 22, 13, 17
@@ -300,7 +301,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
       for (const auto& p : ps) tiles += tiles_of(p, 16 * kind.blocks, 16 * kind.cols);
       const bool whole = kind.cols == 4;
       const bool elements = size.loose_cols < (whole ? 16 * kind.cols : 8) || size.loose_rows_of_lhs < (whole ? 16 * kind.blocks : 8);
-      const double us = static_cast<double>((tiles + 255) / 256) * (loose ? kind.beside + rounds8 * (elements ? kind.elements : kind.unaligned) : 4.0 + rounds8 * kind.aligned);
+      const double us = static_cast<double>((tiles + 255) / 256) * (loose ? kind.beside + rounds8 * (elements ? kind.elements : kind.unaligned) : (path == kPathMfmaWords && kind.blocks == 4 ? 8.5 : 4.0) + rounds8 * kind.aligned);
       if (us < best) { best = us; choice = MfmaChoice{kMfmaSplit, kind.blocks, kind.cols}; }
     }
   }
@@ -315,9 +316,10 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
 //   over 2: 461 / 660 / 490   4227 x 5000 x 3328 over 4: - / 180 / 211   4096 x 16384 x 4096 over 4: 461 / 513 / 448.  The rule takes the least in
 //   all but the last, where it stays with the slots: its estimates are 4 % apart.
 constexpr int64_t kSeveralRounds = 512;
+constexpr double kStagedPartials = 7.0;      // us beside dot_mid_kernel's staged loop where it stores float32 partials (4.7 bf16 results): 1335 x 508 x 4085 over 2 members, unaligned: 46, in one launch 34
 double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
-  return choice.kernel == kMfmaMid ? choice.staged ? mid_staged_us(size) : mid_us(size) : choice.kernel == kMfmaPair ? pair_us(size, layout, choice.loose) : big_us(size, choice.staged);
+  return choice.kernel == kMfmaMid ? choice.staged ? mid_staged_us(size, kStagedPartials) : mid_us(size) : choice.kernel == kMfmaPair ? pair_us(size, layout, choice.loose) : big_us(size, choice.staged);
 }
 // What partials cost beside their launch: 1 us, 2.5 us per sum kernel (one per reduce group) and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
