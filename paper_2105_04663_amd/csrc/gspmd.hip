@@ -145,11 +145,12 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   round counts by its share, as the workgroups no longer start together.  Joined problems meet in slots: 4.6 us
 //   per member, the last arriver at a tile reading the others' contributions one after the other, and 0.05 us per contribution to a tile, 0.1 beyond 256
 //   (beyond the launch without: 2 members, 4 contributions 11 us; 2, 192: 17; 4, 24: 19; 4, 84: 25; 4, 256: 38; 8, 16: 38; 8, 512: 59).
-// dot_mid_kernel: 6.8 us and 0.205 us per 32-wide step while a compute unit has one workgroup, 0.37 with two, then rounds of 512; the members of
+// dot_mid_kernel: 2 us, and rounds of 512 workgroups of 4.5 us and 0.205 us per 32-wide step while a compute unit has one, 0.36 with two, 0.41 where the lhs is K-major; the members of
 //   a joined sum follow each other in one workgroup, 1.8 us apart where they are not alike and whole K steps long; 0.25 us per 32-wide tile
 //   that is left of K; in sums of more than one round of 512 0.44, and 0.30 in a last round of up to 256; a fifth more per step where a
-//   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Lines fitted to drawn launches, this kernel's share, dot_pair_kernel's and the
-//   256 x 256 tiles' 10 us again since outputs leave in whole lines: over 650 drawn products without a sum the choice takes 0.7 % more than the best of all kernels, 1.1 % before.
+//   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Fitted to drawn launches
+//   together with dot_pair_kernel's line and the 256 x 256 tiles' 10 us: over 937 drawn products without a sum the choice takes 0.7 % more than the best
+//   of all kernels pinned one after the other, 1.2 % with the lines from before outputs left in whole lines.
 // Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 118 / 60   512 x 8192 x 512: 117 / 47
 //   2048 x 4096 x 4096: 63 / 60   2048 x 1024 x 4096: 25 / 20   4653 x 7168 x 4288: 245 / 281   1456 x 1415 x 3969, two of them: 37 / 48
 //   2178 x 4736 x 1447, two: 75 / 61   1090 x 1333 x 1568, eight: 60 / 52   4 experts' weight gradients of 512 x 4096 x 8192: 122 / 227
@@ -196,13 +197,13 @@ double big_us(const LaunchSize& s, bool staged) {
   if (s.rows > 96 && full >= 2.0) return (full + part) * (beside + steps * 1.25) + slots;
   return full * (beside + steps * step(1.0)) + (part > 0.0 ? beside + steps * step(part) : 0.0) + slots;
 }
-double mid_us(const LaunchSize& s) {
+double mid_us(const LaunchSize& s, int32_t layout) {
   const double m = static_cast<double>(s.members), left = static_cast<double>((s.k % 64 + 31) / 32);
-  const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 6.8 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
+  const double steps = m * static_cast<double>((s.k + 31) / 32) * (s.broken_lines ? 1.2 : 1.0), beside = 4.5 + (s.whole_steps ? 0.0 : 1.8 * (m - 1.0)) + 0.25 * m * left;
   const int64_t part = s.mid % 512;
   const bool long_sum = s.members > 1 && s.mid > 512;
-  const double one = long_sum ? 0.30 : 0.205, two = long_sum ? 0.44 : 0.37;
-  return static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
+  const double one = long_sum ? 0.30 : 0.205, two = long_sum ? 0.44 : layout & GSPMD_LAYOUT_LHS_K_MAJOR ? 0.41 : 0.36;
+  return 2.0 + static_cast<double>(s.mid / 512) * (beside + steps * two) + (part == 0 ? 0.0 : beside + steps * (part <= 256 ? one : two));
 }
 // Operands that take no direct loads, through registers.  dot_mfma_kernel: 14 us and 2.0 us per 64-wide step (8 and 3.4 up to four), a last round that is not full between 0.8 and 1 of
 // that.  dot_mid_kernel: 4.7 us and per 32-wide step 0.27 us with one operand at odd addresses and 0.31 with both while a compute
@@ -285,7 +286,7 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (size.rows == 0) return choice;
   double best = big_us(size, choice.staged = big_staged(size, path, layout));
   if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
-    const double us = loose ? mid_staged_us(size) : mid_us(size);
+    const double us = loose ? mid_staged_us(size) : mid_us(size, layout);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, 0, loose}; }
   }
   if (pair_takes(size, path, layout)) {
@@ -319,7 +320,7 @@ constexpr int64_t kSeveralRounds = 512;
 constexpr double kStagedPartials = 7.0;      // us beside dot_mid_kernel's staged loop where it stores float32 partials (4.7 bf16 results): 1335 x 508 x 4085 over 2 members, unaligned: 46, in one launch 34
 double sum_us(const std::vector<Problem>& ps, const MfmaChoice& choice, int32_t layout) {
   const LaunchSize size = launch_size(ps, layout);
-  return choice.kernel == kMfmaMid ? choice.staged ? mid_staged_us(size, kStagedPartials) : mid_us(size) : choice.kernel == kMfmaPair ? pair_us(size, layout, choice.loose) : big_us(size, choice.staged);
+  return choice.kernel == kMfmaMid ? choice.staged ? mid_staged_us(size, kStagedPartials) : mid_us(size, layout) : choice.kernel == kMfmaPair ? pair_us(size, layout, choice.loose) : big_us(size, choice.staged);
 }
 // What partials cost beside their launch: 1 us, 2.5 us per sum kernel (one per reduce group) and 0.31 us per MB written and read back.  Measured, one launch / two (us; M x K x N over members): 141 x 7248 x 463 over 8: 60 / 19;
 // 659 x 4880 x 1316 over 2: 53 / 34; 727 x 205 x 74 over 8, unaligned: 51 / 19; 2048 x 8192 x 2048 over 4: 76 / 68, scattered: 77 / 76; 1335 x
