@@ -151,9 +151,9 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Fitted to drawn launches
 //   together with dot_pair_kernel's line and the 256 x 256 tiles' 10 us: over 937 drawn products without a sum the choice takes 0.7 % more than the best
 //   of all kernels pinned one after the other, 1.2 % with the lines from before outputs left in whole lines.
-// Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 118 / 60   512 x 8192 x 512: 117 / 47
-//   2048 x 4096 x 4096: 63 / 60   2048 x 1024 x 4096: 25 / 20   4653 x 7168 x 4288: 245 / 281   1456 x 1415 x 3969, two of them: 37 / 48
-//   2178 x 4736 x 1447, two: 75 / 61   1090 x 1333 x 1568, eight: 60 / 52   4 experts' weight gradients of 512 x 4096 x 8192: 122 / 227
+// Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 120 / 62   512 x 8192 x 512: 117 / 45
+//   2048 x 4096 x 4096: 66 / 60   2048 x 1024 x 4096: 22 / 19   4653 x 7168 x 4288: 255 / 267   1456 x 1415 x 3969, two of them: 38 / 45
+//   2178 x 4736 x 1447, two: 76 / 72   1090 x 1333 x 1568, eight: 61 / 52   2112 x 8000 x 2112: 111 / 90   4096 x 512 x 8192, four, both K-major: 143 / 159
 // Sums, slots / one after the other (K over all members): 2048 x 8192 x 2048 over 4: 78 / 64   1024 x 8192 x 2048 over 2, two groups: 75 / 59
 //   both K-major 2085 x 3540 x 1652 over 2, two groups: 64 / 60   1770 x 3303 x 2085 over 2, two groups: 65 / 67   1572 x 4544 x 3328 over 8: 136 / 88
 struct LaunchSize {
@@ -208,8 +208,8 @@ double mid_us(const LaunchSize& s, int32_t layout) {
 // Operands that take no direct loads, through registers.  dot_mfma_kernel: 14 us and 2.0 us per 64-wide step (8 and 3.4 up to four), a last round that is not full between 0.8 and 1 of
 // that.  dot_mid_kernel: 4.7 us and per 32-wide step 0.27 us with one operand at odd addresses and 0.31 with both while a compute
 // unit has one workgroup, 0.54 and 0.69 with two, a last round of more than 256 again in part.  Fitted to 40 drawn launches (us, 256 x 256 / 128 x 128 tiles;
-// M x K x N): 5995 x 2709 x 877 104 / 63   six of 1432 x 2183 x 775 85 / 57   six of 354 x 817 x 2307 39 / 28   4330 x 146 x 4633 40 / 28   32 of 324 x 753 x 325
-//   38 / 27   32 of 554 x 840 x 669 72 / 46   six of 1083 x 1389 x 1844 55 / 65   six of 975 x 889 x 2316 45 / 47   32 of 716 x 411 x 281 26 / 30
+// M x K x N): 5995 x 2709 x 877 103 / 61   six of 1432 x 2183 x 775 84 / 56   six of 354 x 817 x 2307 38 / 24   4330 x 146 x 4633 40 / 22   32 of 324 x 753 x 325
+//   37 / 24   32 of 554 x 840 x 669 72 / 41   six of 1083 x 1389 x 1844 55 / 62   six of 975 x 889 x 2316 43 / 42   32 of 716 x 411 x 281 25 / 25
 double mid_staged_us(const LaunchSize& s, double beside = 4.7) {
   const bool both = s.a_odd && s.b_odd, any = s.a_odd || s.b_odd;
   const double steps = static_cast<double>((s.k + 31) / 32), one = both ? 0.31 : any ? 0.27 : 0.16, two = both ? 0.69 : any ? 0.54 : 0.32;
@@ -221,10 +221,10 @@ double mid_staged_us(const LaunchSize& s, double beside = 4.7) {
 // dot_pair_kernel: 5.8 us, and rounds of 512 workgroups of 5.2 us and 0.70 us per 32-wide step, two of them on a compute unit, more where an operand is
 //   K-contiguous (its half lines come twice from L2; the lhs is the larger part); in a last round about half of that per step
 //   where every compute unit has one, 2.3 us and three quarters of it where only half of them have; 0.1 and 0.2 us more where rows are not padded to 16 bytes (six of 356 x
-//   2088 x 2142: 34.9 / 40.0 / 38.9).  Measured (us, dot_mfma_kernel / dot_mid_kernel / dot_pair_kernel;
-//   both K-major, then lhs K-contiguous): M x N = 2048 x 4096, K = 512 14.4 / 15.6 / 12.4, 14.5 / 15.4 / 12.9; 1024 21.3 / 22.8 / 19.0, 21.7 / 22.3 / 19.7; 2048 35.5 / 36.9 /
-//   30.6, 35.7 / 34.9 / 33.1   4096 x 4096, K = 200 13.8 / 19.7 / 12.3, 14.8 / 20.8 / 14.4; 512 20.4 / 28.5 / 20.6, 20.4 / 28.8 / 21.5; 2048 51 / 69 / 55, 50 / 68 / 64
-//   4096 x 8192, four of them, K = 64 70 / 100 / 53, 67 / 98 / 52; 200 102 / 150 / 83, 105 / 149 / 90; 512 142 / 238 / 133, 140 / 225 / 145; 1024 223 / 346 / 225, 221 / 336 / 256
+//   2088 x 2142: 34.6 / 37.1 / 38.5).  Measured (us, dot_mfma_kernel / dot_mid_kernel / dot_pair_kernel;
+//   both K-major, then lhs K-contiguous): M x N = 2048 x 4096, K = 512 14.5 / 12.4 / 11.7, 14.2 / 12.0 / 12.1; 1024 21.2 / 19.1 / 18.1, 21.3 / 18.9 / 19.6; 2048 35.7 / 33.3 /
+//   30.6, 35.5 / 32.2 / 34.2   4096 x 4096, K = 200 13.8 / 14.9 / 12.1, 13.6 / 15.1 / 13.7; 512 19.5 / 22.5 / 19.9, 19.2 / 22.2 / 21.7; 2048 53 / 65 / 57, 53 / 64 / 64
+//   4096 x 8192, four of them, K = 64 69 / 61 / 55, 67 / 59 / 54; 200 96 / 103 / 85, 100 / 105 / 91; 512 143 / 159 / 138, 142 / 158 / 148; 1024 238 / 283 / 242, 237 / 282 / 265
 double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
   const double steps = static_cast<double>((s.k + 31) / 32);
   const bool a_lines = layout & GSPMD_LAYOUT_LHS_K_MAJOR, b_lines = !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS);

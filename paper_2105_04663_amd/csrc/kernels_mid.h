@@ -12,7 +12,7 @@
 // with the transpose read.  A wave issues one fragment read or load after each MFMA (all of a tile's ahead of its MFMAs: 240 ns), and
 // the stages come round every five steps, so that their places are constants of the code.  One barrier per step.  With one workgroup
 // on a compute unit ten stages (160 KiB), loads six tiles ahead; with two five stages each, four ahead.
-// Measured (us, with 32-wide steps / now): 2048 x 8192 x 2048 73.5 / 60.5, 512 x 8192 x 512 67.7 / 47.3, 2048 x 4096 x 4096 73 / 60, 2112 x 8000 x
+// Measured (us, with 32-wide steps / now): 2048 x 8192 x 2048 73.5 / 62, 512 x 8192 x 512 67.7 / 45, 2048 x 4096 x 4096 73 / 60, 2112 x 8000 x
 // 2112 118 / 90, both K-contiguous 127 / 92.  2048 x 8192 x 2048 over 4 members: 64 with operands in the memory-side cache, 82 from HBM.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -40,8 +40,8 @@ constexpr int kMidUnroll = 5;                         // K steps after which the
 // STAGED: the variant for operands at odd element addresses, which direct loads do not take: a tile's chunks are loaded into registers two
 // half steps before they are put where the direct load would have put them, and K-major operands' last tiles are moved back so that
 // every chunk is whole.  Bound by the address unit, 64 cycles for a KiB at an odd address (both operands: 430 ns per 32-wide
-// tile, one 270).  Measured (us, before in 256 x 256 staged tiles or dot_split_kernel / now): 601 x 1203 x 697, six of them 49.5 / 21.5,
-// 4999 x 576 x 1193 28.1 / 18.5, 152 x 209 x 1094, 32 of them 23.7 / 22.
+// tile, one 270).  Measured (us, before in 256 x 256 staged tiles or dot_split_kernel / now): 601 x 1203 x 697, six of them 49.5 / 17.5,
+// 4999 x 576 x 1193 28.1 / 15.2, 152 x 209 x 1094, 32 of them 23.7 / 16.6.
 template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU, bool STAGED>
 __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (one: the sums' accumulators take the other half of the registers)
  void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
