@@ -16,6 +16,7 @@ untimed for 80 ms, so that the clock has recovered from the idle staging period 
 from __future__ import annotations
 
 import argparse
+import ctypes
 import json
 import os
 import sys
@@ -31,6 +32,15 @@ FFN_TRAFFIC_BYTES = 3.224e9 + 0.268e9
 FFN_TRAFFIC_SOURCE = ("profiles/dot_mfma_kernel_ffn_share.md: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE per dispatch, scaled by "
                       "bench.py --calibrate-copy; a profiler figure quoted here, not measured by this run")
 METRIC = "per-shard einsum bf16 TFLOP/s and % of MI355X MFMA peak (1 GPU)"
+
+KERNELS = {0: "dot_fallback_kernel", 1: "dot_mfma_kernel", 2: "dot_mid_kernel", 3: "dot_split_kernel", 5: "dot_pair_kernel"}     # csrc/testing.h
+
+
+def kernel_taken(lib) -> str:
+    """The contraction kernel of this thread's last Dot."""
+    launch = (ctypes.c_int32 * 32)()               # gspmd_testing_launch, whose first field it is
+    assert lib.gspmd_testing_last(ctypes.byref(launch)) == 0
+    return KERNELS[launch[0]]
 
 
 def parse():
@@ -242,7 +252,7 @@ def main():
                  # workload has them, the zero fill and the sum of partials
                  "roofline": {"bound": "mfma", "achieved": round(fl / (ev * 1e-3) / 1e12, 2), "peak": PEAK_BF16_TFLOPS,
                               "unit": "TFLOP/s", "frac": round(fl / (ev * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, 4), "flops": fl,
-                              "kernel": "dot_mfma_kernel", "device_ms": round(ev, 4)}}
+                              "kernel": kernel_taken(g.load_library()), "device_ms": round(ev, 4)}}
         if s2.fill is not None:
             entry["fill"] = [int(x) for x in s2.fill]
         del s2
