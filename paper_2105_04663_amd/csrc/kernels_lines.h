@@ -50,6 +50,7 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
         }
     };
     if (epilogue == GSPMD_EPILOGUE_RELU) stage(std::true_type{}); else stage(std::false_type{});
+    staged_in_order();
     const int row = row0 + pass * AT_ONCE * 16 + lane / kLanes, col = col0 + lane % kLanes * V;
     GSPMD_GLOBAL TOut* const c0 = C + static_cast<int64_t>(row) * P.ldc + col;
     const int keep = min(V, P.Nv - col), room = min(V, P.Ns - col);
@@ -76,6 +77,7 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
 #pragma unroll
         for (int e = 0; e < V; ++e) if (e < room) c[e] = o[e];
     }
+    staged_in_order();                          // the next pass stages into what this one reads
   }
 }
 

@@ -26,6 +26,10 @@ __device__ __forceinline__ void global_to_lds16(const void* sbase, uint32_t voff
                :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
+// Between staging in a wave's slice of LDS and reading there what other lanes have staged, and before the next staging.  A wave's LDS accesses are carried out
+// in the order of the code, so nothing waits; but the compiler sees one lane, for which a store and a read at other addresses may change places.
+__device__ __forceinline__ void staged_in_order() { asm volatile("" ::: "memory"); }
+
 __device__ __forceinline__ u32x4_t mask_tail8(u32x4_t v, int keep) {   // keep first `keep` of 8 bf16
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
