@@ -625,6 +625,7 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
         }
     };
     if (relu) stage(std::true_type{}); else stage(std::false_type{});
+    staged_in_order();
     out16_t* c0 = (out16_t*)(Cg + static_cast<int64_t>(m0 + wm * 128 + (lane >> 3)) * P.ldc + n0 + wn * 64 + (lane & 7) * 8);
     const int64_t pitch8 = static_cast<int64_t>(P.ldc);      // 8 rows of bf16 in units of 16 bytes
     const int row0 = wm * 128 + (lane >> 3);
@@ -686,9 +687,11 @@ __global__ __attribute__((aligned(kMfmaCodeAlign))) __launch_bounds__(kMfmaThrea
         }
       };
       if (relu) stage(std::true_type{}); else stage(std::false_type{});
+      staged_in_order();
       u32x4_t v[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) v[i] = *reinterpret_cast<const u32x4_t*>(slice + (i * 4 + (lane >> 4)) * kPitch + (lane & 15) * 16);
+      staged_in_order();
       if (whole) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) c0[(pass * 16 + i) * pitch4] = v[i];
