@@ -74,6 +74,11 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   // Members that are alike follow each other without a break: the loads of the next one are under way while this one's last steps are
   // multiplied (those with something left of K in the loop that is not unrolled, so only short ones).  Others are taken one by one.
   const bool run_on = CHAIN && (P.flags & kProblemRunsOn) != 0;
+  // A sum's kernel with two workgroups on a compute unit has 256 registers, and its loop takes them all: what only a member's start, its rest of K and the
+  // epilogue need is worked out there.  Kept from the start, 7 to 17 registers were spilled and reloaded for every member (us, spilled / now: 2048 x 2048 x 8192 over
+  // 2 members, two groups 64.0 / 61.1, 2048 x 8192 x 4096 over 4 128.0 / 123.4, float32 results of 3072 x 2000 x 3072 over 2 59.7 / 55.8; 31 sums of all layouts 1.00 to 1.07 times as fast).
+  constexpr bool kFewRegisters = CHAIN && PER_CU == 2;
+  auto lane_here = [&]() { return kFewRegisters ? lane_now() : lane; };
 
   float4_t acc[4][4], sum[CHAIN ? 4 : 1][CHAIN ? 4 : 1];
   // Fragment addresses.  LDS offsets in instructions have 16 bits: stages are addressed from a register per four of them (with five
@@ -82,20 +87,34 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   constexpr int kGroups = R == 10 ? 3 : 2;
   const int a_half = wm >> 6, b_half = wn >> 6;
   uint32_t a_reg[kGroups][AKM ? 4 : 2], b_reg[kGroups][BKC ? 2 : 4];
+  auto half_at = [&](int g, int half) { return R == 5 && g == 1 ? (half ? 0 : 4) : g * 4 + half; };
 #pragma unroll
-  for (int g = 0; g < kGroups; ++g) {
-    auto half_at = [&](int half) { return R == 5 && g == 1 ? (half ? 0 : 4) : g * 4 + half; };
+  for (int g = 0; g < (kFewRegisters ? 1 : kGroups); ++g) {
 #pragma unroll
     for (int i = 0; i < (AKM ? 4 : 2); ++i) {
-      a_reg[g][i] = lds0 + (AKM ? (mid_km_frag_offset(wm, lane) ^ (i << 5)) + g * 4 * kMidStage : (kc_half_frag_offset(0, lane) ^ (i * 64)) + half_at(a_half) * kMidStage);
+      a_reg[g][i] = lds0 + (AKM ? (mid_km_frag_offset(wm, lane) ^ (i << 5)) + g * 4 * kMidStage : (kc_half_frag_offset(0, lane) ^ (i * 64)) + half_at(g, a_half) * kMidStage);
       asm volatile("" : "+v"(a_reg[g][i]));
     }
 #pragma unroll
     for (int i = 0; i < (BKC ? 2 : 4); ++i) {
-      b_reg[g][i] = lds0 + kMidPart + (BKC ? (kc_half_frag_offset(0, lane) ^ (i * 64)) + half_at(b_half) * kMidStage : (mid_km_frag_offset(wn, lane) ^ (i << 5)) + g * 4 * kMidStage);
+      b_reg[g][i] = lds0 + kMidPart + (BKC ? (kc_half_frag_offset(0, lane) ^ (i * 64)) + half_at(g, b_half) * kMidStage : (mid_km_frag_offset(wn, lane) ^ (i << 5)) + g * 4 * kMidStage);
       asm volatile("" : "+v"(b_reg[g][i]));
     }
   }
+  // where registers are few the second group's are worked out for every member
+  auto place_groups = [&]() {
+    if constexpr (kFewRegisters) {
+      auto from = [&](uint32_t first, bool kmajor, int half) {
+        uint32_t at;
+        asm volatile("v_add_u32_e32 %0, %1, %2" : "=v"(at) : "s"(kmajor ? 4 * kMidStage : (half_at(1, half) - half_at(0, half)) * kMidStage), "v"(first));
+        return at;
+      };
+#pragma unroll
+      for (int i = 0; i < (AKM ? 4 : 2); ++i) a_reg[1][i] = from(a_reg[0][i], AKM, a_half);
+#pragma unroll
+      for (int i = 0; i < (BKC ? 2 : 4); ++i) b_reg[1][i] = from(b_reg[0][i], !BKC, b_half);
+    }
+  };
   typedef __attribute__((address_space(3))) const u32x4_t lds_u32x4_t;
   auto read_kc = [&](uint32_t at) { return __builtin_bit_cast(bf16x8_t, *(lds_u32x4_t*)(uintptr_t)at); };
   auto read_km = [&](uint32_t at) {
@@ -133,6 +152,7 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
       __syncthreads();                          // every wave has read the last tile of the member before
     }
     clear();
+    place_groups();
     const int64_t a_first = AKM ? static_cast<int64_t>(m0) : static_cast<int64_t>(m0) * P.lda, b_first = BKC ? static_cast<int64_t>(n0) * P.ldb : static_cast<int64_t>(n0);
     const bf16_bits* a_base = static_cast<const bf16_bits*>(P.A) + a_first;
     const bf16_bits* b_base = static_cast<const bf16_bits*>(P.B) + b_first;
@@ -149,6 +169,7 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
     const int tiles = run_on ? own * (members - 1) + last_own : own;
     int a_off[2][2], b_off[2][2];               // this wave's two load instructions of each operand's part, in even and odd tiles
     auto place_loads = [&](int k_valid) {       // in a step of which `k_valid` k exist
+      const int lane = lane_here();
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -361,13 +382,14 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
       typedef GSPMD_GLOBAL const unsigned char* gbytes;
       const int at_part = left > kMfmaBK ? 1 : 0, here = left - at_part * kMfmaBK;
       const bf16_bits *a_tail = a_base + tiles * a_tile, *b_tail = b_base + tiles * b_tile;
-      int lane_here = lane;                     // (the places are worked out here, not kept in registers through the loop above)
-      asm volatile("" : "+v"(lane_here));
-      auto a_place = [&](int j) { return AKM ? a_off[0][j] : kc_load_offset(wave * 2 + j, lane_here, m0, P.Mv, P.lda); };
-      auto b_place = [&](int j) { return BKC ? kc_load_offset(wave * 2 + j, lane_here, n0, P.Nv, P.ldb) : b_off[0][j]; };
+      int lane_rest = lane_here();              // (the places are worked out here, not kept in registers through the loop above)
+      asm volatile("" : "+v"(lane_rest));
+      const int lane_of = kFewRegisters ? lane_rest : lane;
+      auto a_place = [&](int j) { return AKM ? a_off[0][j] : kc_load_offset(wave * 2 + j, lane_rest, m0, P.Mv, P.lda); };
+      auto b_place = [&](int j) { return BKC ? kc_load_offset(wave * 2 + j, lane_rest, n0, P.Nv, P.ldb) : b_off[0][j]; };
       auto chunk = [&](bool kmajor, const bf16_bits* base, int off, int q, int valid) -> u32x4_t {
         u32x4_t v = {0u, 0u, 0u, 0u};
-        const int kr = kmajor ? q * 4 + (lane >> 4) : ((lane & 3) ^ swz_a(q * 16 + (lane >> 2))) * 8;
+        const int kr = kmajor ? q * 4 + (lane_of >> 4) : ((lane_of & 3) ^ swz_a(q * 16 + (lane_of >> 2))) * 8;
         if (!kmajor) v = STAGED ? load_k_elements((GSPMD_GLOBAL const uint16_t*)((gbytes)base + off), valid - kr) : load_k_chunk((GSPMD_GLOBAL const uint32_t*)((gbytes)base + off), valid - kr);
         else if (kr < valid) v = *(GSPMD_GLOBAL const u32x4_elements_t*)((gbytes)base + off);
         return v;
@@ -380,7 +402,7 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
         }
       };
       auto put = [&](int tile, const u32x4_t (&v)[4]) {
-        unsigned char* at = smem + tile * kMidStage + wave * 2048 + lane * 16;
+        unsigned char* at = smem + tile * kMidStage + wave * 2048 + lane_of * 16;
 #pragma unroll
         for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4_t*>(at + (i >> 1) * kMidPart + (i & 1) * 1024) = v[i];
       };
@@ -406,8 +428,8 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
         const uint32_t stage = tile * kMidStage;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          fb[0][i] = BKC ? read_kc(lds0 + stage + kMidPart + kc_frag_offset(wn, lane) + i * 1024) : read_km(b_reg[0][BKC ? 0 : i] + stage);
-          fa[0][i] = AKM ? read_km(a_reg[0][AKM ? i : 0] + stage) : read_kc(lds0 + stage + kc_frag_offset(wm, lane) + i * 1024);
+          fb[0][i] = BKC ? read_kc(lds0 + stage + kMidPart + kc_frag_offset(wn, lane_of) + i * 1024) : read_km(b_reg[0][BKC ? 0 : i] + stage);
+          fa[0][i] = AKM ? read_km(a_reg[0][AKM ? i : 0] + stage) : read_kc(lds0 + stage + kc_frag_offset(wm, lane_of) + i * 1024);
         }
         multiply(0);
       }
@@ -419,17 +441,18 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   GSPMD_GLOBAL TOut* const C = (GSPMD_GLOBAL TOut*)P.C;
   constexpr int kAtOnce = sizeof(TOut) == 2 ? 4 : 2;
   static_assert(4 * line_slice<TOut>(kAtOnce) <= R * kMidStage, "");
+  const int lane_end = lane_here(), t_end = kFewRegisters ? wave * 64 + lane_end : t;
   __syncthreads();                              // every wave's fragment reads are over
-  store_lines<TOut, 4, kAtOnce, !STAGED && sizeof(TOut) == 2>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, epilogue, lane, [&](int i, int j) {
+  store_lines<TOut, 4, kAtOnce, !STAGED && sizeof(TOut) == 2>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, epilogue, lane_end, [&](int i, int j) {
     if constexpr (CHAIN) return sum[i][j]; else return acc[i][j];
   });
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears)
   const int m_done = min(m_nom + kMidTile, P.Mv), moved_end = n0 + kMidTile, col_end = min(n_nom + kMidTile, P.Ns);
-  if (n0 < n_nom) zero_block<kMidThreads, TOut>(C, P.ldc, m0, m_done, moved_end, col_end, t);            // right of a tile that was moved back
+  if (n0 < n_nom) zero_block<kMidThreads, TOut>(C, P.ldc, m0, m_done, moved_end, col_end, t_end);            // right of a tile that was moved back
   if (m_done == P.Mv) {
-    zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n0, min(moved_end, P.Ns), t);
-    if (n0 < n_nom) zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), moved_end, col_end, t);
+    zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), n0, min(moved_end, P.Ns), t_end);
+    if (n0 < n_nom) zero_block<kMidThreads, TOut>(C, P.ldc, P.Mv, rows_cleared(P.Mv, P.Ms), moved_end, col_end, t_end);
   }
 }
 

@@ -64,6 +64,7 @@ __global__ __launch_bounds__(kPairThreads, 2) void dot_pair_kernel(const InlineP
 
   int a_off[4], b_off[2];
   auto place_loads = [&](int k_valid) {         // in a tile of which `k_valid` k exist
+    const int lane = lane_now();                // (as below: nothing that only the last tile needs is kept in registers through the loop)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       a_off[j] = AKM ? mid_km_load_offset<kPairRows>(wave * 4 + j, lane, m0, P.Mv, P.lda, k_valid) : kc_load_offset(wave * 4 + j, lane, m0, P.Mv, P.lda, k_valid);
@@ -117,6 +118,7 @@ __global__ __launch_bounds__(kPairThreads, 2) void dot_pair_kernel(const InlineP
   auto clear_beyond = [&](int stage) {
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     asm volatile("" ::: "memory");
+    const int lane = lane_now();
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const bool kmajor = i < 4 ? AKM : !BKC;

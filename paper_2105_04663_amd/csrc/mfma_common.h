@@ -26,6 +26,13 @@ __device__ __forceinline__ void global_to_lds16(const void* sbase, uint32_t voff
                :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
+// This lane's number in its wave, worked out where it is asked for: what derives from it is neither kept in registers from earlier on nor moved out of a loop.
+__device__ __forceinline__ int lane_now() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
+
 // Between staging in a wave's slice of LDS and reading there what other lanes have staged, and before the next staging.  A wave's LDS accesses are carried out
 // in the order of the code, so nothing waits; but the compiler sees one lane, for which a store and a read at other addresses may change places.
 __device__ __forceinline__ void staged_in_order() { asm volatile("" ::: "memory"); }
