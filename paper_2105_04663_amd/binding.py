@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import ctypes as C
+import math
 import os
 import struct
 import sys
@@ -295,17 +296,36 @@ def plan_dot(mesh: Mesh, dims: DotDims, lhs_sh: Sharding, rhs_sh: Sharding, out_
     n = C.c_int64(0)
     lib = load_library()
     args = (C.byref(m), C.byref(d), C.byref(a), C.byref(b), C.byref(o), int(lhs_row_stride), int(rhs_row_stride),
-            int(out_row_stride), int(partition_id), _fill(lhs_fill))
+            int(out_row_stride), int(partition_id), _fill(lhs_fill, dims, lhs_sh, mesh, partition_id))
     _check(lib.gspmd_plan_dot(*args, None, 0, C.byref(n)), "gspmd_plan_dot")
     arr = (_CGemmDesc * max(1, n.value))()
     _check(lib.gspmd_plan_dot(*args, arr, n.value, C.byref(n)), "gspmd_plan_dot")
     return [{f: getattr(arr[i], f) for f, _ in _CGemmDesc._fields_} for i in range(n.value)]
 
 
-def _fill(fill):
+def _fill(fill, dims: DotDims, lhs_sh: Sharding, mesh: Mesh = None, partition_id: int = -1):
+    """The fill counts as an array.  One is read for every entry of the lhs's batch dimensions (of one partition: up to the last entry of its shard)."""
     if fill is None:
         return None
-    return _i64([int(x) for x in fill])
+    counts = [int(x) for x in fill]
+    shape, batch = [int(n) for n in lhs_sh.global_shape], [int(d) for d in dims.lhs_batch]
+    if any(n <= 0 for n in shape) or any(not 0 <= d < len(shape) for d in batch):      # nothing is read; the library refuses what is wrong
+        return _i64(counts)
+    last = [shape[d] - 1 for d in batch]
+    if mesh is not None and len(counts) < math.prod(shape[d] for d in batch):
+        try:
+            offset, valid, _ = shard_bounds(mesh, lhs_sh, partition_id)
+        except GspmdError:
+            return _i64(counts)
+        if 0 in valid:
+            return _i64(counts)
+        last = [offset[d] + valid[d] - 1 for d in batch]
+    entries = 0
+    for d, at in zip(batch, last):
+        entries = entries * shape[d] + at
+    if len(counts) <= entries:
+        raise ValueError(f"{entries + 1} fill counts are required, one per batch entry; got {len(counts)}")
+    return _i64(counts)
 
 
 def local_dot(mesh: Mesh, dims: DotDims, lhs: ShardBuf, lhs_sh: Sharding, rhs: ShardBuf, rhs_sh: Sharding,
@@ -319,7 +339,7 @@ def local_dot(mesh: Mesh, dims: DotDims, lhs: ShardBuf, lhs_sh: Sharding, rhs: S
     m, d, a, b, o = mesh._c(), dims._c(), lhs_sh._c(), rhs_sh._c(), out_sh._c()
     la, rb, ob = lhs._c(), rhs._c(), out._c()
     _check(load_library().gspmd_local_dot(C.byref(m), C.byref(d), C.byref(la), C.byref(a), C.byref(rb), C.byref(b),
-                                          C.byref(ob), C.byref(o), int(partition_id), _fill(lhs_fill), int(epilogue),
+                                          C.byref(ob), C.byref(o), int(partition_id), _fill(lhs_fill, dims, lhs_sh, mesh, partition_id), int(epilogue),
                                           C.c_void_p(workspace), int(workspace_bytes), C.c_void_p(stream)), "gspmd_local_dot")
 
 
@@ -337,7 +357,7 @@ def grouped_dot(mesh: Mesh, dims: DotDims, lhs_shards: Sequence[ShardBuf], lhs_s
         raise ValueError("one shard buffer per partition is required")
     m, d, a, b, o = mesh._c(), dims._c(), lhs_sh._c(), rhs_sh._c(), out_sh._c()
     _check(load_library().gspmd_grouped_dot(C.byref(m), C.byref(d), _bufs(lhs_shards), C.byref(a), _bufs(rhs_shards), C.byref(b),
-                                            _bufs(out_shards), C.byref(o), _fill(lhs_fill), int(epilogue),
+                                            _bufs(out_shards), C.byref(o), _fill(lhs_fill, dims, lhs_sh), int(epilogue),
                                             C.c_void_p(workspace), int(workspace_bytes), C.c_void_p(stream)), "gspmd_grouped_dot")
 
 
@@ -350,7 +370,7 @@ def grouped_dot_noalloc(mesh: Mesh, dims: DotDims, lhs_shards: Sequence[ShardBuf
         raise ValueError("one shard buffer per partition is required")
     m, d, a, b, o = mesh._c(), dims._c(), lhs_sh._c(), rhs_sh._c(), out_sh._c()
     _check(load_library().gspmd_grouped_dot_noalloc(C.byref(m), C.byref(d), _bufs(lhs_shards), C.byref(a), _bufs(rhs_shards),
-                                                    C.byref(b), _bufs(out_shards), C.byref(o), _fill(lhs_fill), int(epilogue),
+                                                    C.byref(b), _bufs(out_shards), C.byref(o), _fill(lhs_fill, dims, lhs_sh), int(epilogue),
                                                     C.c_void_p(stream)), "gspmd_grouped_dot_noalloc")
 
 
@@ -397,7 +417,7 @@ def resharded_dot(mesh: Mesh, dims: DotDims, lhs_shards: Sequence[ShardBuf], lhs
         raise ValueError("one shard buffer per partition is required")
     m, d, a, b, o = mesh._c(), dims._c(), lhs_sh._c(), rhs_sh._c(), out_sh._c()
     _check(load_library().gspmd_resharded_dot(C.byref(m), C.byref(d), _bufs(lhs_shards), C.byref(a), _bufs(rhs_shards), C.byref(b),
-                                              _bufs(out_shards), C.byref(o), _fill(lhs_fill), int(epilogue),
+                                              _bufs(out_shards), C.byref(o), _fill(lhs_fill, dims, lhs_sh), int(epilogue),
                                               C.c_void_p(workspace), int(workspace_bytes), C.c_void_p(stream)), "gspmd_resharded_dot")
 
 

@@ -106,14 +106,26 @@ static int shards(PyObject* seq, int64_t n, gspmd_shard_buf* out) {
   return 1;
 }
 
+/* Whether `n` fill counts are one for every entry of the lhs's batch dimensions at least: the library reads that many. */
+static int enough_fills(const forms* f, Py_ssize_t n) {
+  int64_t entries = 1;
+  for (int32_t i = 0; i < f->dims->n_batch; ++i) {
+    const int32_t d = f->dims->lhs_batch[i];
+    if (d < 0 || d >= f->lhs->rank || f->lhs->global_shape[d] < 0) return 0;
+    if (f->lhs->global_shape[d] > 0 && entries > n / f->lhs->global_shape[d]) return 0;
+    entries *= f->lhs->global_shape[d];
+  }
+  return f->dims->n_batch >= 0 && entries <= n;
+}
+
 /* fill counts: none (*fill NULL), or a list or tuple of ints, in `few` or in memory of their own */
 enum { kFills = 64 };
-static int fills(PyObject* seq, int64_t* few, int64_t** fill) {
+static int fills(PyObject* seq, const forms* f, int64_t* few, int64_t** fill) {
   *fill = NULL;
   if (seq == Py_None) return 1;
   if (!PyList_CheckExact(seq) && !PyTuple_CheckExact(seq)) return 0;
   const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-  if (n < 1 || !(*fill = n <= kFills ? few : PyMem_Malloc((size_t)n * sizeof(**fill)))) return 0;
+  if (n < 1 || !enough_fills(f, n) || !(*fill = n <= kFills ? few : PyMem_Malloc((size_t)n * sizeof(**fill)))) return 0;
   for (Py_ssize_t i = 0; i < n; ++i)
     if (!plain_int(PySequence_Fast_GET_ITEM(seq, i), *fill + i)) {
       if (*fill != few) PyMem_Free(*fill);
@@ -135,7 +147,7 @@ static PyObject* grouped_dot(PyObject* self, PyObject* const* a, Py_ssize_t n_ar
   gspmd_shard_buf few[3 * kOnStack], *bufs = few;
   int plain = n > 0;
   if (plain && n > kOnStack) plain = (bufs = PyMem_Malloc((size_t)(3 * n) * sizeof(*bufs))) != NULL;
-  plain = plain && shards(a[2], n, bufs) && shards(a[4], n, bufs + n) && shards(a[6], n, bufs + 2 * n) && fills(a[8], few_fills, &fill);
+  plain = plain && shards(a[2], n, bufs) && shards(a[4], n, bufs + n) && shards(a[6], n, bufs + 2 * n) && fills(a[8], &f, few_fills, &fill);
   int32_t status = 0;
   if (plain) {
     Py_BEGIN_ALLOW_THREADS
@@ -158,9 +170,9 @@ static PyObject* local_dot(PyObject* self, PyObject* const* a, Py_ssize_t n_args
   forms f;
   if (n_args != 14 || !local || !plain_int(a[8], &pid) || !plain_int(a[10], &epilogue) || epilogue != (int32_t)epilogue || !plain_int(a[11], &workspace) ||
       workspace < 0 || !plain_int(a[12], &bytes) || !plain_int(a[13], &stream) || stream < 0 || !shard(a[2], &l) || !shard(a[4], &r) || !shard(a[6], &o) ||
-      !fills(a[9], few_fills, &fill)) Py_RETURN_NONE;
-  if (!hold(a, &f)) {
-    if (fill != few_fills) PyMem_Free(fill);
+      !hold(a, &f)) Py_RETURN_NONE;
+  if (!fills(a[9], &f, few_fills, &fill)) {
+    let_go(&f);
     Py_RETURN_NONE;
   }
   int32_t status;

@@ -96,6 +96,37 @@ def test_what_is_not_plain_is_handed_back(native):
     assert native == [None, None]
 
 
+@pytest.mark.parametrize("held", [False, True])
+@pytest.mark.parametrize("P", [1, 4, 70])
+def test_fewer_fill_counts_than_batch_entries(native, P, held):
+    """One count is read for every batch entry, of one partition up to its last: a list that ends earlier would be read beyond its end."""
+    mesh, dims, bufs, sh = d = _dot(P, fill=True)
+    if held:
+        _run(*d, fill=[64] * P)
+        native.clear()
+    for short in ([64] * (P - 1), (64,) * (P - 1), []):
+        for call in (lambda: _run(*d, fill=short),
+                     lambda: g.grouped_dot_noalloc(mesh, dims, bufs[0], sh[0], bufs[1], sh[1], bufs[2], sh[2], short),
+                     lambda: g.resharded_dot(mesh, dims, bufs[0], sh[0], bufs[1], sh[1], bufs[2], sh[2], short, 1 << 30, 1 << 30),
+                     lambda: g.local_dot(mesh, dims, bufs[0][0], sh[0], bufs[1][0], sh[1], bufs[2][0], sh[2], P - 1, short, 1 << 30, 4096),
+                     lambda: g.plan_dot(mesh, dims, *sh, P - 1, lhs_fill=short)):
+            with pytest.raises(ValueError):
+                call()
+    assert all(status is None for status in native)
+    native.clear()
+    _run(*d, fill=[64] * (P + 3))                    # more than are read
+    _run(*d, fill=[64], local=True)                  # partition 0 reads the first alone
+    assert len(g.plan_dot(mesh, dims, *sh, 0, lhs_fill=[64])) == 1
+    assert native == [0, 0 if P == 1 else None]
+
+
+def test_fill_counts_of_what_is_refused_anyway(native):
+    mesh, dims, bufs, sh = _dot(4, fill=True)
+    for m, d, s in ((g.Mesh((4,), (0, 1, 2, 2)), dims, sh), (mesh, g.DotDims((7,), (0,), (2,), (1,)), sh), (mesh, dims, [g.Sharding((4, 64, 32), (0, 0, -1))] + sh[1:])):
+        with pytest.raises(g.GspmdError):
+            g.local_dot(m, d, bufs[0][0], s[0], bufs[1][0], s[1], bufs[2][0], s[2], 0, [64], 1 << 30, 4096)
+
+
 @pytest.mark.parametrize("local", [False, True])
 def test_statuses_are_those_of_ctypes(native, local, monkeypatch):
     mesh, dims, bufs, sh = _dot()
