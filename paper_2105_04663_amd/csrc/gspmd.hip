@@ -1069,7 +1069,7 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
       std::vector<Problem> live;
       for (const auto& q : joined) if (q.Mv > 0) live.push_back(q);
       const MfmaChoice one = pick_kernel(live, kernel_path(live, in_dtype, jlayout), jlayout, true);
-      js.chain = with_records(one.kernel) == kMfmaMid;
+      js.chain = jslots > 0 && with_records(one.kernel) == kMfmaMid;
       ok = one.kernel != kMfmaNone;
       if (ok && t_pin.one_launch >= 0) {
         ok = t_pin.one_launch == 1;
@@ -1097,7 +1097,10 @@ int32_t gspmd_grouped_dot(const gspmd_mesh* mesh, const gspmd_dot_dims* dims,
       js.tiles = jtiles;
       t_last.sums_begin = js.chain ? 0 : table_area;
       t_last.sums_end = js.chain ? 0 : table_area + joined_bytes(jtiles, jslots);
-      return launch_problems(joined, jlayout, in_dtype, out_dtype, epilogue, true, workspace, workspace_bytes, stream, &js);
+      // where only one member of every sum has any K nothing is joined: a launch like any other, by the kernel that the estimate was made for
+      st = launch_problems(joined, jlayout, in_dtype, out_dtype, epilogue, true, workspace, workspace_bytes, stream, jslots > 0 ? &js : nullptr);
+      t_last.one_launch = 1;
+      return st;
     }
   }
 
