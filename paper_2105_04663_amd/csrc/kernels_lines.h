@@ -20,15 +20,24 @@ template <typename TOut> constexpr int line_pitch() { return 64 * static_cast<in
 // LDS bytes of a wave that stages `blocks` rows of blocks at once
 template <typename TOut> constexpr int line_slice(int blocks) { return blocks * 16 * line_pitch<TOut>(); }
 
+// How whole tiles are stored (others, and rows that may start at odd addresses, as kLinesPlain).
+// kLinesThrough, dot_mid_kernel's bf16 outputs: written through to the memory side, where the next kernel finds them.  Left in the caches of the XCDs (kLinesPlain) they are
+// written back when the launch ends, which takes 0.4 to 0.7 us; past all caches (kLinesPast) the next kernel fetches them from HBM.  A product and one that reads it (us, plain / past /
+// through): 1024 x 2048 x 4096, then x 2048 48.2 / 55.1 / 47.4, 2048 x 1024 x 2048, then x 1024 31.2 / 33.4 / 30.6; sums over members 2048 x 8192 x 2048 over 4, then x 1024 83.2 / 85.7 /
+// 82.0, 4096 x 4096 x 2048 over 2, then x 512 78.3 / 82.7 / 77.3; the first product alone 20.9 / 20.2 / 19.9, the first sum 66.8 / 66.0 / 66.0.
+// kLinesPast, dot_pair_kernel's bf16 outputs, launches of many tiles: four experts' weight gradients of 4096 x 8192, K 384 109 us, plain 140, and with an update that reads them 262, 281; of
+// 2048 x 4096, K 2048 29.8, 31.0 and 39.1, 39.5.
+// kLinesPlain where rows start at odd addresses and lines are stored in two parts (601 x 1203 x 697 17.9, past 18.4), and float32 outputs, mostly partial sums that the next kernel
+// reads (4096 x 512 x 2048, four times with their sum, 79.2, past 81.2).
+enum LineStores { kLinesPlain, kLinesPast, kLinesThrough };
+
 // Block (i, j) of BLOCKS x 4 is value(i, j); the wave's first row and column are row0 and col0.  `inside`: all of the workgroup's tile is valid.
-// STREAMED: non-temporal stores, for bf16 outputs, which the launch does not read again: four experts' weight gradients of 4096 x 8192 107 us, without the hint 139; 1500 x 512 x
-// 3000 11.3, 11.7.  Not where rows start at odd addresses and lines are stored in two parts (601 x 1203 x 697 18.4 with it, 17.9 without), nor float32
-// ones, mostly partial sums that the next kernel reads (4096 x 512 x 2048, four times with their sum, 81.2, 79.2).
-template <typename TOut, int BLOCKS, int AT_ONCE, bool STREAMED, typename Value>
+template <typename TOut, int BLOCKS, int AT_ONCE, LineStores STORES, typename Value>
 __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL TOut* C, const Problem& P, int row0, int col0, bool inside, int epilogue, int lane, Value value) {
   constexpr int V = 16 / static_cast<int>(sizeof(TOut)), kLanes = 64 / V, kRowsAt = 64 / kLanes;       // columns of a lane, lanes of a row, rows of a store
   constexpr int kPitch = line_pitch<TOut>();
   typedef TOut out_vec __attribute__((ext_vector_type(V), aligned(sizeof(TOut))));
+  typedef unsigned int line_t __attribute__((vector_size(16)));
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
 #pragma unroll
   for (int pass = 0; pass < BLOCKS / AT_ONCE; ++pass) {
@@ -59,7 +68,8 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
       u32x4_t v = *reinterpret_cast<const u32x4_t*>(slice + (p * kRowsAt + lane / kLanes) * kPitch + lane % kLanes * 16);
       GSPMD_GLOBAL TOut* const c = c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc;
       if (inside) {
-        if constexpr (STREAMED) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)c);
+        if constexpr (STORES == kLinesPast) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)c);
+        else if constexpr (STORES == kLinesThrough) __builtin_amdgcn_global_store_b128((GSPMD_GLOBAL line_t*)c, __builtin_bit_cast(line_t, v), "agent");
         else *(GSPMD_GLOBAL out_vec*)c = __builtin_bit_cast(out_vec, v);
         continue;
       }

@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   static_assert(4 * line_slice<TOut>(kAtOnce) <= R * kMidStage, "");
   const int lane_end = lane_here(), t_end = kFewRegisters ? wave * 64 + lane_end : t;
   __syncthreads();                              // every wave's fragment reads are over
-  store_lines<TOut, 4, kAtOnce, !STAGED && sizeof(TOut) == 2>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, epilogue, lane_end, [&](int i, int j) {
+  store_lines<TOut, 4, kAtOnce, !STAGED && sizeof(TOut) == 2 ? kLinesThrough : kLinesPlain>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, epilogue, lane_end, [&](int i, int j) {
     if constexpr (CHAIN) return sum[i][j]; else return acc[i][j];
   });
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile

@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kPairThreads, 2) void dot_pair_kernel(const InlineP
   constexpr int kAtOnce = sizeof(TOut) == 2 ? 8 : 4;
   static_assert(4 * line_slice<TOut>(kAtOnce) <= kPairLds, "");
   __syncthreads();                              // every wave's fragment reads are over
-  store_lines<TOut, 8, kAtOnce, sizeof(TOut) == 2>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kPairRows <= P.Mv && n0 + kPairCols <= P.Nv, epilogue, lane,
+  store_lines<TOut, 8, kAtOnce, sizeof(TOut) == 2 ? kLinesPast : kLinesPlain>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kPairRows <= P.Mv && n0 + kPairCols <= P.Nv, epilogue, lane,
                                 [&](int i, int j) { return acc[i][j]; });
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears), and right of a tile that was moved back
