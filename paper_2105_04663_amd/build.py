@@ -46,7 +46,14 @@ def build(verbose: bool = False, only=None) -> str:
         list(pool.map(lambda c: _run(c, verbose), cmds))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", LIB + ".tmp"], verbose)
     os.replace(LIB + ".tmp", LIB)
-    if only is None or "call" in only:
+    if only is None:
+        try:
+            build_call(verbose)
+        except (OSError, RuntimeError) as e:      # no C compiler, no Python headers: the binding goes without it
+            if os.path.exists(CALL):
+                os.remove(CALL)                   # of another build, perhaps of another library
+            sys.stderr.write(f"the binding's native entry was not built, calls go through ctypes: {e}\n")
+    elif "call" in only:
         build_call(verbose)
     return LIB
 
