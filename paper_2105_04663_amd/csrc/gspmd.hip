@@ -351,6 +351,13 @@ bool f32_four(int64_t tiles, int64_t k) {
   return each == 4 || (each > 4 && k <= kF32ShortK && (each % 4 == 0 || each % 3 == 1));
 }
 
+// Rows that a load instruction of dot_f32_kernel (up to 8 of them) does not reach with 32-bit offsets.  Element by element such a product took three to four times as
+// long (us, element by element / 64-bit offsets / rows within reach): 64 x 8192 x 4096 461 / 128 / 118, 64 x 2048 x 8192 118 / 36.5 / 33.4, 2048 x 4096 x 64 with a
+// K-contiguous rhs 227 / 66 / 60.5.
+bool f32_wide(const std::vector<Problem>& ps) {
+  return std::any_of(ps.begin(), ps.end(), [](const Problem& p) { return std::max(p.lda, p.ldb) >= kF32MaxStride; });
+}
+
 // While a timeline is recorded dot_mid_kernel's launches go to dot_mfma_kernel, which takes whatever it takes and adds up in the same order.
 MfmaKernel with_records(MfmaKernel kernel) {
   return (kernel == kMfmaMid || kernel == kMfmaPair) && g_timeline.load(std::memory_order_acquire) != nullptr ? kMfmaBig : kernel;
@@ -483,17 +490,18 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
     } else {
       const dim3 grid(static_cast<unsigned>(tiles)), block(256);
       if (in_dtype == GSPMD_F32) {
-        auto go = [&](auto lean) {
-          constexpr bool kLean = decltype(lean)::value;
+        auto go = [&](auto lean, auto wide) {
+          constexpr bool kLean = decltype(lean)::value, kWide = decltype(wide)::value;
           switch (layout & 3) {
-            case 0: hipLaunchKernelGGL((dot_f32_kernel<0, kLean>), grid, block, 0, stream, inl, tab, n, epilogue); break;
-            case 1: hipLaunchKernelGGL((dot_f32_kernel<1, kLean>), grid, block, 0, stream, inl, tab, n, epilogue); break;
-            case 2: hipLaunchKernelGGL((dot_f32_kernel<2, kLean>), grid, block, 0, stream, inl, tab, n, epilogue); break;
-            default: hipLaunchKernelGGL((dot_f32_kernel<3, kLean>), grid, block, 0, stream, inl, tab, n, epilogue);
+            case 0: hipLaunchKernelGGL((dot_f32_kernel<0, kLean, kWide>), grid, block, 0, stream, inl, tab, n, epilogue); break;
+            case 1: hipLaunchKernelGGL((dot_f32_kernel<1, kLean, kWide>), grid, block, 0, stream, inl, tab, n, epilogue); break;
+            case 2: hipLaunchKernelGGL((dot_f32_kernel<2, kLean, kWide>), grid, block, 0, stream, inl, tab, n, epilogue); break;
+            default: hipLaunchKernelGGL((dot_f32_kernel<3, kLean, kWide>), grid, block, 0, stream, inl, tab, n, epilogue);
           }
         };
-        if (f32_four(tiles, launch_size(ps, layout).k)) go(std::true_type{});
-        else go(std::false_type{});
+        if (f32_wide(ps)) go(std::false_type{}, std::true_type{});
+        else if (f32_four(tiles, launch_size(ps, layout).k)) go(std::true_type{}, std::false_type{});
+        else go(std::false_type{}, std::false_type{});
       } else if (out_dtype == GSPMD_F32)
         hipLaunchKernelGGL((dot_fallback_kernel<bf16_bits, float>), grid, block, 0, stream, inl, tab, n, layout, epilogue);
       else

@@ -35,8 +35,9 @@ template <bool LEAN> constexpr int f32_stages() { return LEAN ? 2 : 3; }
 
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-// LEAN: LDS for four workgroups on a compute unit (f32_four).
-template <int LAYOUT, bool LEAN>
+// LEAN: LDS for four workgroups on a compute unit (f32_four).  WIDE: rows beyond 32-bit offsets (512 MiB and more), a lane's offsets in 64 bits and one
+// addition per load.
+template <int LAYOUT, bool LEAN, bool WIDE = false>
 __global__ __launch_bounds__(kF32Threads, LEAN ? 4 : 3) void dot_f32_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
   constexpr int R = f32_stages<LEAN>();
@@ -71,13 +72,14 @@ __global__ __launch_bounds__(kF32Threads, LEAN ? 4 : 3) void dot_f32_kernel(cons
     const int q = wave * 2 + j;
     return reinterpret_cast<uint64_t>(base + (kmajor ? q * 4 : min(x0 + q * 8, valid - 1)) * ld);
   };
-  auto load_offset = [&](bool kmajor, int64_t ld, int x0, int valid, int j) -> uint32_t {
+  typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type offset_t;
+  auto load_offset = [&](bool kmajor, int64_t ld, int x0, int valid, int j) -> offset_t {
     const int q = wave * 2 + j, row = x0 + q * 8;
-    if (kmajor) return static_cast<uint32_t>((lane >> 4) * ld + f32_km_first(x0 + f32_km_chunk(q, lane) * 4, valid)) * 4;
-    return static_cast<uint32_t>((min(row + (lane >> 3), valid - 1) - min(row, valid - 1)) * ld + f32_kc_chunk(q, lane) * 4) * 4;
+    if (kmajor) return static_cast<offset_t>((lane >> 4) * ld + f32_km_first(x0 + f32_km_chunk(q, lane) * 4, valid)) * 4;
+    return static_cast<offset_t>((min(row + (lane >> 3), valid - 1) - min(row, valid - 1)) * ld + f32_kc_chunk(q, lane) * 4) * 4;
   };
   uint64_t a_at[2], b_at[2];
-  uint32_t a_off[2], b_off[2];
+  offset_t a_off[2], b_off[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     a_at[j] = load_base(AKM, A, P.lda, m0, P.Mv, j);
@@ -85,19 +87,16 @@ __global__ __launch_bounds__(kF32Threads, LEAN ? 4 : 3) void dot_f32_kernel(cons
     a_off[j] = load_offset(AKM, P.lda, m0, P.Mv, j);
     b_off[j] = load_offset(!BKC, P.ldb, n0, P.Nv, j);
   }
-  // no whole chunk along m or n, or rows beyond 32-bit offsets
-  const bool slow = (AKM && P.Mv < 4) || (!BKC && P.Nv < 4) || max(P.lda, P.ldb) >= kF32MaxStride;
+  const bool slow = (AKM && P.Mv < 4) || (!BKC && P.Nv < 4);          // no whole chunk along m or n
   const int64_t a_step = (AKM ? static_cast<int64_t>(P.lda) * kF32BK : kF32BK) * 4, b_step = (BKC ? kF32BK : static_cast<int64_t>(P.ldb) * kF32BK) * 4;
   // the i-th of this wave's four loads of the next K step
   auto load_one = [&](int i, uint32_t stage_at) {
     const uint32_t to = stage_at + (i >> 1) * kF32Part + (wave * 2 + (i & 1)) * 1024;
-    if (i < 2) {
-      global_to_lds16(reinterpret_cast<const void*>(a_at[i & 1]), a_off[i & 1], to);
-      a_at[i & 1] += a_step;
-    } else {
-      global_to_lds16(reinterpret_cast<const void*>(b_at[i & 1]), b_off[i & 1], to);
-      b_at[i & 1] += b_step;
-    }
+    uint64_t& at = i < 2 ? a_at[i & 1] : b_at[i & 1];
+    const offset_t off = i < 2 ? a_off[i & 1] : b_off[i & 1];
+    if constexpr (WIDE) global_to_lds16(at + off, to);
+    else global_to_lds16(reinterpret_cast<const void*>(at), off, to);
+    at += i < 2 ? a_step : b_step;
   };
   // Where this lane's fragments are in an operand's part: K-contiguous, four k of a row in one read (halves of the step 64 bytes apart by
   // XOR); K-major, one column of each of two 16-column blocks.

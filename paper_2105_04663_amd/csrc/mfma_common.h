@@ -26,6 +26,11 @@ __device__ __forceinline__ void global_to_lds16(const void* sbase, uint32_t voff
                :: "s"(lds_addr), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
+// the same from an address of every lane's own
+__device__ __forceinline__ void global_to_lds16(uint64_t from, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_addr), "v"(from) : "memory", "m0");
+}
+
 // This lane's number in its wave, worked out where it is asked for: what derives from it is neither kept in registers from earlier on nor moved out of a loop.
 __device__ __forceinline__ int lane_now() {
   int lane;
