@@ -381,6 +381,9 @@ int32_t mark_moved_back(std::vector<Problem>& ps) {
   return moved;
 }
 
+// bf16 outputs of a launch that the caches do not hold for the next one (kernels_lines.h)
+constexpr int64_t kPastBytes = 96000000;
+
 int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dtype, int32_t out_dtype, int32_t epilogue,
                         bool ordered, void* workspace, int64_t workspace_bytes, hipStream_t stream, const JoinSpace* join = nullptr) {
   // problems with an empty static output block write nothing
@@ -473,7 +476,10 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       l.spread = !(layout & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) && std::all_of(ps.begin(), ps.end(), [](const Problem& p) { return p.ldb % 2048 == 0; });
       if (!launch_dot_split(l, layout, out_dtype, split, choice.col_blocks, stream)) return GSPMD_ERR_DEVICE;
     } else if (mid) {
-      const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
+      MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
+      int64_t out_bytes = 0;
+      for (const auto& p : ps) if (p.join_slot == 0) out_bytes += static_cast<int64_t>(p.Mv) * p.Nv * 2;
+      l.past = out_bytes > kPastBytes;
       if (!launch_dot_mid(l, layout, out_dtype, join != nullptr, choice.staged, stream)) return GSPMD_ERR_DEVICE;
     } else if (pair) {
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};

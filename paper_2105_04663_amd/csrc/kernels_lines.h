@@ -25,6 +25,8 @@ template <typename TOut> constexpr int line_slice(int blocks) { return blocks * 
 // written back when the launch ends, which takes 0.4 to 0.7 us; past all caches (kLinesPast) the next kernel fetches them from HBM.  A product and one that reads it (us, plain / past /
 // through): 1024 x 2048 x 4096, then x 2048 48.2 / 55.1 / 47.4, 2048 x 1024 x 2048, then x 1024 31.2 / 33.4 / 30.6; sums over members 2048 x 8192 x 2048 over 4, then x 1024 83.2 / 85.7 /
 // 82.0, 4096 x 4096 x 2048 over 2, then x 512 78.3 / 82.7 / 77.3; the first product alone 20.9 / 20.2 / 19.9, the first sum 66.8 / 66.0 / 66.0.
+// Of a launch that asks for it (`past`) they go past all caches as well: outputs of more than kPastBytes, which the caches do not hold (us, through / past: 64 MB
+// in 8 of 2048 x 300 x 2048 31.1 / 31.5; 128 MB in 8 of 4096 x 200 x 2048 67.9 / 51.2, 16384 x 256 x 4096 57.5 / 48.1; 256 MB in 32 of 2048 x 128 x 2048 102.8 / 77.0).
 // kLinesPast, dot_pair_kernel's bf16 outputs, launches of many tiles: four experts' weight gradients of 4096 x 8192, K 384 109 us, plain 140, and with an update that reads them 262, 281; of
 // 2048 x 4096, K 2048 29.8, 31.0 and 39.1, 39.5.
 // kLinesPlain where rows start at odd addresses and lines are stored in two parts (601 x 1203 x 697 17.9, past 18.4), and float32 outputs, mostly partial sums that the next kernel
@@ -33,7 +35,7 @@ enum LineStores { kLinesPlain, kLinesPast, kLinesThrough };
 
 // Block (i, j) of BLOCKS x 4 is value(i, j); the wave's first row and column are row0 and col0.  `inside`: all of the workgroup's tile is valid.
 template <typename TOut, int BLOCKS, int AT_ONCE, LineStores STORES, typename Value>
-__device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL TOut* C, const Problem& P, int row0, int col0, bool inside, int epilogue, int lane, Value value) {
+__device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL TOut* C, const Problem& P, int row0, int col0, bool inside, int epilogue, int lane, Value value, bool past = false) {
   constexpr int V = 16 / static_cast<int>(sizeof(TOut)), kLanes = 64 / V, kRowsAt = 64 / kLanes;       // columns of a lane, lanes of a row, rows of a store
   constexpr int kPitch = line_pitch<TOut>();
   typedef TOut out_vec __attribute__((ext_vector_type(V), aligned(sizeof(TOut))));
@@ -63,29 +65,54 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
     const int row = row0 + pass * AT_ONCE * 16 + lane / kLanes, col = col0 + lane % kLanes * V;
     GSPMD_GLOBAL TOut* const c0 = C + static_cast<int64_t>(row) * P.ldc + col;
     const int keep = min(V, P.Nv - col), room = min(V, P.Ns - col);
+    constexpr int kStores = AT_ONCE * 16 / kRowsAt;
+    auto staged = [&](int p) { return *reinterpret_cast<const u32x4_t*>(slice + (p * kRowsAt + lane / kLanes) * kPitch + lane % kLanes * 16); };
+    auto at = [&](int p) { return c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc; };
+    auto store = [&](int p, u32x4_t v) {
+      if constexpr (STORES == kLinesPast) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)at(p));
+      else if constexpr (STORES == kLinesThrough) __builtin_amdgcn_global_store_b128((GSPMD_GLOBAL line_t*)at(p), __builtin_bit_cast(line_t, v), "agent");
+      else *(GSPMD_GLOBAL out_vec*)at(p) = __builtin_bit_cast(out_vec, v);
+    };
+    auto store_past = [&](int p, u32x4_t v) {
+      asm volatile("" ::: "memory");            // (or the compiler makes one store of the two, without the hint)
+      __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)at(p));
+      asm volatile("" ::: "memory");
+    };
+    // One read, one store (with all reads first four experts' weight gradients of 4096 x 8192 took 116.6 us, so 114.9); outputs written through all reads first (backward of
+    // 2048 x 2048 x 8192 on 2 x 2 146.2 us, so 144.1).
+    constexpr bool kReadsFirst = STORES == kLinesThrough;
+    if (kReadsFirst && inside) {
+      u32x4_t v[kStores];
 #pragma unroll
-    for (int p = 0; p < AT_ONCE * 16 / kRowsAt; ++p) {
-      u32x4_t v = *reinterpret_cast<const u32x4_t*>(slice + (p * kRowsAt + lane / kLanes) * kPitch + lane % kLanes * 16);
-      GSPMD_GLOBAL TOut* const c = c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc;
-      if (inside) {
-        if constexpr (STORES == kLinesPast) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)c);
-        else if constexpr (STORES == kLinesThrough) __builtin_amdgcn_global_store_b128((GSPMD_GLOBAL line_t*)c, __builtin_bit_cast(line_t, v), "agent");
-        else *(GSPMD_GLOBAL out_vec*)c = __builtin_bit_cast(out_vec, v);
-        continue;
-      }
-      if (row + p * kRowsAt >= P.Mv || room <= 0) continue;
-      if constexpr (sizeof(TOut) == 2) {
-        v = mask_tail8(v, keep);
-      } else {
+      for (int p = 0; p < kStores; ++p) v[p] = staged(p);
+      if (past)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (e >= keep) v[e] = 0u;
-      }
-      const out_vec o = __builtin_bit_cast(out_vec, v);
-      if (room == V) *(GSPMD_GLOBAL out_vec*)c = o;
+        for (int p = 0; p < kStores; ++p) store_past(p, v[p]);
       else
 #pragma unroll
-        for (int e = 0; e < V; ++e) if (e < room) c[e] = o[e];
+        for (int p = 0; p < kStores; ++p) store(p, v[p]);
+    } else {
+#pragma unroll
+      for (int p = 0; p < kStores; ++p) {
+        u32x4_t v = staged(p);
+        if (!kReadsFirst && inside) {
+          store(p, v);
+          continue;
+        }
+        if (row + p * kRowsAt >= P.Mv || room <= 0) continue;
+        if constexpr (sizeof(TOut) == 2) {
+          v = mask_tail8(v, keep);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (e >= keep) v[e] = 0u;
+        }
+        const out_vec o = __builtin_bit_cast(out_vec, v);
+        if (room == V) *(GSPMD_GLOBAL out_vec*)at(p) = o;
+        else
+#pragma unroll
+          for (int e = 0; e < V; ++e) if (e < room) at(p)[e] = o[e];
+      }
     }
     staged_in_order();                          // the next pass stages into what this one reads
   }

@@ -44,7 +44,7 @@ constexpr int kMidUnroll = 5;                         // K steps after which the
 // 4999 x 576 x 1193 28.1 / 15.2, 152 x 209 x 1094, 32 of them 23.7 / 16.6.
 template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU, bool STAGED>
 __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (one: the sums' accumulators take the other half of the registers)
- void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
+ void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue, int past) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
   static_assert(!(STAGED && CHAIN) && (!STAGED || PER_CU == 2), "");
   constexpr int R = mid_stages<PER_CU>(), L = mid_ahead<PER_CU>();
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   __syncthreads();                              // every wave's fragment reads are over
   store_lines<TOut, 4, kAtOnce, !STAGED && sizeof(TOut) == 2 ? kLinesThrough : kLinesPlain>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, epilogue, lane_end, [&](int i, int j) {
     if constexpr (CHAIN) return sum[i][j]; else return acc[i][j];
-  });
+  }, past != 0);
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears)
   const int m_done = min(m_nom + kMidTile, P.Mv), moved_end = n0 + kMidTile, col_end = min(n_nom + kMidTile, P.Ns);
@@ -469,7 +469,7 @@ inline bool launch_dot_mid_as(const MfmaLaunch& l, hipStream_t stream) {
   });
   if (!ok[dev]) return false;
   hipLaunchKernelGGL((dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU, STAGED>), dim3(static_cast<unsigned>(l.tiles)), dim3(kMidThreads), lds, stream, *l.inl, l.tab,
-                     l.n_prob, l.epilogue);
+                     l.n_prob, l.epilogue, l.past ? 1 : 0);
   return hipGetLastError() == hipSuccess;
 }
 

@@ -21,6 +21,7 @@ struct MfmaLaunch {
   unsigned long long* timeline;
   int timeline_records;
   bool spread = false;                   // dot_split_kernel: tiles in spread_tile's order
+  bool past = false;                     // dot_mid_kernel: bf16 outputs past all caches
 };
 
 // `staged`: an operand does not take direct loads, both are loaded at element alignment through registers

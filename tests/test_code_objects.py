@@ -48,18 +48,21 @@ def test_no_kernel_spills(tmp_path):
         assert spilled <= most and scratch <= 4 * (most + 1), (name, spilled, scratch)
 
 
-def test_outputs_of_dot_mid_kernel_stay_where_the_next_kernel_finds_them(tmp_path):
-    """None of its stores goes past the caches: an einsum that reads what it wrote took up to 18 % longer."""
+def test_how_dot_mid_kernel_stores_whole_tiles(tmp_path):
+    """bf16 outputs: a store for each case, past the caches where a launch's outputs are more than these hold, else through to the memory side, where an einsum that
+    reads them finds them (that one took up to 18 % longer with all of them past the caches); float32 outputs and staged tiles, whose lines may be stored in two parts: neither."""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
-    stores = 0
+    seen = {}
     for path in _code_objects(tmp_path):
         with open(path, "rb") as f:
             if b"dot_mid_kernel" not in f.read()[:1 << 16]:
                 continue
         listing = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", path], capture_output=True, text=True).stdout
         for name, body in re.findall(r"^<(\S*dot_mid_kernel\S*)>:\n(.*?)(?=^<|\Z)", listing, re.S | re.M):
-            lines = re.findall(r"global_store_\w+ [^\n]*", body)
-            stores += len(lines)
-            assert not [x for x in lines if re.search(r"\bnt\b", x)], name
-    assert stores >= 40 * 8
+            stores = re.findall(r"global_store_dwordx4 [^\n]*", body)
+            seen[name] = tuple(sum(bool(re.search(hint, x)) for x in stores) for hint in (r"\bnt\b", r"\bsc1\b"))
+    assert len(seen) >= 40
+    for name, (past, through) in seen.items():
+        out, chain, staged = re.search(r"dot_mid_kernelI(\w)Li\dELb(\d)ELi\dELb(\d)E", name).groups()
+        assert (past, through) == ((8, 8) if out == "t" and staged == "0" else (0, 0)), (name, past, through)

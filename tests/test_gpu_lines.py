@@ -42,3 +42,8 @@ def test_edges(M, N, kernel, K, row_align, out_dtype, epilogue):
                                           (PAIR, 136, 72, 130), (PAIR, 264, 72, 390), (PAIR, 512, 136, 254)])
 def test_tiles_that_are_moved_back(kernel, M, K, N, layout, out_dtype, epilogue):
     _same_memory(split.workload(M, K, N, layout), kernel, 0, out_dtype, epilogue)
+
+
+@pytest.mark.parametrize("K", [40, 41])              # direct and staged loads
+def test_outputs_that_the_caches_do_not_hold(K):
+    _same_memory(split.workload(6203, K, 7801, 2), MID, 0, "bf16", 0)          # 97 MB: past the caches
