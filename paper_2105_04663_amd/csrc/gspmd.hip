@@ -150,7 +150,7 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   that is left of K; in sums of more than one round of 512 0.44, and 0.30 in a last round of up to 256; a fifth more per step where a
 //   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Fitted to drawn launches
 //   together with dot_pair_kernel's line and the 256 x 256 tiles' 10 us: over 937 drawn products without a sum the choice takes 0.7 % more than the best
-//   of all kernels pinned one after the other, 1.2 % with the lines from before outputs left in whole lines.
+//   of all kernels pinned one after the other, 1.2 % with the lines from before outputs left in whole lines; few of their operands were beyond 16 MB (drawn_us, below).
 // Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 120 / 62   512 x 8192 x 512: 117 / 45
 //   2048 x 4096 x 4096: 66 / 60   2048 x 1024 x 4096: 22 / 19   4653 x 7168 x 4288: 255 / 267   1456 x 1415 x 3969, two of them: 38 / 45
 //   2178 x 4736 x 1447, two: 76 / 72   1090 x 1333 x 1568, eight: 61 / 52   2112 x 8000 x 2112: 111 / 90   4096 x 512 x 8192, four, both K-major: 143 / 159
@@ -161,11 +161,22 @@ struct LaunchSize {
   int64_t cols = INT32_MAX, fewest_rows = INT32_MAX;
   int64_t loose_cols = INT32_MAX, loose_rows_of_lhs = INT32_MAX;      // fewest of a K-major operand whose rows are not padded to 16 bytes
   bool a_odd = false, b_odd = false;                           // an operand has elements at odd addresses
+  int64_t in_bytes = 0;                                        // of the operands, each buffer once (one that comes round again in order, as on a mesh)
   bool broken_lines = false, whole_steps = true, whole_chunks = true;      // a K-contiguous operand's rows are not whole lines; all K are whole 64-wide steps
 };
 LaunchSize launch_size(const std::vector<Problem>& ps, int32_t layout) {
   LaunchSize s;
+  bool a_again = false, b_again = false;
   for (const auto& p : ps) {
+    const Problem* const before = &p > ps.data() ? &p - 1 : nullptr;
+    if (!before || p.A != before->A) {
+      a_again = a_again || (before && p.A == ps[0].A);
+      if (!a_again) s.in_bytes += static_cast<int64_t>(p.Mv) * p.Kv * 2;
+    }
+    if (!before || p.B != before->B) {
+      b_again = b_again || (before && p.B == ps[0].B);
+      if (!b_again) s.in_bytes += static_cast<int64_t>(p.Nv) * p.Kv * 2;
+    }
     s.rows = std::max<int64_t>(s.rows, p.Mv);
     s.k = std::max<int64_t>(s.k, p.Kv);
     s.cols = std::min<int64_t>(s.cols, p.Nv);
@@ -264,6 +275,12 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 //   N = 3: 236 / 98, 96, 60 / 57, 78     7: 270 / 134, 120, 69 / 74, 92     9: 88 / 148, 130, 72 / 24, 24     10: 79 / 148, 130, 73 / 17, 20     31: 88 / 148, 130, 76 / 24, 24
 // While a timeline is recorded the launches that this gives to dot_mid_kernel, which writes no records, go to dot_mfma_kernel
 // (with_records): the choice is the same with and without, so results are.
+// Operands beyond 16 MB: 0.09 us per MB more in dot_mid_kernel and 0.04 in dot_pair_kernel than in 256 x 256 tiles, whose workgroups draw them from HBM (and from the memory-side
+// cache) less often.  Without it, fitted to operands of which few were larger, launches that stream weights went to 128 x 128 tiles (us, dot_mfma_kernel / dot_mid_kernel): experts'
+// products of 8 x 363 x 2176 x 3840 47 / 71, 16 x 339 x 1344 x 6144 94 / 126, 8 x 279 x 3968 x 6016 140 / 178, 4 x 369 x 1600 x 8064 37 / 55, unpadded 16 x 289 x 1600 x 5760 104 / 131,
+// staged 32 x 2440 x 1759 x 665 291 / 352; below they are alike: 8 x 142 x 3904 x 2112 64 / 54.  Over 1800 products drawn like layers, experts' products of both directions, meshes and at random
+// the choice takes 1.3 % more than the best of the three kernels, 2.1 % without it; over 500 with few rows and large weights 1.1 %, 2.4 % (of all nine variants).
+double drawn_us(const LaunchSize& s, double per_mb) { return per_mb * std::max(0.0, static_cast<double>(s.in_bytes) * 1e-6 - 16.0); }
 constexpr int32_t kMidShortK = 1024;      // members with something left of K that dot_mid_kernel runs through one loop
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 // dot_mfma_kernel's direct variants take a K-major rhs with loose rows from one of their tiles of columns on
@@ -286,11 +303,11 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (size.rows == 0) return choice;
   double best = big_us(size, choice.staged = big_staged(size, path, layout));
   if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
-    const double us = loose ? mid_staged_us(size) : mid_us(size, layout);
+    const double us = (loose ? mid_staged_us(size) : mid_us(size, layout)) + (size.members == 1 ? drawn_us(size, 0.09) : 0.0);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, 0, loose}; }
   }
   if (pair_takes(size, path, layout)) {
-    const double us = pair_us(size, layout, path == kPathMfmaWords);
+    const double us = pair_us(size, layout, path == kPathMfmaWords) + drawn_us(size, 0.04);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaPair, 0, 0, false, path == kPathMfmaWords}; }
   }
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {
