@@ -67,16 +67,10 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
     const int keep = min(V, P.Nv - col), room = min(V, P.Ns - col);
     constexpr int kStores = AT_ONCE * 16 / kRowsAt;
     auto staged = [&](int p) { return *reinterpret_cast<const u32x4_t*>(slice + (p * kRowsAt + lane / kLanes) * kPitch + lane % kLanes * 16); };
-    auto at = [&](int p) { return c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc; };
-    auto store = [&](int p, u32x4_t v) {
-      if constexpr (STORES == kLinesPast) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)at(p));
-      else if constexpr (STORES == kLinesThrough) __builtin_amdgcn_global_store_b128((GSPMD_GLOBAL line_t*)at(p), __builtin_bit_cast(line_t, v), "agent");
-      else *(GSPMD_GLOBAL out_vec*)at(p) = __builtin_bit_cast(out_vec, v);
-    };
-    auto store_past = [&](int p, u32x4_t v) {
-      asm volatile("" ::: "memory");            // (or the compiler makes one store of the two, without the hint)
-      __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)at(p));
-      asm volatile("" ::: "memory");
+    auto store = [&](GSPMD_GLOBAL TOut* c, u32x4_t v) {
+      if constexpr (STORES == kLinesPast) __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v), (GSPMD_GLOBAL out_vec*)c);
+      else if constexpr (STORES == kLinesThrough) __builtin_amdgcn_global_store_b128((GSPMD_GLOBAL line_t*)c, __builtin_bit_cast(line_t, v), "agent");
+      else *(GSPMD_GLOBAL out_vec*)c = __builtin_bit_cast(out_vec, v);
     };
     // One read, one store (with all reads first four experts' weight gradients of 4096 x 8192 took 116.6 us, so 114.9); outputs written through all reads first (backward of
     // 2048 x 2048 x 8192 on 2 x 2 146.2 us, so 144.1).
@@ -87,16 +81,21 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
       for (int p = 0; p < kStores; ++p) v[p] = staged(p);
       if (past)
 #pragma unroll
-        for (int p = 0; p < kStores; ++p) store_past(p, v[p]);
+        for (int p = 0; p < kStores; ++p) {
+          asm volatile("" ::: "memory");        // (or the compiler makes one store of the two, without the hint)
+          __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v[p]), (GSPMD_GLOBAL out_vec*)(c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc));
+          asm volatile("" ::: "memory");
+        }
       else
 #pragma unroll
-        for (int p = 0; p < kStores; ++p) store(p, v[p]);
+        for (int p = 0; p < kStores; ++p) store(c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc, v[p]);
     } else {
 #pragma unroll
       for (int p = 0; p < kStores; ++p) {
         u32x4_t v = staged(p);
+        GSPMD_GLOBAL TOut* const c = c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc;
         if (!kReadsFirst && inside) {
-          store(p, v);
+          store(c, v);
           continue;
         }
         if (row + p * kRowsAt >= P.Mv || room <= 0) continue;
@@ -108,10 +107,10 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
             if (e >= keep) v[e] = 0u;
         }
         const out_vec o = __builtin_bit_cast(out_vec, v);
-        if (room == V) *(GSPMD_GLOBAL out_vec*)at(p) = o;
+        if (room == V) *(GSPMD_GLOBAL out_vec*)c = o;
         else
 #pragma unroll
-          for (int e = 0; e < V; ++e) if (e < room) at(p)[e] = o[e];
+          for (int e = 0; e < V; ++e) if (e < room) c[e] = o[e];
       }
     }
     staged_in_order();                          // the next pass stages into what this one reads

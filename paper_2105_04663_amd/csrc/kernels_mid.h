@@ -35,6 +35,7 @@ constexpr int kMidStage = 2 * kMidPart;
 // LDS stages with one and with two workgroups on a compute unit, and how many tiles ahead of the multiplication loads are issued
 template <int PER_CU> constexpr int mid_stages() { return PER_CU == 1 ? 10 : 5; }
 template <int PER_CU> constexpr int mid_ahead() { return PER_CU == 1 ? 6 : 4; }
+constexpr int kStorePast = 256;                       // beside the epilogue in a launch's arguments: bf16 outputs past all caches
 constexpr int kMidUnroll = 5;                         // K steps after which the stages come round: their places are then constants of the code
 
 // STAGED: the variant for operands at odd element addresses, which direct loads do not take: a tile's chunks are loaded into registers two
@@ -44,7 +45,7 @@ constexpr int kMidUnroll = 5;                         // K steps after which the
 // 4999 x 576 x 1193 28.1 / 15.2, 152 x 209 x 1094, 32 of them 23.7 / 16.6.
 template <typename TOut, int LAYOUT, bool CHAIN, int PER_CU, bool STAGED>
 __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (one: the sums' accumulators take the other half of the registers)
- void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue, int past) {
+ void dot_mid_kernel(const InlineProblems inl, const Problem* __restrict__ tab, int n_prob, int epilogue) {
   constexpr bool AKM = (LAYOUT & GSPMD_LAYOUT_LHS_K_MAJOR) != 0, BKC = (LAYOUT & GSPMD_LAYOUT_RHS_K_CONTIGUOUS) != 0;
   static_assert(!(STAGED && CHAIN) && (!STAGED || PER_CU == 2), "");
   constexpr int R = mid_stages<PER_CU>(), L = mid_ahead<PER_CU>();
@@ -441,11 +442,12 @@ __global__ __launch_bounds__(kMidThreads, CHAIN && PER_CU == 1 ? 1 : 2)   // (on
   GSPMD_GLOBAL TOut* const C = (GSPMD_GLOBAL TOut*)P.C;
   constexpr int kAtOnce = sizeof(TOut) == 2 ? 4 : 2;
   static_assert(4 * line_slice<TOut>(kAtOnce) <= R * kMidStage, "");
+  constexpr bool kHinted = !STAGED && sizeof(TOut) == 2;
   const int lane_end = lane_here(), t_end = kFewRegisters ? wave * 64 + lane_end : t;
   __syncthreads();                              // every wave's fragment reads are over
-  store_lines<TOut, 4, kAtOnce, !STAGED && sizeof(TOut) == 2 ? kLinesThrough : kLinesPlain>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, epilogue, lane_end, [&](int i, int j) {
+  store_lines<TOut, 4, kAtOnce, kHinted ? kLinesThrough : kLinesPlain>(smem + wave * line_slice<TOut>(kAtOnce), C, P, m0 + wm, n0 + wn, m0 + kMidTile <= P.Mv && n0 + kMidTile <= P.Nv, kHinted ? epilogue & ~kStorePast : epilogue, lane_end, [&](int i, int j) {
     if constexpr (CHAIN) return sum[i][j]; else return acc[i][j];
-  }, past != 0);
+  }, kHinted && (epilogue & kStorePast) != 0);
   // zeros of the static block below the last row tile, over this tile's columns (what lies further down, and whole tile
   // columns of padding, the fill kernel clears)
   const int m_done = min(m_nom + kMidTile, P.Mv), moved_end = n0 + kMidTile, col_end = min(n_nom + kMidTile, P.Ns);
@@ -469,7 +471,7 @@ inline bool launch_dot_mid_as(const MfmaLaunch& l, hipStream_t stream) {
   });
   if (!ok[dev]) return false;
   hipLaunchKernelGGL((dot_mid_kernel<TOut, LAYOUT, CHAIN, PER_CU, STAGED>), dim3(static_cast<unsigned>(l.tiles)), dim3(kMidThreads), lds, stream, *l.inl, l.tab,
-                     l.n_prob, l.epilogue, l.past ? 1 : 0);
+                     l.n_prob, !STAGED && sizeof(TOut) == 2 && l.past ? l.epilogue | kStorePast : l.epilogue);
   return hipGetLastError() == hipSuccess;
 }
 
