@@ -87,16 +87,23 @@ __global__ __launch_bounds__(kF32Threads, LEAN ? 4 : 3) void dot_f32_kernel(cons
     a_off[j] = load_offset(AKM, P.lda, m0, P.Mv, j);
     b_off[j] = load_offset(!BKC, P.ldb, n0, P.Nv, j);
   }
-  const bool slow = (AKM && P.Mv < 4) || (!BKC && P.Nv < 4);          // no whole chunk along m or n
+  // no whole chunk along m or n (or rows that this variant's offsets do not reach, which the host gives to WIDE)
+  const bool slow = (AKM && P.Mv < 4) || (!BKC && P.Nv < 4) || (!WIDE && max(P.lda, P.ldb) >= kF32MaxStride);
   const int64_t a_step = (AKM ? static_cast<int64_t>(P.lda) * kF32BK : kF32BK) * 4, b_step = (BKC ? kF32BK : static_cast<int64_t>(P.ldb) * kF32BK) * 4;
   // the i-th of this wave's four loads of the next K step
   auto load_one = [&](int i, uint32_t stage_at) {
     const uint32_t to = stage_at + (i >> 1) * kF32Part + (wave * 2 + (i & 1)) * 1024;
-    uint64_t& at = i < 2 ? a_at[i & 1] : b_at[i & 1];
-    const offset_t off = i < 2 ? a_off[i & 1] : b_off[i & 1];
-    if constexpr (WIDE) global_to_lds16(at + off, to);
-    else global_to_lds16(reinterpret_cast<const void*>(at), off, to);
-    at += i < 2 ? a_step : b_step;
+    auto load = [&](uint64_t from, offset_t off) {
+      if constexpr (WIDE) global_to_lds16(from + off, to);
+      else global_to_lds16(reinterpret_cast<const void*>(from), off, to);
+    };
+    if (i < 2) {
+      load(a_at[i & 1], a_off[i & 1]);
+      a_at[i & 1] += a_step;
+    } else {
+      load(b_at[i & 1], b_off[i & 1]);
+      b_at[i & 1] += b_step;
+    }
   };
   // Where this lane's fragments are in an operand's part: K-contiguous, four k of a row in one read (halves of the step 64 bytes apart by
   // XOR); K-major, one column of each of two 16-column blocks.
