@@ -222,7 +222,8 @@ int32_t gspmd_dot_workspace_bytes(const gspmd_mesh* mesh, const gspmd_dot_dims* 
  * epilogue: a gspmd_epilogue applied to every valid output element; padding stays 0.
  * lhs_fill (host, nullable): the number of occupied positions, per GLOBAL batch entry (row-major over the
  * global batch dims), of the first lhs dimension that is not a batch dimension -- the capacity slots of the
- * mixture-of-experts einsums (Section 5.4).  If that dimension is non-contracting it must be the only
+ * mixture-of-experts einsums (Section 5.4).  One count is read for every batch entry (by gspmd_local_dot and gspmd_plan_dot
+ * up to the last entry of the partition's shard).  If that dimension is non-contracting it must be the only
  * non-contracting lhs dimension: rows at global position >= fill are masked and their out rows are 0.  If it
  * is contracting (the experts' weight gradient) it must be the outermost contracting dimension: positions
  * >= fill take no part in the sum in either operand.

@@ -149,8 +149,9 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   a joined sum follow each other in one workgroup, 1.8 us apart where they are not alike and whole K steps long; 0.25 us per 32-wide tile
 //   that is left of K; in sums of more than one round of 512 0.44, and 0.30 in a last round of up to 256; a fifth more per step where a
 //   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Fitted to drawn launches
-//   together with dot_pair_kernel's line and the 256 x 256 tiles' 10 us: over 937 drawn products without a sum the choice takes 0.7 % more than the best
-//   of all kernels pinned one after the other, 1.2 % with the lines from before outputs left in whole lines; few of their operands were beyond 16 MB (drawn_us, below).
+//   together with dot_pair_kernel's line and the 256 x 256 tiles' 10 us; few of those had operands beyond 16 MB (drawn_us, below).  Over products drawn afresh the choice takes
+//   1.6 % more than the best of all kernels pinned one after the other (300 layers, experts' products and others of more than few rows), 1.1 % (120 with few rows and large operands),
+//   1.2 % (160 meshes of dense rows), 0.2 % (120 feed-forward layers); 4.9 % where any extents are drawn (160, most of them of 4 to 12 us).
 // Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 120 / 62   512 x 8192 x 512: 117 / 45
 //   2048 x 4096 x 4096: 66 / 60   2048 x 1024 x 4096: 22 / 19   4653 x 7168 x 4288: 255 / 267   1456 x 1415 x 3969, two of them: 38 / 45
 //   2178 x 4736 x 1447, two: 76 / 72   1090 x 1333 x 1568, eight: 61 / 52   2112 x 8000 x 2112: 111 / 90   4096 x 512 x 8192, four, both K-major: 143 / 159

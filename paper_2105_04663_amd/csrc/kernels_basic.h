@@ -94,7 +94,7 @@ __device__ __forceinline__ int lookup_problem_index(const Problem* __restrict__ 
   if (tab) return find_problem(tab, n_prob, tile);
   if (n_prob == 1) return 0;
   // One load and a ballot: a search takes five dependent ones in a table of 32, a microsecond before every tile (4 x 8 mesh of 5998 x 3072 x 9999, 3.75 tiles
-  // a compute unit: 295 -> 289 us; six of 601 x 1203 x 697 20.2 -> 19.9).
+  // a compute unit: 286.1 -> 283.8 us on one card; six of 601 x 1203 x 697 20.13 -> 19.84).
   static_assert(kInlineProblems <= 64, "a lane for every problem");
   const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const int begin = first_kernel_argument<Problem>()[min(lane, n_prob - 1)].tile_begin;

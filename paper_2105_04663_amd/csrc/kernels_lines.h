@@ -1,9 +1,9 @@
 // The end of a bf16 MFMA kernel: a wave's 16 x 16 accumulator blocks, 64 columns wide, out to global memory in whole lines.  In the accumulators'
 // own order (a lane holds columns n .. n + 3 of row m of a block) an instruction stores 32 bytes (bf16) or 64 (float32) of each of 16 rows;
 // staged through the wave's own slice of LDS it stores 16 bytes per lane, lines of 128 or 256 bytes, at the output's element alignment.
-// dot_mid_kernel's tiles all end at about the same time, so what their stores take is time that nothing hides.  Measured there (us, in the accumulators' order / whole lines):
-// 2048 x 1024 x 2048 12.3 / 10.5, 1500 x 512 x 3000 13.4 / 11.3, four of 1000 x 768 x 1024 11.8 / 9.7, six of 601 x 1203 x 697 19.9 / 18.0, 32 of 152 x 209 x 1094 19.3 / 15.7, sums of
-// 2048 x 8192 x 2048 over 4 members 61.0 / 59.7 and over 2, two groups, 63.7 / 60.8; float32 outputs 2048 x 1024 x 4096, four times with their sum, 105.8 / 102.6.
+// dot_mid_kernel's tiles all end at about the same time, so what their stores take is time that nothing hides.  Measured there (us, in the accumulators' order / whole lines, both
+// revisions in turn on one card): 2048 x 1024 x 2048 12.4 / 10.6, 1500 x 512 x 3000 13.5 / 11.8, four of 1000 x 768 x 1024 12.2 / 9.5, six of 601 x 1203 x 697 20.0 / 17.8, sums of
+// 2048 x 8192 x 2048 over 4 members 63.3 / 61.1 and over 2, two groups, 62.4 / 60.3; float32 outputs 2048 x 1024 x 4096 20.9 / 20.0.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
