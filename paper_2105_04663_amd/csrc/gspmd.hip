@@ -279,9 +279,15 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 // Operands beyond 16 MB: 0.09 us per MB more in dot_mid_kernel and 0.04 in dot_pair_kernel than in 256 x 256 tiles, whose workgroups draw them from HBM (and from the memory-side
 // cache) less often.  Without it, fitted to operands of which few were larger, launches that stream weights went to 128 x 128 tiles (us, dot_mfma_kernel / dot_mid_kernel): experts'
 // products of 8 x 363 x 2176 x 3840 47 / 71, 16 x 339 x 1344 x 6144 94 / 126, 8 x 279 x 3968 x 6016 140 / 178, 4 x 369 x 1600 x 8064 37 / 55, unpadded 16 x 289 x 1600 x 5760 104 / 131,
-// staged 32 x 2440 x 1759 x 665 291 / 352; below they are alike: 8 x 142 x 3904 x 2112 64 / 54.  Over 1800 products drawn like layers, experts' products of both directions, meshes and at random
-// the choice takes 1.3 % more than the best of the three kernels, 2.1 % without it; over 500 with few rows and large weights 1.1 %, 2.4 % (of all nine variants).
-double drawn_us(const LaunchSize& s, double per_mb) { return per_mb * std::max(0.0, static_cast<double>(s.in_bytes) * 1e-6 - 16.0); }
+// staged 32 x 2440 x 1759 x 665 291 / 352; below they are alike: 8 x 142 x 3904 x 2112 64 / 54.
+// Up to 128 rows 0.05 in dot_mid_kernel too, which then draws every weight once (dot_mfma_kernel / dot_mid_kernel; 4 x 35 x 3640 x 7781 63 / 46, 16 x 36 x 4057 x 1491 69 / 46,
+// dot_split_kernel 68); and beyond them nothing where 256 x 256 tiles leave half of the compute units idle, which then draw less than HBM gives (16 x 272 x 3760 x 1280 with 64 to 128 of them 97 / 85,
+// dot_pair_kernel 93; 16 x 269 x 2452 x 1072 61 / 62 / 67).
+constexpr int64_t kDrawnTiles = 128;
+double drawn_us(const LaunchSize& s, double narrow, double wide) {
+  const double per_mb = s.rows <= kMidTile ? narrow : s.big >= kDrawnTiles ? wide : 0.0;
+  return per_mb * std::max(0.0, static_cast<double>(s.in_bytes) * 1e-6 - 16.0);
+}
 constexpr int32_t kMidShortK = 1024;      // members with something left of K that dot_mid_kernel runs through one loop
 constexpr int64_t kSplitAnyKRows = 256, kSplitMinK = 1024;
 // dot_mfma_kernel's direct variants take a K-major rhs with loose rows from one of their tiles of columns on
@@ -304,11 +310,11 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (size.rows == 0) return choice;
   double best = big_us(size, choice.staged = big_staged(size, path, layout));
   if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
-    const double us = (loose ? mid_staged_us(size) : mid_us(size, layout)) + (size.members == 1 ? drawn_us(size, 0.09) : 0.0);
+    const double us = (loose ? mid_staged_us(size) : mid_us(size, layout)) + (size.members == 1 ? drawn_us(size, 0.05, 0.09) : 0.0);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, 0, loose}; }
   }
   if (pair_takes(size, path, layout)) {
-    const double us = pair_us(size, layout, path == kPathMfmaWords) + drawn_us(size, 0.04);
+    const double us = pair_us(size, layout, path == kPathMfmaWords) + drawn_us(size, 0.04, 0.04);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaPair, 0, 0, false, path == kPathMfmaWords}; }
   }
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {

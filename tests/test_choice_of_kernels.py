@@ -6,13 +6,13 @@ import paper_2105_04663_amd as g
 from tests.pin import MFMA, MID, last, pinned
 
 
-def _taken(E, M, K, N, align):
+def _taken(E, M, K, N, align=8, fill=None):
     mesh, dims = g.Mesh((1,), (0,)), g.DotDims((0,), (0,), (2,), (1,))
     shapes = ((E, M, K), (E, K, N), (E, M, N))
     sh = [g.Sharding(s, (-1, -1, -1)) for s in shapes]
     bufs = [g.ShardBuf((1 << 40) + (i << 36), g.BF16, -(-s[2] // align) * align) for i, s in enumerate(shapes)]
     with pinned(dry_run=True):
-        g.local_dot(mesh, dims, bufs[0], sh[0], bufs[1], sh[1], bufs[2], sh[2], 0, None, 1 << 45, g.dot_workspace_bytes(mesh, dims, *sh, -1, False))
+        g.local_dot(mesh, dims, bufs[0], sh[0], bufs[1], sh[1], bufs[2], sh[2], 0, fill, 1 << 45, g.dot_workspace_bytes(mesh, dims, *sh, -1, fill is not None))
         return last()[0]
 
 
@@ -28,6 +28,20 @@ def test_streamed_weights(E, M, K, N, align):
 @pytest.mark.parametrize("E,M,K,N", [(1, 2048, 1024, 2048), (4, 384, 1344, 768), (1, 1024, 2048, 4096)])
 def test_operands_that_the_caches_hold(E, M, K, N):
     assert _taken(E, M, K, N, 8) == MID
+
+
+# Up to 128 rows every weight is drawn once whatever the tile (us, dot_mfma_kernel / dot_mid_kernel / dot_split_kernel's best)
+@pytest.mark.parametrize("E,M,K,N,fill", [(4, 35, 3640, 7781, [18, 25, 30, 35]),           # 63 / 46 / 67
+                                          (16, 36, 4057, 1491, [24, 29, 34] * 5 + [28])])  # 69 / 46 / 68
+def test_streamed_weights_of_few_rows(E, M, K, N, fill):
+    assert _taken(E, M, K, N, 8, fill) == MID
+
+
+# Beyond them, where 256 x 256 tiles leave half of the compute units idle (us, dot_mfma_kernel / dot_mid_kernel / dot_pair_kernel)
+@pytest.mark.parametrize("E,M,K,N,fill", [(16, 272, 3760, 1280, [140, 250] * 7 + [230, 272]),       # 97 / 85 / 93
+                                          (4, 193, 3200, 6898, [100, 190, 150, 193])])              # 68 / 65 / 67
+def test_streamed_weights_in_few_tiles(E, M, K, N, fill):
+    assert _taken(E, M, K, N, 8, fill) == MID
 
 
 def test_a_buffer_that_several_partitions_share_counts_once():
