@@ -407,7 +407,10 @@ int32_t mark_moved_back(std::vector<Problem>& ps) {
 
 // bf16 outputs of a launch that the caches do not hold for the next one (kernels_lines.h), and those of more than one round of dot_mid_kernel's workgroups: in the caches
 // they take the place of operands that later tiles read (7592 x 3776 x 2240, 1080 tiles, us, through / past: 138.5 / 126.7, with a product of x 1024 that reads them 160 / 165).
-constexpr int64_t kPastBytes = 96000000, kPastTiles = 512;
+// And those of a launch whose operands fill a quarter of the memory-side cache: what the outputs take there, operands lose that come round again (679 x 8000 x 4992, three sets of operands
+// in turn, 68 / 55; 512 x 8192 x 5120 68.6 / 64.1, with a product of x 512 that reads them 98.8 / 97.2), and what the next kernel gains is little beside them (2000 x 9000 x 2000 on 2 x 2 84 / 84 and 124 /
+// 127, the worst of eleven; below it is 6 to 18 %).
+constexpr int64_t kPastBytes = 96000000, kPastTiles = 512, kPastInBytes = 64000000;
 
 int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dtype, int32_t out_dtype, int32_t epilogue,
                         bool ordered, void* workspace, int64_t workspace_bytes, hipStream_t stream, const JoinSpace* join = nullptr) {
@@ -504,7 +507,7 @@ int32_t launch_problems(std::vector<Problem>& all, int32_t layout, int32_t in_dt
       MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};
       int64_t out_bytes = 0;
       for (const auto& p : ps) if (p.join_slot == 0) out_bytes += static_cast<int64_t>(p.Mv) * p.Nv * 2;
-      l.past = out_bytes > kPastBytes || tiles > kPastTiles;
+      l.past = out_bytes > kPastBytes || tiles > kPastTiles || launch_size(ps, layout).in_bytes > kPastInBytes;
       if (!launch_dot_mid(l, layout, out_dtype, join != nullptr, choice.staged, stream)) return GSPMD_ERR_DEVICE;
     } else if (pair) {
       const MfmaLaunch l{&inl, tab, n, static_cast<int>(tiles), epilogue, nullptr, nullptr, nullptr, 0};

@@ -47,3 +47,7 @@ def test_tiles_that_are_moved_back(kernel, M, K, N, layout, out_dtype, epilogue)
 @pytest.mark.parametrize("K", [40, 41])              # direct and staged loads
 def test_outputs_that_the_caches_do_not_hold(K):
     _same_memory(split.workload(6203, K, 7801, 2), MID, 0, "bf16", 0)          # 97 MB: past the caches
+
+
+def test_operands_that_take_much_of_the_caches():
+    _same_memory(split.workload(391, 20000, 1402, 2), MID, 8, "bf16", 1)       # 72 MB: past the caches
