@@ -27,6 +27,9 @@ template <typename TOut> constexpr int line_slice(int blocks) { return blocks * 
 // 82.0, 4096 x 4096 x 2048 over 2, then x 512 78.3 / 82.7 / 77.3; the first product alone 20.9 / 20.2 / 19.9, the first sum 66.8 / 66.0 / 66.0.
 // Of a launch that asks for it (`past`) they go past all caches as well: outputs of more than kPastBytes, which the caches do not hold (us, through / past: 64 MB
 // in 8 of 2048 x 300 x 2048 31.1 / 31.5; 128 MB in 8 of 4096 x 200 x 2048 67.9 / 51.2, 16384 x 256 x 4096 57.5 / 48.1; 256 MB in 32 of 2048 x 128 x 2048 102.8 / 77.0).
+// Rows that are not whole lines of 128 bytes apart are left in the caches all the same, which put together the parts of a line that two stores, often of two workgroups, write (us,
+// through / plain, then with a product of x 512 that reads them): 3940 x 1536 x 1984 on 2 x 4 29.0 / 28.3, 52.0 / 51.4; 5079 x 100 x 934 on 2 x 3, dense, 8.9 / 8.3, 24.8 / 24.1; 4925 x 552 x 928 16.1 /
+// 15.9, 36.8 / 36.6; 3994 x 1216 x 1063 on 2 x 4 21.1 / 20.8, 39.7 / 39.0.
 // kLinesPast, dot_pair_kernel's bf16 outputs, launches of many tiles: four experts' weight gradients of 4096 x 8192, K 384 109 us, plain 140, and with an update that reads them 262, 281; of
 // 2048 x 4096, K 2048 29.8, 31.0 and 39.1, 39.5.
 // kLinesPlain where rows start at odd addresses and lines are stored in two parts (601 x 1203 x 697 17.9, past 18.4), and float32 outputs, mostly partial sums that the next kernel
@@ -75,6 +78,7 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
     // One read, one store (with all reads first four experts' weight gradients of 4096 x 8192 took 116.6 us, so 114.9); outputs written through all reads first (backward of
     // 2048 x 2048 x 8192 on 2 x 2 146.2 us, so 144.1).
     constexpr bool kReadsFirst = STORES == kLinesThrough;
+    const bool rows_are_lines = !(((static_cast<uint32_t>(P.ldc) * static_cast<uint32_t>(sizeof(TOut))) | static_cast<uint32_t>(reinterpret_cast<uintptr_t>(P.C))) & 127);
     if (kReadsFirst && inside) {
       u32x4_t v[kStores];
 #pragma unroll
@@ -82,8 +86,15 @@ __device__ __forceinline__ void store_lines(unsigned char* slice, GSPMD_GLOBAL T
       if (past)
 #pragma unroll
         for (int p = 0; p < kStores; ++p) {
-          asm volatile("" ::: "memory");        // (or the compiler makes one store of the two, without the hint)
+          asm volatile("" ::: "memory");        // (or the compiler makes one store of the three, without the hint)
           __builtin_nontemporal_store(__builtin_bit_cast(out_vec, v[p]), (GSPMD_GLOBAL out_vec*)(c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc));
+          asm volatile("" ::: "memory");
+        }
+      else if (!rows_are_lines)
+#pragma unroll
+        for (int p = 0; p < kStores; ++p) {
+          asm volatile("" ::: "memory");
+          *(GSPMD_GLOBAL out_vec*)(c0 + static_cast<int64_t>(p) * kRowsAt * P.ldc) = __builtin_bit_cast(out_vec, v[p]);
           asm volatile("" ::: "memory");
         }
       else

@@ -50,7 +50,8 @@ def test_no_kernel_spills(tmp_path):
 
 def test_how_dot_mid_kernel_stores_whole_tiles(tmp_path):
     """bf16 outputs: a store for each case, past the caches where a launch's outputs are more than these hold, else through to the memory side, where an einsum that
-    reads them finds them (that one took up to 18 % longer with all of them past the caches); float32 outputs and staged tiles, whose lines may be stored in two parts: neither."""
+    reads them finds them (that one took up to 18 % longer with all of them past the caches), and rows that are not whole lines with neither hint; float32 outputs and staged tiles, whose lines
+    may be stored in two parts: neither."""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     seen = {}
@@ -61,8 +62,10 @@ def test_how_dot_mid_kernel_stores_whole_tiles(tmp_path):
         listing = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", path], capture_output=True, text=True).stdout
         for name, body in re.findall(r"^<(\S*dot_mid_kernel\S*)>:\n(.*?)(?=^<|\Z)", listing, re.S | re.M):
             stores = re.findall(r"global_store_dwordx4 [^\n]*", body)
-            seen[name] = tuple(sum(bool(re.search(hint, x)) for x in stores) for hint in (r"\bnt\b", r"\bsc1\b"))
+            seen[name] = tuple(sum(bool(re.search(hint, x)) for x in stores) for hint in (r"\bnt\b", r"\bsc1\b", r"^(?!.*\b(nt|sc1)\b)"))
     assert len(seen) >= 40
-    for name, (past, through) in seen.items():
+    for name, (past, through, plain) in seen.items():
         out, chain, staged = re.search(r"dot_mid_kernelI(\w)Li\dELb(\d)ELi\dELb(\d)E", name).groups()
-        assert (past, through) == ((8, 8) if out == "t" and staged == "0" else (0, 0)), (name, past, through)
+        hinted = out == "t" and staged == "0"
+        assert (past, through) == ((8, 8) if hinted else (0, 0)), (name, past, through)
+        assert not hinted or plain >= 16, (name, plain)          # eight of whole tiles, eight at edges
