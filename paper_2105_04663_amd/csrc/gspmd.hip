@@ -282,10 +282,11 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 // staged 32 x 2440 x 1759 x 665 291 / 352; below they are alike: 8 x 142 x 3904 x 2112 64 / 54.
 // Up to 128 rows 0.05 in dot_mid_kernel too, which then draws every weight once (dot_mfma_kernel / dot_mid_kernel; 4 x 35 x 3640 x 7781 63 / 46, 16 x 36 x 4057 x 1491 69 / 46,
 // dot_split_kernel 68); and beyond them nothing where 256 x 256 tiles leave half of the compute units idle, which then draw less than HBM gives (16 x 272 x 3760 x 1280 with 64 to 128 of them 97 / 85,
-// dot_pair_kernel 93; 16 x 269 x 2452 x 1072 61 / 62 / 67).
+// dot_pair_kernel 93; 16 x 269 x 2452 x 1072 61 / 62 / 67).  Nor where the lhs is K-major, whose tiles draw whole lines of it whatever their rows: experts' weight gradients of 8 x 3648 x 505 to 915 x
+// 1152 64 / 57 / 53, 4 x 1152 x 528 to 578 x 7104 53 / 44 / 47, 8 x 1728 x 368 to 633 x 2896 63 / 60 / 53 (of 308 drawn ones none was faster with it).
 constexpr int64_t kDrawnTiles = 128;
-double drawn_us(const LaunchSize& s, double narrow, double wide) {
-  const double per_mb = s.rows <= kMidTile ? narrow : s.big >= kDrawnTiles ? wide : 0.0;
+double drawn_us(const LaunchSize& s, int32_t layout, double narrow, double wide) {
+  const double per_mb = layout & GSPMD_LAYOUT_LHS_K_MAJOR ? 0.0 : s.rows <= kMidTile ? narrow : s.big >= kDrawnTiles ? wide : 0.0;
   return per_mb * std::max(0.0, static_cast<double>(s.in_bytes) * 1e-6 - 16.0);
 }
 constexpr int32_t kMidShortK = 1024;      // members with something left of K that dot_mid_kernel runs through one loop
@@ -310,11 +311,11 @@ MfmaChoice choose_mfma(const std::vector<Problem>& ps, KernelPath path, int32_t 
   if (size.rows == 0) return choice;
   double best = big_us(size, choice.staged = big_staged(size, path, layout));
   if (!loose || (size.members == 1 && mid_stages_whole(size, layout))) {
-    const double us = (loose ? mid_staged_us(size) : mid_us(size, layout)) + (size.members == 1 ? drawn_us(size, 0.05, 0.09) : 0.0);
+    const double us = (loose ? mid_staged_us(size) : mid_us(size, layout)) + (size.members == 1 ? drawn_us(size, layout, 0.05, 0.09) : 0.0);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaMid, 0, 0, loose}; }
   }
   if (pair_takes(size, path, layout)) {
-    const double us = pair_us(size, layout, path == kPathMfmaWords) + drawn_us(size, 0.04, 0.04);
+    const double us = pair_us(size, layout, path == kPathMfmaWords) + drawn_us(size, layout, 0.04, 0.04);
     if (us < 0.95 * best) { best = us; choice = MfmaChoice{kMfmaPair, 0, 0, false, path == kPathMfmaWords}; }
   }
   if (!ordered && (loose || size.rows <= kSplitAnyKRows || size.k >= kSplitMinK)) {

@@ -3,7 +3,7 @@
 import pytest
 
 import paper_2105_04663_amd as g
-from tests.pin import MFMA, MID, last, pinned
+from tests.pin import MFMA, MID, PAIR, last, pinned
 
 
 def _taken(E, M, K, N, align=8, fill=None):
@@ -42,6 +42,20 @@ def test_streamed_weights_of_few_rows(E, M, K, N, fill):
                                           (4, 193, 3200, 6898, [100, 190, 150, 193])])              # 68 / 65 / 67
 def test_streamed_weights_in_few_tiles(E, M, K, N, fill):
     assert _taken(E, M, K, N, 8, fill) == MID
+
+
+# A K-major lhs: experts' weight gradients of E x M x (fill) x N (us, dot_mfma_kernel / dot_mid_kernel / dot_pair_kernel)
+@pytest.mark.parametrize("C,M,N,filled", [(924, 3648, 1152, [915, 555, 505, 788, 636, 553, 827, 901]),         # 64 / 57 / 53
+                                          (580, 1152, 7104, [556, 539, 578, 528]),                              # 53 / 44 / 47
+                                          (689, 1728, 2896, [559, 377, 368, 633, 484, 431, 539, 464])])         # 63 / 60 / 53
+def test_weight_gradients(C, M, N, filled):
+    E = len(filled)
+    mesh, dims = g.Mesh((1,), (0,)), g.DotDims((0,), (0,), (1,), (1,))
+    sh = [g.Sharding(s, (-1, -1, -1)) for s in ((E, C, M), (E, C, N), (E, M, N))]
+    bufs = [g.ShardBuf((1 << 40) + (i << 36), g.BF16) for i in range(3)]
+    with pinned(dry_run=True):
+        g.local_dot(mesh, dims, bufs[0], sh[0], bufs[1], sh[1], bufs[2], sh[2], 0, filled, 1 << 45, g.dot_workspace_bytes(mesh, dims, *sh, -1, True))
+        assert last()[0] in (MID, PAIR)
 
 
 def test_a_buffer_that_several_partitions_share_counts_once():
