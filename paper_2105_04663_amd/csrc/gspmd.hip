@@ -150,8 +150,8 @@ thread_local gspmd_testing_launch t_last{GSPMD_TESTING_BY_RULE, 0, GSPMD_TESTING
 //   that is left of K; in sums of more than one round of 512 0.44, and 0.30 in a last round of up to 256; a fifth more per step where a
 //   K-contiguous operand's rows are not whole lines of 128 bytes (2112 x 8000 x 2112: 90 us, with rows of 8032 elements 117).  Fitted to drawn launches
 //   together with dot_pair_kernel's line and the 256 x 256 tiles' 10 us; few of those had operands beyond 16 MB (drawn_us, below).  Over products drawn afresh the choice takes
-//   1.6 % more than the best of all kernels pinned one after the other (300 layers, experts' products and others of more than few rows), 1.1 % (120 with few rows and large operands),
-//   1.2 % (160 meshes of dense rows), 0.2 % (120 feed-forward layers); 4.9 % where any extents are drawn (160, most of them of 4 to 12 us).
+//   0.8 % more than the best of all kernels pinned one after the other (150 experts' products), 1.3 % (50 of their weight gradients), 0.3 % and 1.5 % (80 feed-forward layers of up to
+//   256 rows, 80 of more), 0.9 % (80 meshes of dense rows); 5.2 % where any extents are drawn (120, most of them of 4 to 12 us).
 // Measured (one problem, M x K x N, us, dot_mfma_kernel / dot_mid_kernel): 2048 x 8192 x 2048: 120 / 62   512 x 8192 x 512: 117 / 45
 //   2048 x 4096 x 4096: 66 / 60   2048 x 1024 x 4096: 22 / 19   4653 x 7168 x 4288: 255 / 267   1456 x 1415 x 3969, two of them: 38 / 45
 //   2178 x 4736 x 1447, two: 76 / 72   1090 x 1333 x 1568, eight: 61 / 52   2112 x 8000 x 2112: 111 / 90   4096 x 512 x 8192, four, both K-major: 143 / 159
@@ -279,10 +279,10 @@ double pair_us(const LaunchSize& s, int32_t layout, bool loose) {
 // Operands beyond 16 MB: 0.09 us per MB more in dot_mid_kernel and 0.04 in dot_pair_kernel than in 256 x 256 tiles, whose workgroups draw them from HBM (and from the memory-side
 // cache) less often.  Without it, fitted to operands of which few were larger, launches that stream weights went to 128 x 128 tiles (us, dot_mfma_kernel / dot_mid_kernel): experts'
 // products of 8 x 363 x 2176 x 3840 47 / 71, 16 x 339 x 1344 x 6144 94 / 126, 8 x 279 x 3968 x 6016 140 / 178, 4 x 369 x 1600 x 8064 37 / 55, unpadded 16 x 289 x 1600 x 5760 104 / 131,
-// staged 32 x 2440 x 1759 x 665 291 / 352; below they are alike: 8 x 142 x 3904 x 2112 64 / 54.
+// staged 32 x 2440 x 1759 x 665 291 / 352.
 // Up to 128 rows 0.05 in dot_mid_kernel too, which then draws every weight once (dot_mfma_kernel / dot_mid_kernel; 4 x 35 x 3640 x 7781 63 / 46, 16 x 36 x 4057 x 1491 69 / 46,
 // dot_split_kernel 68); and beyond them nothing where 256 x 256 tiles leave half of the compute units idle, which then draw less than HBM gives (16 x 272 x 3760 x 1280 with 64 to 128 of them 97 / 85,
-// dot_pair_kernel 93; 16 x 269 x 2452 x 1072 61 / 62 / 67).  Nor where the lhs is K-major, whose tiles draw whole lines of it whatever their rows: experts' weight gradients of 8 x 3648 x 505 to 915 x
+// dot_pair_kernel 93; 16 x 269 x 2452 x 1072 61 / 62 / 67; 8 x 142 x 3904 x 2112 64 / 54).  Nor where the lhs is K-major: weight gradients have short K, and their outputs bound them, 8 x 3648 x 505 to 915 x
 // 1152 64 / 57 / 53, 4 x 1152 x 528 to 578 x 7104 53 / 44 / 47, 8 x 1728 x 368 to 633 x 2896 63 / 60 / 53 (of 308 drawn ones none was faster with it).
 constexpr int64_t kDrawnTiles = 128;
 double drawn_us(const LaunchSize& s, int32_t layout, double narrow, double wide) {
